@@ -1,6 +1,6 @@
 // Plain LDS-tiled GEMM with fp32 FMA accumulation: C[m,n] = sum_k A[m,k] * W[n,k].
 // This is the fp32 debug path (model dtype fp32) and the cross-check for the bf16 MFMA kernel.
-// Tile 64x64x32, 256 threads; thread (ty, tx) owns rows ty*8..ty*8+7 and the column pair (tx, tx+32).
+// Tile 64x64x32 or 16x64x32, 256 threads; thread (ty, tx) owns TR rows from ty*TR and the column pair (tx, tx+32).
 #pragma once
 
 #include "common.h"
@@ -24,57 +24,70 @@ __device__ __forceinline__ void load8(const bf16 *p, float *out) {
   }
 }
 
-// grid: (N/64, ceil(M/64)).  Requirements checked by the host: N % 64 == 0, K % 32 == 0.
+// grid: (N/64, ceil(M/(8*TR))).  Requirements checked by the host: N % 64 == 0, K % 32 == 0.
 // For Epi::kDual the second weight block starts N rows after the first (W is [2N, K]: gate | up).
-template <typename T, typename Epi>
+// TR rows per thread: 8 (64-row tiles) or 2 (16-row tiles, for launches that leave most of the chip idle; see the
+// launch).  The next K slab is requested before the current one is multiplied, and operands are read from LDS four k
+// at a time (rows of 36 floats: 16-byte aligned, and 16 consecutive rows spread over the banks).  Every output still
+// sums its products one by one in ascending k, so neither TR nor the slab width changes a bit.
+// 4 blocks of 33 rows on the two-layer d256 fp32 model: the down projection was 74 us on 12 workgroups (one k at a time
+// from LDS, slab loads exposed); with k_attn_simple's change the whole pass went from 560 to 305 us.
+template <typename T, typename Epi, int TR>
 __global__ void __launch_bounds__(256) k_gemm_simple(int M, int N, int K, const T *__restrict__ A,
                                                      const T *__restrict__ W, Epi epi) {
-  constexpr int BK = 32;
-  __shared__ float As[64][BK + 1];
-  __shared__ float Bs[64][BK + 1];
-  __shared__ float Bs2[Epi::kDual ? 64 : 1][BK + 1];
+  constexpr int BK = 32, LS = BK + 4, BM = 8 * TR;
+  __shared__ __attribute__((aligned(16))) float As[BM][LS];
+  __shared__ __attribute__((aligned(16))) float Bs[64][LS];
+  __shared__ __attribute__((aligned(16))) float Bs2[Epi::kDual ? 64 : 1][LS];
   const int t = threadIdx.x, tx = t & 31, ty = t >> 5;
-  const int m0 = blockIdx.y * 64, n0 = blockIdx.x * 64;
+  const int m0 = blockIdx.y * BM, n0 = blockIdx.x * 64;
   const int lr = t >> 2, lk = (t & 3) * 8;
+  const bool loads_a = lr < BM;   // the first BM * 4 threads bring in the activation rows
 
-  float acc[8][2], acc2[8][2];
+  float acc[TR][2], acc2[TR][2];
 #pragma unroll
-  for (int i = 0; i < 8; ++i) acc[i][0] = acc[i][1] = acc2[i][0] = acc2[i][1] = 0.f;
+  for (int i = 0; i < TR; ++i) acc[i][0] = acc[i][1] = acc2[i][0] = acc2[i][1] = 0.f;
 
-  for (int k0 = 0; k0 < K; k0 += BK) {
-    float va[8], vb[8], vb2[8];
-    if (m0 + lr < M) {
-      load8(A + static_cast<size_t>(m0 + lr) * K + k0 + lk, va);
-    } else {
+  float va[8], vb[8], vb2[8];
 #pragma unroll
-      for (int i = 0; i < 8; ++i) va[i] = 0.f;
-    }
+  for (int i = 0; i < 8; ++i) va[i] = 0.f;
+  auto request = [&](int k0) {
+    if (loads_a && m0 + lr < M) load8(A + static_cast<size_t>(m0 + lr) * K + k0 + lk, va);
     load8(W + static_cast<size_t>(n0 + lr) * K + k0 + lk, vb);
     if (Epi::kDual) load8(W + static_cast<size_t>(N + n0 + lr) * K + k0 + lk, vb2);
+  };
+  auto put = [&](float *dst, const float *v) {
+    reinterpret_cast<floatx4 *>(dst)[0] = floatx4{v[0], v[1], v[2], v[3]};
+    reinterpret_cast<floatx4 *>(dst)[1] = floatx4{v[4], v[5], v[6], v[7]};
+  };
+  request(0);
+  for (int k0 = 0; k0 < K; k0 += BK) {
     __syncthreads();  // previous tile fully consumed
-#pragma unroll
-    for (int i = 0; i < 8; ++i) {
-      As[lr][lk + i] = va[i];
-      Bs[lr][lk + i] = vb[i];
-      if (Epi::kDual) Bs2[lr][lk + i] = vb2[i];
-    }
+    if (loads_a) put(&As[lr][lk], va);
+    put(&Bs[lr][lk], vb);
+    if (Epi::kDual) put(&Bs2[lr][lk], vb2);
     __syncthreads();
-#pragma unroll 8
-    for (int kk = 0; kk < BK; ++kk) {
-      float b0 = Bs[tx][kk], b1 = Bs[tx + 32][kk];
-      float c0 = 0.f, c1 = 0.f;
+    if (k0 + BK < K) request(k0 + BK);
+#pragma unroll
+    for (int kk = 0; kk < BK; kk += 4) {
+      const floatx4 b0 = *reinterpret_cast<const floatx4 *>(&Bs[tx][kk]);
+      const floatx4 b1 = *reinterpret_cast<const floatx4 *>(&Bs[tx + 32][kk]);
+      floatx4 c0 = {0.f, 0.f, 0.f, 0.f}, c1 = c0;
       if (Epi::kDual) {
-        c0 = Bs2[tx][kk];
-        c1 = Bs2[tx + 32][kk];
+        c0 = *reinterpret_cast<const floatx4 *>(&Bs2[tx][kk]);
+        c1 = *reinterpret_cast<const floatx4 *>(&Bs2[tx + 32][kk]);
       }
 #pragma unroll
-      for (int i = 0; i < 8; ++i) {
-        float a = As[ty * 8 + i][kk];
-        acc[i][0] = fmaf(a, b0, acc[i][0]);
-        acc[i][1] = fmaf(a, b1, acc[i][1]);
-        if (Epi::kDual) {
-          acc2[i][0] = fmaf(a, c0, acc2[i][0]);
-          acc2[i][1] = fmaf(a, c1, acc2[i][1]);
+      for (int i = 0; i < TR; ++i) {
+        const floatx4 a = *reinterpret_cast<const floatx4 *>(&As[ty * TR + i][kk]);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          acc[i][0] = fmaf(a[e], b0[e], acc[i][0]);
+          acc[i][1] = fmaf(a[e], b1[e], acc[i][1]);
+          if (Epi::kDual) {
+            acc2[i][0] = fmaf(a[e], c0[e], acc2[i][0]);
+            acc2[i][1] = fmaf(a[e], c1[e], acc2[i][1]);
+          }
         }
       }
     }
@@ -82,8 +95,8 @@ __global__ void __launch_bounds__(256) k_gemm_simple(int M, int N, int K, const 
 
   if constexpr (std::is_same<Epi, EpiLMHead>::value) {
 #pragma unroll
-    for (int i = 0; i < 8; ++i) {
-      int m = m0 + ty * 8 + i;
+    for (int i = 0; i < TR; ++i) {
+      int m = m0 + ty * TR + i;
       Top2 tp = top2_init();
       top2_push(tp, acc[i][0], n0 + tx);
       top2_push(tp, acc[i][1], n0 + tx + 32);
@@ -108,8 +121,8 @@ __global__ void __launch_bounds__(256) k_gemm_simple(int M, int N, int K, const 
     }
   } else {
 #pragma unroll
-    for (int i = 0; i < 8; ++i) {
-      int m = m0 + ty * 8 + i;
+    for (int i = 0; i < TR; ++i) {
+      int m = m0 + ty * TR + i;
       if (m >= M) continue;
       if constexpr (Epi::kDual) {
         epi.pair2(m, n0 + tx, acc[i][0], acc[i][1], acc2[i][0], acc2[i][1]);

@@ -388,9 +388,16 @@ int launch_gemm(const hsd_ctx *ctx, hipStream_t st, int site, int M, int N, int 
   if constexpr (std::is_same<Epi, EpiResidualNorm>::value) {
     return HSD_EINVAL;   // this epilogue exists for the MFMA kernels only (the caller never gets here with it)
   } else {
-    dim3 grid(N / 64, (M + 63) / 64);
-    hipLaunchKernelGGL((k_gemm_simple<T, Epi>), grid, dim3(256), 0, st, M, N, K, static_cast<const T *>(A),
-                       static_cast<const T *>(W), epi);
+    // 16-row tiles while 64-row ones would not give every compute unit a workgroup: a workgroup's walk over K sets the
+    // launch's time then, and it is shorter with fewer rows.  Same bits either way.
+    const int64_t n64 = static_cast<int64_t>(N / 64) * ((M + 63) / 64);
+    if (n64 < (ctx->n_cu > 0 ? ctx->n_cu : 256)) {
+      hipLaunchKernelGGL((k_gemm_simple<T, Epi, 2>), dim3(N / 64, (M + 15) / 16), dim3(256), 0, st, M, N, K,
+                         static_cast<const T *>(A), static_cast<const T *>(W), epi);
+    } else {
+      hipLaunchKernelGGL((k_gemm_simple<T, Epi, 8>), dim3(N / 64, (M + 63) / 64), dim3(256), 0, st, M, N, K,
+                         static_cast<const T *>(A), static_cast<const T *>(W), epi);
+    }
     HSD_LAUNCH_CHECK();
     return HSD_OK;
   }
