@@ -20,11 +20,17 @@ struct RowScale {
   const float *ss;   // [rows][n_parts] partial sums of squares, or nullptr: the operand is already normalised
   int n_parts;       // d_model / 64
   float inv_d, eps;
+  const float *ss2 = nullptr;   // narrow tiles left each piece as two sums (ss, ss2); added here as sum8_lanes adds them
   __device__ __forceinline__ float at(int m) const {
     if (ss == nullptr) return 1.0f;
     const float *p = ss + static_cast<size_t>(m) * n_parts;
     float s = 0.f;
-    for (int i = 0; i < n_parts; ++i) s += p[i];
+    if (ss2 != nullptr) {
+      const float *p2 = ss2 + static_cast<size_t>(m) * n_parts;
+      for (int i = 0; i < n_parts; ++i) s += p[i] + p2[i];
+    } else {
+      for (int i = 0; i < n_parts; ++i) s += p[i];
+    }
     return 1.0f / sqrtf(s * inv_d + eps);
   }
 };
@@ -142,11 +148,16 @@ struct EpiResidual {
   }
 };
 
-// Sum over the 8 adjacent lanes that hold one 64-column piece of a row (lanes 8k .. 8k+7), by lane-crossing moves
+// Sum over the 8 adjacent lanes that hold one 64-column piece of a row (lanes 8k .. 8k+7), or over the 4 that hold half
+// of one (sum8_lanes is the sum of its halves' sum4_lanes, bit for bit), by lane-crossing moves
 // inside the vector unit; every lane ends up with the same bits (the additions pair up commutatively).
-__device__ __forceinline__ float sum8_lanes(float v) {
+__device__ __forceinline__ float sum4_lanes(float v) {
   v += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0xB1, 0xf, 0xf, true));   // quad_perm [1,0,3,2]
   v += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x4E, 0xf, 0xf, true));   // quad_perm [2,3,0,1]
+  return v;
+}
+__device__ __forceinline__ float sum8_lanes(float v) {
+  v = sum4_lanes(v);
   v += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x141, 0xf, 0xf, true));  // row_half_mirror
   return v;
 }
@@ -162,6 +173,8 @@ struct EpiResidualNorm {
   const float *gain;  // [ld] gain of the norm that follows, or nullptr
   bf16 *h;            // [M][ld]
   float *ss;          // [M][ld / 64]
+  float *ss2 = nullptr;   // [M][ld / 64], narrow tiles only: a tile holds half of a piece (columns 0-15 and 32-47, or
+                          //   16-31 and 48-63: four lanes) and stores that half's sum, the first in ss, the second here
   static constexpr int kPiece = 4;
   __device__ __forceinline__ void piece(int m, int n, float (&lo)[4], float (&hi)[4]) const {
     float *p = x + static_cast<size_t>(m) * ld + n;
@@ -188,6 +201,11 @@ struct EpiResidualNorm {
     bf16 *hp = h + static_cast<size_t>(m) * ld + n;
     *reinterpret_cast<bf16x4 *>(hp) = __builtin_convertvector(h0, bf16x4);
     *reinterpret_cast<bf16x4 *>(hp + 32) = __builtin_convertvector(h1, bf16x4);
+    if (ss2 != nullptr) {
+      sq = sum4_lanes(sq);
+      if ((n & 15) == 0) ((n & 16) ? ss2 : ss)[static_cast<size_t>(m) * (ld >> 6) + (n >> 6)] = sq;
+      return;
+    }
     // the 8 lanes n % 64 / 4 = 0..7 of this row hold the 64-column piece between them
     sq = sum8_lanes(sq);
     if ((n & 63) == 0) ss[static_cast<size_t>(m) * (ld >> 6) + (n >> 6)] = sq;

@@ -41,7 +41,12 @@ struct GemmCfg {
   static constexpr int kLoadsP = BP * kChunks / kThreads, kLoadsQ = BQ * kChunks / kThreads;
   static constexpr int kEpiStride = TN * 32 + 4;              // floats per row of a wave's epilogue staging region
   static_assert(WM * WN * 32 * kEpiStride * 4 <= kSmemBytes, "epilogue staging must fit in the operand stages");
-  static_assert(BP % (WM * 32) == 0 && BQ % (WN * 64) == 0, "wave tile must be made of 32-row / 64-col groups");
+  // BQ = 32 (one wave column) is the narrow form: two 16-column runs 32 apart, i.e. half of a 64-column group with the
+  // partners of its columns, 32 further on (see gemm_q_col), for launches bound by how many compute units stream the
+  // weights
+  static constexpr bool kNarrow = BQ == 32;
+  static_assert(BP % (WM * 32) == 0 && (BQ % (WN * 64) == 0 || (kNarrow && WN == 1)),
+                "wave tile must be made of 32-row / 64-col groups");
   static_assert(BP * kChunks % kThreads == 0 && BQ * kChunks % kThreads == 0, "tile loads must divide evenly");
 };
 
@@ -61,6 +66,16 @@ __device__ __forceinline__ void xcd_tile(int pid, int tiles_fast, int n_tiles, i
 __device__ __forceinline__ void gemm_tile_of(int pid, int M, int w_rows, int tiles_act, int tiles_w, int &ta, int &tw) {
   if (M >= 4 * w_rows) xcd_tile(pid, tiles_w, tiles_act * tiles_w, tw, ta);
   else xcd_tile(pid, tiles_act, tiles_act * tiles_w, ta, tw);
+}
+
+// First output column of weight tile tw (normal mode), and the column of the tile's Q row r relative to it.
+template <typename Cfg>
+__device__ __forceinline__ int gemm_q_col0(int tw) {
+  return Cfg::kNarrow ? (tw >> 1) * 64 + (tw & 1) * 16 : tw * Cfg::BQ;
+}
+template <typename Cfg>
+__device__ __forceinline__ int gemm_q_col(int r) {
+  return Cfg::kNarrow ? (r & 15) + (r >> 4) * 32 : r;
 }
 
 // Tile counts for (M, N) in a mode: activation tiles first, weight tiles second.
@@ -163,7 +178,10 @@ __device__ __forceinline__ void gemm_epilogue(floatx16 (&acc)[Cfg::TM][Cfg::TN],
     // gate/up pairs in dual mode), so that adjacent lanes write adjacent 16-byte pieces of one row.  Each wave
     // uses a private region (32 rows of TN*32 + 4 floats); LDS executes a wave's accesses in program order, so
     // only the compiler has to be kept from reordering them (wave-scope fences).
-    constexpr int ST = Cfg::kEpiStride, PC = Epi::kPiece, LPR = 32 / PC, RPI = 64 / LPR;  // lanes per row, rows per pass
+    constexpr int ST = Cfg::kEpiStride, PC = Epi::kPiece;
+    constexpr int PART = Cfg::kNarrow ? 16 : 32;            // columns between a staged column and its partner
+    constexpr int LPR = PART / PC, RPI = 64 / LPR;          // lanes per row, rows per pass
+    constexpr int JG = Cfg::kNarrow ? 1 : TN / 2;
     float *wst = stage + (wi * Cfg::WN + wj) * 32 * ST;
     const int pc = lane % LPR, pr = lane / LPR;
 #pragma unroll
@@ -184,13 +202,13 @@ __device__ __forceinline__ void gemm_epilogue(floatx16 (&acc)[Cfg::TM][Cfg::TN],
         float rsc = 1.0f;
         if constexpr (Epi::kRowScale) rsc = rsl[wi * (BP / Cfg::WM) + i * 32 + r];
 #pragma unroll
-        for (int jg = 0; jg < TN / 2; ++jg) {
+        for (int jg = 0; jg < JG; ++jg) {
           float lo[PC], hi[PC];
           const float *src = wst + r * ST + jg * 64 + PC * pc;
 #pragma unroll
           for (int q = 0; q < PC / 4; ++q) {
             const floatx4 a = *reinterpret_cast<const floatx4 *>(src + 4 * q);
-            const floatx4 b = *reinterpret_cast<const floatx4 *>(src + 32 + 4 * q);
+            const floatx4 b = *reinterpret_cast<const floatx4 *>(src + PART + 4 * q);
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
               lo[4 * q + e] = Epi::kRowScale ? a[e] * rsc : a[e];

@@ -240,7 +240,11 @@ using GemmCfgD128 = GemmCfgD<128, 128, 4, 4>;
 // 12 = the same kernel with ONE multiplying wave on a 32x64 tile (token-by-token decoding, see effective_gemm_cfg)
 using GemmCfgD32 = GemmCfgD<32, 64, 6, 2, 1, 1>;
 using GemmCfgD64n = GemmCfgD<64, 64, 6, 2, 2, 1>;   // 13: two multiplying waves on a 64x64 tile
+using GemmCfgD32n = GemmCfgD<32, 32, 8, 2, 1, 1>;   // 14: half a 64-column group per workgroup (never selected by hand)
 
+
+// Narrow tiles keep a second plane of row sums (EpiResidualNorm::ss2) in the q or the attention-output buffer.
+bool narrow_ok(const hsd_model_desc &d) { return d.n_q_heads * d.head_dim * 2 >= d.d_model / 64 * 4; }
 
 // Tile configuration actually used at a call site for a given problem (the launch and everything sized from the
 // tile shape, like the LM-head partial records, must agree on it).  -1 = plain kernels.
@@ -270,6 +274,10 @@ int effective_gemm_cfg(const hsd_ctx *ctx, int site, int M, int N, int K) {
     const int64_t cu_n = ctx->n_cu > 0 ? ctx->n_cu : 256;
     const int64_t cols64 = ((site == kSiteGateUp ? 2 * static_cast<int64_t>(N) : N) + 63) / 64;
     if (site == kSiteLM) cfg = M <= 128 ? 0 : cfg;
+    // ... and half as wide again (14) where that too stays within one workgroup per unit: a pass over 1 row of the
+    // 24-layer model 1398 -> 1314 us, a step of 16 rows 1429 -> 1314, 7 blocks of up to 48 rows 1677 -> 1565 (all with
+    // 12 before).  Not gate/up, whose 64-column tiles are 128 workgroups already.
+    else if (site != kSiteGateUp && static_cast<int64_t>((M + 31) / 32) * cols64 * 2 <= cu_n && narrow_ok(ctx->desc)) cfg = 14;
     else if (static_cast<int64_t>((M + 31) / 32) * cols64 <= cu_n) cfg = 12;
     else if (static_cast<int64_t>((M + 63) / 64) * cols64 <= cu_n) cfg = 13;
     else if (M <= 64) cfg = 10;                                        // one row tile
@@ -292,7 +300,7 @@ int effective_gemm_cfg(const hsd_ctx *ctx, int site, int M, int N, int K) {
   // the two-role kernels: not for the swapped LM-head mode
   if ((cfg == 7 || cfg == 9) && site == kSiteLM) cfg = cfg == 7 ? 0 : 2;
   // the LDS-direct kernels: not the swapped mode, 32-bit operand offsets
-  if ((cfg == 10 || cfg == 11 || cfg == 12 || cfg == 13) &&
+  if ((cfg == 10 || cfg == 11 || cfg == 12 || cfg == 13 || cfg == 14) &&
       (site == kSiteLM || static_cast<int64_t>(M) * K * 2 >= (int64_t{1} << 31) ||
        (site == kSiteGateUp ? 2 : 1) * static_cast<int64_t>(N) * K * 2 >= (int64_t{1} << 31)))
     cfg = cfg == 11 ? 0 : 2;
@@ -381,6 +389,10 @@ int launch_gemm(const hsd_ctx *ctx, hipStream_t st, int site, int M, int N, int 
       case 13:
         if constexpr (GemmModeOf<Epi>::value != kModeSwapLM)
           return launch_gemm_mfma_d<GemmCfgD64n>(st, M, N, K, A, W, epi);
+        break;
+      case 14:
+        if constexpr (GemmModeOf<Epi>::value == kModeNormal)
+          return launch_gemm_mfma_d<GemmCfgD32n>(st, M, N, K, A, W, epi);
         break;
       default: return launch_gemm_mfma<GemmCfg0>(st, M, N, K, A, W, epi);
     }
@@ -545,13 +557,13 @@ int forward(hsd_ctx *ctx, hipStream_t st, const hsd_kv_pool *pool, const hsd_bat
   };
   // x += A W^T.  MFMA path: the epilogue also prepares the norm that follows (operand x * gain and the row sums of
   // squares, see RowScale), so that norm never runs as a kernel; plain path: residual only, then the norm kernel.
-  auto residual_proj = [&](int site, int prof, const void *A, const void *W, int K, const float *next_gain) -> int {
+  auto residual_proj = [&](int site, int prof, const void *A, const void *W, int K, const float *next_gain, float *ss2) -> int {
     {
       ProfScope ps(ctx, st, prof);
       int rc2;
       if constexpr (std::is_same<T, bf16>::value) {
         if (mfma_path) {
-          EpiResidualNorm en{ws.x, d.d_model, next_gain, static_cast<bf16 *>(ws.h), ws.ss};
+          EpiResidualNorm en{ws.x, d.d_model, next_gain, static_cast<bf16 *>(ws.h), ws.ss, ss2};
           rc2 = launch_gemm<T>(ctx, st, site, Tq, d.d_model, K, A, W, en);
           return rc2;
         }
@@ -563,12 +575,20 @@ int forward(hsd_ctx *ctx, hipStream_t st, const hsd_kv_pool *pool, const hsd_bat
   };
   const RowScale rs_none{nullptr, 0, 0.f, 0.f};
   const RowScale rs_fused{mfma_path ? ws.ss : nullptr, d.d_model / 64, 1.0f / static_cast<float>(d.d_model), d.rms_eps};
+  // Second plane of the row sums where the output or down projection runs narrow tiles.  It lies in a buffer that is
+  // idle from that projection until its readers are done: the output projection's (read by gate/up) in q, the down
+  // projection's (read by the next layer's QKV, which writes q, or by the LM head) in the attention output.
+  float *const o_ss2 = effective_gemm_cfg<T>(ctx, kSiteO, Tq, d.d_model, qdim) == 14 ? static_cast<float *>(ws.q) : nullptr;
+  float *const down_ss2 = effective_gemm_cfg<T>(ctx, kSiteDown, Tq, d.d_model, d.d_ffn) == 14 ? static_cast<float *>(ws.a) : nullptr;
+  RowScale rs_o = rs_fused, rs_down = rs_fused;
+  rs_o.ss2 = o_ss2;
+  rs_down.ss2 = down_ss2;
 
   if ((rc = norm(ctx->attn_norm[0]))) return rc;
   for (int l = 0; l < d.n_layers; ++l) {
     PagedKV kv{pool->k_pool, pool->v_pool, b->block_table, b->max_blocks_per_seq, pool->n_blocks, d.n_kv_heads, l};
     // layer 0 reads the operand the norm kernel normalised; later layers the one the previous down projection left
-    EpiQKV<T> eq{d.n_q_heads, d.n_kv_heads, meta, kv, static_cast<T *>(ws.q), l == 0 ? rs_none : rs_fused};
+    EpiQKV<T> eq{d.n_q_heads, d.n_kv_heads, meta, kv, static_cast<T *>(ws.q), l == 0 ? rs_none : rs_down};
     {
       ProfScope ps(ctx, st, HSD_PROF_GEMM_QKV);
       if ((rc = launch_gemm<T>(ctx, st, kSiteQKV, Tq, qdim + 2 * kvdim, d.d_model, ws.h, ctx->wqkv[l], eq))) return rc;
@@ -577,15 +597,15 @@ int forward(hsd_ctx *ctx, hipStream_t st, const hsd_kv_pool *pool, const hsd_bat
       ProfScope ps(ctx, st, HSD_PROF_ATTENTION);
       if ((rc = launch_attention<T>(ctx, st, b, meta, kv, ws, page_mode))) return rc;
     }
-    if ((rc = residual_proj(kSiteO, HSD_PROF_GEMM_O, ws.a, ctx->wo[l], qdim, ctx->ffn_norm[l]))) return rc;
-    EpiSwiGLU<T> es{static_cast<T *>(ws.u), d.d_ffn, rs_fused};
+    if ((rc = residual_proj(kSiteO, HSD_PROF_GEMM_O, ws.a, ctx->wo[l], qdim, ctx->ffn_norm[l], o_ss2))) return rc;
+    EpiSwiGLU<T> es{static_cast<T *>(ws.u), d.d_ffn, rs_o};
     {
       ProfScope ps(ctx, st, HSD_PROF_GEMM_GATE_UP);
       if ((rc = launch_gemm<T>(ctx, st, kSiteGateUp, Tq, d.d_ffn, d.d_model, ws.h, ctx->w_gate_up[l], es))) return rc;
     }
     // the norm that follows: next layer's attention norm, or the final norm before the LM head (none for prefill)
     const float *next_gain = (l + 1 < d.n_layers) ? ctx->attn_norm[l + 1] : (with_head ? ctx->final_norm : nullptr);
-    if ((rc = residual_proj(kSiteDown, HSD_PROF_GEMM_DOWN, ws.u, ctx->w_down[l], d.d_ffn, next_gain))) return rc;
+    if ((rc = residual_proj(kSiteDown, HSD_PROF_GEMM_DOWN, ws.u, ctx->w_down[l], d.d_ffn, next_gain, down_ss2))) return rc;
     if (ctx->sync_layers && hipStreamSynchronize(st) != hipSuccess) return HSD_EHIP;
   }
   if (!with_head) return HSD_OK;
@@ -601,7 +621,7 @@ int forward(hsd_ctx *ctx, hipStream_t st, const hsd_kv_pool *pool, const hsd_bat
   }
   const int n_tiles = lm_head_tiles<T>(ctx, Tq);
   EpiLMHead el{ws.lm_part, n_tiles, d.vocab, dump_slot, b->logits_dump, b->tokens, ws.row_end,
-               relaxed ? ws.want_logit : nullptr, rs_fused};
+               relaxed ? ws.want_logit : nullptr, rs_down};
   {
     ProfScope ps(ctx, st, HSD_PROF_GEMM_LM_HEAD);
     if ((rc = launch_gemm<T>(ctx, st, kSiteLM, Tq, d.vocab, d.d_model, ws.h, ctx->lm_head, el))) return rc;

@@ -1,6 +1,6 @@
-"""Kernels chosen for launches of few rows against the general ones, bit for bit: the 16-row tiles of the fp32 path
-against the 64-row ones that a block with enough rows takes.  Every output sums its products in one fixed order in
-both, so the tolerance is zero."""
+"""Kernels chosen for launches of few rows against the general ones, bit for bit: the narrow (32-column) tiles of the
+bf16 projections against a tile set by hand, the 16-row tiles of the fp32 path against the 64-row ones that a block
+with enough rows takes.  Every output sums its products in one fixed order in all of them, so the tolerance is zero."""
 import numpy as np
 import pytest
 
@@ -22,6 +22,17 @@ def _round(desc, weights, seed, draft, debug=None):
     res = out.argmax.cpu().numpy().copy(), out.margin.cpu().numpy().copy(), out.logits.cpu().numpy().copy()
     eng.close()
     return res
+
+
+@pytest.mark.parametrize("rows", [1, 31, 32, 33, 65, 225])
+def test_narrow_tiles_match_the_general_tile(rows):
+    desc, seed = W.ModelDesc(3, 256, 8, 2, 64, 512, 1024, "bf16"), 17
+    weights = W.make_weights(desc, seed)
+    draft = np.random.default_rng(rows).integers(0, desc.vocab, size=rows - 1).astype(np.int32)
+    chosen = _round(desc, weights, seed, draft)
+    for cfg in (2, 12):
+        for a, b in zip(chosen, _round(desc, weights, seed, draft, {"gemm_cfg": (cfg, cfg, cfg, cfg, 0)})):
+            np.testing.assert_array_equal(a, b)
 
 
 @pytest.mark.parametrize("rows", [1, 15, 17, 64])
