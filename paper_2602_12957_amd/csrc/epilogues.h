@@ -165,7 +165,12 @@ __device__ __forceinline__ float sum8_lanes(float v) {
 // x += A W^T as EpiResidual, and everything the RMSNorm after it needs (see RowScale): h = x * gain
 // in the GEMM operand type and the sum of squares of each 64-column piece of the row.  With gain == nullptr (no
 // norm follows: last layer of a prefill) only x is updated.  MFMA kernels only.
-struct EpiResidualNorm {
+// HALF: the narrow tile's form.  Such a tile holds half of a piece (columns 0-15 and 32-47, or 16-31 and 48-63: four
+// lanes) and stores that half's sum, the first in ss, the second in ss2.  A type of its own, so that the wide tiles'
+// epilogues carry nothing of it: decided at run time it cost O 0.1 to 0.4 and down 0.1 to 0.5 us per launch at 1 k to
+// 6.5 k rows, and the persistent 256x256 kernel two spilled registers.
+template <bool HALF>
+struct EpiResidualNormT {
   static constexpr bool kDual = false;
   static constexpr bool kRowScale = false;
   float *x;
@@ -173,8 +178,7 @@ struct EpiResidualNorm {
   const float *gain;  // [ld] gain of the norm that follows, or nullptr
   bf16 *h;            // [M][ld]
   float *ss;          // [M][ld / 64]
-  float *ss2 = nullptr;   // [M][ld / 64], narrow tiles only: a tile holds half of a piece (columns 0-15 and 32-47, or
-                          //   16-31 and 48-63: four lanes) and stores that half's sum, the first in ss, the second here
+  float *ss2;         // [M][ld / 64], HALF only
   static constexpr int kPiece = 4;
   __device__ __forceinline__ void piece(int m, int n, float (&lo)[4], float (&hi)[4]) const {
     float *p = x + static_cast<size_t>(m) * ld + n;
@@ -201,16 +205,18 @@ struct EpiResidualNorm {
     bf16 *hp = h + static_cast<size_t>(m) * ld + n;
     *reinterpret_cast<bf16x4 *>(hp) = __builtin_convertvector(h0, bf16x4);
     *reinterpret_cast<bf16x4 *>(hp + 32) = __builtin_convertvector(h1, bf16x4);
-    if (ss2 != nullptr) {
+    if constexpr (HALF) {
       sq = sum4_lanes(sq);
       if ((n & 15) == 0) ((n & 16) ? ss2 : ss)[static_cast<size_t>(m) * (ld >> 6) + (n >> 6)] = sq;
-      return;
+    } else {
+      // the 8 lanes n % 64 / 4 = 0..7 of this row hold the 64-column piece between them
+      sq = sum8_lanes(sq);
+      if ((n & 63) == 0) ss[static_cast<size_t>(m) * (ld >> 6) + (n >> 6)] = sq;
     }
-    // the 8 lanes n % 64 / 4 = 0..7 of this row hold the 64-column piece between them
-    sq = sum8_lanes(sq);
-    if ((n & 63) == 0) ss[static_cast<size_t>(m) * (ld >> 6) + (n >> 6)] = sq;
   }
 };
+using EpiResidualNorm = EpiResidualNormT<false>;
+using EpiResidualHalf = EpiResidualNormT<true>;
 
 // u = silu(A Wg^T) * (A Wu^T), written in the GEMM operand type.
 template <typename T>

@@ -391,7 +391,8 @@ int launch_gemm(const hsd_ctx *ctx, hipStream_t st, int site, int M, int N, int 
           return launch_gemm_mfma_d<GemmCfgD64n>(st, M, N, K, A, W, epi);
         break;
       case 14:
-        if constexpr (GemmModeOf<Epi>::value == kModeNormal)
+        // (the residual projections' narrow launch has an epilogue of its own and does not come this way)
+        if constexpr (GemmModeOf<Epi>::value == kModeNormal && !std::is_same<Epi, EpiResidualNorm>::value)
           return launch_gemm_mfma_d<GemmCfgD32n>(st, M, N, K, A, W, epi);
         break;
       default: return launch_gemm_mfma<GemmCfg0>(st, M, N, K, A, W, epi);
@@ -563,7 +564,11 @@ int forward(hsd_ctx *ctx, hipStream_t st, const hsd_kv_pool *pool, const hsd_bat
       int rc2;
       if constexpr (std::is_same<T, bf16>::value) {
         if (mfma_path) {
-          EpiResidualNorm en{ws.x, d.d_model, next_gain, static_cast<bf16 *>(ws.h), ws.ss, ss2};
+          if (ss2 != nullptr) {   // narrow tiles (see o_ss2 below)
+            EpiResidualHalf eh{ws.x, d.d_model, next_gain, static_cast<bf16 *>(ws.h), ws.ss, ss2};
+            return launch_gemm_mfma_d<GemmCfgD32n>(st, Tq, d.d_model, K, A, W, eh);
+          }
+          EpiResidualNorm en{ws.x, d.d_model, next_gain, static_cast<bf16 *>(ws.h), ws.ss, nullptr};
           rc2 = launch_gemm<T>(ctx, st, site, Tq, d.d_model, K, A, W, en);
           return rc2;
         }
