@@ -1,13 +1,16 @@
 """Kernels chosen for launches of few rows against the general ones, bit for bit: the narrow (32-column) tiles of the
 bf16 projections against a tile set by hand, the 16-row tiles of the fp32 path against the 64-row ones that a block
-with enough rows takes.  Every output sums its products in one fixed order in all of them, so the tolerance is zero."""
+with enough rows takes at every projection.  Every output sums its products in one fixed order in all of them, so the
+tolerance is zero.  And the plain kernels on a bf16 model against the oracle, with the bar of the bf16 parity tests."""
 import numpy as np
 import pytest
+import torch
 
+import oracle as O
 import workloads as W
 from workloads.generators import SequenceSpec
 
-from hsd_testlib import make_engine, prefix_rows
+from hsd_testlib import gated_compare_argmax, make_engine, prefix_rows
 
 pytestmark = pytest.mark.gpu
 
@@ -35,12 +38,62 @@ def test_narrow_tiles_match_the_general_tile(rows):
             np.testing.assert_array_equal(a, b)
 
 
-@pytest.mark.parametrize("rows", [1, 15, 17, 64])
-def test_fp32_small_tiles_match_the_large_block(rows):
-    """1040 rows x 1024 gate/up columns or vocabulary entries are 17 x 16 tiles of 64 rows, one per compute unit and more."""
-    desc, seed = W.ModelDesc(2, 128, 4, 1, 64, 1024, 1024, "fp32"), 19
+@pytest.mark.parametrize("rows", [1, 33])
+@pytest.mark.parametrize("d_model", [2048, 2176])
+def test_row_sums_of_a_wide_model_with_one_head(rows, d_model):
+    """One head of 64: the narrow tiles' second plane of row sums (d_model / 64 floats a row) fills q and the attention
+    output exactly at d_model 2048 and does not fit at 2176, where the wider tile has to be taken."""
+    desc, seed = W.ModelDesc(2, d_model, 1, 1, 64, 128, 512, "bf16"), 23
     weights = W.make_weights(desc, seed)
-    draft = np.random.default_rng(3).integers(0, desc.vocab, size=1039).astype(np.int32)
-    large, small = _round(desc, weights, seed, draft), _round(desc, weights, seed, draft[:rows - 1])
-    for a, b in zip(large, small):
-        np.testing.assert_array_equal(a[:rows], b)
+    draft = np.random.default_rng(rows).integers(0, desc.vocab, size=rows - 1).astype(np.int32)
+    for a, b in zip(_round(desc, weights, seed, draft), _round(desc, weights, seed, draft, {"gemm_cfg": (2, 2, 2, 2, 0)})):
+        np.testing.assert_array_equal(a, b)
+
+
+LARGE_FP32 = W.ModelDesc(1, 1024, 16, 4, 64, 1024, 1024, "fp32")
+
+
+@pytest.fixture(scope="module")
+def large_block():
+    """A block long enough that every projection of the fp32 model takes 64-row tiles (the last tile has 16 rows)."""
+    desc, seed = LARGE_FP32, 19
+    n_cu = torch.cuda.get_device_properties(0).multi_processor_count
+    n = 64 * -(-n_cu // 16) + 16
+    qkv = (desc.n_q_heads + 2 * desc.n_kv_heads) * desc.head_dim
+    for cols in (qkv, desc.d_model, desc.d_ffn, desc.vocab):
+        assert cols // 64 * -(-n // 64) >= n_cu
+    weights = W.make_weights(desc, seed)
+    draft = np.random.default_rng(3).integers(0, desc.vocab, size=n - 1).astype(np.int32)
+    return weights, seed, draft, _round(desc, weights, seed, draft)
+
+
+@pytest.mark.parametrize("first, rows", [(0, 1), (0, 15), (0, 64), (500, 17), (1008, 32)])
+def test_fp32_small_tiles_match_the_large_block(large_block, first, rows):
+    """Rows first .. first + rows - 1 of the large block, scored on top of the rows before them, which come in 64 at a
+    time: 16-row tiles at every projection, in the K/V they leave as in the rows compared."""
+    desc = LARGE_FP32
+    weights, seed, draft, large = large_block
+    spec = SequenceSpec(0, 37, 3, len(draft), 0.0)
+    eng = make_engine(desc, weights, [spec], max_total_q=64, max_dump=64)
+    _, _, tok, emb, pending = prefix_rows(desc, seed, spec)
+    block = np.concatenate([[pending], draft]).astype(np.int32)
+    eng.prefill([0], [tok], [emb])
+    if first:
+        eng.prefill([0], [block[:first]], chunk=64)
+    out = eng.verify([0], [block[first:first + rows]], "region", dump_rows=np.arange(rows))
+    for a, b in zip(large, (out.argmax, out.margin, out.logits)):
+        np.testing.assert_array_equal(a[first:first + rows], b.cpu().numpy())
+    eng.close()
+
+
+@pytest.mark.parametrize("rows", [1, 33])
+def test_plain_kernels_on_a_bf16_model(rows):
+    desc, seed = W.ModelDesc(3, 256, 8, 2, 64, 512, 1024, "bf16"), 29
+    weights = W.make_weights(desc, seed)
+    vis, prompt = W.make_prefix(desc, seed, 0, 37, 3)
+    draft = np.random.default_rng(rows).integers(0, desc.vocab, size=rows - 1).astype(np.int32)
+    cache, pending = O.prefill(desc, weights, vis, prompt)
+    _, _, u_hat, ref = O.verify_block(desc, weights, cache, pending, draft)
+    argmax, _, logits = _round(desc, weights, seed, draft, {"force_simple": 1})
+    assert np.abs(logits - ref).max() <= 2e-2
+    assert len(gated_compare_argmax(argmax, u_hat, O.top2_margin(ref))[0]) == 0
