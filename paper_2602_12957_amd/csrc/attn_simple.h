@@ -58,7 +58,7 @@ __global__ void __launch_bounds__(256) k_attn_simple(int n_q_heads, RowMeta meta
     l = l * corr + wave_sum(pj);
     acc *= corr;
     // the values of eight keys are requested before the first is used (a key without a block reads block 0 and is left
-    // out); one at a time, each key cost a memory latency (72 us for 132 rows over 271 to 303 keys)
+    // out); one at a time, each key cost a memory latency (132 rows of 4 heads over 272 to 304 keys: 74.5 -> 50.3 us)
     const int lim = min(kWave, n_keys - j0);
     for (int j8 = 0; j8 < lim; j8 += 8) {
       float vv[8];

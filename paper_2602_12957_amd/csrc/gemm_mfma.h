@@ -10,7 +10,8 @@
 // The kernel is written on two K-contiguous matrices P (MFMA "i" side) and Q ("j" side).  In the 32x32
 // result tile, lane l holds column j = l % 32 and rows i = 8*(v/4) + 4*(l/32) + v%4 for register v.
 //  - normal mode  (P = activations, Q = weights): a lane owns one output column and many rows; two adjacent
-//    N sub-tiles of a wave are columns n and n+32 of the same head -> rotary pairs stay in one lane.
+//    N sub-tiles of a wave are columns n and n+32 of the same head -> rotary pairs stay in one lane.  (The narrow
+//    form has one sub-tile: 16 columns and the 16 that lie 32 further on; pairs meet in the epilogue's staging.)
 //  - swapped mode (P = weights, Q = activations): a lane owns one token and many vocabulary entries, so
 //    the LM-head arg-max folds in registers with no cross-lane traffic.
 //  - dual mode: the Q tile alternates 32 gate rows and 32 up rows, so gate and up of the same output
@@ -175,9 +176,11 @@ __device__ __forceinline__ void gemm_epilogue(floatx16 (&acc)[Cfg::TM][Cfg::TN],
     // Accumulators go through LDS to turn the MFMA result layout (a lane owns one COLUMN of 16 scattered rows)
     // into row pieces of PC = Epi::kPiece columns: in every 64-column group of a 32-row sub-tile, the 32/PC lanes
     // l % (32/PC) of a row own columns PC*(l % (32/PC)) .. +PC-1 and their partners 32 further on (rotary pairs;
-    // gate/up pairs in dual mode), so that adjacent lanes write adjacent 16-byte pieces of one row.  Each wave
-    // uses a private region (32 rows of TN*32 + 4 floats); LDS executes a wave's accesses in program order, so
-    // only the compiler has to be kept from reordering them (wave-scope fences).
+    // gate/up pairs in dual mode), so that adjacent lanes write adjacent 16-byte pieces of one row.  In the narrow form
+    // staged columns 0-15 are output columns n0 .. n0+15 and 16-31 are n0+32 .. n0+47: 16/PC lanes own a row, and a
+    // column's partner is staged 16 further on.  Each wave uses a private region (32 rows of TN*32 + 4 floats); LDS
+    // executes a wave's accesses in program order, so only the compiler has to be kept from reordering them (wave-scope
+    // fences).
     constexpr int ST = Cfg::kEpiStride, PC = Epi::kPiece;
     constexpr int PART = Cfg::kNarrow ? 16 : 32;            // columns between a staged column and its partner
     constexpr int LPR = PART / PC, RPI = 64 / LPR;          // lanes per row, rows per pass

@@ -30,8 +30,9 @@ __device__ __forceinline__ void load8(const bf16 *p, float *out) {
 // launch).  The next K slab is requested before the current one is multiplied, and operands are read from LDS four k
 // at a time (rows of 36 floats: 16-byte aligned, and 16 consecutive rows spread over the banks).  Every output still
 // sums its products one by one in ascending k, so neither TR nor the slab width changes a bit.
-// 4 blocks of 33 rows on the two-layer d256 fp32 model: the down projection was 74 us on 12 workgroups (one k at a time
-// from LDS, slab loads exposed); with k_attn_simple's change the whole pass went from 560 to 305 us.
+// 4 blocks of 33 rows on the two-layer d256 fp32 model, down projection (12 workgroups of 64-row tiles, 36 of 16-row
+// ones) and whole pass in us, each step on top of the one before: 77.4 and 576 with exposed slab loads and one k at a
+// time from LDS; the next slab requested early 73.2 and 563; four k at a time 52.8 and 493; 16-row tiles 24.2 and 359.
 template <typename T, typename Epi, int TR>
 __global__ void __launch_bounds__(256) k_gemm_simple(int M, int N, int K, const T *__restrict__ A,
                                                      const T *__restrict__ W, Epi epi) {

@@ -240,7 +240,8 @@ using GemmCfgD128 = GemmCfgD<128, 128, 4, 4>;
 // 12 = the same kernel with ONE multiplying wave on a 32x64 tile (token-by-token decoding, see effective_gemm_cfg)
 using GemmCfgD32 = GemmCfgD<32, 64, 6, 2, 1, 1>;
 using GemmCfgD64n = GemmCfgD<64, 64, 6, 2, 2, 1>;   // 13: two multiplying waves on a 64x64 tile
-using GemmCfgD32n = GemmCfgD<32, 32, 8, 2, 1, 1>;   // 14: half a 64-column group per workgroup (never selected by hand)
+using GemmCfgD32n = GemmCfgD<32, 32, 8, 2, 1, 1>;   // 14: half a 64-column group per workgroup (not in dual mode; never
+                                                    //     selected by hand)
 
 
 // Narrow tiles keep a second plane of row sums (EpiResidualNorm::ss2) in the q or the attention-output buffer.
@@ -274,9 +275,12 @@ int effective_gemm_cfg(const hsd_ctx *ctx, int site, int M, int N, int K) {
     const int64_t cu_n = ctx->n_cu > 0 ? ctx->n_cu : 256;
     const int64_t cols64 = ((site == kSiteGateUp ? 2 * static_cast<int64_t>(N) : N) + 63) / 64;
     if (site == kSiteLM) cfg = M <= 128 ? 0 : cfg;
-    // ... and half as wide again (14) where that too stays within one workgroup per unit: a pass over 1 row of the
-    // 24-layer model 1398 -> 1314 us, a step of 16 rows 1429 -> 1314, 7 blocks of up to 48 rows 1677 -> 1565 (all with
-    // 12 before).  Not gate/up, whose 64-column tiles are 128 workgroups already.
+    // ... and half as wide again (14) where that too stays within one workgroup per unit.  24-layer model, 12 against 14:
+    // down 17.9 -> 15.7 us at 1 row, 21.1 -> 16.5 at 128, 21.3 -> 16.7 at 256; O 9.2 -> 8.6, 10.6 -> 9.3, 10.9 -> 9.4; QKV
+    // 10.4 -> 9.7 at 1, 11.9 -> 10.7 at 128 (events around each launch).  The launches that add up two planes of row sums
+    // pay 0.1 to 0.5 us (gate/up) and up to 2 (LM head at 256 rows) of it back.  A pass over 1 row 1380 -> 1319 us, a
+    // step of 16 rows 1425 -> 1313, 7 blocks of up to 48 rows 1660 -> 1566.  Not gate/up: the dual mode has no narrow
+    // form (its weight tile alternates 32 gate rows and 32 up rows).
     else if (site != kSiteGateUp && static_cast<int64_t>((M + 31) / 32) * cols64 * 2 <= cu_n && narrow_ok(ctx->desc)) cfg = 14;
     else if (static_cast<int64_t>((M + 31) / 32) * cols64 <= cu_n) cfg = 12;
     else if (static_cast<int64_t>((M + 63) / 64) * cols64 <= cu_n) cfg = 13;
@@ -348,7 +352,8 @@ int launch_gemm(const hsd_ctx *ctx, hipStream_t st, int site, int M, int N, int 
             const int m_main = static_cast<int>(256 * r_main);
             const int rc = launch_gemm_mfma8(st, m_main, N, K, A, W, epi, ctx->n_cu);
             if (rc != HSD_OK) return rc;
-            // the narrowest tile that still gives at most one workgroup per compute unit (see effective_gemm_cfg)
+            // the narrowest tile, from 32x64 on, that still gives at most one workgroup per compute unit (see
+            // effective_gemm_cfg; not 32x32: the main launch and every reader work with one plane of row sums)
             const int64_t cols64 = (w_cols + 63) / 64;
             if (((rem + 31) / 32) * cols64 <= cu) return launch_gemm_mfma_d<GemmCfgD32>(st, M, N, K, A, W, epi, m_main);
             if (((rem + 63) / 64) * cols64 <= cu) return launch_gemm_mfma_d<GemmCfgD64n>(st, M, N, K, A, W, epi, m_main);
@@ -402,7 +407,11 @@ int launch_gemm(const hsd_ctx *ctx, hipStream_t st, int site, int M, int N, int 
     return HSD_EINVAL;   // this epilogue exists for the MFMA kernels only (the caller never gets here with it)
   } else {
     // 16-row tiles while 64-row ones would not give every compute unit a workgroup: a workgroup's walk over K sets the
-    // launch's time then, and it is shorter with fewer rows.  Same bits either way.
+    // launch's time then, and it is shorter with fewer rows, although each multiply-add takes more LDS reads.  Same bits
+    // either way.  16-row / 64-row tiles in us, by the number of 64-row tiles: 32 (down, d_model 256) 24 / 52; 240 to
+    // 252, just below the line, gate/up 24 / 29, QKV 18 / 23, down 50 / 56, QKV of d_model 1024 47 / 58; 256 to 384 gate/up
+    // 30 / 36 and 33 / 36, at d_model 1024 77 / 99 and 110 / 124; 512 gate/up 42 / 38, at d_model 1024 143 / 127, LM head
+    // 31 / 30; 1024 LM head 52 / 44.  They cross between 1.5 and 2 tiles per unit: the line is on the safe side of it.
     const int64_t n64 = static_cast<int64_t>(N / 64) * ((M + 63) / 64);
     if (n64 < (ctx->n_cu > 0 ? ctx->n_cu : 256)) {
       hipLaunchKernelGGL((k_gemm_simple<T, Epi, 2>), dim3(N / 64, (M + 15) / 16), dim3(256), 0, st, M, N, K,
