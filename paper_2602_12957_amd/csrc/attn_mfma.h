@@ -59,8 +59,15 @@ struct __attribute__((aligned(32))) AttnTile {
   int32_t slot;         // state row (seq_len / block_table row)
   int32_t S, base, Lq;  // cached length, first row and number of rows of the sequence's block
   int32_t y;            // kv head * (head groups per kv head) + head group
-  int32_t pad;
+  int32_t pack;         // k_attn_wide only: 4 * (index of the set among the tile's head sets) + log2(heads per set)
 };
+
+// Query sets of k_attn_wide.  A set is 32 columns: 2^lhp query heads of 32 >> lhp rows each, as many heads as the rows of
+// the sequence leave room for, so that short blocks read K and V once for several heads.  g4 = query heads of a kv head
+// among the sets of a tile (1, 2 or 4); a tile of 32 rows (or the whole short block) is g4 >> lhp sets, and the sets of a
+// sequence are numbered tile by tile.
+__host__ __device__ inline int attn_wide_lhp(int Lq, int g4) { return (g4 == 4 && Lq <= 8) ? 2 : (g4 >= 2 && Lq <= 16) ? 1 : 0; }
+__host__ __device__ inline int attn_wide_sets(int Lq, int g4) { return ((Lq + 31) / 32) * (g4 >> attn_wide_lhp(Lq, g4)); }
 
 constexpr int kAttnMaxGroups = 1024;   // task groups placed by the balancing pass (more: plain order)
 // Workgroups in the launch for `max_tiles` query tiles (an upper bound known on the host), `n_y` head groups and
@@ -70,6 +77,8 @@ __host__ __device__ inline int attn_grid_size(int max_tiles, int n_y, int sub_ti
 }
 
 // Task table of an attention launch: tasks[i] is the task of workgroup i, for i < n_wg = attn_grid_size(...).
+// wide_g4 = 0: a task is a tile of q_tile rows.  wide_g4 > 0 (k_attn_wide): a task is a query set (see attn_wide_lhp);
+// "tile" below then means a set, q_tile is 32.
 //
 // Placement.  Workgroup i runs on XCD i % 8 (workgroups go to the 8 XCDs round robin), and each XCD has its own L2.
 // The tiles of one sequence and kv head read the same K/V, so they should meet in one L2: tasks are grouped by
@@ -84,7 +93,7 @@ __host__ __device__ inline int attn_grid_size(int max_tiles, int n_y, int sub_ti
 __global__ void __launch_bounds__(1024) k_attn_tiles(int n_seq, const int32_t *__restrict__ cu_q,
                                                      const int32_t *__restrict__ seq_slot, int n_slots,
                                                      const int32_t *__restrict__ seq_len, int q_tile, int n_y,
-                                                     int sub_tiles, int n_wg, AttnTile *__restrict__ tasks) {
+                                                     int sub_tiles, int n_wg, int wide_g4, AttnTile *__restrict__ tasks) {
   __shared__ int s_cnt[HSD_MAX_SEQ];      // per sequence: groups (or tiles) before it, after the scan
   __shared__ int s_part[1024];
   __shared__ int g_work[kAttnMaxGroups], g_key[kAttnMaxGroups], g_n[kAttnMaxGroups];
@@ -92,32 +101,41 @@ __global__ void __launch_bounds__(1024) k_attn_tiles(int n_seq, const int32_t *_
   __shared__ int g_bin[kAttnMaxGroups], g_pos[kAttnMaxGroups];
   const int t = threadIdx.x;
   const AttnTile none{-1, 0, 0, 0, 0, 0, 0, 0};
+  auto tiles_of = [&](int Lq) { return wide_g4 > 0 ? attn_wide_sets(Lq, wide_g4) : (Lq + q_tile - 1) / q_tile; };
+  auto task_of = [&](int s, int tile, int slot, int S, int base, int Lq, int y) {
+    if (wide_g4 <= 0) return AttnTile{s, tile, slot, S, base, Lq, y, 0};
+    const int lhp = attn_wide_lhp(Lq, wide_g4), sets = wide_g4 >> lhp;
+    return AttnTile{s, tile / sets, slot, S, base, Lq, y, 4 * (tile % sets) + lhp};
+  };
   for (int i = t; i < n_wg; i += blockDim.x) tasks[i] = none;
   for (int s = t; s < n_seq; s += blockDim.x) {
-    const int tiles = (cu_q[s + 1] - cu_q[s] + q_tile - 1) / q_tile;
+    const int tiles = tiles_of(cu_q[s + 1] - cu_q[s]);
     s_cnt[s] = n_y * ((tiles + sub_tiles - 1) / sub_tiles);
   }
   __syncthreads();   // also: the padding above is complete before any task is written
   const int n_groups = block_exclusive_scan_4096(s_cnt, n_seq, s_part);
   if (n_groups > kAttnMaxGroups) {
     __syncthreads();
-    for (int s = t; s < n_seq; s += blockDim.x) s_cnt[s] = (cu_q[s + 1] - cu_q[s] + q_tile - 1) / q_tile;
+    for (int s = t; s < n_seq; s += blockDim.x) s_cnt[s] = tiles_of(cu_q[s + 1] - cu_q[s]);
     __syncthreads();
     block_exclusive_scan_4096(s_cnt, n_seq, s_part);
     for (int s = t; s < n_seq; s += blockDim.x) {
       const int slot = slot_of(seq_slot, s, n_slots), base = cu_q[s], Lq = cu_q[s + 1] - base;
-      const int tiles = (Lq + q_tile - 1) / q_tile, S = seq_len[slot];
+      const int tiles = tiles_of(Lq), S = seq_len[slot];
       for (int k = 0; k < tiles; ++k)
         for (int y = 0; y < n_y; ++y) {
           const int i = (s_cnt[s] + k) * n_y + y;
-          if (i < n_wg) tasks[i] = AttnTile{s, tiles - 1 - k, slot, S, base, Lq, y, 0};
+          if (i < n_wg) tasks[i] = task_of(s, tiles - 1 - k, slot, S, base, Lq, y);
         }
     }
     return;
   }
   // group t of the batch: sequence s, head group y = local % n_y, tiles [t0, t1) with t0 = (local / n_y) * sub_tiles
   int gs = 0, gy = 0, t0 = 0, t1 = 0, slot = 0, S = 0, base = 0, Lq = 0;
-  auto stages_of = [&](int tile) { return (S + min((tile + 1) * q_tile, Lq) + kAttnKeys - 1) / kAttnKeys; };
+  auto stages_of = [&](int tile) {
+    const int rt = wide_g4 > 0 ? tile / (wide_g4 >> attn_wide_lhp(Lq, wide_g4)) : tile;
+    return (S + min((rt + 1) * q_tile, Lq) + kAttnKeys - 1) / kAttnKeys;
+  };
   if (t < n_groups) {
     int lo = 0, hi = n_seq - 1;   // last sequence whose first group is <= t (every sequence has at least one)
     while (lo < hi) {
@@ -132,7 +150,7 @@ __global__ void __launch_bounds__(1024) k_attn_tiles(int n_seq, const int32_t *_
     base = cu_q[gs];
     Lq = cu_q[gs + 1] - base;
     t0 = (local / n_y) * sub_tiles;
-    t1 = min(t0 + sub_tiles, (Lq + q_tile - 1) / q_tile);
+    t1 = min(t0 + sub_tiles, tiles_of(Lq));
     int w = 0;
     for (int tile = t0; tile < t1; ++tile) w += stages_of(tile);
     g_work[t] = w;
@@ -192,7 +210,7 @@ __global__ void __launch_bounds__(1024) k_attn_tiles(int n_seq, const int32_t *_
   if (t < n_groups) {
     for (int k = 0; k < t1 - t0; ++k) {   // heaviest tile first
       const int i = 8 * (g_pos[t] + k) + g_bin[t];
-      if (i < n_wg) tasks[i] = AttnTile{gs, t1 - 1 - k, slot, S, base, Lq, gy, 0};
+      if (i < n_wg) tasks[i] = task_of(gs, t1 - 1 - k, slot, S, base, Lq, gy);
     }
   }
 }

@@ -13,6 +13,7 @@
 #include "../../include/hsd.h"
 #include "attn_mfma.h"
 #include "attn_simple.h"
+#include "attn_wide.h"
 #include "common.h"
 #include "epilogues.h"
 #include "gemm_mfma.h"
@@ -488,7 +489,7 @@ int launch_attention(const hsd_ctx *ctx, hipStream_t st, const hsd_batch *b, con
       bf16 *o = static_cast<bf16 *>(ws.a);
       if (kv.layer == 0) {  // the task table depends on the batch only: built once per pass
         hipLaunchKernelGGL(k_attn_tiles, dim3(1), dim3(1024), 0, st, b->n_seq, b->cu_q, b->seq_slot, b->n_slots,
-                           b->seq_len, q_tile, n_y, sub_tiles, n_wg, ws.attn_tiles);
+                           b->seq_len, q_tile, n_y, sub_tiles, n_wg, 0, ws.attn_tiles);
         HSD_LAUNCH_CHECK();
       }
       // Key split (desc.attn_key_chunk > 0): one workgroup per (query tile, chunk of keys); no sequence can hold
@@ -504,6 +505,28 @@ int launch_attention(const hsd_ctx *ctx, hipStream_t st, const hsd_batch *b, con
       const bool tree = meta.row_end != nullptr;
       int rc = HSD_OK;
 #define HSD_ATTN_CASE(G4, QS)                                                                                      \
+// Query sets of a k_attn_wide launch at most, over every way `total_q` rows can be dealt to `n_seq` blocks: g4 sets a
+// 32-row tile; and with g4 = 4 a block of L rows has at most 1 + 7 (L - 1) / 32 (1 up to 8 rows, 2 up to 16, 4 up to 32,
+// 8 at 33, where the bound is met, 4 more every 32 rows).
+int attn_wide_max_sets(int total_q, int n_seq, int g4) {
+  const int64_t by_tile = static_cast<int64_t>(g4) * (total_q / 32 + n_seq);
+  const int64_t by_row = n_seq + (int64_t{7} * (total_q - n_seq) + 31) / 32;
+  return static_cast<int>(g4 == 4 ? std::min(by_tile, by_row) : by_tile);
+}
+
+template <bool TREE>
+int launch_attn_wide(hipStream_t st, int n_wg, int n_q_heads, int g4, const AttnTile *tiles, const PagedKV &kv, const bf16 *q,
+                     bf16 *o, const int32_t *row_end) {
+  constexpr size_t smem = sizeof(AttnWideLds);
+  auto kern = k_attn_wide<TREE>;
+  static const hipError_t attr_rc = hipFuncSetAttribute(reinterpret_cast<const void *>(kern),
+                                                        hipFuncAttributeMaxDynamicSharedMemorySize, smem);
+  if (attr_rc != hipSuccess) return HSD_EHIP;
+  hipLaunchKernelGGL(kern, dim3(n_wg), dim3(64 * (kAttnWideScorers + 4)), smem, st, n_q_heads, g4, tiles, kv, q, o, row_end);
+  HSD_LAUNCH_CHECK();
+  return HSD_OK;
+}
+
   if (g4 == G4 && qs == QS) {                                                                                      \
     if (tree && chunk > 0) rc = launch_attn_mfma<G4, QS, true, true>(st, grid_z, ctx->n_cu, d.n_q_heads, ws.attn_tiles, kv, q, o, meta.row_end, sp);       \
     else if (tree) rc = launch_attn_mfma<G4, QS, true, false>(st, grid_z, ctx->n_cu, d.n_q_heads, ws.attn_tiles, kv, q, o, meta.row_end, sp);             \
@@ -518,6 +541,32 @@ int launch_attention(const hsd_ctx *ctx, hipStream_t st, const hsd_batch *b, con
         hipLaunchKernelGGL(k_attn_merge, dim3(static_cast<unsigned>((n_thr + 255) / 256)), dim3(256), 0, st,
                            d.n_q_heads, meta.row_slot, sp, o);
         HSD_LAUNCH_CHECK();
+      }
+      // Few query sets: the keys of each are spread over a workgroup's waves (k_attn_wide; same bits, so the choice may
+      // follow the batch).  Its workgroups read K and V once per head where k_attn_mfma's read them once per four, so it
+      // loses when the chip is full.  Launch times in us, k_attn_mfma / k_attn_wide (events, 16 heads on 4 kv heads, 1055
+      // keys), by query sets: 4 (one token) 18.5 / 14.9, 4096 keys 47.7 / 33.5; 16 (1 block of 32 rows) 21.0 / 14.9; 128
+      // 21.9 / 15.5; 256 21.0 / 16.0; 208 (a block of 401) 23.7 / 20.0; 512: 8 blocks of 128 rows 21.6 / 20.0, 32 of 32
+      // 22.4 / 22.3, 64 of 16 24.8 / 25.5, 512 keys 15.7 / 15.5; 624 (3 of 401) 24.3 / 27.5; 1056 29 / 40.  The line is at
+      // 2.25 sets per compute unit of what a batch of this size can be expected to have: half a tile lost per block.
+      const int64_t rows = b->total_q, n = b->n_seq;
+      const int64_t by_tile = g4 * (2 * rows + 32 * n) / 64, by_row = n + (rows - n) / 8;
+      const int64_t sets = (g4 == 4 ? std::min(by_tile, by_row) : by_tile) * n_y;
+      const int64_t cu = ctx->n_cu > 0 ? ctx->n_cu : 256;
+      if (d.attn_key_chunk == 0 && 4 * sets <= 9 * cu) {
+        const int max_sets = attn_wide_max_sets(b->total_q, b->n_seq, g4);
+        const int sub_sets = 8;   // two 32-row tiles of four heads share an XCD
+        const int n_wg = attn_grid_size(max_sets, n_y, sub_sets);
+        if (kv.layer == 0) {
+          hipLaunchKernelGGL(k_attn_tiles, dim3(1), dim3(1024), 0, st, b->n_seq, b->cu_q, b->seq_slot, b->n_slots,
+                             b->seq_len, 32, n_y, sub_sets, n_wg, g4, ws.attn_tiles);
+          HSD_LAUNCH_CHECK();
+        }
+        const bf16 *q = static_cast<const bf16 *>(ws.q);
+        bf16 *o = static_cast<bf16 *>(ws.a);
+        return meta.row_end != nullptr
+                   ? launch_attn_wide<true>(st, n_wg, d.n_q_heads, g4, ws.attn_tiles, kv, q, o, meta.row_end)
+                   : launch_attn_wide<false>(st, n_wg, d.n_q_heads, g4, ws.attn_tiles, kv, q, o, nullptr);
       }
       return HSD_OK;
     }

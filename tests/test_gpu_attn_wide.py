@@ -1,0 +1,68 @@
+"""k_attn_wide (passes of few query sets) against k_attn_mfma, bit for bit: the same blocks scored alone and in one
+batch with a block so long that the pass takes the general kernel.  Both kernels run the same instructions on a row's
+keys in the same order, so the tolerance is zero.  Block lengths around the set sizes (8, 16, 32 rows), cached lengths
+around the 64-key groups and the 256-key steps, chains and packed trees, every grouping of query heads."""
+import numpy as np
+import pytest
+import torch
+
+import workloads as W
+from paper_2602_12957_amd.runtime import Engine
+
+pytestmark = pytest.mark.gpu
+
+BLOCKS = [(0, 1), (1, 8), (55, 9), (63, 1), (64, 16), (191, 65), (192, 17), (255, 1), (256, 7), (511, 33), (513, 2), (1300, 32)]
+
+
+def _tree(rng, rows):
+    """(tokens, end, depth) of a random packed tree of `rows` nodes in pre-order."""
+    depth = np.zeros(rows, np.int32)
+    for i in range(1, rows):
+        depth[i] = rng.integers(max(1, depth[i - 1] - 2), depth[i - 1] + 2)
+    end = np.array([next((j for j in range(i + 1, rows) if depth[j] <= depth[i]), rows) for i in range(rows)], np.int32)
+    return rng.integers(0, 256, size=rows).astype(np.int32), end, depth
+
+
+@pytest.mark.parametrize("tree", [False, True])
+@pytest.mark.parametrize("n_q, n_kv", [(16, 4), (8, 1), (4, 2), (2, 2)])
+def test_wide_attention_matches_the_general_kernel(n_q, n_kv, tree):
+    desc = W.tiny_model(2, 128, n_q, n_kv, 64, 128, 256, "bf16")
+    weights = W.make_weights(desc, 41)
+    rng = np.random.default_rng(n_q + 100 * tree)
+    n_cu = torch.cuda.get_device_properties(0).multi_processor_count
+    long_rows = 32 * (3 * n_cu // n_q + 1)     # more than 2.25 query sets per compute unit on its own
+    n = len(BLOCKS)
+    blocks, trees = [], []
+    for _, rows in BLOCKS + [(0, long_rows)]:
+        if tree and rows < long_rows:
+            tok, end, dep = _tree(rng, rows)
+        else:
+            tok = rng.integers(0, desc.vocab, size=rows).astype(np.int32)
+            end, dep = np.full(rows, rows, np.int32), np.arange(rows, dtype=np.int32)
+        blocks.append(tok)
+        trees.append((end, dep))
+    rows = sum(len(b) for b in blocks[:n])
+    maxb = max(max((s + r) // 16 + 2 for s, r in BLOCKS), long_rows // 16 + 2)
+    pool = sum((s + len(b)) // 16 + 2 for (s, _), b in zip(BLOCKS + [(0, 0)], blocks))
+    eng = Engine(desc, weights, pool, n + 1, maxb, rows + long_rows, rows)
+    cached = [i for i in range(n) if BLOCKS[i][0]]
+    eng.prefill(cached, [rng.integers(0, desc.vocab, size=BLOCKS[i][0]).astype(np.int32) for i in cached])
+    eng.snapshot()
+
+    def score(members):
+        eng.restore()
+        out = eng.verify(members, [blocks[i] for i in members], "region", dump_rows=np.arange(rows), log_tau=-0.3,
+                         trees=[trees[i] for i in members] if tree else None)
+        return [x[:rows].cpu().numpy().copy() for x in (out.logits, out.argmax, out.margin, out.gap)]
+
+    general = score(list(range(n + 1)))
+    for a, b in zip(general, score(list(range(n)))):
+        np.testing.assert_array_equal(a, b)
+    at = 0
+    for i in range(n):                          # each block alone as well: other set counts, other task tables
+        eng.restore()
+        out = eng.verify([i], [blocks[i]], "region", dump_rows=np.arange(len(blocks[i])), log_tau=-0.3, trees=[trees[i]] if tree else None)
+        np.testing.assert_array_equal(general[0][at:at + len(blocks[i])], out.logits.cpu().numpy(), err_msg=str(BLOCKS[i]))
+        at += len(blocks[i])
+    assert int(eng.status.item()) == 0
+    eng.close()
