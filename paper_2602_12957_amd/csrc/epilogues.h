@@ -20,14 +20,23 @@ struct RowScale {
   const float *ss;   // [rows][n_parts] partial sums of squares, or nullptr: the operand is already normalised
   int n_parts;       // d_model / 64
   float inv_d, eps;
-  const float *ss2 = nullptr;   // narrow tiles left each piece as two sums (ss, ss2); added here as sum8_lanes adds them
+  // Narrow tiles left each piece as two or four sums: the first in ss, the others in planes of this stride from ss2 on
+  // (the row count times n_parts).  They are added here in the order sum8_lanes adds them.
+  const float *ss2 = nullptr;
+  int n_sums = 1;
+  int plane = 0;
   __device__ __forceinline__ float at(int m) const {
     if (ss == nullptr) return 1.0f;
     const float *p = ss + static_cast<size_t>(m) * n_parts;
     float s = 0.f;
-    if (ss2 != nullptr) {
+    if (n_sums > 1) {
       const float *p2 = ss2 + static_cast<size_t>(m) * n_parts;
-      for (int i = 0; i < n_parts; ++i) s += p[i] + p2[i];
+      if (n_sums == 2) {
+        for (int i = 0; i < n_parts; ++i) s += p[i] + p2[i];
+      } else {
+        const float *p3 = p2 + plane, *p4 = p3 + plane;
+        for (int i = 0; i < n_parts; ++i) s += (p[i] + p2[i]) + (p3[i] + p4[i]);
+      }
     } else {
       for (int i = 0; i < n_parts; ++i) s += p[i];
     }
@@ -148,11 +157,14 @@ struct EpiResidual {
   }
 };
 
-// Sum over the 8 adjacent lanes that hold one 64-column piece of a row (lanes 8k .. 8k+7), or over the 4 that hold half
-// of one (sum8_lanes is the sum of its halves' sum4_lanes, bit for bit), by lane-crossing moves
+// Sum over the 8 adjacent lanes that hold one 64-column piece of a row (lanes 8k .. 8k+7), over the 4 that hold half of
+// one or the 2 that hold a quarter (each is the sum of its halves' sums, bit for bit), by lane-crossing moves
 // inside the vector unit; every lane ends up with the same bits (the additions pair up commutatively).
+__device__ __forceinline__ float sum2_lanes(float v) {
+  return v + __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0xB1, 0xf, 0xf, true));   // quad_perm [1,0,3,2]
+}
 __device__ __forceinline__ float sum4_lanes(float v) {
-  v += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0xB1, 0xf, 0xf, true));   // quad_perm [1,0,3,2]
+  v = sum2_lanes(v);
   v += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x4E, 0xf, 0xf, true));   // quad_perm [2,3,0,1]
   return v;
 }
@@ -165,11 +177,11 @@ __device__ __forceinline__ float sum8_lanes(float v) {
 // x += A W^T as EpiResidual, and everything the RMSNorm after it needs (see RowScale): h = x * gain
 // in the GEMM operand type and the sum of squares of each 64-column piece of the row.  With gain == nullptr (no
 // norm follows: last layer of a prefill) only x is updated.  MFMA kernels only.
-// HALF: the narrow tile's form.  Such a tile holds half of a piece (columns 0-15 and 32-47, or 16-31 and 48-63: four
-// lanes) and stores that half's sum, the first in ss, the second in ss2.  A type of its own, so that the wide tiles'
-// epilogues carry nothing of it: decided at run time it cost O 0.1 to 0.4 and down 0.1 to 0.5 us per launch at 1 k to
+// SUMS > 1: the narrow tiles' forms.  Such a tile holds half of a piece (columns 0-15 and 32-47, or 16-31 and 48-63: four
+// lanes) or a quarter (columns 8i .. 8i+7 and their partners: two lanes) and stores that part's sum, the first in ss, the
+// others in their planes from ss2 on.  Types of their own, so that the wide tiles' epilogues carry nothing of it: decided at run time it cost O 0.1 to 0.4 and down 0.1 to 0.5 us per launch at 1 k to
 // 6.5 k rows, and the persistent 256x256 kernel two spilled registers.
-template <bool HALF>
+template <int SUMS>
 struct EpiResidualNormT {
   static constexpr bool kDual = false;
   static constexpr bool kRowScale = false;
@@ -178,7 +190,8 @@ struct EpiResidualNormT {
   const float *gain;  // [ld] gain of the norm that follows, or nullptr
   bf16 *h;            // [M][ld]
   float *ss;          // [M][ld / 64]
-  float *ss2;         // [M][ld / 64], HALF only
+  float *ss2;         // SUMS - 1 planes [M][ld / 64], `plane` floats apart
+  int plane;
   static constexpr int kPiece = 4;
   __device__ __forceinline__ void piece(int m, int n, float (&lo)[4], float (&hi)[4]) const {
     float *p = x + static_cast<size_t>(m) * ld + n;
@@ -205,9 +218,12 @@ struct EpiResidualNormT {
     bf16 *hp = h + static_cast<size_t>(m) * ld + n;
     *reinterpret_cast<bf16x4 *>(hp) = __builtin_convertvector(h0, bf16x4);
     *reinterpret_cast<bf16x4 *>(hp + 32) = __builtin_convertvector(h1, bf16x4);
-    if constexpr (HALF) {
-      sq = sum4_lanes(sq);
-      if ((n & 15) == 0) ((n & 16) ? ss2 : ss)[static_cast<size_t>(m) * (ld >> 6) + (n >> 6)] = sq;
+    if constexpr (SUMS > 1) {
+      sq = SUMS == 2 ? sum4_lanes(sq) : sum2_lanes(sq);
+      constexpr int COLS = 32 / SUMS;   // columns of a part up to their partners
+      const int part = (n & 31) / COLS;
+      float *dst = part == 0 ? ss : ss2 + static_cast<size_t>(part - 1) * plane;
+      if (n % COLS == 0) dst[static_cast<size_t>(m) * (ld >> 6) + (n >> 6)] = sq;
     } else {
       // the 8 lanes n % 64 / 4 = 0..7 of this row hold the 64-column piece between them
       sq = sum8_lanes(sq);
@@ -215,8 +231,9 @@ struct EpiResidualNormT {
     }
   }
 };
-using EpiResidualNorm = EpiResidualNormT<false>;
-using EpiResidualHalf = EpiResidualNormT<true>;
+using EpiResidualNorm = EpiResidualNormT<1>;
+using EpiResidualHalf = EpiResidualNormT<2>;
+using EpiResidualQuarter = EpiResidualNormT<4>;
 
 // u = silu(A Wg^T) * (A Wu^T), written in the GEMM operand type.
 template <typename T>

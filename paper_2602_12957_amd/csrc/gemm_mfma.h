@@ -10,8 +10,7 @@
 // The kernel is written on two K-contiguous matrices P (MFMA "i" side) and Q ("j" side).  In the 32x32
 // result tile, lane l holds column j = l % 32 and rows i = 8*(v/4) + 4*(l/32) + v%4 for register v.
 //  - normal mode  (P = activations, Q = weights): a lane owns one output column and many rows; two adjacent
-//    N sub-tiles of a wave are columns n and n+32 of the same head -> rotary pairs stay in one lane.  (The narrow
-//    form has one sub-tile: 16 columns and the 16 that lie 32 further on; pairs meet in the epilogue's staging.)
+//    N sub-tiles of a wave are columns n and n+32 of the same head -> rotary pairs stay in one lane.
 //  - swapped mode (P = weights, Q = activations): a lane owns one token and many vocabulary entries, so
 //    the LM-head arg-max folds in registers with no cross-lane traffic.
 //  - dual mode: the Q tile alternates 32 gate rows and 32 up rows, so gate and up of the same output
@@ -42,12 +41,7 @@ struct GemmCfg {
   static constexpr int kLoadsP = BP * kChunks / kThreads, kLoadsQ = BQ * kChunks / kThreads;
   static constexpr int kEpiStride = TN * 32 + 4;              // floats per row of a wave's epilogue staging region
   static_assert(WM * WN * 32 * kEpiStride * 4 <= kSmemBytes, "epilogue staging must fit in the operand stages");
-  // BQ = 32 (one wave column) is the narrow form: two 16-column runs 32 apart, i.e. half of a 64-column group with the
-  // partners of its columns, 32 further on (see gemm_q_col), for launches bound by how many compute units stream the
-  // weights
-  static constexpr bool kNarrow = BQ == 32;
-  static_assert(BP % (WM * 32) == 0 && (BQ % (WN * 64) == 0 || (kNarrow && WN == 1)),
-                "wave tile must be made of 32-row / 64-col groups");
+  static_assert(BP % (WM * 32) == 0 && BQ % (WN * 64) == 0, "wave tile must be made of 32-row / 64-col groups");
   static_assert(BP * kChunks % kThreads == 0 && BQ * kChunks % kThreads == 0, "tile loads must divide evenly");
 };
 
@@ -67,16 +61,6 @@ __device__ __forceinline__ void xcd_tile(int pid, int tiles_fast, int n_tiles, i
 __device__ __forceinline__ void gemm_tile_of(int pid, int M, int w_rows, int tiles_act, int tiles_w, int &ta, int &tw) {
   if (M >= 4 * w_rows) xcd_tile(pid, tiles_w, tiles_act * tiles_w, tw, ta);
   else xcd_tile(pid, tiles_act, tiles_act * tiles_w, ta, tw);
-}
-
-// First output column of weight tile tw (normal mode), and the column of the tile's Q row r relative to it.
-template <typename Cfg>
-__device__ __forceinline__ int gemm_q_col0(int tw) {
-  return Cfg::kNarrow ? (tw >> 1) * 64 + (tw & 1) * 16 : tw * Cfg::BQ;
-}
-template <typename Cfg>
-__device__ __forceinline__ int gemm_q_col(int r) {
-  return Cfg::kNarrow ? (r & 15) + (r >> 4) * 32 : r;
 }
 
 // Tile counts for (M, N) in a mode: activation tiles first, weight tiles second.
@@ -176,15 +160,11 @@ __device__ __forceinline__ void gemm_epilogue(floatx16 (&acc)[Cfg::TM][Cfg::TN],
     // Accumulators go through LDS to turn the MFMA result layout (a lane owns one COLUMN of 16 scattered rows)
     // into row pieces of PC = Epi::kPiece columns: in every 64-column group of a 32-row sub-tile, the 32/PC lanes
     // l % (32/PC) of a row own columns PC*(l % (32/PC)) .. +PC-1 and their partners 32 further on (rotary pairs;
-    // gate/up pairs in dual mode), so that adjacent lanes write adjacent 16-byte pieces of one row.  In the narrow form
-    // staged columns 0-15 are output columns n0 .. n0+15 and 16-31 are n0+32 .. n0+47: 16/PC lanes own a row, and a
-    // column's partner is staged 16 further on.  Each wave uses a private region (32 rows of TN*32 + 4 floats); LDS
+    // gate/up pairs in dual mode), so that adjacent lanes write adjacent 16-byte pieces of one row.  Each wave uses a private region (32 rows of TN*32 + 4 floats); LDS
     // executes a wave's accesses in program order, so only the compiler has to be kept from reordering them (wave-scope
     // fences).
     constexpr int ST = Cfg::kEpiStride, PC = Epi::kPiece;
-    constexpr int PART = Cfg::kNarrow ? 16 : 32;            // columns between a staged column and its partner
-    constexpr int LPR = PART / PC, RPI = 64 / LPR;          // lanes per row, rows per pass
-    constexpr int JG = Cfg::kNarrow ? 1 : TN / 2;
+    constexpr int LPR = 32 / PC, RPI = 64 / LPR;            // lanes per row, rows per pass
     float *wst = stage + (wi * Cfg::WN + wj) * 32 * ST;
     const int pc = lane % LPR, pr = lane / LPR;
 #pragma unroll
@@ -205,13 +185,13 @@ __device__ __forceinline__ void gemm_epilogue(floatx16 (&acc)[Cfg::TM][Cfg::TN],
         float rsc = 1.0f;
         if constexpr (Epi::kRowScale) rsc = rsl[wi * (BP / Cfg::WM) + i * 32 + r];
 #pragma unroll
-        for (int jg = 0; jg < JG; ++jg) {
+        for (int jg = 0; jg < TN / 2; ++jg) {
           float lo[PC], hi[PC];
           const float *src = wst + r * ST + jg * 64 + PC * pc;
 #pragma unroll
           for (int q = 0; q < PC / 4; ++q) {
             const floatx4 a = *reinterpret_cast<const floatx4 *>(src + 4 * q);
-            const floatx4 b = *reinterpret_cast<const floatx4 *>(src + PART + 4 * q);
+            const floatx4 b = *reinterpret_cast<const floatx4 *>(src + 32 + 4 * q);
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
               lo[4 * q + e] = Epi::kRowScale ? a[e] * rsc : a[e];

@@ -33,7 +33,7 @@ struct GemmCfgD : GemmCfg<BP_, BQ_, 64, WM_, WN_> {
   static constexpr int kStageBytes = (BP_ + BQ_) * 64 * 2;         // P rows, then Q rows, 128 bytes each
   static constexpr int kSmemBytes = STAGES_ * kStageBytes;         // operand stages; kRowScaleBytes more follow them
   static constexpr int kLoads = (BP_ + BQ_) / 8;                   // load instructions per slice (8 rows each)
-  static constexpr int kMulWaves = WM_ * WN_;                      // multiplying waves: 2 x 2, or 1 x 1 for tiny row counts
+  static constexpr int kMulWaves = WM_ * WN_;                      // multiplying waves
   static constexpr int kThreadsD = 64 * (WM_ * WN_ + LW_);         // the multiplying waves and the requesting ones
   static_assert((LW_ == 1 || LW_ == 2 || LW_ == 4) && ((BP_ + BQ_) / 8) % LW_ == 0, "requests divide evenly over the waves");
   static_assert((BP_ / 8) % LW_ == 0, "every request slot of a wave is all P or all Q");
@@ -61,7 +61,7 @@ __device__ __forceinline__ void lds_load16(__amdgpu_buffer_rsrc_t rs, LdsBytePtr
 template <typename Cfg, int MODE, typename Epi>
 __global__ void __launch_bounds__(Cfg::kThreadsD) k_gemm_mfma_d(int M, int N, int K, int m_base, const bf16 *__restrict__ A,
                                                      const bf16 *__restrict__ W, Epi epi) {
-  static_assert(MODE == kModeNormal || (MODE == kModeDual && !Cfg::kNarrow), "normal or dual mode");
+  static_assert(MODE == kModeNormal || MODE == kModeDual, "normal or dual mode");
   constexpr int BP = Cfg::BP, BQ = Cfg::BQ, BK = Cfg::BK, TM = Cfg::TM, TN = Cfg::TN, S = Cfg::kStages;
   constexpr int ROWB = BK * 2, LW = Cfg::kLoaderWaves, NL = Cfg::kLoads / LW;   // NL: requests per wave and slice
   extern __shared__ __attribute__((aligned(16))) unsigned char smem_raw[];
@@ -71,7 +71,7 @@ __global__ void __launch_bounds__(Cfg::kThreadsD) k_gemm_mfma_d(int M, int N, in
   int tiles_act, tiles_w, ta, tw;
   gemm_tiles<Cfg, MODE>(M - m_base, N, tiles_act, tiles_w);
   gemm_tile_of(blockIdx.x, M - m_base, (MODE == kModeDual) ? 2 * N : N, tiles_act, tiles_w, ta, tw);
-  const int m0 = m_base + ta * BP, n0 = (MODE == kModeDual) ? tw * (BQ / 2) : gemm_q_col0<Cfg>(tw);
+  const int m0 = m_base + ta * BP, n0 = tw * ((MODE == kModeDual) ? BQ / 2 : BQ);
   const int nk = K / BK;
 
   if (wave >= Cfg::kMulWaves) {
@@ -99,7 +99,7 @@ __global__ void __launch_bounds__(Cfg::kThreadsD) k_gemm_mfma_d(int M, int N, in
         const int wq = r / WNC, tn = (r % WNC) >> 5;
         row = min(((tn & 1) ? N : 0) + n0 + wq * (WNC / 2) + (tn >> 1) * 32 + (r & 31), 2 * N - 1);
       } else {
-        row = min(n0 + gemm_q_col<Cfg>(r), N - 1);
+        row = min(n0 + r, N - 1);
       }
       voff[j] = (row * K + kc * 8) * 2;
     }

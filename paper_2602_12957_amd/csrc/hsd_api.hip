@@ -21,6 +21,7 @@
 #include "gemm_mfma8p.h"
 #include "gemm_mfma_ws.h"
 #include "gemm_mfma_d.h"
+#include "gemm_mfma_r.h"
 #include "probes.h"
 #include "gemm_simple.h"
 #include "misc_kernels.h"
@@ -226,6 +227,21 @@ int launch_gemm_mfma_d(hipStream_t st, int M, int N, int K, const void *A, const
   return HSD_OK;
 }
 
+template <typename Cfg, typename Epi>
+int launch_gemm_mfma_r(hipStream_t st, int M, int N, int K, const void *A, const void *W, Epi epi, int m_base = 0) {
+  constexpr int MODE = GemmModeOf<Epi>::value;
+  auto kern = k_gemm_mfma_r<Cfg, MODE, Epi>;
+  constexpr int smem = Cfg::kSmemBytes + kRowScaleBytes;
+  static const hipError_t attr_rc = hipFuncSetAttribute(reinterpret_cast<const void *>(kern),
+                                                        hipFuncAttributeMaxDynamicSharedMemorySize, smem);
+  if (attr_rc != hipSuccess) return HSD_EHIP;
+  const int tiles = (M - m_base + Cfg::BP - 1) / Cfg::BP * (N / Cfg::kCols / (MODE == kModeDual ? 1 : 2));
+  hipLaunchKernelGGL(kern, dim3(tiles), dim3(Cfg::kThreads), smem, st, M, N, K, m_base, static_cast<const bf16 *>(A),
+                     static_cast<const bf16 *>(W), epi);
+  HSD_LAUNCH_CHECK();
+  return HSD_OK;
+}
+
 // Tile configurations of the MFMA GEMM (hsd_debug_set selects one for experiments; default per call site).
 using GemmCfg0 = GemmCfg<128, 128, 64, 2, 2>;
 using GemmCfg1 = GemmCfg<256, 128, 64, 2, 2>;
@@ -238,15 +254,22 @@ using GemmCfg5 = GemmCfg<128, 128, 64, 4, 2>;   // 8 waves, wave tile 32x64
 // 8 = k_gemm_mfma8, 10 and 11 = k_gemm_mfma_d (64x128 / 128x128 tile, a requesting wave and LDS-direct loads)
 using GemmCfgD64 = GemmCfgD<64, 128, 5, 2>;    // two requesting waves: two independent in-order load streams
 using GemmCfgD128 = GemmCfgD<128, 128, 4, 4>;
-// 12 = the same kernel with ONE multiplying wave on a 32x64 tile (token-by-token decoding, see effective_gemm_cfg)
-using GemmCfgD32 = GemmCfgD<32, 64, 6, 2, 1, 1>;
-using GemmCfgD64n = GemmCfgD<64, 64, 6, 2, 2, 1>;   // 13: two multiplying waves on a 64x64 tile
-using GemmCfgD32n = GemmCfgD<32, 32, 8, 2, 1, 1>;   // 14: half a 64-column group per workgroup (not in dual mode; never
-                                                    //     selected by hand)
+// 12 to 19 = k_gemm_mfma_r (16-row multiplying waves; activation rows x weight rows of a tile), by what a tile reads
+using GemmCfgR24 = GemmCfgR<2, 4, 256, 3>;     // 12: 32 x 64
+using GemmCfgR44 = GemmCfgR<4, 4, 128, 4>;     // 13: 64 x 64
+using GemmCfgR11 = GemmCfgR<1, 1, 512, 4>;     // 14: 16 x 16  (14 and up: never selected by hand)
+using GemmCfgR21 = GemmCfgR<2, 1, 512, 3>;     // 15: 32 x 16
+using GemmCfgR22 = GemmCfgR<2, 2, 256, 4>;     // 16: 32 x 32
+using GemmCfgR42 = GemmCfgR<4, 2, 256, 3>;     // 17: 64 x 32
+using GemmCfgR84 = GemmCfgR<8, 4, 128, 3>;     // 18: 128 x 64
+using GemmCfgR94 = GemmCfgR<9, 4, 128, 3>;     // 19: 144 x 64
 
-
-// Narrow tiles keep a second plane of row sums (EpiResidualNorm::ss2) in the q or the attention-output buffer.
-bool narrow_ok(const hsd_model_desc &d) { return d.n_q_heads * d.head_dim * 2 >= d.d_model / 64 * 4; }
+// Sums per 64-column piece of a residual row that a configuration leaves (see RowScale).  Those past the first lie in
+// planes in the q or the attention-output buffer, whichever is idle until their readers are done.
+int sums_of_cfg(int cfg) { return cfg == 14 || cfg == 15 ? 4 : cfg == 16 || cfg == 17 ? 2 : 1; }
+bool sums_fit(const hsd_model_desc &d, int cfg) {
+  return static_cast<int64_t>(d.n_q_heads) * d.head_dim * 2 >= int64_t{sums_of_cfg(cfg) - 1} * (d.d_model / 64) * 4;
+}
 
 // Tile configuration actually used at a call site for a given problem (the launch and everything sized from the
 // tile shape, like the LM-head partial records, must agree on it).  -1 = plain kernels.
@@ -260,38 +283,39 @@ int effective_gemm_cfg(const hsd_ctx *ctx, int site, int M, int N, int K) {
   // over K plus fixed costs as long as the launch fits the chip in one round, so fewer rows take smaller tiles: more
   // workgroups, each with less arithmetic per K slice (measured per site on the 24-layer model at 16 to 1856 rows).
   if (!ctx->gemm_cfg_forced) {
-    // 9 / 7: 64x128 / 128x128 tiles with four operand-moving waves; 10: the 64x128 tile fed by a requesting wave
-    // (k_gemm_mfma_d).  Measured with operands that come from HBM, as they do inside a pass (24 layers of weights
-    // do not stay in any cache): the requesting-wave kernel wins up to ~512 rows (16 rows, K = 4096: 19.5 us against
-    // 23.7; 512 rows: 20.7 against 25.4) and loses from ~1 k to ~2 k rows (1856 rows: 35.8 against 32.0), although
-    // it wins there too when the operands are cache resident (25.7 against 28.3).
-    // At ~4 k rows the 128x128 tile of the same kernel (11) yields one workgroup per compute unit on the square
-    // projections and wins there (4096 x 1024, K = 4096: 47.3 us against 56.5).
-    // With few rows the weights are all there is to read, from HBM, and a compute unit streams them at a rate that
-    // neither deeper rings nor more requesting waves raise (the down projection's 8 workgroups of 64x128 tiles at 16
-    // rows: 0.34 TB/s): what helps is more compute units, i.e. narrower tiles, as long as the launch stays within one
-    // workgroup per unit -- 32x64 tiles with one multiplying wave (12), else 64x64 with two (13).  Measured with
-    // operands from HBM, K = 4096, N = 1024: 16 rows 15.6 us (64x128: 24.5), 512 rows 18.6 (31.0), 1024 rows 23.6 with
-    // 64x64 (32.4; two-role kernel 30.0); K = 1024, N = 1536: 256 rows 6.8 (8.3), 512 rows 9.9 with 64x64 (12.3).
+    // As long as a launch fits the chip in one round its time is that of one workgroup's bytes through a compute unit's
+    // load path: 50 B/ns whatever the tile (less where they are weights from HBM), plus 3 us.  So every projection takes
+    // the tile that reads least among those that give at most one workgroup per unit, from 16 x 16 (32 KB per 512 of K)
+    // to 144 x 64.  24-layer model, events around each launch (2.5 us more than the trace), us, old tile / this one:
+    //   down (K = 4096)  1 row 15.4 / 9.3, 64 16.1 / 10.7 (16 x 16); 128 16.5 / 12.2 (32 x 16); 256 16.5 / 14.9 (32 x 32);
+    //                    512 22.0 / 18.0 (64 x 32); 1008 25.7 / 24.1 (64 x 64); 1280 32.3 / 30.9, 1856 34.0 / 31.1 (128 x 64)
+    //   O                1 row 8.6 / 7.2, 128 9.2 / 8.3, 512 11.9 / 10.2, 1008 12.9 / 12.2, 1856 16.2 / 15.2
+    //   QKV              1 row 9.8 / 8.8, 64 11.2 / 10.8, 320 12.0 / 11.3, 512 12.8 / 12.5, 1008 15.0 / 14.5, 1280 18.6 / 14.9
+    //   gate/up          32 rows 12.0 / 11.0 (32 x 32), 64 12.0 / 11.4 (32 x 64), 128 13.8 / 13.2, 256 15.0 / 14.3
+    // The other side of the line: gate/up 320 rows 17.7 / 21.4 (128 x 64, 384 tiles), QKV 1856 20.3 / 24.0 (360).
+    // Of the two tiles with 96 rows, 64 x 32 is ahead with K = 4096 (512 rows 18.0 / 20.5) and 32 x 64 in dual mode (11.4 /
+    // 11.9).  Past one round: 9 / 7: 64x128 / 128x128 tiles with four operand-moving waves; 10: the 64x128 tile fed by a
+    // requesting wave (k_gemm_mfma_d), for one row tile.  At ~4 k rows its 128x128 tile (11) yields one workgroup per unit
+    // on the square projections and wins there (4096 x 1024, K = 4096: 47.3 us against 56.5).
     const int64_t cu_n = ctx->n_cu > 0 ? ctx->n_cu : 256;
-    const int64_t cols64 = ((site == kSiteGateUp ? 2 * static_cast<int64_t>(N) : N) + 63) / 64;
+    auto one_round = [&](int c, int rows, int w_rows) {
+      return (static_cast<int64_t>(M) + rows - 1) / rows * ((site == kSiteGateUp ? 2 : 1) * static_cast<int64_t>(N) / w_rows) <= cu_n &&
+             (site == kSiteGateUp ? w_rows >= 32 : sums_fit(ctx->desc, c));
+    };
     if (site == kSiteLM) cfg = M <= 128 ? 0 : cfg;
-    // ... and half as wide again (14) where that too stays within one workgroup per unit.  24-layer model, 12 against 14:
-    // down 17.9 -> 15.7 us at 1 row, 21.1 -> 16.5 at 128, 21.3 -> 16.7 at 256; O 9.2 -> 8.6, 10.6 -> 9.3, 10.9 -> 9.4; QKV
-    // 10.4 -> 9.7 at 1, 11.9 -> 10.7 at 128 (events around each launch).  The launches that add up two planes of row sums
-    // pay 0.1 to 0.5 us (gate/up) and up to 2 (LM head at 256 rows) of it back.  A pass over 1 row 1380 -> 1319 us, a
-    // step of 16 rows 1425 -> 1313, 7 blocks of up to 48 rows 1660 -> 1566.  Not gate/up: the dual mode has no narrow
-    // form (its weight tile alternates 32 gate rows and 32 up rows).
-    else if (site != kSiteGateUp && static_cast<int64_t>((M + 31) / 32) * cols64 * 2 <= cu_n && narrow_ok(ctx->desc)) cfg = 14;
-    else if (static_cast<int64_t>((M + 31) / 32) * cols64 <= cu_n) cfg = 12;
-    else if (static_cast<int64_t>((M + 63) / 64) * cols64 <= cu_n) cfg = 13;
+    else if (one_round(14, 16, 16)) cfg = 14;
+    else if (one_round(15, 32, 16)) cfg = 15;
+    else if (one_round(16, 32, 32)) cfg = 16;
+    else if (site != kSiteGateUp && one_round(17, 64, 32)) cfg = 17;
+    else if (one_round(12, 32, 64)) cfg = 12;
+    else if (one_round(13, 64, 64)) cfg = 13;
+    else if (one_round(18, 128, 64)) cfg = 18;
+    else if (site != kSiteGateUp && one_round(19, 144, 64)) cfg = 19;
     else if (M <= 64) cfg = 10;                                        // one row tile
-    else if (site != kSiteGateUp && M <= 512) cfg = 10;
     else if ((site == kSiteO || site == kSiteDown) && M >= 3072) cfg = 11;
-    else if (site == kSiteQKV) cfg = M <= 1024 ? 9 : 7;
-    else if (site == kSiteO || site == kSiteDown) cfg = 9;   // down walks all of K in one workgroup: small tiles,
-                                                             // so that a pass over ~2 k rows still fills the chip
-    else if (site == kSiteGateUp) cfg = M <= 256 ? 9 : (M <= 1024 ? 7 : cfg);
+    else if (site == kSiteQKV) cfg = 7;
+    else if (site == kSiteO || site == kSiteDown) cfg = 9;
+    else if (site == kSiteGateUp) cfg = M <= 1024 ? 7 : cfg;
   }
   // ... and a pass over many rows (prefill chunks, long-document blocks) has enough row tiles to fill the chip with
   // the 256x256 tile also on the narrower projections (measured crossover: about 6 k rows at N = 1536)
@@ -305,7 +329,7 @@ int effective_gemm_cfg(const hsd_ctx *ctx, int site, int M, int N, int K) {
   // the two-role kernels: not for the swapped LM-head mode
   if ((cfg == 7 || cfg == 9) && site == kSiteLM) cfg = cfg == 7 ? 0 : 2;
   // the LDS-direct kernels: not the swapped mode, 32-bit operand offsets
-  if ((cfg == 10 || cfg == 11 || cfg == 12 || cfg == 13 || cfg == 14) &&
+  if (cfg >= 10 &&
       (site == kSiteLM || static_cast<int64_t>(M) * K * 2 >= (int64_t{1} << 31) ||
        (site == kSiteGateUp ? 2 : 1) * static_cast<int64_t>(N) * K * 2 >= (int64_t{1} << 31)))
     cfg = cfg == 11 ? 0 : 2;
@@ -353,11 +377,12 @@ int launch_gemm(const hsd_ctx *ctx, hipStream_t st, int site, int M, int N, int 
             const int m_main = static_cast<int>(256 * r_main);
             const int rc = launch_gemm_mfma8(st, m_main, N, K, A, W, epi, ctx->n_cu);
             if (rc != HSD_OK) return rc;
-            // the narrowest tile, from 32x64 on, that still gives at most one workgroup per compute unit (see
-            // effective_gemm_cfg; not 32x32: the main launch and every reader work with one plane of row sums)
-            const int64_t cols64 = (w_cols + 63) / 64;
-            if (((rem + 31) / 32) * cols64 <= cu) return launch_gemm_mfma_d<GemmCfgD32>(st, M, N, K, A, W, epi, m_main);
-            if (((rem + 63) / 64) * cols64 <= cu) return launch_gemm_mfma_d<GemmCfgD64n>(st, M, N, K, A, W, epi, m_main);
+            // the tile that reads least among those that stay within one workgroup per compute unit, as in
+            // effective_gemm_cfg, from 64 weight rows on: the main launch and every reader work with one sum per piece
+            const int64_t cols64 = w_cols / 64;
+            if (((rem + 31) / 32) * cols64 <= cu) return launch_gemm_mfma_r<GemmCfgR24>(st, M, N, K, A, W, epi, m_main);
+            if (((rem + 63) / 64) * cols64 <= cu) return launch_gemm_mfma_r<GemmCfgR44>(st, M, N, K, A, W, epi, m_main);
+            if (((rem + 127) / 128) * cols64 <= cu) return launch_gemm_mfma_r<GemmCfgR84>(st, M, N, K, A, W, epi, m_main);
             return launch_gemm_mfma_d<GemmCfgD64>(st, M, N, K, A, W, epi, m_main);
           }
         }
@@ -388,19 +413,22 @@ int launch_gemm(const hsd_ctx *ctx, hipStream_t st, int site, int M, int N, int 
         if constexpr (GemmModeOf<Epi>::value != kModeSwapLM)
           return launch_gemm_mfma_d<GemmCfgD128>(st, M, N, K, A, W, epi);
         break;
-      case 12:
-        if constexpr (GemmModeOf<Epi>::value != kModeSwapLM)
-          return launch_gemm_mfma_d<GemmCfgD32>(st, M, N, K, A, W, epi);
-        break;
-      case 13:
-        if constexpr (GemmModeOf<Epi>::value != kModeSwapLM)
-          return launch_gemm_mfma_d<GemmCfgD64n>(st, M, N, K, A, W, epi);
-        break;
-      case 14:
-        // (the residual projections' narrow launch has an epilogue of its own and does not come this way)
-        if constexpr (GemmModeOf<Epi>::value == kModeNormal && !std::is_same<Epi, EpiResidualNorm>::value)
-          return launch_gemm_mfma_d<GemmCfgD32n>(st, M, N, K, A, W, epi);
-        break;
+#define HSD_CASE_R(c, cfg_t, ok)                                                                       \
+  case c:                                                                                            \
+    if constexpr (GemmModeOf<Epi>::value != kModeSwapLM && !std::is_same<Epi, EpiResidual>::value && (ok)) \
+      return launch_gemm_mfma_r<cfg_t>(st, M, N, K, A, W, epi);                                      \
+    break;
+      // 14 to 17: the residual projections have epilogues of their own there (see residual_proj); 16 weight rows are not
+      // enough for dual mode
+      HSD_CASE_R(12, GemmCfgR24, true)
+      HSD_CASE_R(13, GemmCfgR44, true)
+      HSD_CASE_R(14, GemmCfgR11, Epi::kRowScale && !Epi::kDual)
+      HSD_CASE_R(15, GemmCfgR21, Epi::kRowScale && !Epi::kDual)
+      HSD_CASE_R(16, GemmCfgR22, Epi::kRowScale)
+      HSD_CASE_R(17, GemmCfgR42, Epi::kRowScale && !Epi::kDual)
+      HSD_CASE_R(18, GemmCfgR84, true)
+      HSD_CASE_R(19, GemmCfgR94, !Epi::kDual)
+#undef HSD_CASE_R
       default: return launch_gemm_mfma<GemmCfg0>(st, M, N, K, A, W, epi);
     }
   }
@@ -467,44 +495,6 @@ int launch_attn_mfma(hipStream_t st, dim3 grid, int n_cu, int n_q_heads, const A
   return HSD_OK;
 }
 
-template <typename T>
-int launch_attention(const hsd_ctx *ctx, hipStream_t st, const hsd_batch *b, const RowMeta &meta, const PagedKV &kv,
-                     const Workspace &ws, bool page_mode) {
-  const hsd_model_desc &d = ctx->desc;
-  const int group = d.n_q_heads / d.n_kv_heads;
-  if constexpr (std::is_same<T, bf16>::value) {
-    if (!ctx->force_simple && (group == 1 || group == 2 || group % 4 == 0)) {
-      // Work split, fixed per model and entry point (never chosen from the batch; and one row's arithmetic is the
-      // same in both, so results stay bitwise batch-invariant): g4 query heads of a kv head among the query sets of
-      // a workgroup; 4 query sets for region-level batches (many short blocks: more, smaller workgroups), 8 for
-      // page-level ones (few long blocks: each K/V stage in LDS serves twice the queries).
-      const int g4 = group >= 4 ? 4 : group, qs = page_mode ? 8 : 4;
-      const int q_tile = 32 * (qs / g4);
-      const int max_tiles = b->total_q / q_tile + b->n_seq;
-      const int n_y = d.n_kv_heads * ((group + g4 - 1) / g4);
-      const int sub_tiles = 256 / q_tile;   // tiles of one sequence and head group that share an XCD: 256 rows
-      const int n_wg = attn_grid_size(max_tiles, n_y, sub_tiles);
-      const dim3 grid(n_wg, 1);
-      const bf16 *q = static_cast<const bf16 *>(ws.q);
-      bf16 *o = static_cast<bf16 *>(ws.a);
-      if (kv.layer == 0) {  // the task table depends on the batch only: built once per pass
-        hipLaunchKernelGGL(k_attn_tiles, dim3(1), dim3(1024), 0, st, b->n_seq, b->cu_q, b->seq_slot, b->n_slots,
-                           b->seq_len, q_tile, n_y, sub_tiles, n_wg, 0, ws.attn_tiles);
-        HSD_LAUNCH_CHECK();
-      }
-      // Key split (desc.attn_key_chunk > 0): one workgroup per (query tile, chunk of keys); no sequence can hold
-      // more keys than its block-table row addresses, which bounds the chunks worth launching.
-      const int chunk = d.attn_key_chunk;
-      int n_chunks = 1;
-      if (chunk > 0) {
-        const int64_t max_keys = static_cast<int64_t>(b->max_blocks_per_seq) * HSD_KV_BLOCK_TOKENS;
-        n_chunks = static_cast<int>(std::min<int64_t>(kAttnMaxChunks, (max_keys + chunk - 1) / chunk));
-      }
-      const dim3 grid_z(grid.x, grid.y, n_chunks);
-      const AttnSplit sp{chunk, b->total_q, ws.attn_part_o, ws.attn_part_ml};
-      const bool tree = meta.row_end != nullptr;
-      int rc = HSD_OK;
-#define HSD_ATTN_CASE(G4, QS)                                                                                      \
 // Query sets of a k_attn_wide launch at most, over every way `total_q` rows can be dealt to `n_seq` blocks: g4 sets a
 // 32-row tile; and with g4 = 4 a block of L rows has at most 1 + 7 (L - 1) / 32 (1 up to 8 rows, 2 up to 16, 4 up to 32,
 // 8 at 33, where the bound is met, 4 more every 32 rows).
@@ -527,21 +517,21 @@ int launch_attn_wide(hipStream_t st, int n_wg, int n_q_heads, int g4, const Attn
   return HSD_OK;
 }
 
-  if (g4 == G4 && qs == QS) {                                                                                      \
-    if (tree && chunk > 0) rc = launch_attn_mfma<G4, QS, true, true>(st, grid_z, ctx->n_cu, d.n_q_heads, ws.attn_tiles, kv, q, o, meta.row_end, sp);       \
-    else if (tree) rc = launch_attn_mfma<G4, QS, true, false>(st, grid_z, ctx->n_cu, d.n_q_heads, ws.attn_tiles, kv, q, o, meta.row_end, sp);             \
-    else if (chunk > 0) rc = launch_attn_mfma<G4, QS, false, true>(st, grid_z, ctx->n_cu, d.n_q_heads, ws.attn_tiles, kv, q, o, meta.row_end, sp);        \
-    else rc = launch_attn_mfma<G4, QS, false, false>(st, grid_z, ctx->n_cu, d.n_q_heads, ws.attn_tiles, kv, q, o, meta.row_end, sp);                      \
-  }
-      HSD_ATTN_CASE(4, 4) HSD_ATTN_CASE(4, 8) HSD_ATTN_CASE(2, 4) HSD_ATTN_CASE(2, 8) HSD_ATTN_CASE(1, 4) HSD_ATTN_CASE(1, 8)
-#undef HSD_ATTN_CASE
-      if (rc != HSD_OK) return rc;
-      if (chunk > 0) {
-        const int64_t n_thr = static_cast<int64_t>(d.n_q_heads) * b->total_q * 16;
-        hipLaunchKernelGGL(k_attn_merge, dim3(static_cast<unsigned>((n_thr + 255) / 256)), dim3(256), 0, st,
-                           d.n_q_heads, meta.row_slot, sp, o);
-        HSD_LAUNCH_CHECK();
-      }
+template <typename T>
+int launch_attention(const hsd_ctx *ctx, hipStream_t st, const hsd_batch *b, const RowMeta &meta, const PagedKV &kv,
+                     const Workspace &ws, bool page_mode) {
+  const hsd_model_desc &d = ctx->desc;
+  const int group = d.n_q_heads / d.n_kv_heads;
+  if constexpr (std::is_same<T, bf16>::value) {
+    if (!ctx->force_simple && (group == 1 || group == 2 || group % 4 == 0)) {
+      // Work split, fixed per model and entry point (never chosen from the batch; and one row's arithmetic is the
+      // same in both, so results stay bitwise batch-invariant): g4 query heads of a kv head among the query sets of
+      // a workgroup; 4 query sets for region-level batches (many short blocks: more, smaller workgroups), 8 for
+      // page-level ones (few long blocks: each K/V stage in LDS serves twice the queries).
+      const int g4 = group >= 4 ? 4 : group, qs = page_mode ? 8 : 4;
+      const int q_tile = 32 * (qs / g4);
+      const int max_tiles = b->total_q / q_tile + b->n_seq;
+      const int n_y = d.n_kv_heads * ((group + g4 - 1) / g4);
       // Few query sets: the keys of each are spread over a workgroup's waves (k_attn_wide; same bits, so the choice may
       // follow the batch).  Its workgroups read K and V once per head where k_attn_mfma's read them once per four, so it
       // loses when the chip is full.  Launch times in us, k_attn_mfma / k_attn_wide (events, 16 heads on 4 kv heads, 1055
@@ -567,6 +557,44 @@ int launch_attn_wide(hipStream_t st, int n_wg, int n_q_heads, int g4, const Attn
         return meta.row_end != nullptr
                    ? launch_attn_wide<true>(st, n_wg, d.n_q_heads, g4, ws.attn_tiles, kv, q, o, meta.row_end)
                    : launch_attn_wide<false>(st, n_wg, d.n_q_heads, g4, ws.attn_tiles, kv, q, o, nullptr);
+      }
+      const int sub_tiles = 256 / q_tile;   // tiles of one sequence and head group that share an XCD: 256 rows
+      const int n_wg = attn_grid_size(max_tiles, n_y, sub_tiles);
+      const dim3 grid(n_wg, 1);
+      const bf16 *q = static_cast<const bf16 *>(ws.q);
+      bf16 *o = static_cast<bf16 *>(ws.a);
+      if (kv.layer == 0) {  // the task table depends on the batch only: built once per pass
+        hipLaunchKernelGGL(k_attn_tiles, dim3(1), dim3(1024), 0, st, b->n_seq, b->cu_q, b->seq_slot, b->n_slots,
+                           b->seq_len, q_tile, n_y, sub_tiles, n_wg, 0, ws.attn_tiles);
+        HSD_LAUNCH_CHECK();
+      }
+      // Key split (desc.attn_key_chunk > 0): one workgroup per (query tile, chunk of keys); no sequence can hold
+      // more keys than its block-table row addresses, which bounds the chunks worth launching.
+      const int chunk = d.attn_key_chunk;
+      int n_chunks = 1;
+      if (chunk > 0) {
+        const int64_t max_keys = static_cast<int64_t>(b->max_blocks_per_seq) * HSD_KV_BLOCK_TOKENS;
+        n_chunks = static_cast<int>(std::min<int64_t>(kAttnMaxChunks, (max_keys + chunk - 1) / chunk));
+      }
+      const dim3 grid_z(grid.x, grid.y, n_chunks);
+      const AttnSplit sp{chunk, b->total_q, ws.attn_part_o, ws.attn_part_ml};
+      const bool tree = meta.row_end != nullptr;
+      int rc = HSD_OK;
+#define HSD_ATTN_CASE(G4, QS)                                                                                      \
+  if (g4 == G4 && qs == QS) {                                                                                      \
+    if (tree && chunk > 0) rc = launch_attn_mfma<G4, QS, true, true>(st, grid_z, ctx->n_cu, d.n_q_heads, ws.attn_tiles, kv, q, o, meta.row_end, sp);       \
+    else if (tree) rc = launch_attn_mfma<G4, QS, true, false>(st, grid_z, ctx->n_cu, d.n_q_heads, ws.attn_tiles, kv, q, o, meta.row_end, sp);             \
+    else if (chunk > 0) rc = launch_attn_mfma<G4, QS, false, true>(st, grid_z, ctx->n_cu, d.n_q_heads, ws.attn_tiles, kv, q, o, meta.row_end, sp);        \
+    else rc = launch_attn_mfma<G4, QS, false, false>(st, grid_z, ctx->n_cu, d.n_q_heads, ws.attn_tiles, kv, q, o, meta.row_end, sp);                      \
+  }
+      HSD_ATTN_CASE(4, 4) HSD_ATTN_CASE(4, 8) HSD_ATTN_CASE(2, 4) HSD_ATTN_CASE(2, 8) HSD_ATTN_CASE(1, 4) HSD_ATTN_CASE(1, 8)
+#undef HSD_ATTN_CASE
+      if (rc != HSD_OK) return rc;
+      if (chunk > 0) {
+        const int64_t n_thr = static_cast<int64_t>(d.n_q_heads) * b->total_q * 16;
+        hipLaunchKernelGGL(k_attn_merge, dim3(static_cast<unsigned>((n_thr + 255) / 256)), dim3(256), 0, st,
+                           d.n_q_heads, meta.row_slot, sp, o);
+        HSD_LAUNCH_CHECK();
       }
       return HSD_OK;
     }
@@ -622,13 +650,17 @@ int forward(hsd_ctx *ctx, hipStream_t st, const hsd_kv_pool *pool, const hsd_bat
       int rc2;
       if constexpr (std::is_same<T, bf16>::value) {
         if (mfma_path) {
-          if (ss2 != nullptr) {   // narrow tiles (see o_ss2 below)
-            EpiResidualHalf eh{ws.x, d.d_model, next_gain, static_cast<bf16 *>(ws.h), ws.ss, ss2};
-            return launch_gemm_mfma_d<GemmCfgD32n>(st, Tq, d.d_model, K, A, W, eh);
+          const int plane = Tq * (d.d_model / 64), cfg = effective_gemm_cfg<T>(ctx, site, Tq, d.d_model, K);
+          const EpiResidualHalf eh{ws.x, d.d_model, next_gain, static_cast<bf16 *>(ws.h), ws.ss, ss2, plane};
+          const EpiResidualQuarter e4{ws.x, d.d_model, next_gain, static_cast<bf16 *>(ws.h), ws.ss, ss2, plane};
+          const EpiResidualNorm en{ws.x, d.d_model, next_gain, static_cast<bf16 *>(ws.h), ws.ss, nullptr, 0};
+          switch (cfg) {   // narrow tiles
+            case 14: return launch_gemm_mfma_r<GemmCfgR11>(st, Tq, d.d_model, K, A, W, e4);
+            case 15: return launch_gemm_mfma_r<GemmCfgR21>(st, Tq, d.d_model, K, A, W, e4);
+            case 16: return launch_gemm_mfma_r<GemmCfgR22>(st, Tq, d.d_model, K, A, W, eh);
+            case 17: return launch_gemm_mfma_r<GemmCfgR42>(st, Tq, d.d_model, K, A, W, eh);
           }
-          EpiResidualNorm en{ws.x, d.d_model, next_gain, static_cast<bf16 *>(ws.h), ws.ss, nullptr};
-          rc2 = launch_gemm<T>(ctx, st, site, Tq, d.d_model, K, A, W, en);
-          return rc2;
+          return launch_gemm<T>(ctx, st, site, Tq, d.d_model, K, A, W, en);
         }
       }
       EpiResidual er{ws.x, d.d_model};
@@ -638,14 +670,16 @@ int forward(hsd_ctx *ctx, hipStream_t st, const hsd_kv_pool *pool, const hsd_bat
   };
   const RowScale rs_none{nullptr, 0, 0.f, 0.f};
   const RowScale rs_fused{mfma_path ? ws.ss : nullptr, d.d_model / 64, 1.0f / static_cast<float>(d.d_model), d.rms_eps};
-  // Second plane of the row sums where the output or down projection runs narrow tiles.  It lies in a buffer that is
+  // Further planes of the row sums where the output or down projection runs narrow tiles.  They lie in a buffer that is
   // idle from that projection until its readers are done: the output projection's (read by gate/up) in q, the down
   // projection's (read by the next layer's QKV, which writes q, or by the LM head) in the attention output.
-  float *const o_ss2 = effective_gemm_cfg<T>(ctx, kSiteO, Tq, d.d_model, qdim) == 14 ? static_cast<float *>(ws.q) : nullptr;
-  float *const down_ss2 = effective_gemm_cfg<T>(ctx, kSiteDown, Tq, d.d_model, d.d_ffn) == 14 ? static_cast<float *>(ws.a) : nullptr;
+  const int o_sums = sums_of_cfg(effective_gemm_cfg<T>(ctx, kSiteO, Tq, d.d_model, qdim));
+  const int down_sums = sums_of_cfg(effective_gemm_cfg<T>(ctx, kSiteDown, Tq, d.d_model, d.d_ffn));
+  float *const o_ss2 = static_cast<float *>(ws.q), *const down_ss2 = static_cast<float *>(ws.a);
   RowScale rs_o = rs_fused, rs_down = rs_fused;
-  rs_o.ss2 = o_ss2;
-  rs_down.ss2 = down_ss2;
+  rs_o.ss2 = o_ss2, rs_o.n_sums = o_sums;
+  rs_down.ss2 = down_ss2, rs_down.n_sums = down_sums;
+  rs_o.plane = rs_down.plane = Tq * (d.d_model / 64);
 
   if ((rc = norm(ctx->attn_norm[0]))) return rc;
   for (int l = 0; l < d.n_layers; ++l) {

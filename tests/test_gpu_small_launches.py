@@ -50,6 +50,18 @@ def test_row_sums_of_a_wide_model_with_one_head(rows, d_model):
         np.testing.assert_array_equal(a, b)
 
 
+@pytest.mark.parametrize("rows", [16, 17, 129, 257, 513, 700, 1025, 2049, 4097])
+@pytest.mark.parametrize("d_model, d_ffn", [(256, 512), (384, 640)])
+def test_16_row_tiles_match_the_general_tile(rows, d_model, d_ffn):
+    """Row counts on both sides of the lines between the 16-row kernel's tiles (16 x 16 to 144 x 64) for these widths,
+    and contraction lengths that are whole stages of 512 or 256 (256, 512) or leave a partly filled one (384, 640)."""
+    desc, seed = W.ModelDesc(2, d_model, 8, 2, 64, d_ffn, 512, "bf16"), 31
+    weights = W.make_weights(desc, seed)
+    draft = np.random.default_rng(rows).integers(0, desc.vocab, size=rows - 1).astype(np.int32)
+    for a, b in zip(_round(desc, weights, seed, draft), _round(desc, weights, seed, draft, {"gemm_cfg": (2, 2, 2, 2, 0)})):
+        np.testing.assert_array_equal(a, b)
+
+
 LARGE_FP32 = W.ModelDesc(1, 1024, 16, 4, 64, 1024, 1024, "fp32")
 
 
