@@ -25,21 +25,35 @@ struct RowScale {
   const float *ss2 = nullptr;
   int n_sums = 1;
   int plane = 0;
+  // The parts are read 16 at a time before any is added: one after the other they cost a trip to the cache each, 2.5 us in
+  // front of the epilogue of a launch over one row.
+  template <int SUMS>
+  __device__ __forceinline__ float sum(int m) const {
+    typedef float floatx4u __attribute__((ext_vector_type(4), aligned(4)));
+    const float *p[4];
+    p[0] = ss + static_cast<size_t>(m) * n_parts;
+#pragma unroll
+    for (int q = 1; q < SUMS; ++q) p[q] = ss2 + static_cast<size_t>(q - 1) * plane + static_cast<size_t>(m) * n_parts;
+    auto add = [](float a, float b, float c, float d) { return SUMS == 1 ? a : SUMS == 2 ? a + b : (a + b) + (c + d); };
+    float s = 0.f;
+    int i = 0;
+    for (; i + 16 <= n_parts; i += 16) {
+      floatx4 v[4][SUMS];
+#pragma unroll
+      for (int j = 0; j < 4; ++j)
+#pragma unroll
+        for (int q = 0; q < SUMS; ++q) v[j][q] = *reinterpret_cast<const floatx4u *>(p[q] + i + 4 * j);
+#pragma unroll
+      for (int j = 0; j < 4; ++j)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) s += add(v[j][0][e], v[j][SUMS > 1 ? 1 : 0][e], v[j][SUMS > 2 ? 2 : 0][e], v[j][SUMS > 2 ? 3 : 0][e]);
+    }
+    for (; i < n_parts; ++i) s += add(p[0][i], p[SUMS > 1 ? 1 : 0][i], p[SUMS > 2 ? 2 : 0][i], p[SUMS > 2 ? 3 : 0][i]);
+    return s;
+  }
   __device__ __forceinline__ float at(int m) const {
     if (ss == nullptr) return 1.0f;
-    const float *p = ss + static_cast<size_t>(m) * n_parts;
-    float s = 0.f;
-    if (n_sums > 1) {
-      const float *p2 = ss2 + static_cast<size_t>(m) * n_parts;
-      if (n_sums == 2) {
-        for (int i = 0; i < n_parts; ++i) s += p[i] + p2[i];
-      } else {
-        const float *p3 = p2 + plane, *p4 = p3 + plane;
-        for (int i = 0; i < n_parts; ++i) s += (p[i] + p2[i]) + (p3[i] + p4[i]);
-      }
-    } else {
-      for (int i = 0; i < n_parts; ++i) s += p[i];
-    }
+    const float s = n_sums == 1 ? sum<1>(m) : n_sums == 2 ? sum<2>(m) : sum<4>(m);
     return 1.0f / sqrtf(s * inv_d + eps);
   }
 };
