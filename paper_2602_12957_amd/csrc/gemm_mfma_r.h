@@ -57,8 +57,9 @@ __global__ void __launch_bounds__(Cfg::kThreads) k_gemm_mfma_r(int M, int N, int
   const int t = threadIdx.x, lane = t & 63;
   const int wave = __builtin_amdgcn_readfirstlane(t >> 6);
   const int tiles_act = (M - m_base + BP - 1) / BP;
+  // (the grid is computed, not read: gridDim lies behind the kernel arguments in memory, a read on the way to the first load)
   int ta, tw;
-  xcd_tile(blockIdx.x, tiles_act, gridDim.x, ta, tw);
+  xcd_tile(blockIdx.x, tiles_act, tiles_act * (N / (MODE == kModeDual ? COLS : 2 * COLS)), ta, tw);
   const int m0 = m_base + ta * BP;
   constexpr int GR = CW > 4 ? 1 : 4 / CW;              // tiles of a 64-column group
   const int n0 = (MODE == kModeDual) ? tw * COLS : (CW > 4 ? tw * (CW / 4) * 64 : tw / GR * 64 + tw % GR * COLS);
@@ -125,30 +126,55 @@ __global__ void __launch_bounds__(Cfg::kThreads) k_gemm_mfma_r(int M, int N, int
   for (int c = 0; c < CW; ++c) acc[c] = floatx4{0.f, 0.f, 0.f, 0.f};
   const int fr = lane & 15, kg = lane >> 4;            // operand row; k group of the lane: piece 4 kk + kg of a 32-wide step
   const unsigned char *pa = smem_raw + (wave * 16 + fr) * RB, *pb = smem_raw + (BP + fr) * RB;
+  // Half a stage at a time: the fragments of one half are read while the other half's products run.  A stage's products
+  // are one chain, and a step of read, wait, multiply took 60 cycles of it against 25 without the reads (K = 4096).
+  constexpr int HS = Cfg::SK / 64;                     // 32-wide steps of half a stage
+  bf16x8 fa[2][HS], fb[2][HS][CW];
   int slot = 0;
-  auto mma = [&](int kk) {
-    const int off = slot * Cfg::kStageBytes + (((4 * kk + kg) ^ fr) << 4);
-    const bf16x8 a = *reinterpret_cast<const bf16x8 *>(pa + off);
-#pragma unroll
-    for (int c = 0; c < CW; ++c) {
-      const bf16x8 b = *reinterpret_cast<const bf16x8 *>(pb + c * 16 * RB + off);
-      acc[c] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, acc[c], 0, 0, 0);
+#define HSD_GR_READ(h)                                                                                 \
+  _Pragma("unroll") for (int i = 0; i < HS; ++i) {                                                     \
+    const int off = slot * Cfg::kStageBytes + (((4 * ((h) * HS + i) + kg) ^ fr) << 4);                 \
+    fa[h][i] = *reinterpret_cast<const bf16x8 *>(pa + off);                                            \
+    _Pragma("unroll") for (int c = 0; c < CW; ++c) fb[h][i][c] = *reinterpret_cast<const bf16x8 *>(pb + c * 16 * RB + off); \
+  }                                                                                                    \
+  __builtin_amdgcn_sched_barrier(0);
+#define HSD_GR_MMA(h)                                                                                  \
+  _Pragma("unroll") for (int i = 0; i < HS; ++i) _Pragma("unroll") for (int c = 0; c < CW; ++c)        \
+      acc[c] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fa[h][i], fb[h][i][c], acc[c], 0, 0, 0);        \
+  __builtin_amdgcn_sched_barrier(0);
+  if (nf > 0) {
+    __builtin_amdgcn_s_barrier();                      // barrier 0: stage 0 is complete
+    __builtin_amdgcn_sched_barrier(0);
+    HSD_GR_READ(0)
+    for (int s = 0; s < nf; ++s) {
+      HSD_GR_READ(1)
+      HSD_GR_MMA(0)
+      slot = slot + 1 == S ? 0 : slot + 1;
+      if (s + 1 < nf) {
+        __builtin_amdgcn_s_waitcnt(0xC07F);            // lgkmcnt(0): this wave is done with stage s ...
+        __builtin_amdgcn_s_barrier();                  // ... barrier s + 1: stage s + 1 is complete
+        __builtin_amdgcn_sched_barrier(0);
+        HSD_GR_READ(0)
+      }
+      HSD_GR_MMA(1)
     }
-  };
-  for (int s = 0; s < nf; ++s) {
-    __builtin_amdgcn_s_barrier();                      // barrier s: stage s is complete
-    __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-    for (int kk = 0; kk < Cfg::SK / 32; ++kk) mma(kk);
-    __builtin_amdgcn_sched_barrier(0);
-    slot = slot + 1 == S ? 0 : slot + 1;
   }
   if (nf < ns) {
+    __builtin_amdgcn_s_waitcnt(0xC07F);
     __builtin_amdgcn_s_barrier();
     __builtin_amdgcn_sched_barrier(0);
-    for (int kk = 0; kk < (K - nf * Cfg::SK) / 32; ++kk) mma(kk);
+    for (int kk = 0; kk < (K - nf * Cfg::SK) / 32; ++kk) {
+      const int off = slot * Cfg::kStageBytes + (((4 * kk + kg) ^ fr) << 4);
+      const bf16x8 a = *reinterpret_cast<const bf16x8 *>(pa + off);
+#pragma unroll
+      for (int c = 0; c < CW; ++c)
+        acc[c] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, *reinterpret_cast<const bf16x8 *>(pb + c * 16 * RB + off), acc[c], 0, 0, 0);
+    }
     __builtin_amdgcn_sched_barrier(0);
   }
+#undef HSD_GR_READ
+#undef HSD_GR_MMA
+  __builtin_amdgcn_s_waitcnt(0xC07F);
   __builtin_amdgcn_s_barrier();                        // the epilogue stages through the operand stages
 
   // Result layout: lane l holds column l % 16 (of sub-tile c) and rows 4 (l / 16) + v.  Through LDS to row pieces of
