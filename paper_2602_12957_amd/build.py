@@ -10,6 +10,9 @@ HIPCC_FLAGS = [
     "-O3", "--offload-arch=gfx950", "-std=c++17", "-shared", "-fPIC",
     # hipcc -O3 must not form packed-fp32 instructions on the test machines
     "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
+    # the command processor hands the first kernel arguments to a wave in registers instead of the wave reading them from
+    # memory before it can form its first address
+    "-mllvm", "-amdgpu-kernarg-preload-count=16",
 ]
 
 
