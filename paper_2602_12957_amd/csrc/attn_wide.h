@@ -15,9 +15,11 @@
 // absolute positions, even and odd groups in separate sums, the reference point of a group = the largest seen so far in
 // its parity), so the two kernels give the same bits and the choice between them may follow the batch.
 //
-// Query sets.  A set is 32 columns: 32 rows of one query head, or, where a sequence has few rows, the rows of several
+// Query sets.  A set is QW = 32 columns: 32 rows of one query head, or, where a sequence has few rows, the rows of several
 // query heads of one kv head (16 rows of two heads, 8 rows of four), so that K and V are read once for all of them.  The
-// task table says which (AttnTile::pack).
+// task table says which (AttnTile::pack).  A pass whose every block fits 16 columns (4 rows of four heads: token-by-token
+// decoding) takes QW = 16: half the maxima, exponentials and probabilities, products on 16x16x32 instructions (the same
+// sums as on 32x32x16, see gemm_mfma_r.h).
 #pragma once
 
 #include "attn_mfma.h"
@@ -27,22 +29,43 @@ namespace hsd {
 // LDS: probabilities of two steps of four groups (4 KB a group: [page][lane][8 bf16]), the groups' maxima of two steps, and
 // the odd parity's (O, reference point, sum) for the final fold
 constexpr int kAttnWideScorers = 4;
+template <int QW>
 struct AttnWideLds {
-  uint4 p[2][kAttnWideScorers][4][64];
-  float mg[2][kAttnWideScorers][32];
-  uint16_t k[kAttnWideScorers][64 * kKsStride];   // a scoring wave's own 64 keys
-  float fold[2][18][64];
+  uint4 p[2][kAttnWideScorers][QW / 8][64];
+  float mg[2][kAttnWideScorers][QW];
+  uint16_t k[kAttnWideScorers][64 * kKsStride];   // a scoring wave's own 64 keys (see k_row)
+  float fold[2][QW / 2 + 2][64];
 };
+// Offset of a key's row in AttnWideLds::k: rows 144 B apart, those of odd pages 16 B further, so that the fragment reads of
+// 16 rows (16 keys in a row, or 8 of a page and the same 8 of the next) cover all 64 banks once.
+__device__ __forceinline__ int k_row(int key) { return key * kKsStride + ((key >> 4) & 1) * 8; }
+
+// Exchange with the lanes 16 away (the max and the sum over l and l ^ 16), as half_max and half_sum
+__device__ __forceinline__ float quarter_max(float x) {
+  const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+  return fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1]));
+}
+__device__ __forceinline__ float quarter_sum(float x) {
+  const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+  return __uint_as_float(r[0]) + __uint_as_float(r[1]);
+}
+// Value of the other lane half
+__device__ __forceinline__ float other_half(float x, int half) {
+  const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+  return __uint_as_float(half ? r[0] : r[1]);
+}
 
 // NS scoring waves and four accumulating ones; a step covers NS 64-key groups.
 // grid: attn_grid_size(...) tasks, block 64 * (NS + 4), dynamic LDS sizeof(AttnWideLds).
 // Two barriers a step, executed by every wave: behind the first the maxima of the step's groups are in LDS, behind the
 // second its probabilities.  The accumulating waves work on a step between its second barrier and that of the next step.
-// What bounds it (in-kernel timestamps, one token at 1055 keys, 12 us): 2.2 us until the first scores (descriptor, page
-// ids, keys: three dependent reads from HBM), five steps of 1.2 us (0.25 products, 0.35 maximum, 0.4 exponentials, the
-// rest the unit's load path, which takes 64 KB a step at 64 B a cycle) and 1.1 us of last accumulation, fold and store.
-// Eight scoring waves: 13.4 us (the load path again); keys and values requested two steps ahead: 13.8 us.
-template <bool TREE>
+// What bounds it (in-kernel timestamps, one token at 1055 keys, 10.2 us): 2.6 us until the first scores (descriptor, page
+// ids, keys: three dependent reads), five steps of 1.1 us -- the unit's load path takes 64 KB a step at 64 B a cycle, and a
+// scoring wave stalls in the issue of its requests -- and 1 us of last accumulation, fold and store.  On the way here: 12.3
+// us with 32 columns, 11.5 with 16, 10.2 with pages numbered once per 16 steps instead of a 64-bit product per page and
+// use.  Tried on top: eight scoring waves (32 columns: 13.4 us against 12.1), keys and values two steps ahead (13.8), the
+// next step's products under the exponentials and all LDS reads of a step up front (10.7).
+template <int QW, bool TREE>
 __global__ void __launch_bounds__(64 * (kAttnWideScorers + 4), 4) k_attn_wide(int n_q_heads, int g4, const AttnTile *__restrict__ tiles,
                                                                            PagedKV kv, const bf16 *__restrict__ q,
                                                                            bf16 *__restrict__ out,
@@ -50,7 +73,7 @@ __global__ void __launch_bounds__(64 * (kAttnWideScorers + 4), 4) k_attn_wide(in
   constexpr int NS = kAttnWideScorers;
   static_assert(NS % 4 == 0 && 16 % (NS / 2) == 0, "an even number of groups a step and parity, page ids of whole steps in 64 lanes");
   extern __shared__ __attribute__((aligned(16))) unsigned char smem_raw[];
-  AttnWideLds &sm = *reinterpret_cast<AttnWideLds *>(smem_raw);
+  AttnWideLds<QW> &sm = *reinterpret_cast<AttnWideLds<QW> *>(smem_raw);
 
   typedef const int32_t __attribute__((address_space(4))) *ConstI32;
   const ConstI32 td = (ConstI32)(reinterpret_cast<const int32_t *>(tiles + blockIdx.x));
@@ -59,8 +82,9 @@ __global__ void __launch_bounds__(64 * (kAttnWideScorers + 4), 4) k_attn_wide(in
 
   const int group = n_q_heads / kv.n_kv_heads, hb = (group + g4 - 1) / g4;
   const int kvh = ty / hb, hgrp = ty % hb;
-  const int lhp = pack & 3, rshift = 5 - lhp;                      // 2^lhp heads of 2^rshift rows each
-  const int t = threadIdx.x, lane = t & 63, half = lane >> 5, qj = lane & 31;
+  const int lhp = pack & 3, rshift = (QW == 32 ? 5 : 4) - lhp;     // 2^lhp heads of 2^rshift rows each
+  // QW = 32: operand row / result column l % 32, k group l / 32.  QW = 16: l % 16 and l / 16.
+  const int t = threadIdx.x, lane = t & 63, half = lane >> 5, qj = lane & (QW - 1), kg = lane / QW;
   const int wave = __builtin_amdgcn_readfirstlane(t >> 6);
   const int head = kvh * group + hgrp * g4 + ((pack >> 2) << lhp) + (qj >> rshift);
   const int row0 = tile << rshift, row = row0 + (qj & ((1 << rshift) - 1));
@@ -74,25 +98,30 @@ __global__ void __launch_bounds__(64 * (kAttnWideScorers + 4), 4) k_attn_wide(in
 
   const int32_t *table_row = kv.block_table + static_cast<size_t>(slot) * kv.max_blocks_per_seq;
   const int last_entry = kv.max_blocks_per_seq - 1;
-  // Element offset of the page whose id lane `src` of `ids` holds.  An id out of range (a page beyond the data of this
-  // round, a damaged table) reads block 0 instead; every position such a page could stand for is masked and its V zeroed.
-  auto page_off = [&](int ids, int src) {
-    const int id = __builtin_amdgcn_readlane(ids, src);
-    return kv_block_offset(kv, (id >= 0 && id < kv.n_blocks) ? id : 0, kvh);
+  // Pages are numbered through the pool, (layer, block, kv head); a lane turns the id it fetched into such a number once.  An
+  // id out of range (a page beyond the data of this round, a damaged table) becomes block 0; every position such a page
+  // could stand for is masked and its V zeroed.
+  auto page_number = [&](int entry) {
+    const int id = table_row[min(entry, last_entry)];
+    return (kv.layer * kv.n_blocks + ((id >= 0 && id < kv.n_blocks) ? id : 0)) * kv.n_kv_heads + kvh;
   };
-
+  // element offset of the page whose number lane `src` of `pages` holds
+  auto page_off = [&](int pages, int src) {
+    return static_cast<size_t>(static_cast<uint32_t>(__builtin_amdgcn_readlane(pages, src))) * (kBlk * kHd);
+  };
   if (wave >= 4) {
     // ---- a scoring wave: groups w, w + NS, w + 2 NS, ...
     const int w = wave - 4;
     const bf16 *kpool = static_cast<const bf16 *>(kv.k_pool);
-    Frag8 qf[4];
-    // page ids: lane 4 s + p holds the id of page p of this wave's group in step s0 + s (16 steps at a time)
-    auto fetch_ids = [&](int s0) { return table_row[min(((s0 + (lane >> 2)) * NS + w) * 4 + (lane & 3), last_entry)]; };
-    int ids = fetch_ids(0);
+    constexpr int KQ = QW / 8;   // k-steps over the 64 dims: 4 of 16, or 2 of 32
+    Frag8 qf[KQ];
+    // pages: lane 4 s + p holds the number of page p of this wave's group in step s0 + s (16 steps at a time)
+    auto fetch_pages = [&](int s0) { return page_number(((s0 + (lane >> 2)) * NS + w) * 4 + (lane & 3)); };
+    int pages = fetch_pages(0);
     {
-      const bf16 *qp = q + static_cast<size_t>(base + my_row) * qdim + head * kHd + half * 8;
+      const bf16 *qp = q + static_cast<size_t>(base + my_row) * qdim + head * kHd + kg * 8;
 #pragma unroll
-      for (int kk = 0; kk < 4; ++kk) qf[kk].u = *reinterpret_cast<const uint4 *>(qp + kk * 16);
+      for (int kk = 0; kk < KQ; ++kk) qf[kk].u = *reinterpret_cast<const uint4 *>(qp + kk * (64 / KQ));
     }
     // K of a group: four pages of 2 KB, loaded as they lie (64 lanes read 1 KB in a row; a load in operand order, 32 rows of
     // 128 bytes, takes the address unit 64 cycles instead of 16), turned into operands through the wave's own LDS rows
@@ -100,7 +129,7 @@ __global__ void __launch_bounds__(64 * (kAttnWideScorers + 4), 4) k_attn_wide(in
     auto load_k = [&](int s) {
 #pragma unroll
       for (int pg = 0; pg < 4; ++pg) {
-        const bf16 *kp = kpool + page_off(ids, (s & 15) * 4 + pg) + lane * 8;
+        const bf16 *kp = kpool + page_off(pages, (s & 15) * 4 + pg) + lane * 8;
 #pragma unroll
         for (int c = 0; c < 2; ++c) rk[2 * pg + c] = *reinterpret_cast<const u32x4 *>(kp + c * 512);
       }
@@ -110,7 +139,7 @@ __global__ void __launch_bounds__(64 * (kAttnWideScorers + 4), 4) k_attn_wide(in
       __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");   // LDS runs a wave's accesses in order: only the compiler
       __builtin_amdgcn_wave_barrier();                         // has to be kept from reordering them
 #pragma unroll
-      for (int i = 0; i < 8; ++i) *reinterpret_cast<u32x4 *>(ks + (8 * i + (lane >> 3)) * kKsStride + (lane & 7) * 8) = rk[i];
+      for (int i = 0; i < 8; ++i) *reinterpret_cast<u32x4 *>(ks + k_row(8 * i + (lane >> 3)) + (lane & 7) * 8) = rk[i];
       __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
       __builtin_amdgcn_wave_barrier();
       __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
@@ -121,24 +150,44 @@ __global__ void __launch_bounds__(64 * (kAttnWideScorers + 4), 4) k_attn_wide(in
     float m_run = -INFINITY;   // largest reference point of this wave's parity in the steps so far
     for (int s = 0; s < n_steps; ++s) {
       const int g = s * NS + w, kb = g * 64;
-      floatx16 st[2];
+      // Scores of 64 keys x QW queries: register v of block b is key_of(b, v) of the group.  QW = 16: blocks 2 p and 2 p + 1
+      // cover pages 2 p and 2 p + 1, the keys dealt to the operand rows so that a lane's eight registers of the two are the
+      // eight contraction slots that the second product takes from it.
+      constexpr int NB = QW == 32 ? 2 : 4, NV = QW == 32 ? 16 : 4;
+      auto key_of = [&](int b, int v) {
+        return QW == 32 ? 32 * b + 8 * (v >> 2) + 4 * half + (v & 3) : 32 * (b >> 1) + 8 * (b & 1) + 16 * (kg >> 1) + 4 * (kg & 1) + v;
+      };
+      float st[NB][NV];
       float mi = -INFINITY;
       if (g < n_groups) {
 #pragma unroll
-        for (int b = 0; b < 2; ++b) {
+        for (int b = 0; b < NB; ++b) {
+          if constexpr (QW == 32) {
+            floatx16 acc;
 #pragma unroll
-          for (int v = 0; v < 16; ++v) st[b][v] = 0.f;
+            for (int v = 0; v < 16; ++v) acc[v] = 0.f;
 #pragma unroll
-          for (int kk = 0; kk < 4; ++kk) {
-            const bf16x8 a = *reinterpret_cast<const bf16x8 *>(ks + (b * 32 + qj) * kKsStride + kk * 16 + half * 8);
-            st[b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, qf[kk].v, st[b], 0, 0, 0);
+            for (int kk = 0; kk < 4; ++kk)
+              acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(*reinterpret_cast<const bf16x8 *>(ks + k_row(b * 32 + qj) + kk * 16 + half * 8),
+                                                            qf[kk].v, acc, 0, 0, 0);
+#pragma unroll
+            for (int v = 0; v < NV; ++v) st[b][v] = acc[v];
+          } else {
+            const int key = 32 * (b >> 1) + 8 * (b & 1) + 16 * (qj >> 3) + 4 * ((qj >> 2) & 1) + (qj & 3);
+            floatx4 acc = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+            for (int kk = 0; kk < 2; ++kk)
+              acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(*reinterpret_cast<const bf16x8 *>(ks + k_row(key) + kk * 32 + kg * 8),
+                                                            qf[kk].v, acc, 0, 0, 0);
+#pragma unroll
+            for (int v = 0; v < NV; ++v) st[b][v] = acc[v];
           }
         }
       }
       if (s + 1 < n_steps) {
         store_k();
         if (s + 2 < n_steps) {
-          if (((s + 2) & 15) == 0) ids = fetch_ids(s + 2);
+          if (((s + 2) & 15) == 0) pages = fetch_pages(s + 2);
           load_k(s + 2);
         }
       }
@@ -146,16 +195,13 @@ __global__ void __launch_bounds__(64 * (kAttnWideScorers + 4), 4) k_attn_wide(in
         if constexpr (TREE) {
           if (kb + 63 >= S) {  // the group reaches into the block: tree-ancestry mask (see k_attn_mfma)
 #pragma unroll
-            for (int b = 0; b < 2; ++b) {
-              int e_sub[16];   // half of the keys at a time: the other half's registers decide between one and two workgroups a unit
+            for (int b = 0; b < NB; ++b) {
+              int e_sub[NV];   // a block at a time: the registers of all would decide between one and two workgroups a unit
 #pragma unroll
-              for (int v = 0; v < 16; ++v) {
-                const int kpos = kb + 32 * b + 8 * (v >> 2) + 4 * half + (v & 3);
-                e_sub[v] = row_end[base + min(max(kpos - S, 0), Lq - 1)];
-              }
+              for (int v = 0; v < NV; ++v) e_sub[v] = row_end[base + min(max(kb + key_of(b, v) - S, 0), Lq - 1)];
 #pragma unroll
-              for (int v = 0; v < 16; ++v) {
-                const int kpos = kb + 32 * b + 8 * (v >> 2) + 4 * half + (v & 3);
+              for (int v = 0; v < NV; ++v) {
+                const int kpos = kb + key_of(b, v);
                 const bool vis = (kpos <= pos_j) & ((kpos < S) | (e_sub[v] > base + my_row));
                 st[b][v] = vis ? st[b][v] : -INFINITY;
               }
@@ -163,19 +209,21 @@ __global__ void __launch_bounds__(64 * (kAttnWideScorers + 4), 4) k_attn_wide(in
           }
         } else if (kb + 63 > S + row0) {  // the group reaches past the first query: causal mask
 #pragma unroll
-          for (int b = 0; b < 2; ++b)
+          for (int b = 0; b < NB; ++b)
 #pragma unroll
-            for (int v = 0; v < 16; ++v) {
-              const int kpos = kb + 32 * b + 8 * (v >> 2) + 4 * half + (v & 3);
-              if (kpos > pos_j) st[b][v] = -INFINITY;
-            }
+            for (int v = 0; v < NV; ++v)
+              if (kb + key_of(b, v) > pos_j) st[b][v] = -INFINITY;
         }
-        float mx = fmaxf(st[0][0], st[1][0]);
+        float mx = st[0][0];
 #pragma unroll
-        for (int v = 1; v < 16; ++v) mx = fmaxf(fmaxf(mx, st[0][v]), st[1][v]);
-        mi = ceilf(half_max(mx) * sc);   // integer reference point in the base-2 exponent domain (see k_attn_mfma)
+        for (int b = 0; b < NB; ++b)
+#pragma unroll
+          for (int v = 0; v < NV; ++v) mx = fmaxf(mx, st[b][v]);
+        mx = half_max(mx);
+        if constexpr (QW == 16) mx = quarter_max(mx);
+        mi = ceilf(mx * sc);   // integer reference point in the base-2 exponent domain (see k_attn_mfma)
       }
-      if (half == 0) sm.mg[s & 1][w][qj] = mi;
+      if (kg == 0) sm.mg[s & 1][w][qj] = mi;
       __syncthreads();
       // the reference point at this group: the largest of the parity's groups up to and including it
       float m_new = m_run;
@@ -190,13 +238,16 @@ __global__ void __launch_bounds__(64 * (kAttnWideScorers + 4), 4) k_attn_wide(in
         // a query that has seen no visible key yet: reference point 0 yields p = 0 without producing inf - inf
         const float msc = m_new == -INFINITY ? 0.f : m_new;
 #pragma unroll
-        for (int pg = 0; pg < 4; ++pg) {
+        for (int f = 0; f < QW / 8; ++f) {   // operand f: page f of the group, or pages 2 f and 2 f + 1
           floatx8 pv;
 #pragma unroll
-          for (int e = 0; e < 8; ++e) pv[e] = __builtin_amdgcn_exp2f(fmaf(st[pg >> 1][8 * (pg & 1) + e], sc, -msc));
+          for (int e = 0; e < 8; ++e) {
+            const float x = QW == 32 ? st[f >> 1][8 * (f & 1) + e] : st[2 * f + (e >> 2)][e & 3];
+            pv[e] = __builtin_amdgcn_exp2f(fmaf(x, sc, -msc));
+          }
           Frag8 pf;
           pf.v = __builtin_convertvector(pv, bf16x8);
-          sm.p[s & 1][w][pg][lane] = pf.u;
+          sm.p[s & 1][w][f][lane] = pf.u;
         }
       }
       __syncthreads();
@@ -210,27 +261,49 @@ __global__ void __launch_bounds__(64 * (kAttnWideScorers + 4), 4) k_attn_wide(in
   constexpr int SPF = 16 / KG;                   // steps whose page ids fit 64 lanes: lane (s * KG + k) * 4 + page
   const int i = wave & 1, par = wave >> 1;
   const bf16 *vpool = static_cast<const bf16 *>(kv.v_pool);
-  auto fetch_ids = [&](int s0) {
+  auto fetch_pages = [&](int s0) {
     const int x = lane >> 2;
-    return table_row[min(((s0 + x / KG) * NS + 2 * (x % KG) + par) * 4 + (lane & 3), last_entry)];
+    return page_number(((s0 + x / KG) * NS + 2 * (x % KG) + par) * 4 + (lane & 3));
   };
+  // V operands of a group.  QW = 32: page f, dims 32 i + l % 32, slots 8 (l / 32) ..  QW = 16: pages 2 (f / 2) + l / 32,
+  // dims 32 i + 16 (f % 2) + l % 16, slots 8 (l / 16 % 2) ..
   Frag8 vf[KG][4];
-  int ids = fetch_ids(0);
+  int pages = fetch_pages(0);
   auto load_v = [&](int s, int k) {
+    const int l0 = ((s % SPF) * KG + k) * 4;
+    if constexpr (QW == 32) {
 #pragma unroll
-    for (int pg = 0; pg < 4; ++pg) {
-      const bf16 *vp = vpool + page_off(ids, ((s % SPF) * KG + k) * 4 + pg) + (i * 32 + qj) * kBlk + half * 8;
-      vf[k][pg].u = *reinterpret_cast<const uint4 *>(vp);
+      for (int f = 0; f < 4; ++f)
+        vf[k][f].u = *reinterpret_cast<const uint4 *>(vpool + page_off(pages, l0 + f) + (i * 32 + qj) * kBlk + half * 8);
+    } else {
+#pragma unroll
+      for (int p = 0; p < 2; ++p) {
+        const size_t o0 = page_off(pages, l0 + 2 * p), o1 = page_off(pages, l0 + 2 * p + 1);
+        const bf16 *vp = vpool + (half ? o1 : o0) + (i * 32 + qj) * kBlk + (kg & 1) * 8;
+#pragma unroll
+        for (int d = 0; d < 2; ++d) vf[k][2 * p + d].u = *reinterpret_cast<const uint4 *>(vp + d * 16 * kBlk);
+      }
     }
   };
 #pragma unroll
   for (int k = 0; k < KG; ++k) load_v(0, k);
-  floatx16 o;
+  constexpr int NO = QW / 2;       // accumulators of a lane: 32 dims x QW queries over 64 lanes
+  floatx16 o32;
+  floatx4 o16[2];
 #pragma unroll
-  for (int v = 0; v < 16; ++v) o[v] = 0.f;
+  for (int v = 0; v < 16; ++v) o32[v] = 0.f;
+#pragma unroll
+  for (int v = 0; v < 8; ++v) o16[v >> 2][v & 3] = 0.f;
   float m_run = -INFINITY, l_run = 0.f;
   typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
   const bf16x2 ones = {static_cast<__bf16>(1.0f), static_cast<__bf16>(1.0f)};
+  // the row sum of a lane's eight slots, two per instruction, in ascending order (as in k_attn_mfma)
+  auto add8 = [&](float l, const bf16x8 &x) {
+    l = __builtin_amdgcn_fdot2_f32_bf16(__builtin_shufflevector(x, x, 0, 1), ones, l, false);
+    l = __builtin_amdgcn_fdot2_f32_bf16(__builtin_shufflevector(x, x, 2, 3), ones, l, false);
+    l = __builtin_amdgcn_fdot2_f32_bf16(__builtin_shufflevector(x, x, 4, 5), ones, l, false);
+    return __builtin_amdgcn_fdot2_f32_bf16(__builtin_shufflevector(x, x, 6, 7), ones, l, false);
+  };
 
   auto accumulate = [&](int s, int k) {
     const int w = 2 * k + par, g = s * NS + w;
@@ -239,38 +312,53 @@ __global__ void __launch_bounds__(64 * (kAttnWideScorers + 4), 4) k_attn_wide(in
       // slots of positions that hold no data of this sequence must read as 0 (their probability is 0, but 0 * stale-NaN
       // would poison the product); slot order of a V page: see kv_v_slot
 #pragma unroll
-      for (int pg = 0; pg < 4; ++pg)
+      for (int f = 0; f < 4; ++f)
 #pragma unroll
         for (int e = 0; e < 8; ++e) {
-          const int tok = (e < 4 ? 0 : 4) + 4 * half + e;
-          if (g * 64 + pg * kBlk + tok >= n_valid) vf[k][pg].h[e] = 0;
+          const int page = QW == 32 ? f : 2 * (f >> 1) + half, hf = QW == 32 ? half : (kg & 1);
+          const int tok = (e < 4 ? 0 : 4) + 4 * hf + e;
+          if (g * 64 + page * kBlk + tok >= n_valid) vf[k][f].h[e] = 0;
         }
     }
     const float m_new = fmaxf(m_run, sm.mg[s & 1][w][qj]);
     if (__any(m_new != m_run)) {
       const float corr = (m_run == -INFINITY) ? 0.f : ldexpf(1.0f, static_cast<int>(m_run - m_new));
       l_run *= corr;
+      if constexpr (QW == 32) {
 #pragma unroll
-      for (int v = 0; v < 16; ++v) o[v] *= corr;
+        for (int v = 0; v < 16; ++v) o32[v] *= corr;
+      } else {
+#pragma unroll
+        for (int v = 0; v < 8; ++v) o16[v >> 2][v & 3] *= corr;
+      }
     }
     m_run = m_new;
-    Frag8 pf[4];
+    Frag8 pf[QW / 8];
 #pragma unroll
-    for (int pg = 0; pg < 4; ++pg) pf[pg].u = sm.p[s & 1][w][pg][lane];
+    for (int f = 0; f < QW / 8; ++f) pf[f].u = sm.p[s & 1][w][f][lane];
+    if constexpr (QW == 32) {
 #pragma unroll
-    for (int pg = 0; pg < 4; ++pg) {
-      o = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf[k][pg].v, pf[pg].v, o, 0, 0, 0);
-      l_run = __builtin_amdgcn_fdot2_f32_bf16(__builtin_shufflevector(pf[pg].v, pf[pg].v, 0, 1), ones, l_run, false);
-      l_run = __builtin_amdgcn_fdot2_f32_bf16(__builtin_shufflevector(pf[pg].v, pf[pg].v, 2, 3), ones, l_run, false);
-      l_run = __builtin_amdgcn_fdot2_f32_bf16(__builtin_shufflevector(pf[pg].v, pf[pg].v, 4, 5), ones, l_run, false);
-      l_run = __builtin_amdgcn_fdot2_f32_bf16(__builtin_shufflevector(pf[pg].v, pf[pg].v, 6, 7), ones, l_run, false);
+      for (int f = 0; f < 4; ++f) {
+        o32 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf[k][f].v, pf[f].v, o32, 0, 0, 0);
+        l_run = add8(l_run, pf[f].v);
+      }
+    } else {
+      // the lower lane half holds page 2 p, the upper page 2 p + 1: the sum passes through both in turn and is kept in
+      // the lower half
+#pragma unroll
+      for (int p = 0; p < 2; ++p) {
+#pragma unroll
+        for (int d = 0; d < 2; ++d) o16[d] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(vf[k][2 * p + d].v, pf[p].v, o16[d], 0, 0, 0);
+        l_run = other_half(add8(l_run, pf[p].v), half);
+        l_run = other_half(add8(l_run, pf[p].v), half);
+      }
     }
   };
 
   __syncthreads();   // first step: maxima
   __syncthreads();   // first step: probabilities
   for (int s = 0; s + 1 < n_steps; ++s) {
-    if ((s + 1) % SPF == 0) ids = fetch_ids(s + 1);
+    if ((s + 1) % SPF == 0) pages = fetch_pages(s + 1);
 #pragma unroll
     for (int k = 0; k < KG; ++k) {
       accumulate(s, k);
@@ -283,27 +371,35 @@ __global__ void __launch_bounds__(64 * (kAttnWideScorers + 4), 4) k_attn_wide(in
   for (int k = 0; k < KG; ++k) accumulate(n_steps - 1, k);
 
   // ---- fold the two parities (even first), as k_attn_mfma does
-  l_run = half_sum(l_run);
+  l_run = QW == 32 ? half_sum(l_run) : quarter_sum(l_run);
+  if constexpr (QW == 16) {
+    const float lower = other_half(l_run, half);
+    l_run = half ? lower : l_run;
+  }
+  float o[NO];
+#pragma unroll
+  for (int v = 0; v < NO; ++v) o[v] = QW == 32 ? o32[v] : o16[(v >> 2) & 1][v & 3];
   if (par == 1) {
 #pragma unroll
-    for (int v = 0; v < 16; ++v) sm.fold[i][v][lane] = o[v];
-    sm.fold[i][16][lane] = m_run;
-    sm.fold[i][17][lane] = l_run;
+    for (int v = 0; v < NO; ++v) sm.fold[i][v][lane] = o[v];
+    sm.fold[i][NO][lane] = m_run;
+    sm.fold[i][NO + 1][lane] = l_run;
   }
   __syncthreads();
   if (par == 0 && row < Lq) {
-    const float m_b = sm.fold[i][16][lane], l_b = sm.fold[i][17][lane];
+    const float m_b = sm.fold[i][NO][lane], l_b = sm.fold[i][NO + 1][lane];
     const float m_tot = fmaxf(m_run, m_b);
     const float ca = (m_run > -INFINITY) ? ldexpf(1.0f, static_cast<int>(m_run - m_tot)) : 0.f;
     const float cb = (m_b > -INFINITY) ? ldexpf(1.0f, static_cast<int>(m_b - m_tot)) : 0.f;
     const float inv = 1.0f / (l_run * ca + l_b * cb);
-    bf16 *op = out + static_cast<size_t>(base + row) * qdim + head * kHd + i * 32 + 4 * half;
+    // four dims in a row: 8 g + 4 (l / 32), or 16 g + 4 (l / 16)
+    bf16 *op = out + static_cast<size_t>(base + row) * qdim + head * kHd + i * 32 + 4 * kg;
 #pragma unroll
-    for (int gq = 0; gq < 4; ++gq) {
+    for (int gq = 0; gq < NO / 4; ++gq) {
       floatx4 ov;
 #pragma unroll
       for (int e = 0; e < 4; ++e) ov[e] = (o[4 * gq + e] * ca + sm.fold[i][4 * gq + e][lane] * cb) * inv;
-      *reinterpret_cast<bf16x4 *>(op + 8 * gq) = __builtin_convertvector(ov, bf16x4);
+      *reinterpret_cast<bf16x4 *>(op + (256 / QW) * gq) = __builtin_convertvector(ov, bf16x4);
     }
   }
 }

@@ -504,11 +504,11 @@ int attn_wide_max_sets(int total_q, int n_seq, int g4) {
   return static_cast<int>(g4 == 4 ? std::min(by_tile, by_row) : by_tile);
 }
 
-template <bool TREE>
+template <int QW, bool TREE>
 int launch_attn_wide(hipStream_t st, int n_wg, int n_q_heads, int g4, const AttnTile *tiles, const PagedKV &kv, const bf16 *q,
                      bf16 *o, const int32_t *row_end) {
-  constexpr size_t smem = sizeof(AttnWideLds);
-  auto kern = k_attn_wide<TREE>;
+  constexpr size_t smem = sizeof(AttnWideLds<QW>);
+  auto kern = k_attn_wide<QW, TREE>;
   static const hipError_t attr_rc = hipFuncSetAttribute(reinterpret_cast<const void *>(kern),
                                                         hipFuncAttributeMaxDynamicSharedMemorySize, smem);
   if (attr_rc != hipSuccess) return HSD_EHIP;
@@ -554,9 +554,13 @@ int launch_attention(const hsd_ctx *ctx, hipStream_t st, const hsd_batch *b, con
         }
         const bf16 *q = static_cast<const bf16 *>(ws.q);
         bf16 *o = static_cast<bf16 *>(ws.a);
-        return meta.row_end != nullptr
-                   ? launch_attn_wide<true>(st, n_wg, d.n_q_heads, g4, ws.attn_tiles, kv, q, o, meta.row_end)
-                   : launch_attn_wide<false>(st, n_wg, d.n_q_heads, g4, ws.attn_tiles, kv, q, o, nullptr);
+        const bool tree = meta.row_end != nullptr;
+        // 16 columns where they hold the longest block there can be
+        if (b->total_q - b->n_seq + 1 <= 16 / g4)
+          return tree ? launch_attn_wide<16, true>(st, n_wg, d.n_q_heads, g4, ws.attn_tiles, kv, q, o, meta.row_end)
+                      : launch_attn_wide<16, false>(st, n_wg, d.n_q_heads, g4, ws.attn_tiles, kv, q, o, nullptr);
+        return tree ? launch_attn_wide<32, true>(st, n_wg, d.n_q_heads, g4, ws.attn_tiles, kv, q, o, meta.row_end)
+                    : launch_attn_wide<32, false>(st, n_wg, d.n_q_heads, g4, ws.attn_tiles, kv, q, o, nullptr);
       }
       const int sub_tiles = 256 / q_tile;   // tiles of one sequence and head group that share an XCD: 256 rows
       const int n_wg = attn_grid_size(max_tiles, n_y, sub_tiles);
