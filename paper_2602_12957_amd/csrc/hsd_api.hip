@@ -25,6 +25,7 @@
 #include "probes.h"
 #include "gemm_simple.h"
 #include "misc_kernels.h"
+#include "pass_setup.h"
 
 using namespace hsd;
 
@@ -468,7 +469,6 @@ int lm_head_tiles(const hsd_ctx *ctx, int M) {
   }
 }
 
-// Verification attention: bf16 goes to the MFMA kernel when the GQA group size fits its wave mapping.
 // A compute unit has 160 KB of LDS; a request above half of it keeps a workgroup alone on its compute unit.
 constexpr size_t kLdsExclusive = 84 * 1024;
 
@@ -517,60 +517,69 @@ int launch_attn_wide(hipStream_t st, int n_wg, int n_q_heads, int g4, const Attn
   return HSD_OK;
 }
 
+// How a pass's attention is split into tasks; decided once per pass, the task table is built accordingly.
+struct AttnPlan {
+  bool mfma = false;   // bf16 with a grouping of query heads that fits the kernels; otherwise the plain kernel
+  bool wide = false;   // k_attn_wide
+  int g4 = 0, qs = 0, q_tile = 0, n_y = 0, sub_tiles = 0, n_wg = 0;
+};
+
 template <typename T>
-int launch_attention(const hsd_ctx *ctx, hipStream_t st, const hsd_batch *b, const RowMeta &meta, const PagedKV &kv,
-                     const Workspace &ws, bool page_mode) {
+AttnPlan plan_attention(const hsd_ctx *ctx, const hsd_batch *b, bool page_mode) {
+  AttnPlan p;
   const hsd_model_desc &d = ctx->desc;
   const int group = d.n_q_heads / d.n_kv_heads;
+  if (!std::is_same<T, bf16>::value || ctx->force_simple || !(group == 1 || group == 2 || group % 4 == 0)) return p;
+  p.mfma = true;
+  // Work split, fixed per model and entry point (and one row's arithmetic is the same in all, so results stay bitwise
+  // batch-invariant): g4 query heads of a kv head among the query sets of a workgroup; 4 query sets for region-level
+  // batches (many short blocks: more, smaller workgroups), 8 for page-level ones (few long blocks: each K/V stage in LDS
+  // serves twice the queries).
+  const int g4 = p.g4 = group >= 4 ? 4 : group;
+  const int n_y = p.n_y = d.n_kv_heads * ((group + g4 - 1) / g4);
+  // Few query sets: the keys of each are spread over a workgroup's waves (k_attn_wide; same bits, so the choice may
+  // follow the batch).  Its workgroups read K and V once per head where k_attn_mfma's read them once per four, so it
+  // loses when the chip is full.  Launch times in us, k_attn_mfma / k_attn_wide (events, 16 heads on 4 kv heads, 1055
+  // keys), by query sets: 4 (one token) 18.5 / 14.9, 4096 keys 47.7 / 33.5; 16 (1 block of 32 rows) 21.0 / 14.9; 128
+  // 21.9 / 15.5; 256 21.0 / 16.0; 208 (a block of 401) 23.7 / 20.0; 512: 8 blocks of 128 rows 21.6 / 20.0, 32 of 32
+  // 22.4 / 22.3, 64 of 16 24.8 / 25.5, 512 keys 15.7 / 15.5; 624 (3 of 401) 24.3 / 27.5; 1056 29 / 40.  The line is at
+  // 2.25 sets per compute unit of what a batch of this size can be expected to have: half a tile lost per block.
+  const int64_t rows = b->total_q, n = b->n_seq;
+  const int64_t by_tile = g4 * (2 * rows + 32 * n) / 64, by_row = n + (rows - n) / 8;
+  const int64_t sets = (g4 == 4 ? std::min(by_tile, by_row) : by_tile) * n_y;
+  const int64_t cu = ctx->n_cu > 0 ? ctx->n_cu : 256;
+  p.wide = d.attn_key_chunk == 0 && 4 * sets <= 9 * cu;
+  if (p.wide) {
+    p.q_tile = 32;
+    p.sub_tiles = 8;   // two 32-row tiles of four heads share an XCD
+    p.n_wg = attn_grid_size(attn_wide_max_sets(b->total_q, b->n_seq, g4), n_y, p.sub_tiles);
+  } else {
+    p.qs = page_mode ? 8 : 4;
+    p.q_tile = 32 * (p.qs / g4);
+    p.sub_tiles = 256 / p.q_tile;   // tiles of one sequence and head group that share an XCD: 256 rows
+    p.n_wg = attn_grid_size(b->total_q / p.q_tile + b->n_seq, n_y, p.sub_tiles);
+  }
+  return p;
+}
+
+// Verification attention of one layer.
+template <typename T>
+int launch_attention(const hsd_ctx *ctx, hipStream_t st, const hsd_batch *b, const RowMeta &meta, const PagedKV &kv,
+                     const Workspace &ws, const AttnPlan &plan) {
+  const hsd_model_desc &d = ctx->desc;
   if constexpr (std::is_same<T, bf16>::value) {
-    if (!ctx->force_simple && (group == 1 || group == 2 || group % 4 == 0)) {
-      // Work split, fixed per model and entry point (never chosen from the batch; and one row's arithmetic is the
-      // same in both, so results stay bitwise batch-invariant): g4 query heads of a kv head among the query sets of
-      // a workgroup; 4 query sets for region-level batches (many short blocks: more, smaller workgroups), 8 for
-      // page-level ones (few long blocks: each K/V stage in LDS serves twice the queries).
-      const int g4 = group >= 4 ? 4 : group, qs = page_mode ? 8 : 4;
-      const int q_tile = 32 * (qs / g4);
-      const int max_tiles = b->total_q / q_tile + b->n_seq;
-      const int n_y = d.n_kv_heads * ((group + g4 - 1) / g4);
-      // Few query sets: the keys of each are spread over a workgroup's waves (k_attn_wide; same bits, so the choice may
-      // follow the batch).  Its workgroups read K and V once per head where k_attn_mfma's read them once per four, so it
-      // loses when the chip is full.  Launch times in us, k_attn_mfma / k_attn_wide (events, 16 heads on 4 kv heads, 1055
-      // keys), by query sets: 4 (one token) 18.5 / 14.9, 4096 keys 47.7 / 33.5; 16 (1 block of 32 rows) 21.0 / 14.9; 128
-      // 21.9 / 15.5; 256 21.0 / 16.0; 208 (a block of 401) 23.7 / 20.0; 512: 8 blocks of 128 rows 21.6 / 20.0, 32 of 32
-      // 22.4 / 22.3, 64 of 16 24.8 / 25.5, 512 keys 15.7 / 15.5; 624 (3 of 401) 24.3 / 27.5; 1056 29 / 40.  The line is at
-      // 2.25 sets per compute unit of what a batch of this size can be expected to have: half a tile lost per block.
-      const int64_t rows = b->total_q, n = b->n_seq;
-      const int64_t by_tile = g4 * (2 * rows + 32 * n) / 64, by_row = n + (rows - n) / 8;
-      const int64_t sets = (g4 == 4 ? std::min(by_tile, by_row) : by_tile) * n_y;
-      const int64_t cu = ctx->n_cu > 0 ? ctx->n_cu : 256;
-      if (d.attn_key_chunk == 0 && 4 * sets <= 9 * cu) {
-        const int max_sets = attn_wide_max_sets(b->total_q, b->n_seq, g4);
-        const int sub_sets = 8;   // two 32-row tiles of four heads share an XCD
-        const int n_wg = attn_grid_size(max_sets, n_y, sub_sets);
-        if (kv.layer == 0) {
-          hipLaunchKernelGGL(k_attn_tiles, dim3(1), dim3(1024), 0, st, b->n_seq, b->cu_q, b->seq_slot, b->n_slots,
-                             b->seq_len, 32, n_y, sub_sets, n_wg, g4, ws.attn_tiles);
-          HSD_LAUNCH_CHECK();
-        }
-        const bf16 *q = static_cast<const bf16 *>(ws.q);
-        bf16 *o = static_cast<bf16 *>(ws.a);
-        const bool tree = meta.row_end != nullptr;
+    if (plan.mfma) {
+      const int g4 = plan.g4, qs = plan.qs, n_wg = plan.n_wg;
+      const bool tree = meta.row_end != nullptr;
+      const bf16 *q = static_cast<const bf16 *>(ws.q);
+      bf16 *o = static_cast<bf16 *>(ws.a);
+      if (plan.wide) {
         // 16 columns where they hold the longest block there can be
         if (b->total_q - b->n_seq + 1 <= 16 / g4)
           return tree ? launch_attn_wide<16, true>(st, n_wg, d.n_q_heads, g4, ws.attn_tiles, kv, q, o, meta.row_end)
                       : launch_attn_wide<16, false>(st, n_wg, d.n_q_heads, g4, ws.attn_tiles, kv, q, o, nullptr);
         return tree ? launch_attn_wide<32, true>(st, n_wg, d.n_q_heads, g4, ws.attn_tiles, kv, q, o, meta.row_end)
                     : launch_attn_wide<32, false>(st, n_wg, d.n_q_heads, g4, ws.attn_tiles, kv, q, o, nullptr);
-      }
-      const int sub_tiles = 256 / q_tile;   // tiles of one sequence and head group that share an XCD: 256 rows
-      const int n_wg = attn_grid_size(max_tiles, n_y, sub_tiles);
-      const dim3 grid(n_wg, 1);
-      const bf16 *q = static_cast<const bf16 *>(ws.q);
-      bf16 *o = static_cast<bf16 *>(ws.a);
-      if (kv.layer == 0) {  // the task table depends on the batch only: built once per pass
-        hipLaunchKernelGGL(k_attn_tiles, dim3(1), dim3(1024), 0, st, b->n_seq, b->cu_q, b->seq_slot, b->n_slots,
-                           b->seq_len, q_tile, n_y, sub_tiles, n_wg, 0, ws.attn_tiles);
-        HSD_LAUNCH_CHECK();
       }
       // Key split (desc.attn_key_chunk > 0): one workgroup per (query tile, chunk of keys); no sequence can hold
       // more keys than its block-table row addresses, which bounds the chunks worth launching.
@@ -580,9 +589,8 @@ int launch_attention(const hsd_ctx *ctx, hipStream_t st, const hsd_batch *b, con
         const int64_t max_keys = static_cast<int64_t>(b->max_blocks_per_seq) * HSD_KV_BLOCK_TOKENS;
         n_chunks = static_cast<int>(std::min<int64_t>(kAttnMaxChunks, (max_keys + chunk - 1) / chunk));
       }
-      const dim3 grid_z(grid.x, grid.y, n_chunks);
+      const dim3 grid_z(n_wg, 1, n_chunks);
       const AttnSplit sp{chunk, b->total_q, ws.attn_part_o, ws.attn_part_ml};
-      const bool tree = meta.row_end != nullptr;
       int rc = HSD_OK;
 #define HSD_ATTN_CASE(G4, QS)                                                                                      \
   if (g4 == G4 && qs == QS) {                                                                                      \
@@ -619,26 +627,32 @@ int forward(hsd_ctx *ctx, hipStream_t st, const hsd_kv_pool *pool, const hsd_bat
   const bool relaxed = with_head && b->log_tau < 0.f;   // Eq. 11 with tau < 1: needs the draft tokens' own logits
   int rc;
 
-  hipLaunchKernelGGL(k_row_meta, dim3((Tq * 32 + 255) / 256), dim3(256), 0, st, b->n_seq, Tq, b->cu_q, b->seq_slot,
-                     b->n_slots, b->seq_len, d.rope_theta, ws.row_seq, ws.row_pos, ws.row_slot, ws.row_base, ws.rope_cs,
-                     b->tree_end, b->tree_depth, ws.row_end, relaxed ? ws.row_par : nullptr, ws.want_logit, b->status);
-  HSD_LAUNCH_CHECK();
-  hipLaunchKernelGGL(k_kv_reserve, dim3(1), dim3(1024), 0, st, b->n_seq, b->cu_q, b->seq_slot, b->n_slots,
-                     b->seq_len, b->block_table, b->max_blocks_per_seq, pool->n_blocks, pool->free_list,
-                     pool->free_count, b->status);
-  HSD_LAUNCH_CHECK();
-  hipLaunchKernelGGL(k_row_kv, dim3((Tq + 255) / 256), dim3(256), 0, st, Tq, ws.row_seq, ws.row_slot, b->block_table,
-                     b->max_blocks_per_seq, pool->n_blocks, ws.row_kv);
-  HSD_LAUNCH_CHECK();
-  hipLaunchKernelGGL((k_embed<T>), dim3(Tq), dim3(256), 0, st, d.d_model, d.vocab, b->tokens, b->embeds,
-                     static_cast<const T *>(ctx->tok_embed), ws.x);
-  HSD_LAUNCH_CHECK();
+  const AttnPlan plan = plan_attention<T>(ctx, b, page_mode);
+  const bool dump = with_head && b->n_dump > 0 && b->logits_dump != nullptr;
+  {
+    ProfScope prof(ctx, st, HSD_PROF_RMSNORM);   // the pass's first norm is in here
+    PassSetup ps{};
+    ps.n_seq = b->n_seq, ps.total_q = Tq, ps.n_slots = b->n_slots, ps.max_blocks = b->max_blocks_per_seq, ps.n_blocks = pool->n_blocks;
+    ps.d = d.d_model, ps.vocab = d.vocab, ps.n_dump = dump ? b->n_dump : 0;
+    ps.cu_q = b->cu_q, ps.seq_slot = b->seq_slot, ps.seq_len = b->seq_len, ps.tokens = b->tokens;
+    ps.tree_end = b->tree_end, ps.tree_depth = b->tree_depth, ps.dump_rows = b->dump_rows;
+    ps.embeds = b->embeds, ps.gain = ctx->attn_norm[0], ps.table = ctx->tok_embed;
+    ps.block_table = b->block_table, ps.free_list = pool->free_list, ps.free_count = pool->free_count, ps.status = b->status;
+    ps.row_seq = ws.row_seq, ps.row_pos = ws.row_pos, ps.row_slot = ws.row_slot, ps.row_base = ws.row_base, ps.row_end = ws.row_end;
+    ps.row_par = relaxed ? ws.row_par : nullptr, ps.row_kv = ws.row_kv, ps.dump_slot = ws.dump_slot;
+    ps.rope_cs = ws.rope_cs, ps.want_logit = ws.want_logit, ps.x = ws.x, ps.h = ws.h;
+    ps.rope_theta = d.rope_theta, ps.eps = d.rms_eps;
+    ps.tasks = ws.attn_tiles, ps.q_tile = plan.q_tile, ps.n_y = plan.n_y, ps.sub_tiles = plan.sub_tiles, ps.n_wg = plan.n_wg;
+    ps.wide_g4 = plan.wide ? plan.g4 : 0;
+    hipLaunchKernelGGL((k_pass_setup<T>), dim3(setup_blocks(Tq)), dim3(1024), 0, st, ps);
+    HSD_LAUNCH_CHECK();
+  }
 
   const bool tree = b->tree_end != nullptr;
   RowMeta meta{ws.row_seq, ws.row_pos, ws.rope_cs, ws.row_kv, ws.row_slot, ws.row_base, tree ? ws.row_end : nullptr};
   const bool mfma_path = std::is_same<T, bf16>::value && !ctx->force_simple;
 
-  // RMSNorm as a kernel of its own: the first norm of a pass, and every norm of the plain-kernel path
+  // RMSNorm as a kernel of its own: every norm of the plain-kernel path but the first
   auto norm = [&](const float *gain) -> int {
     ProfScope ps(ctx, st, HSD_PROF_RMSNORM);
     hipLaunchKernelGGL((k_rmsnorm<T>), dim3((Tq + 3) / 4), dim3(256), 0, st, Tq, d.d_model, d.rms_eps, ws.x, gain,
@@ -685,10 +699,9 @@ int forward(hsd_ctx *ctx, hipStream_t st, const hsd_kv_pool *pool, const hsd_bat
   rs_down.ss2 = down_ss2, rs_down.n_sums = down_sums;
   rs_o.plane = rs_down.plane = Tq * (d.d_model / 64);
 
-  if ((rc = norm(ctx->attn_norm[0]))) return rc;
   for (int l = 0; l < d.n_layers; ++l) {
     PagedKV kv{pool->k_pool, pool->v_pool, b->block_table, b->max_blocks_per_seq, pool->n_blocks, d.n_kv_heads, l};
-    // layer 0 reads the operand the norm kernel normalised; later layers the one the previous down projection left
+    // layer 0 reads the operand the set-up launch normalised; later layers the one the previous down projection left
     EpiQKV<T> eq{d.n_q_heads, d.n_kv_heads, meta, kv, static_cast<T *>(ws.q), l == 0 ? rs_none : rs_down};
     {
       ProfScope ps(ctx, st, HSD_PROF_GEMM_QKV);
@@ -696,7 +709,7 @@ int forward(hsd_ctx *ctx, hipStream_t st, const hsd_kv_pool *pool, const hsd_bat
     }
     {
       ProfScope ps(ctx, st, HSD_PROF_ATTENTION);
-      if ((rc = launch_attention<T>(ctx, st, b, meta, kv, ws, page_mode))) return rc;
+      if ((rc = launch_attention<T>(ctx, st, b, meta, kv, ws, plan))) return rc;
     }
     if ((rc = residual_proj(kSiteO, HSD_PROF_GEMM_O, ws.a, ctx->wo[l], qdim, ctx->ffn_norm[l], o_ss2))) return rc;
     EpiSwiGLU<T> es{static_cast<T *>(ws.u), d.d_ffn, rs_o};
@@ -711,15 +724,7 @@ int forward(hsd_ctx *ctx, hipStream_t st, const hsd_kv_pool *pool, const hsd_bat
   }
   if (!with_head) return HSD_OK;
 
-  const int32_t *dump_slot = nullptr;
-  if (b->n_dump > 0 && b->logits_dump != nullptr) {
-    hipLaunchKernelGGL(k_fill_i32, dim3((Tq + 255) / 256), dim3(256), 0, st, ws.dump_slot, Tq, -1);
-    HSD_LAUNCH_CHECK();
-    hipLaunchKernelGGL(k_dump_slots, dim3((b->n_dump + 255) / 256), dim3(256), 0, st, b->dump_rows, b->n_dump, Tq,
-                       ws.dump_slot);
-    HSD_LAUNCH_CHECK();
-    dump_slot = ws.dump_slot;
-  }
+  const int32_t *dump_slot = dump ? ws.dump_slot : nullptr;
   const int n_tiles = lm_head_tiles<T>(ctx, Tq);
   EpiLMHead el{ws.lm_part, n_tiles, d.vocab, dump_slot, b->logits_dump, b->tokens, ws.row_end,
                relaxed ? ws.want_logit : nullptr, rs_down};
@@ -727,9 +732,14 @@ int forward(hsd_ctx *ctx, hipStream_t st, const hsd_kv_pool *pool, const hsd_bat
     ProfScope ps(ctx, st, HSD_PROF_GEMM_LM_HEAD);
     if ((rc = launch_gemm<T>(ctx, st, kSiteLM, Tq, d.vocab, d.d_model, ws.h, ctx->lm_head, el))) return rc;
   }
+  // a batch of single rows needs no acceptance kernel: the reduction writes alpha = 0 and the bonus (and the stop rows are
+  // the roots, which the tree kernel has to say)
+  const bool single = Tq == b->n_seq && !tree;
   hipLaunchKernelGGL(k_lm_reduce, dim3((Tq + 3) / 4), dim3(256), 0, st, Tq, n_tiles, ws.lm_part, b->argmax,
-                     b->top2_margin, relaxed ? ws.row_max : nullptr);
+                     b->top2_margin, relaxed ? ws.row_max : nullptr, single ? b->accept_len : nullptr, b->bonus,
+                     relaxed ? b->draft_gap : nullptr);
   HSD_LAUNCH_CHECK();
+  if (single) return HSD_OK;
   if (relaxed) {
     hipLaunchKernelGGL(k_draft_gap, dim3((Tq + 255) / 256), dim3(256), 0, st, Tq, ws.row_par, ws.want_logit,
                        ws.row_max, b->draft_gap);

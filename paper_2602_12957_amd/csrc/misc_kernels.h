@@ -7,133 +7,106 @@
 namespace hsd {
 
 // ------------------------------------------------------------------------------------------------
-// Row metadata of every packed row: sequence, rotary position and (cos, sin) table, cache slot, and the packed
-// tree it belongs to.  A chain block is the tree in which every row's subtree is the rest of the block.
+// What a pass needs before its first projection, in one launch (k_pass_setup below): the pieces are independent, each is a
+// few microseconds of dependent reads, and launches of their own would cost as much again each.
+// ------------------------------------------------------------------------------------------------
+struct AttnTile;   // attn_mfma.h
+struct PassSetup {
+  int n_seq, total_q, n_slots, max_blocks, n_blocks, d, vocab, n_dump;
+  const int32_t *cu_q, *seq_slot, *seq_len, *tokens, *tree_end, *tree_depth, *dump_rows;
+  const float *embeds, *gain;
+  const void *table;
+  int32_t *block_table, *free_list, *free_count, *status;
+  int32_t *row_seq, *row_pos, *row_slot, *row_base, *row_end, *row_par, *row_kv, *dump_slot;
+  float2 *rope_cs;
+  float *want_logit, *x;
+  void *h;
+  float rope_theta, eps;
+  // attention task table (n_wg = 0: none), see attn_tiles_block
+  AttnTile *tasks;
+  int q_tile, n_y, sub_tiles, n_wg, wide_g4;
+};
+
+// Last sequence whose first row is <= r
+__device__ __forceinline__ int seq_of_row(const int32_t *cu_q, int n_seq, int r) {
+  int lo = 0, hi = n_seq - 1;
+  while (lo < hi) {
+    const int mid = (lo + hi + 1) >> 1;
+    if (cu_q[mid] <= r) lo = mid; else hi = mid - 1;
+  }
+  return lo;
+}
+
+// Row metadata of packed row r: sequence, rotary position and (cos, sin) table, cache slot, and the packed tree it
+// belongs to.  A chain block is the tree in which every row's subtree is the rest of the block.
 //   row_pos  = seq_len + depth   (position on the row's own root-to-node path: what the rotary embedding sees)
 //   row_slot = seq_len + local index (where its K/V are stored until commit)
 //   row_end  = GLOBAL row index one past the row's subtree, clamped into (row, end of the sequence's block]
 //   row_par  = GLOBAL row index of the parent (nearest earlier row whose subtree contains this one), -1 for a root
-// The angle is formed in fp64 (position * theta^(-2i/64)) so that positions of many thousands lose
-// nothing before the fp32 rounding of cos/sin themselves.
-// grid: ceil(T*32 / 256) blocks of 256 threads; thread -> (row, frequency index i)
-// ------------------------------------------------------------------------------------------------
-__global__ void k_row_meta(int n_seq, int total_q, const int32_t *__restrict__ cu_q,
-                           const int32_t *__restrict__ seq_slot, int n_slots,
-                           const int32_t *__restrict__ seq_len, float rope_theta, int32_t *__restrict__ row_seq,
-                           int32_t *__restrict__ row_pos, int32_t *__restrict__ row_slot,
-                           int32_t *__restrict__ row_base, float2 *__restrict__ rope_cs,
-                           const int32_t *__restrict__ tree_end,
-                           const int32_t *__restrict__ tree_depth, int32_t *__restrict__ row_end,
-                           int32_t *__restrict__ row_par, float *__restrict__ want_logit,
-                           int32_t *__restrict__ status) {
-  int gid = blockIdx.x * blockDim.x + threadIdx.x;
-  int r = gid >> 5, i = gid & 31;
-  if (r >= total_q) return;
-  // binary search: largest s with cu_q[s] <= r
-  int lo = 0, hi = n_seq - 1;
-  while (lo < hi) {
-    int mid = (lo + hi + 1) >> 1;
-    if (cu_q[mid] <= r) lo = mid; else hi = mid - 1;
-  }
-  const int base = cu_q[lo], stop = cu_q[lo + 1], local = r - base;
-  int slot = slot_of(seq_slot, lo, n_slots);
+// The angle is formed in fp64 (position * theta^(-2i/64)) so that positions of many thousands lose nothing before the fp32
+// rounding of cos/sin themselves.  32 adjacent lanes call it for one row, lane i with frequency index i; all of them look
+// for the parent, 32 rows at a time (a walk by one lane was a read per row: 12 us for trees of 126 rows).
+__device__ __forceinline__ void row_meta(const PassSetup &ps, int r, int i) {
+  const int s = seq_of_row(ps.cu_q, ps.n_seq, r);
+  const int base = ps.cu_q[s], stop = ps.cu_q[s + 1], local = r - base;
+  const int slot = slot_of(ps.seq_slot, s, ps.n_slots), len = ps.seq_len[slot];
   int depth = local;
-  if (tree_depth != nullptr) {
-    depth = tree_depth[r];
+  if (ps.tree_depth != nullptr) {
+    depth = ps.tree_depth[r];
     if (depth < 0 || depth > local || (local > 0 && depth == 0)) {
       depth = local > 0 ? 1 : 0;
-      if (i == 0) atomicOr(status, HSD_STATUS_BAD_TREE);
+      if (i == 0) atomicOr(ps.status, HSD_STATUS_BAD_TREE);
     }
   }
-  int pos = seq_len[slot] + depth;
+  const int pos = len + depth;
+  int par = local > 0 ? r - 1 : -1;
+  if (ps.row_par != nullptr && ps.tree_end != nullptr && local > 0) {
+    // nearest earlier row whose (clamped) subtree reaches past r; row `base` (the root) always qualifies
+    par = base;
+    for (int hi = r - 1; hi > base; hi -= 32) {
+      const int j = hi - i;
+      const int ej = j > base ? base + ps.tree_end[j] : 0;
+      const uint32_t hit = static_cast<uint32_t>(__ballot(j > base && ej > r && ej <= stop) >> (threadIdx.x & 32));
+      if (hit != 0) {
+        par = hi - (__ffs(hit) - 1);
+        break;
+      }
+    }
+  }
   if (i == 0) {
-    row_seq[r] = slot;
-    row_pos[r] = pos;
-    row_slot[r] = seq_len[slot] + local;
-    row_base[r] = base;
+    ps.row_seq[r] = slot;
+    ps.row_pos[r] = pos;
+    ps.row_slot[r] = len + local;
+    ps.row_base[r] = base;
     int e = stop;
-    if (tree_end != nullptr) {
-      e = base + tree_end[r];
+    if (ps.tree_end != nullptr) {
+      e = base + ps.tree_end[r];
       if (e <= r || e > stop || (local == 0 && e != stop)) {
         e = local == 0 ? stop : r + 1;
-        atomicOr(status, HSD_STATUS_BAD_TREE);
+        atomicOr(ps.status, HSD_STATUS_BAD_TREE);
       }
     }
-    row_end[r] = e;
-    if (row_par != nullptr) {
-      // nearest earlier row whose (clamped) subtree reaches past r; row `base` (the root) always qualifies
-      int p = -1;
-      if (local > 0) {
-        p = base;
-        if (tree_end == nullptr) {
-          p = r - 1;
-        } else {
-          for (int j = r - 1; j > base; --j) {
-            int ej = base + tree_end[j];
-            if (ej > r && ej <= stop) { p = j; break; }
-          }
-        }
-      }
-      row_par[r] = p;
-      want_logit[r] = -INFINITY;
+    ps.row_end[r] = e;
+    if (ps.row_par != nullptr) {
+      ps.row_par[r] = par;
+      ps.want_logit[r] = -INFINITY;
     }
   }
-  double inv_freq = pow(static_cast<double>(rope_theta), -2.0 * i / static_cast<double>(kHd));
-  double ang = static_cast<double>(pos) * inv_freq;
+  const double inv_freq = pow(static_cast<double>(ps.rope_theta), -2.0 * i / static_cast<double>(kHd));
+  const double ang = static_cast<double>(pos) * inv_freq;
   double sn, cs;
   sincos(ang, &sn, &cs);
-  rope_cs[static_cast<size_t>(r) * 32 + i] = make_float2(static_cast<float>(cs), static_cast<float>(sn));
+  ps.rope_cs[static_cast<size_t>(r) * 32 + i] = make_float2(static_cast<float>(cs), static_cast<float>(sn));
 }
 
-// Where each packed row's key and value land in the paged pools: 16 * block id + slot within the block, or -1
-// when the table holds no valid block for the row's position (reservation failed).  Block ids are the same in
-// every layer, so the projection epilogues of all layers read this one array instead of walking
-// row -> sequence -> table themselves.  Runs after the reservation kernel.
-// grid: ceil(T / 256) blocks of 256 threads
-__global__ void k_row_kv(int total_q, const int32_t *__restrict__ row_seq, const int32_t *__restrict__ row_slot,
-                         const int32_t *__restrict__ block_table, int max_blocks_per_seq, int n_blocks,
-                         int32_t *__restrict__ row_kv) {
-  int r = blockIdx.x * blockDim.x + threadIdx.x;
-  if (r >= total_q) return;
-  const int pos = row_slot[r], bi = pos / kBlk;
-  int b = -1;
-  if (bi < max_blocks_per_seq) b = block_table[static_cast<size_t>(row_seq[r]) * max_blocks_per_seq + bi];
-  row_kv[r] = (b >= 0 && b < n_blocks) ? b * kBlk + pos % kBlk : -1;
-}
-
-// dump_slot[r] = index into logits_dump for row r, or -1.  Two launches: fill -1, then scatter.
-__global__ void k_fill_i32(int32_t *p, int n, int32_t v) {
-  int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < n) p[i] = v;
-}
-__global__ void k_dump_slots(const int32_t *__restrict__ dump_rows, int n_dump, int total_q,
-                             int32_t *__restrict__ dump_slot) {
-  int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < n_dump) {
-    int r = dump_rows[i];
-    if (r >= 0 && r < total_q) dump_slot[r] = i;
-  }
-}
-
-// ------------------------------------------------------------------------------------------------
-// Embedding gather: x[r,:] = tok_embed[tokens[r],:] (widened to fp32) or embeds[r,:] if tokens[r] < 0.
-// grid: T blocks; block 256 threads strided over d.
-// ------------------------------------------------------------------------------------------------
-template <typename T>
-__global__ void k_embed(int d, int vocab, const int32_t *__restrict__ tokens, const float *__restrict__ embeds,
-                        const T *__restrict__ table, float *__restrict__ x) {
-  int r = blockIdx.x;
-  int t = tokens[r];
-  float *xr = x + static_cast<size_t>(r) * d;
-  if (t >= 0) {
-    if (t >= vocab) t = vocab - 1;  // ids are validated by the caller; clamp keeps the read in bounds
-    const T *src = table + static_cast<size_t>(t) * d;
-    for (int c = threadIdx.x; c < d; c += blockDim.x) xr[c] = to_f32(src[c]);
-  } else if (embeds != nullptr) {
-    const float *src = embeds + static_cast<size_t>(r) * d;
-    for (int c = threadIdx.x; c < d; c += blockDim.x) xr[c] = src[c];
-  } else {
-    for (int c = threadIdx.x; c < d; c += blockDim.x) xr[c] = 0.f;
+// dump_slot[r] = index into logits_dump for row r, or -1.  One block of 1024 threads.
+__device__ inline void dump_slots_block(const PassSetup &ps) {
+  for (int r = threadIdx.x; r < ps.total_q; r += 1024) ps.dump_slot[r] = -1;
+  __threadfence_block();
+  __syncthreads();
+  for (int i = threadIdx.x; i < ps.n_dump; i += 1024) {
+    const int r = ps.dump_rows[i];
+    if (r >= 0 && r < ps.total_q) ps.dump_slot[r] = i;
   }
 }
 
@@ -192,30 +165,69 @@ __global__ void k_rmsnorm(int n_rows, int d, float eps, const float *__restrict_
   norm_write_row<T>(xr, cache, n4, lane, ss, d, eps, gain, h + static_cast<size_t>(r) * d);
 }
 
+// Residual row r and the first norm's operand: x[r,:] = table[tokens[r],:] (widened to fp32), or embeds[r,:] if tokens[r] < 0
+// (zeros without embeds), and h[r,:] as k_rmsnorm makes it from x -- same lanes, same sums.  One wave.
+__device__ __forceinline__ floatx4 load4(const float *p) { return *reinterpret_cast<const floatx4 *>(p); }
+__device__ __forceinline__ floatx4 load4(const bf16 *p) {
+  const uint2 u = *reinterpret_cast<const uint2 *>(p);
+  return floatx4{__uint_as_float(u.x << 16), __uint_as_float(u.x & 0xffff0000u), __uint_as_float(u.y << 16), __uint_as_float(u.y & 0xffff0000u)};
+}
+template <typename T>
+__device__ __forceinline__ void embed_norm_row(const PassSetup &ps, int r, int lane) {
+  const int t = min(ps.tokens[r], ps.vocab - 1);   // ids are validated by the caller; clamp keeps the read in bounds
+  const T *tok = static_cast<const T *>(ps.table) + static_cast<size_t>(max(t, 0)) * ps.d;
+  const float *emb = ps.embeds != nullptr ? ps.embeds + static_cast<size_t>(r) * ps.d : nullptr;
+  floatx4 *xr = reinterpret_cast<floatx4 *>(ps.x + static_cast<size_t>(r) * ps.d);
+  const int n4 = ps.d >> 2;
+  auto value = [&](int c) { return t >= 0 ? load4(tok + 4 * c) : emb != nullptr ? load4(emb + 4 * c) : floatx4{0.f, 0.f, 0.f, 0.f}; };
+  floatx4 cache[kNormCache];
+  float ss = 0.f;
+#pragma unroll
+  for (int i = 0; i < kNormCache; ++i) {
+    const int c = lane + kWave * i;
+    if (c < n4) {
+      cache[i] = value(c);
+      xr[c] = cache[i];
+      ss += sumsq4(cache[i]);
+    }
+  }
+  for (int c = lane + kWave * kNormCache; c < n4; c += kWave) {
+    const floatx4 v = value(c);
+    xr[c] = v;
+    ss += sumsq4(v);
+  }
+  norm_write_row<T>(xr, cache, n4, lane, ss, ps.d, ps.eps, ps.gain, static_cast<T *>(ps.h) + static_cast<size_t>(r) * ps.d);
+}
+
 // ------------------------------------------------------------------------------------------------
-// Block-wide exclusive scan of up to HSD_MAX_SEQ ints held in LDS (1024 threads, 4 items each).
+// Block-wide exclusive scan of up to HSD_MAX_SEQ ints held in LDS (1024 threads, 4 items each), which the caller's barrier
+// has made visible.
 // On return s_val[i] holds the exclusive prefix and the function returns the grand total.
 // ------------------------------------------------------------------------------------------------
-__device__ inline int block_exclusive_scan_4096(int *s_val, int n, int *s_part /*[1024]*/) {
-  int t = threadIdx.x;
-  int base = t * 4;
+__device__ inline int block_exclusive_scan_4096(int *s_val, int n, int *s_part /*[16]*/) {
+  const int t = threadIdx.x, lane = t & 63, wave = t >> 6, base = t * 4;
   int v[4], sum = 0;
 #pragma unroll
   for (int j = 0; j < 4; ++j) {
     v[j] = (base + j < n) ? s_val[base + j] : 0;
     sum += v[j];
   }
-  s_part[t] = sum;
-  __syncthreads();
-  // Hillis-Steele inclusive scan over the 1024 partial sums
-  for (int off = 1; off < 1024; off <<= 1) {
-    int add = (t >= off) ? s_part[t - off] : 0;
-    __syncthreads();
-    s_part[t] += add;
-    __syncthreads();
+  int incl = sum;
+#pragma unroll
+  for (int off = 1; off < kWave; off <<= 1) {
+    const int up = __shfl_up(incl, off, kWave);
+    if (lane >= off) incl += up;
   }
-  int total = s_part[1023];
-  int run = s_part[t] - sum;
+  if (lane == kWave - 1) s_part[wave] = incl;
+  __syncthreads();
+  int before = 0, total = 0;
+#pragma unroll
+  for (int w = 0; w < 16; ++w) {
+    const int p = s_part[w];
+    if (w < wave) before += p;
+    total += p;
+  }
+  int run = before + incl - sum;
 #pragma unroll
   for (int j = 0; j < 4; ++j) {
     if (base + j < n) s_val[base + j] = run;
@@ -229,27 +241,28 @@ __device__ inline int block_exclusive_scan_4096(int *s_val, int n, int *s_part /
 // KV block reservation for the speculative append.  For every sequence, every block-table slot that
 // covers positions seq_len .. seq_len+q_len-1 and holds no block gets one popped from the free stack.
 // Deterministic: sequence s takes its blocks after all sequences < s, slots in increasing order.
-// One block of 1024 threads (16 waves; waves stride over sequences, lanes over slots).
+// Afterwards row_kv[r] = where packed row r's key and value land in the paged pools: 16 * block id + slot within the block,
+// or -1 when the table holds no valid block for the row's position (reservation failed).  Block ids are the same in every
+// layer, so the projection epilogues of all layers read this one array instead of walking row -> sequence -> table
+// themselves.
+// One block of 1024 threads (16 waves; waves stride over sequences, lanes over slots).  `lds`: HSD_MAX_SEQ + 18 ints.
 // ------------------------------------------------------------------------------------------------
-__global__ void __launch_bounds__(1024) k_kv_reserve(int n_seq, const int32_t *__restrict__ cu_q,
-                                                     const int32_t *__restrict__ seq_slot, int n_slots,
-                                                     const int32_t *__restrict__ seq_len,
-                                                     int32_t *__restrict__ block_table, int maxb, int n_blocks,
-                                                     int32_t *__restrict__ free_list, int32_t *__restrict__ free_count,
-                                                     int32_t *__restrict__ status) {
-  __shared__ int s_cnt[HSD_MAX_SEQ];
-  __shared__ int s_part[1024];
-  __shared__ int s_flags;
-  int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-  if (threadIdx.x == 0) s_flags = 0;
+__device__ inline void kv_reserve_block(const PassSetup &ps, int *lds) {
+  int *s_cnt = lds, *s_part = lds + HSD_MAX_SEQ, *s_flags = s_part + 16;
+  const int32_t *__restrict__ cu_q = ps.cu_q;
+  const int maxb = ps.max_blocks, n_seq = ps.n_seq;
+  int32_t *block_table = ps.block_table;
+  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+  if (threadIdx.x == 0) *s_flags = 0;
   __syncthreads();
   for (int s = wave; s < n_seq; s += 16) {
-    int sl = slot_of(seq_slot, s, n_slots);
-    if (lane == 0 && seq_slot != nullptr && seq_slot[s] != sl) atomicOr(&s_flags, HSD_STATUS_BAD_SLOT);
-    int S = seq_len[sl], Lq = cu_q[s + 1] - cu_q[s];
-    int lo = S / kBlk, hi = (S + Lq + kBlk - 1) / kBlk;
+    const int sl = slot_of(ps.seq_slot, s, ps.n_slots);
+    if (lane == 0 && ps.seq_slot != nullptr && ps.seq_slot[s] != sl) atomicOr(s_flags, HSD_STATUS_BAD_SLOT);
+    const int S = ps.seq_len[sl], Lq = cu_q[s + 1] - cu_q[s];
+    const int lo = S / kBlk;
+    int hi = (S + Lq + kBlk - 1) / kBlk;
     if (hi > maxb) {
-      if (lane == 0) atomicOr(&s_flags, HSD_STATUS_TABLE_OVERFLOW);
+      if (lane == 0) atomicOr(s_flags, HSD_STATUS_TABLE_OVERFLOW);
       hi = maxb;
     }
     int cnt = 0;
@@ -258,32 +271,43 @@ __global__ void __launch_bounds__(1024) k_kv_reserve(int n_seq, const int32_t *_
     if (lane == 0) s_cnt[s] = cnt;
   }
   __syncthreads();
-  int total = block_exclusive_scan_4096(s_cnt, n_seq, s_part);
-  int avail = *free_count;
-  if (avail > n_blocks) avail = n_blocks;
+  const int total = block_exclusive_scan_4096(s_cnt, n_seq, s_part);
+  int avail = *ps.free_count;
+  if (avail > ps.n_blocks) avail = ps.n_blocks;
   if (total > avail) {
-    if (threadIdx.x == 0) atomicOr(status, s_flags | HSD_STATUS_POOL_EXHAUSTED);
-    return;  // nothing is taken; slots stay -1 and every later kernel skips them
-  }
-  for (int s = wave; s < n_seq; s += 16) {
-    int sl = slot_of(seq_slot, s, n_slots);
-    int S = seq_len[sl], Lq = cu_q[s + 1] - cu_q[s];
-    int lo = S / kBlk, hi = (S + Lq + kBlk - 1) / kBlk;
-    if (hi > maxb) hi = maxb;
-    int taken = s_cnt[s];  // exclusive prefix = blocks taken by earlier sequences
-    for (int i0 = lo; i0 < hi; i0 += kWave) {
-      int i = i0 + lane;
-      bool need = (i < hi) && (block_table[static_cast<size_t>(sl) * maxb + i] < 0);
-      unsigned long long m = __ballot(need);
-      int rank = __popcll(m & ((1ull << lane) - 1ull));
-      if (need) block_table[static_cast<size_t>(sl) * maxb + i] = free_list[avail - 1 - (taken + rank)];
-      taken += __popcll(m);
+    // nothing is taken; slots stay -1 and every later kernel skips them
+    if (threadIdx.x == 0) atomicOr(ps.status, *s_flags | HSD_STATUS_POOL_EXHAUSTED);
+  } else {
+    for (int s = wave; s < n_seq; s += 16) {
+      const int sl = slot_of(ps.seq_slot, s, ps.n_slots);
+      const int S = ps.seq_len[sl], Lq = cu_q[s + 1] - cu_q[s];
+      const int lo = S / kBlk;
+      int hi = (S + Lq + kBlk - 1) / kBlk;
+      if (hi > maxb) hi = maxb;
+      int taken = s_cnt[s];  // exclusive prefix = blocks taken by earlier sequences
+      for (int i0 = lo; i0 < hi; i0 += kWave) {
+        const int i = i0 + lane;
+        const bool need = (i < hi) && (block_table[static_cast<size_t>(sl) * maxb + i] < 0);
+        const unsigned long long m = __ballot(need);
+        const int rank = __popcll(m & ((1ull << lane) - 1ull));
+        if (need) block_table[static_cast<size_t>(sl) * maxb + i] = ps.free_list[avail - 1 - (taken + rank)];
+        taken += __popcll(m);
+      }
     }
   }
-  __syncthreads();
-  if (threadIdx.x == 0) {
-    *free_count = avail - total;
-    if (s_flags) atomicOr(status, s_flags);
+  __threadfence_block();
+  __syncthreads();   // the table is complete (for this block, which is all that reads it here)
+  if (threadIdx.x == 0 && total <= avail) {
+    *ps.free_count = avail - total;
+    if (*s_flags) atomicOr(ps.status, *s_flags);
+  }
+  for (int r = threadIdx.x; r < ps.total_q; r += 1024) {
+    const int s = seq_of_row(cu_q, n_seq, r);
+    const int sl = slot_of(ps.seq_slot, s, ps.n_slots);
+    const int pos = ps.seq_len[sl] + (r - cu_q[s]), bi = pos / kBlk;
+    int b = -1;
+    if (bi < maxb) b = block_table[static_cast<size_t>(sl) * maxb + bi];
+    ps.row_kv[r] = (b >= 0 && b < ps.n_blocks) ? b * kBlk + pos % kBlk : -1;
   }
 }
 
@@ -301,7 +325,7 @@ __global__ void __launch_bounds__(1024) k_kv_commit(int n_seq, const int32_t *__
                                                     int commit_all) {
   __shared__ int s_cnt[HSD_MAX_SEQ];
   __shared__ int s_new[HSD_MAX_SEQ];
-  __shared__ int s_part[1024];
+  __shared__ int s_part[16];
   int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
   for (int s = wave; s < n_seq; s += 16) {
     int sl = slot_of(seq_slot, s, n_slots);
@@ -375,7 +399,8 @@ __global__ void k_pool_init(int n_blocks, int32_t *__restrict__ free_list, int32
 // arg-max of probabilities) and the top-1/top-2 logit margin.
 // ------------------------------------------------------------------------------------------------
 __global__ void k_lm_reduce(int n_rows, int n_tiles, const Top2 *__restrict__ part, int32_t *__restrict__ argmax,
-                            float *__restrict__ margin, float *__restrict__ row_max) {
+                            float *__restrict__ margin, float *__restrict__ row_max, int32_t *__restrict__ accept_len,
+                            int32_t *__restrict__ bonus, float *__restrict__ draft_gap) {
   int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
   int r = blockIdx.x * 4 + wave;
   if (r >= n_rows) return;
@@ -393,6 +418,11 @@ __global__ void k_lm_reduce(int n_rows, int n_tiles, const Top2 *__restrict__ pa
     argmax[r] = t.i1;
     if (margin != nullptr) margin[r] = t.m1 - t.m2;
     if (row_max != nullptr) row_max[r] = t.m1;
+    if (accept_len != nullptr) {   // every block is its pending token alone: nothing to accept, the arg-max is the bonus
+      accept_len[r] = 0;
+      bonus[r] = t.i1;
+      if (draft_gap != nullptr) draft_gap[r] = -INFINITY;
+    }
   }
 }
 
