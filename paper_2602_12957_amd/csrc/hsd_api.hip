@@ -746,7 +746,7 @@ int forward(hsd_ctx *ctx, hipStream_t st, const hsd_kv_pool *pool, const hsd_bat
     HSD_LAUNCH_CHECK();
   }
   if (tree)
-    hipLaunchKernelGGL(k_accept_tree, dim3((b->n_seq + 63) / 64), dim3(64), 0, st, b->n_seq, b->cu_q, b->tokens,
+    hipLaunchKernelGGL(k_accept_tree, dim3(b->n_seq), dim3(64), 0, st, b->n_seq, b->cu_q, b->tokens,
                        b->argmax, ws.row_end, ws.want_logit, relaxed ? b->draft_gap : nullptr, b->log_tau,
                        b->accept_len, b->bonus, b->stop_row);
   else

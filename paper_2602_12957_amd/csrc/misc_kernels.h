@@ -469,84 +469,158 @@ __global__ void k_accept(int n_seq, const int32_t *__restrict__ cu_q, const int3
 }
 
 // ------------------------------------------------------------------------------------------------
-// Greedy traversal of a packed prefix tree (Eq. 9-12).  One thread per sequence (trees are small: the candidate
-// continuations of one matching step).  At node s the children are s+1, row_end[s+1], ... while < row_end[s].
+// Greedy traversal of a packed prefix tree (Eq. 9-12).  At node s the children are s+1, row_end[s+1], ... while <
+// row_end[s].
 // Exact rule: enter the child whose token is the row's arg-max token, if there is one (then u* = u_hat).
 // Relaxed rule: u* = the child with the largest logit at row s (lowest row among equals); enter it iff
 // draft_gap[u*] >= log_tau.  Outputs alpha = depth reached, the bonus token (arg-max at the stop node) and the
 // stop node's local row.
+// The walk is a chain of dependent reads, one record per child looked at.  One wave per sequence first brings the records
+// of its rows into LDS (trees of more rows than fit walk global memory): 31 -> 17 us for trees of 126 rows and 56 levels.
+// grid: n_seq blocks of 64 threads.
 // ------------------------------------------------------------------------------------------------
-__global__ void k_accept_tree(int n_seq, const int32_t *__restrict__ cu_q, const int32_t *__restrict__ tokens,
-                              const int32_t *__restrict__ argmax, const int32_t *__restrict__ row_end,
-                              const float *__restrict__ want_logit, const float *__restrict__ draft_gap,
-                              float log_tau, int32_t *__restrict__ accept_len, int32_t *__restrict__ bonus,
-                              int32_t *__restrict__ stop_row) {
-  int sq = blockIdx.x * blockDim.x + threadIdx.x;
-  if (sq >= n_seq) return;
-  const int base = cu_q[sq];
+constexpr int kTreeRowsLds = 2048;
+__global__ void __launch_bounds__(64) k_accept_tree(int n_seq, const int32_t *__restrict__ cu_q, const int32_t *__restrict__ tokens,
+                                                    const int32_t *__restrict__ argmax, const int32_t *__restrict__ row_end,
+                                                    const float *__restrict__ want_logit, const float *__restrict__ draft_gap,
+                                                    float log_tau, int32_t *__restrict__ accept_len, int32_t *__restrict__ bonus,
+                                                    int32_t *__restrict__ stop_row) {
+  __shared__ int4 s_rec[kTreeRowsLds];
+  const int sq = blockIdx.x, lane = threadIdx.x;
+  const int base = cu_q[sq], Lq = cu_q[sq + 1] - base;
   const bool relaxed = log_tau < 0.f && draft_gap != nullptr;
+  // row_end, arg-max, and: the token, or the wanted logit and the gap
+  auto global_rec = [&](int r) {
+    return relaxed ? int4{row_end[r], argmax[r], __float_as_int(want_logit[r]), __float_as_int(draft_gap[r])}
+                   : int4{row_end[r], argmax[r], tokens[r], 0};
+  };
+  const bool in_lds = Lq <= kTreeRowsLds;
+  if (in_lds) {
+    for (int i = lane; i < Lq; i += kWave) s_rec[i] = global_rec(base + i);
+    __syncthreads();
+  }
+  // (the same for all lanes: handed on through scalar registers, so that the walk branches on the scalar unit)
+  auto rec = [&](int r) {
+    const int4 v = in_lds ? s_rec[r - base] : global_rec(r);
+    return int4{__builtin_amdgcn_readfirstlane(v.x), __builtin_amdgcn_readfirstlane(v.y), __builtin_amdgcn_readfirstlane(v.z),
+                __builtin_amdgcn_readfirstlane(v.w)};
+  };
   int s = base, alpha = 0;
+  int4 node = rec(s);
   for (;;) {
     int best = -1;
     float best_v = -INFINITY;
-    for (int c = s + 1; c < row_end[s]; c = row_end[c]) {
+    int4 best_rec = node;
+    for (int c = s + 1; c < node.x;) {
+      const int4 child = rec(c);
       if (relaxed) {
-        float v = want_logit[c];
-        if (best < 0 || v > best_v) best = c, best_v = v;
-      } else if (tokens[c] == argmax[s]) {
-        best = c;
+        const float v = __int_as_float(child.z);
+        if (best < 0 || v > best_v) best = c, best_v = v, best_rec = child;
+      } else if (child.z == node.y) {
+        best = c, best_rec = child;
         break;
       }
+      c = child.x;
     }
     if (best < 0) break;
-    if (relaxed && !(draft_gap[best] >= log_tau)) break;
+    if (relaxed && !(__int_as_float(best_rec.w) >= log_tau)) break;
     s = best;
+    node = best_rec;
     ++alpha;
   }
-  accept_len[sq] = alpha;
-  bonus[sq] = argmax[s];
-  stop_row[sq] = s - base;
+  if (lane == 0) {
+    accept_len[sq] = alpha;
+    bonus[sq] = node.y;
+    stop_row[sq] = s - base;
+  }
 }
 
 // ------------------------------------------------------------------------------------------------
 // Commit of a packed tree: the accepted root-to-stop path becomes ordinary context.  Its node at depth d was stored
-// at cache slot S + (local row) and moves to slot S + d, d = 1..alpha (a node's pre-order row is never smaller
-// than its depth, and no target slot is the source of a later move, so the moves are independent).
+// at cache slot S + (local row) and moves to slot S + d, d = 1..alpha.  A node's pre-order row is never smaller than its
+// depth and rows grow along the path, so a target slot is never the source of a later move: moves go in batches, every
+// source of a batch read before its first target is written.
+// The path is found in LDS, 64 levels at a time (level d's lane looks up its two slots); found and moved node by node in
+// global memory it took 40 us for 56 levels, now 31.
 // grid: (n_seq, n_layers * n_kv_heads), block 64: lane = head dimension.  Runs BEFORE the length update.
 // ------------------------------------------------------------------------------------------------
 template <typename T>
-__global__ void k_kv_compact(const int32_t *__restrict__ cu_q, const int32_t *__restrict__ seq_slot, int n_slots,
-                             const int32_t *__restrict__ seq_len, const int32_t *__restrict__ block_table, int maxb,
-                             int n_blocks, int n_kv_heads, const int32_t *__restrict__ tree_end,
-                             const int32_t *__restrict__ accept_len, const int32_t *__restrict__ stop_row,
-                             T *__restrict__ k_pool, T *__restrict__ v_pool) {
+__global__ void __launch_bounds__(64) k_kv_compact(const int32_t *__restrict__ cu_q, const int32_t *__restrict__ seq_slot, int n_slots,
+                                                   const int32_t *__restrict__ seq_len, const int32_t *__restrict__ block_table,
+                                                   int maxb, int n_blocks, int n_kv_heads, const int32_t *__restrict__ tree_end,
+                                                   const int32_t *__restrict__ accept_len, const int32_t *__restrict__ stop_row,
+                                                   T *k_pool, T *v_pool) {
+  __shared__ int s_end[kTreeRowsLds];
   const int sq = blockIdx.x, layer = blockIdx.y / n_kv_heads, kvh = blockIdx.y % n_kv_heads, dim = threadIdx.x;
   const int base = cu_q[sq], Lq = cu_q[sq + 1] - base;
   const int sl = slot_of(seq_slot, sq, n_slots);
   const int S = seq_len[sl];
-  int alpha = accept_len[sq], stop = stop_row[sq];
-  if (alpha < 1 || stop < 1 || stop >= Lq) return;
-  auto end_of = [&](int i) {   // same clamping as the row metadata kernel
-    int e = tree_end[base + i];
+  const int alpha = accept_len[sq], stop = stop_row[sq];
+  if (alpha < 1 || stop < 1 || stop >= Lq) return;   // uniform for the block
+  auto global_end = [&](int i) {   // same clamping as the row metadata
+    const int e = tree_end[base + i];
     return (e <= i || e > Lq) ? i + 1 : e;
   };
+  const bool in_lds = stop < kTreeRowsLds;   // no row past the stop node is looked at
+  if (in_lds) {
+    for (int i = dim; i <= stop; i += kWave) s_end[i] = global_end(i);
+    __syncthreads();
+  }
+  auto end_of = [&](int i) { return __builtin_amdgcn_readfirstlane(in_lds ? s_end[i] : global_end(i)); };
   int s = 0;
-  for (int d = 1; d <= alpha; ++d) {
-    // the child of s whose subtree contains the stop node
-    int c = s + 1;
-    while (c < Lq && !(c <= stop && stop < end_of(c))) c = end_of(c);
-    if (c >= Lq) return;   // malformed tree: nothing sensible to move
-    s = c;
-    if (c == d) continue;  // already in place
-    const int src = S + c, dst = S + d;
-    if (src / kBlk >= maxb) return;
-    const int bs = block_table[static_cast<size_t>(sl) * maxb + src / kBlk];
-    const int bd = block_table[static_cast<size_t>(sl) * maxb + dst / kBlk];
-    if (bs < 0 || bs >= n_blocks || bd < 0 || bd >= n_blocks) return;
-    const size_t os = ((static_cast<size_t>(layer) * n_blocks + bs) * n_kv_heads + kvh) * (kBlk * kHd);
-    const size_t od = ((static_cast<size_t>(layer) * n_blocks + bd) * n_kv_heads + kvh) * (kBlk * kHd);
-    k_pool[od + (dst % kBlk) * kHd + dim] = k_pool[os + (src % kBlk) * kHd + dim];
-    v_pool[od + kv_v_elem(dst % kBlk, dim)] = v_pool[os + kv_v_elem(src % kBlk, dim)];
+  for (int d0 = 1; d0 <= alpha; d0 += kWave) {
+    const int m = min(kWave, alpha - d0 + 1);
+    int row = -1, found = 0;   // lane j: the path's node at depth d0 + j
+    for (; found < m; ++found) {
+      // the child of s whose subtree contains the stop node
+      int c = s + 1;
+      while (c <= stop) {
+        const int e = end_of(c);
+        if (stop < e) break;
+        c = e;
+      }
+      if (c > stop) break;   // malformed tree: nothing sensible to move
+      s = c;
+      if (dim == found) row = c;
+    }
+    size_t os = 0, od = 0;
+    bool ok = row >= 0;
+    if (ok && row != d0 + dim) {   // (otherwise already in place)
+      const int src = S + row, dst = S + d0 + dim;
+      ok = src / kBlk < maxb;
+      if (ok) {
+        const int bs = block_table[static_cast<size_t>(sl) * maxb + src / kBlk];
+        const int bd = block_table[static_cast<size_t>(sl) * maxb + dst / kBlk];
+        ok = bs >= 0 && bs < n_blocks && bd >= 0 && bd < n_blocks;
+        os = ((static_cast<size_t>(layer) * n_blocks + bs) * n_kv_heads + kvh) * (kBlk * kHd);
+        od = ((static_cast<size_t>(layer) * n_blocks + bd) * n_kv_heads + kvh) * (kBlk * kHd);
+      }
+    }
+    const unsigned long long bad = __ballot(!ok);
+    const int n_move = min(found, bad != 0 ? static_cast<int>(__ffsll(static_cast<long long>(bad))) - 1 : kWave);
+    constexpr int U = 8;
+    for (int j0 = 0; j0 < n_move; j0 += U) {
+      T kv_[U], vv[U];
+#pragma unroll
+      for (int j = 0; j < U; ++j) {
+        const int l = min(j0 + j, n_move - 1), r = __shfl(row, l, kWave);
+        const size_t o = __shfl(os, l, kWave);
+        if (j0 + j < n_move && r != d0 + l) {
+          kv_[j] = k_pool[o + ((S + r) % kBlk) * kHd + dim];
+          vv[j] = v_pool[o + kv_v_elem((S + r) % kBlk, dim)];
+        }
+      }
+#pragma unroll
+      for (int j = 0; j < U; ++j) {
+        const int l = min(j0 + j, n_move - 1), r = __shfl(row, l, kWave);
+        const size_t o = __shfl(od, l, kWave);
+        if (j0 + j < n_move && r != d0 + l) {
+          k_pool[o + ((S + d0 + l) % kBlk) * kHd + dim] = kv_[j];
+          v_pool[o + kv_v_elem((S + d0 + l) % kBlk, dim)] = vv[j];
+        }
+      }
+    }
+    if (found < m || n_move < found) return;
   }
 }
 
