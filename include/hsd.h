@@ -274,6 +274,21 @@ int hsd_debug_set(hsd_ctx *ctx, int knob, int64_t value);
 enum { HSD_PROBE_MFMA = 0, HSD_PROBE_LOAD_REG = 1, HSD_PROBE_LOAD_LDS = 2, HSD_PROBE_LDS_READ = 3 };
 int hsd_probe_launch(void *stream, int kind, int n_workgroups, int iters, int arg, void *scratch, size_t scratch_bytes);
 
+/* Host helpers of decoupled verification (host memory only, no device work, no context).
+ * hsd_drafts_create copies a sequence's draft set: draft i is tokens[offsets[i] .. offsets[i+1]-1]; offsets[0] = 0, not
+ * decreasing.  hsd_drafts_tree matches `window` (the last accepted tokens; n_window = 0: every draft is a candidate from
+ * its start) against the drafts (Eq. 5-6), cuts the candidates at the largest common depth whose packed tree has at most
+ * max_packed rows (depth 1 at least) and packs them under the root `pending` (Eq. 7) as hsd_batch describes.  *n_rows is
+ * the number of rows, also when it exceeds `capacity` (HSD_ENOSPC: nothing was written).  HSD_ERANGE: a token of the tree
+ * is no int32.  hsd_tree_path writes the tokens of rows at depth 1 .. alpha on the way from the root to row `stop`;
+ * HSD_EINVAL if there is no such path.  Calls on different sets, and reading calls on one set, may run in parallel. */
+typedef struct hsd_drafts hsd_drafts;
+int hsd_drafts_create(const int64_t *tokens, const int64_t *offsets, int32_t n_drafts, hsd_drafts **out);
+void hsd_drafts_destroy(hsd_drafts *drafts);
+int hsd_drafts_tree(const hsd_drafts *drafts, const int64_t *window, int32_t n_window, int64_t pending, int64_t max_packed,
+                    int32_t capacity, int32_t *tokens, int32_t *tree_end, int32_t *tree_depth, int32_t *n_rows);
+int hsd_tree_path(const int32_t *tokens, const int32_t *tree_end, int32_t n_rows, int32_t stop, int32_t alpha, int32_t *path);
+
 #ifdef __cplusplus
 }
 #endif

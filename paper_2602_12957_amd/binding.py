@@ -82,7 +82,11 @@ HSD_PROBE_MFMA, HSD_PROBE_LOAD_REG, HSD_PROBE_LOAD_LDS, HSD_PROBE_LDS_READ = ran
 
 EXPORTS = ["hsd_probe_launch", "hsd_verify_region_batch_noalloc", "hsd_noalloc_scratch_bytes", "hsd_debug_set", "hsd_profile_enable", "hsd_profile_read", "hsd_status_string", "hsd_validate_model", "hsd_validate_batch", "hsd_create", "hsd_destroy",
            "hsd_workspace_bytes", "hsd_kv_pool_init", "hsd_verify_region_batch", "hsd_verify_page",
-           "hsd_kv_commit_rollback", "hsd_prefill"]
+           "hsd_kv_commit_rollback", "hsd_prefill", "hsd_drafts_create", "hsd_drafts_destroy", "hsd_drafts_tree", "hsd_tree_path"]
+lib.hsd_drafts_create.argtypes = [vp, vp, i32, C.POINTER(vp)]
+lib.hsd_drafts_destroy.argtypes, lib.hsd_drafts_destroy.restype = [vp], None
+lib.hsd_drafts_tree.argtypes = [vp, vp, i32, C.c_int64, C.c_int64, i32, vp, vp, vp, C.POINTER(i32)]
+lib.hsd_tree_path.argtypes = [vp, vp, i32, i32, i32, vp]
 
 
 class HsdError(RuntimeError):
@@ -130,3 +134,17 @@ def hsd_debug_set(ctx, knob, value):
     check("hsd_debug_set", lib.hsd_debug_set(ctx, knob, value))
 def hsd_probe_launch(stream, kind, n_workgroups, iters, arg, scratch, scratch_bytes):
     check("hsd_probe_launch", lib.hsd_probe_launch(stream, kind, n_workgroups, iters, arg, scratch, scratch_bytes))
+
+def hsd_drafts_create(tokens, offsets):
+    """tokens, offsets: int64 numpy arrays"""
+    out = vp()
+    check("hsd_drafts_create", lib.hsd_drafts_create(tokens.ctypes.data, offsets.ctypes.data, len(offsets) - 1, C.byref(out)))
+    return out
+def hsd_drafts_destroy(drafts): lib.hsd_drafts_destroy(drafts)
+def hsd_drafts_tree(drafts, window, pending, max_packed, out):
+    """window: int64 array; out: int32 array [3, capacity].  Returns (status, rows)."""
+    n, cap, a = i32(), out.shape[1], out.ctypes.data
+    rc = lib.hsd_drafts_tree(drafts, window.ctypes.data, len(window), pending, max_packed, cap, a, a + 4 * cap, a + 8 * cap, C.byref(n))
+    return rc, n.value
+def hsd_tree_path(tokens, tree_end, stop, alpha, path):
+    check("hsd_tree_path", lib.hsd_tree_path(tokens.ctypes.data, tree_end.ctypes.data, len(tokens), stop, alpha, path.ctypes.data))

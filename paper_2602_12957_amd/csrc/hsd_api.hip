@@ -15,6 +15,7 @@
 #include "attn_simple.h"
 #include "attn_wide.h"
 #include "common.h"
+#include "draft_trees.h"
 #include "epilogues.h"
 #include "gemm_mfma.h"
 #include "gemm_mfma8.h"
@@ -34,6 +35,10 @@ using namespace hsd;
 // uses the array's name as an address, only the pointer hipGetSymbolAddress returns for the current device.
 constexpr size_t kStaticWsBytes = size_t{16} << 20;
 static __device__ __align__(256) unsigned char g_static_ws[kStaticWsBytes];
+
+struct hsd_drafts {
+  DraftSet set;
+};
 
 struct hsd_ctx {
   hsd_model_desc desc;
@@ -1046,6 +1051,72 @@ int hsd_kv_commit_rollback(hsd_ctx *ctx, void *stream, const hsd_kv_pool *pool, 
                      b->seq_slot, b->n_slots, b->seq_len, b->block_table, b->max_blocks_per_seq, pool->n_blocks, pool->free_list,
                      pool->free_count, b->accept_len, b->bonus, pending_out, 0);
   HSD_LAUNCH_CHECK();
+  return HSD_OK;
+}
+
+int hsd_drafts_create(const int64_t *tokens, const int64_t *offsets, int32_t n_drafts, hsd_drafts **out) {
+  if (out == nullptr) return HSD_EINVAL;
+  *out = nullptr;
+  if (n_drafts < 0 || offsets == nullptr || offsets[0] != 0) return HSD_EINVAL;
+  for (int32_t i = 0; i < n_drafts; ++i)
+    if (offsets[i + 1] < offsets[i]) return HSD_EINVAL;
+  if (tokens == nullptr && offsets[n_drafts] > 0) return HSD_EINVAL;
+  hsd_drafts *d = new (std::nothrow) hsd_drafts();
+  if (d == nullptr) return HSD_ENOSPC;
+  try {
+    d->set.begin.assign(offsets, offsets + n_drafts + 1);
+    if (offsets[n_drafts] > 0) d->set.tokens.assign(tokens, tokens + offsets[n_drafts]);
+  } catch (...) {   // out of host memory
+    delete d;
+    return HSD_ENOSPC;
+  }
+  *out = d;
+  return HSD_OK;
+}
+
+void hsd_drafts_destroy(hsd_drafts *drafts) { delete drafts; }
+
+int hsd_drafts_tree(const hsd_drafts *drafts, const int64_t *window, int32_t n_window, int64_t pending, int64_t max_packed,
+                    int32_t capacity, int32_t *tokens, int32_t *tree_end, int32_t *tree_depth, int32_t *n_rows) {
+  if (drafts == nullptr || n_rows == nullptr || n_window < 0 || (n_window > 0 && window == nullptr) || capacity < 0 ||
+      (capacity > 0 && (tokens == nullptr || tree_end == nullptr || tree_depth == nullptr)))
+    return HSD_EINVAL;
+  *n_rows = 0;
+  try {
+    DraftTree t;
+    t.build(drafts->set, window, n_window, pending, max_packed);
+    const size_t n = t.token.size();
+    if (n > 0x7fffffffu) return HSD_ERANGE;
+    for (const int64_t v : t.token)
+      if (v != static_cast<int32_t>(v)) return HSD_ERANGE;
+    *n_rows = static_cast<int32_t>(n);
+    if (*n_rows > capacity) return HSD_ENOSPC;
+    for (size_t v = 0; v < n; ++v) {
+      const int32_t r = t.row[v];
+      tokens[r] = static_cast<int32_t>(t.token[v]);
+      tree_end[r] = r + t.size[v];
+      tree_depth[r] = t.depth[v];
+    }
+  } catch (...) {
+    return HSD_ENOSPC;
+  }
+  return HSD_OK;
+}
+
+int hsd_tree_path(const int32_t *tokens, const int32_t *tree_end, int32_t n_rows, int32_t stop, int32_t alpha, int32_t *path) {
+  if (tokens == nullptr || tree_end == nullptr || n_rows < 1 || stop < 0 || stop >= n_rows || alpha < 0 || (alpha > 0 && path == nullptr))
+    return HSD_EINVAL;
+  int32_t row = 0;
+  for (int32_t d = 0; d < alpha; ++d) {
+    int32_t c = row + 1;
+    while (c <= stop && stop >= tree_end[c]) {
+      if (tree_end[c] <= c) return HSD_EINVAL;
+      c = tree_end[c];
+    }
+    if (c > stop) return HSD_EINVAL;
+    path[d] = tokens[c];
+    row = c;
+  }
   return HSD_OK;
 }
 

@@ -135,8 +135,8 @@ class Engine:
         self.k_pool = torch.zeros(pool_elems, dtype=es, device=self.dev)
         self.v_pool = torch.zeros(pool_elems, dtype=es, device=self.dev)
         # all KV bookkeeping lives in one int32 buffer so that a snapshot/restore is a single device copy
-        # (the outputs the host reads back every round -- status, alpha, bonus -- sit together at its end: one copy)
-        n_state = n_blocks + 1 + n_slots + n_slots * max_blocks_per_seq + 1 + 2 * n_slots
+        # (the outputs the host reads back every round -- status, alpha, bonus, stop rows -- sit together at its end: one copy)
+        n_state = n_blocks + 1 + n_slots + n_slots * max_blocks_per_seq + 1 + 3 * n_slots
         self._state = torch.zeros(n_state, dtype=torch.int32, device=self.dev)
         o = 0
         self.free_list = self._state[o:o + n_blocks]; o += n_blocks
@@ -147,7 +147,8 @@ class Engine:
         self.status = self._state[o:o + 1]
         self.accept_len = self._state[o + 1:o + 1 + n_slots]
         self.bonus = self._state[o + 1 + n_slots:o + 1 + 2 * n_slots]
-        self._readback = self._state[o:o + 1 + 2 * n_slots]
+        self.stop_row = self._state[o + 1 + 2 * n_slots:o + 1 + 3 * n_slots]
+        self._readback = self._state[o:o + 1 + 3 * n_slots]
         self._snapshot = torch.zeros_like(self._state)
         self.cpool = B.hsd_kv_pool(_ptr(self.k_pool), _ptr(self.v_pool), n_blocks, _ptr(self.free_list),
                                    _ptr(self.free_count))
@@ -161,9 +162,8 @@ class Engine:
         self.argmax = torch.zeros(max_total_q, dtype=torch.int32, device=self.dev)
         self.margin = torch.zeros(max_total_q, dtype=torch.float32, device=self.dev)
         self.gap = torch.zeros(max_total_q, dtype=torch.float32, device=self.dev)
-        self.stop_row = torch.zeros(n_slots, dtype=torch.int32, device=self.dev)
         self.pending = torch.zeros(n_slots, dtype=torch.int32, device=self.dev)
-        self._h_out = torch.empty(2 * n_slots + 1, dtype=torch.int32).pin_memory()
+        self._h_out = torch.empty(3 * n_slots + 1, dtype=torch.int32).pin_memory()
         self.embeds = None
         self.logits_dump = (torch.zeros((max_dump, desc.vocab), dtype=torch.float32, device=self.dev)
                             if max_dump > 0 else None)
@@ -350,12 +350,14 @@ class Engine:
         B.hsd_kv_commit_rollback(self.ctx, self.stream, self.cpool, self._batch,
                                  _ptr(pending_out if pending_out is not None else self.pending))
 
-    def read_acceptance(self, n: int):
-        """Small device-to-host readback of (alpha, bonus, status); synchronises the stream."""
+    def read_acceptance(self, n: int, stop_rows: bool = False):
+        """Small device-to-host readback of (alpha, bonus, status), with stop_rows also of the stop nodes' local rows (tree
+        blocks); synchronises the stream."""
         self._h_out.copy_(self._readback, non_blocking=True)
         torch.cuda.current_stream(self.dev).synchronize()
-        h = self._h_out.numpy()
-        return h[1:1 + n].copy(), h[1 + self.n_slots:1 + self.n_slots + n].copy(), int(h[0])
+        h, m = self._h_out.numpy(), self.n_slots
+        res = h[1:1 + n].copy(), h[1 + m:1 + m + n].copy(), int(h[0])
+        return res + (h[1 + 2 * m:1 + 2 * m + n].copy(),) if stop_rows else res
 
     def greedy_decode(self, slots: Sequence[int], pending: Sequence[int], n_tokens: int,
                       mode: str = "region") -> np.ndarray:

@@ -13,7 +13,8 @@ from typing import List, Optional, Sequence
 
 import numpy as np
 
-from .runtime import Engine, pack_prefix_tree
+from . import binding as B
+from .runtime import Engine
 
 
 def match_candidates(accepted: Sequence[int], drafts: Sequence[Sequence[int]], n: int) -> List[List[int]]:
@@ -62,6 +63,47 @@ def cap_candidates(candidates: Sequence[Sequence[int]], max_packed: int) -> List
     return out
 
 
+class DraftTrees:
+    """A sequence's draft set in the library: `tree` is match_candidates, cap_candidates and runtime.pack_prefix_tree in
+    one native call."""
+
+    def __init__(self, drafts: Sequence[Sequence[int]]):
+        rows = [self._ints(d) for d in drafts]
+        offsets = np.zeros(len(rows) + 1, dtype=np.int64)
+        np.cumsum([len(r) for r in rows], out=offsets[1:])
+        self._set = B.hsd_drafts_create(np.concatenate(rows) if rows else np.zeros(0, np.int64), offsets)
+
+    @staticmethod
+    def _ints(d):
+        a = np.asarray(d)
+        return np.ascontiguousarray(a, dtype=np.int64) if a.ndim == 1 and a.dtype.kind in "iu" and a.dtype != np.uint64 else \
+            np.fromiter((int(t) for t in d), dtype=np.int64, count=len(d))
+
+    def tree(self, accepted: Sequence[int], n: int, pending: int, max_packed: int):
+        """(tokens, tree_end, tree_depth) of the capped, packed candidates that follow the last n accepted tokens."""
+        window = np.asarray(accepted[-n:] if n > 0 else [], dtype=np.int64)
+        out = np.empty((3, max(min(max_packed, 4096), 1)), dtype=np.int32)
+        rc, rows = B.hsd_drafts_tree(self._set, window, int(pending), int(max_packed), out)
+        if rc == B.HSD_ENOSPC and rows > out.shape[1]:
+            out = np.empty((3, rows), dtype=np.int32)
+            rc, rows = B.hsd_drafts_tree(self._set, window, int(pending), int(max_packed), out)
+        if rc == B.HSD_ERANGE:
+            raise OverflowError("a token of the packed tree does not fit 32 bits")
+        B.check("hsd_drafts_tree", rc)
+        return out[0, :rows], out[1, :rows], out[2, :rows]
+
+    def close(self):
+        if self._set is not None:
+            B.hsd_drafts_destroy(self._set)
+            self._set = None
+
+    def __del__(self):
+        try:
+            self.close()
+        except Exception:
+            pass
+
+
 class SpecDecoder:
     """SpecDecode(p_theta, z, Y~) (Eq. 1) for a batch of sequences whose prefixes are already in the engine's cache."""
 
@@ -79,32 +121,25 @@ class SpecDecoder:
         done = [False] * n
         stats = dict(rounds=0, rows=0, accepted=0, plain_steps=0, seq_rounds=0,
                      per_seq=[[] for _ in range(n)])      # per sequence: (tree rows, accepted) of each of its rounds
+        draft_trees = [DraftTrees(draft_sets[i]) for i in range(n)]
         while not all(done):
             active = [i for i in range(n) if not done[i]]
             blocks, trees = [], []
             for i in active:
-                cands = cap_candidates(match_candidates(out[i], draft_sets[i], self.n_window), self.max_packed)
-                t, e, d = pack_prefix_tree(pend[i], cands)
+                t, e, d = draft_trees[i].tree(out[i], self.n_window, pend[i], self.max_packed)
                 blocks.append(t), trees.append((e, d))
                 stats["plain_steps"] += int(len(t) == 1)
                 stats["rows"] += len(t)
-            o = self.eng.verify([slots[i] for i in active], blocks, self.mode, log_tau=self.log_tau, trees=trees)
+            self.eng.verify([slots[i] for i in active], blocks, self.mode, log_tau=self.log_tau, trees=trees)
             self.eng.commit()
-            alpha, bonus, status = self.eng.read_acceptance(len(active))
+            alpha, bonus, status, stop = self.eng.read_acceptance(len(active), stop_rows=True)
             if status:
                 raise RuntimeError(f"SpecDecoder: device status {status}")
-            stop = o.stop_row.cpu().numpy()
             for j, i in enumerate(active):
-                # the accepted path: walk from the stop node up through the packed tree
-                e, d = trees[j]
-                path, s = [], int(stop[j])
-                row = 0
-                for depth in range(1, int(alpha[j]) + 1):
-                    c = row + 1
-                    while not (c <= s < e[c]):
-                        c = int(e[c])
-                    path.append(int(blocks[j][c]))
-                    row = c
+                # the accepted path: from the root down to the stop node
+                path = np.empty(int(alpha[j]), dtype=np.int32)
+                B.hsd_tree_path(blocks[j], trees[j][0], int(stop[j]), len(path), path)
+                path = path.tolist()
                 out[i].extend(path)
                 out[i].append(int(bonus[j]))
                 pend[i] = int(bonus[j])
