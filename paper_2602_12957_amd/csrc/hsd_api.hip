@@ -299,6 +299,8 @@ int effective_gemm_cfg(const hsd_ctx *ctx, int site, int M, int N, int K) {
     //   QKV              1 row 9.8 / 8.8, 64 11.2 / 10.8, 320 12.0 / 11.3, 512 12.8 / 12.5, 1008 15.0 / 14.5, 1280 18.6 / 14.9
     //   gate/up          32 rows 12.0 / 11.0 (32 x 32), 64 12.0 / 11.4 (32 x 64), 128 13.8 / 13.2, 256 15.0 / 14.3
     // The other side of the line: gate/up 320 rows 17.7 / 21.4 (128 x 64, 384 tiles), QKV 1856 20.3 / 24.0 (360).
+    // Gate/up beyond: 128x128 tiles (7) while they fit one round (512 rows: 18.3; 256x128 23.4), then 256x128 (6; 768 rows
+    // 26.2 / 23.7, 1008 27.9 / 26.1), then 256x256 (1280 rows 33.1; 256x128 42.7).
     // Of the two tiles with 96 rows, 64 x 32 is ahead with K = 4096 (512 rows 18.0 / 20.5) and 32 x 64 in dual mode (11.4 /
     // 11.9).  Past one round: 9 / 7: 64x128 / 128x128 tiles with four operand-moving waves; 10: the 64x128 tile fed by a
     // requesting wave (k_gemm_mfma_d), for one row tile.  At ~4 k rows its 128x128 tile (11) yields one workgroup per unit
@@ -321,7 +323,8 @@ int effective_gemm_cfg(const hsd_ctx *ctx, int site, int M, int N, int K) {
     else if ((site == kSiteO || site == kSiteDown) && M >= 3072) cfg = 11;
     else if (site == kSiteQKV) cfg = 7;
     else if (site == kSiteO || site == kSiteDown) cfg = 9;
-    else if (site == kSiteGateUp) cfg = M <= 1024 ? 7 : cfg;
+    else if (site == kSiteGateUp && one_round(7, 128, 128)) cfg = 7;
+    else if (site == kSiteGateUp && one_round(6, 256, 128)) cfg = 6;
   }
   // ... and a pass over many rows (prefill chunks, long-document blocks) has enough row tiles to fill the chip with
   // the 256x256 tile also on the narrower projections (measured crossover: about 6 k rows at N = 1536)
