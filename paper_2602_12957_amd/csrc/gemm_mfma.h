@@ -113,14 +113,24 @@ __device__ __forceinline__ void gemm_epilogue(floatx16 (&acc)[Cfg::TM][Cfg::TN],
 #pragma unroll
           for (int v = 0; v < 16; ++v) acc[i][j][v] *= rsc;
       }
-      Top2 tp = top2_init();
+      // Top two of the lane's TM * 16 logits, whose ids ascend with e = 16 i + v: four instructions a value (the second
+      // largest of three is their median) where comparing records took nine (the launch at 1856 rows 152 -> 131 us).
+      auto id_of = [&](int e) { return n0 + wi * (BP / Cfg::WM) + (e >> 4) * 32 + 8 * ((e & 15) >> 2) + 4 * half + (e & 3); };
+      float m1 = -INFINITY, m2 = -INFINITY;
+      int e1 = 0;
 #pragma unroll
-      for (int i = 0; i < TM; ++i)
+      for (int e = 0; e < TM * 16; ++e) {
+        const float x = acc[e >> 4][j][e & 15];
+        e1 = x > m1 ? e : e1;
+        m2 = __builtin_amdgcn_fmed3f(m1, m2, x);
+        m1 = fmaxf(m1, x);
+      }
+      Top2 tp{m1, id_of(e1), m2};
+      if (m1 == -INFINITY) {   // nothing above -inf: the record as comparing gives it (first -inf, or none among NaNs)
+        tp = top2_init();
 #pragma unroll
-        for (int v = 0; v < 16; ++v) {
-          int n = n0 + wi * (BP / Cfg::WM) + i * 32 + 8 * (v >> 2) + 4 * half + (v & 3);
-          top2_push(tp, acc[i][j][v], n);
-        }
+        for (int e = 0; e < TM * 16; ++e) top2_push(tp, acc[e >> 4][j][e & 15], id_of(e));
+      }
       if (epi.want_logit != nullptr && m < M) {
         // this lane holds row m's logits at ids nb + 32*i + 8*(v/4) + 4*half + v%4, i < TM, v < 16
         const int nb = n0 + wi * (BP / Cfg::WM);
