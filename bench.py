@@ -317,7 +317,7 @@ def headline_extras(out, st, args):
         "batch": n, "weight_stream_frac_of_hbm_peak": round(weight_bytes / (dar / n_ar) / (PEAK_HBM_GBPS * 1e9), 4),
         "speedup_to_completion": round(out["to_completion"]["committed_tokens_per_s"] / ar_rate, 2),
         "note": "same library, one token per sequence and pass; a pass over 16 rows leaves most of the chip idle "
-                "(serial attention tasks, weights streamed by 32 to 128 workgroups), so the ratio flatters verification (see weight_stream_frac_of_hbm_peak)"}
+                "(64 attention tasks, weights streamed by 64 to 256 workgroups, launch latency), so the ratio flatters verification (see weight_stream_frac_of_hbm_peak)"}
     # --- relaxed acceptance (paper Section 3.2, Eq. 11; operating point tau = 0.75, Section 4.1) on near-miss drafts:
     # the greedy target with 15 % of its tokens replaced by the model's own second choice at that position
     eng.restore()

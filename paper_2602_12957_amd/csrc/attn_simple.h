@@ -9,6 +9,7 @@
 
 #include "common.h"
 #include "gemm_simple.h"
+#include "misc_kernels.h"
 
 namespace hsd {
 
@@ -35,8 +36,12 @@ __global__ void __launch_bounds__(256) k_attn_simple(int n_q_heads, RowMeta meta
   // 16 consecutive values of a lane's dimension as they lie in a V page (one page, slot order: kv_v_slot)
   auto load_page = [&](int id, float *v) {
     const T *p = vpool + kv_block_offset(kv, max(id, 0), kvh) + lane * kBlk;
-    load8(p, v);
-    load8(p + 8, v + 8);
+#pragma unroll
+    for (int i = 0; i < 16; i += 4) {   // (the pool needs no more than its elements' alignment)
+      const floatx4 x = load4(p + i);
+#pragma unroll
+      for (int e = 0; e < 4; ++e) v[i + e] = x[e];
+    }
   };
   const float scale = 0.125f;  // 1/sqrt(64)
   float m = -INFINITY, l = 0.f, acc = 0.f;

@@ -152,18 +152,6 @@ struct EpiResidual {
   static constexpr bool kRowScale = false;
   float *x;
   int ld;
-  static constexpr int kPiece = 4;
-  __device__ __forceinline__ void piece(int m, int n, float (&lo)[4], float (&hi)[4]) const {
-    float *p = x + static_cast<size_t>(m) * ld + n;
-    const floatx4 a = *reinterpret_cast<const floatx4 *>(p), b = *reinterpret_cast<const floatx4 *>(p + 32);
-#pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      lo[e] += a[e];
-      hi[e] += b[e];
-    }
-    store_row(p, lo);
-    store_row(p + 32, hi);
-  }
   __device__ __forceinline__ void pair(int m, int n, float lo, float hi) const {
     float *p = x + static_cast<size_t>(m) * ld + n;
     p[0] += lo;

@@ -360,7 +360,8 @@ int effective_gemm_cfg(const hsd_ctx *ctx, int site, int M, int N, int K) {
 template <typename T, typename Epi>
 int launch_gemm(const hsd_ctx *ctx, hipStream_t st, int site, int M, int N, int K, const void *A, const void *W,
                 const Epi &epi) {
-  if constexpr (std::is_same<T, bf16>::value) {
+  // (the plain path's residual epilogue goes to the plain kernels only)
+  if constexpr (std::is_same<T, bf16>::value && !std::is_same<Epi, EpiResidual>::value) {
     const int cfg = effective_gemm_cfg<T>(ctx, site, M, N, K);
     if constexpr (GemmModeOf<Epi>::value != kModeSwapLM) {
       // Rounds over the chip.  The 256x256 kernel runs one tile per compute unit at a time, so a tile count just
@@ -424,7 +425,7 @@ int launch_gemm(const hsd_ctx *ctx, hipStream_t st, int site, int M, int N, int 
         break;
 #define HSD_CASE_R(c, cfg_t, ok)                                                                       \
   case c:                                                                                            \
-    if constexpr (GemmModeOf<Epi>::value != kModeSwapLM && !std::is_same<Epi, EpiResidual>::value && (ok)) \
+    if constexpr (GemmModeOf<Epi>::value != kModeSwapLM && (ok))                                     \
       return launch_gemm_mfma_r<cfg_t>(st, M, N, K, A, W, epi);                                      \
     break;
       // 14 to 17: the residual projections have epilogues of their own there (see residual_proj); 16 weight rows are not

@@ -167,10 +167,15 @@ __global__ void k_rmsnorm(int n_rows, int d, float eps, const float *__restrict_
 
 // Residual row r and the first norm's operand: x[r,:] = table[tokens[r],:] (widened to fp32), or embeds[r,:] if tokens[r] < 0
 // (zeros without embeds), and h[r,:] as k_rmsnorm makes it from x -- same lanes, same sums.  One wave.
-__device__ __forceinline__ floatx4 load4(const float *p) { return *reinterpret_cast<const floatx4 *>(p); }
+// Table and embeddings come from the caller and need no more than their element's alignment.
+__device__ __forceinline__ floatx4 load4(const float *p) {
+  typedef float floatx4u __attribute__((ext_vector_type(4), aligned(4)));
+  return *reinterpret_cast<const floatx4u *>(p);
+}
 __device__ __forceinline__ floatx4 load4(const bf16 *p) {
-  const uint2 u = *reinterpret_cast<const uint2 *>(p);
-  return floatx4{__uint_as_float(u.x << 16), __uint_as_float(u.x & 0xffff0000u), __uint_as_float(u.y << 16), __uint_as_float(u.y & 0xffff0000u)};
+  typedef uint32_t u32x2u __attribute__((ext_vector_type(2), aligned(2)));
+  const u32x2u u = *reinterpret_cast<const u32x2u *>(p);
+  return floatx4{__uint_as_float(u[0] << 16), __uint_as_float(u[0] & 0xffff0000u), __uint_as_float(u[1] << 16), __uint_as_float(u[1] & 0xffff0000u)};
 }
 template <typename T>
 __device__ __forceinline__ void embed_norm_row(const PassSetup &ps, int r, int lane) {
