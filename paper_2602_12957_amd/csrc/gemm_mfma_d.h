@@ -46,8 +46,10 @@ typedef __attribute__((address_space(3))) unsigned char *LdsBytePtr;
 // One LDS-direct load: lane l's 16 bytes at buffer offset voff(l) + soff go to LDS address dst + 16 l (dst is wave
 // uniform).  A plain function on purpose: called with template-dependent arguments the builtin itself makes the host
 // pass drop the enclosing kernel's instantiation without a diagnostic.
+// (NT: with the non-temporal hint, so that the caches do not keep the line in place of others)
+template <bool NT = false>
 __device__ __forceinline__ void lds_load16(__amdgpu_buffer_rsrc_t rs, LdsBytePtr dst, int voff, int soff) {
-  __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, dst, 16, voff, soff, 0, 0);
+  __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, dst, 16, voff, soff, 0, NT ? 2 : 0);
 }
 
 // s_waitcnt vmcnt(N) with the other counters left alone (N < 64)

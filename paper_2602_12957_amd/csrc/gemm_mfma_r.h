@@ -52,7 +52,8 @@ struct GemmCfgR {
 // grid: ceil((M - m_base) / BP) * (N / kCols / (dual ? 1 : 2)) workgroups of Cfg::kThreads threads, Cfg::kSmemBytes +
 // kRowScaleBytes dynamic LDS; the tiles cover rows m_base .. M-1 (see k_gemm_mfma_d).  K a multiple of 32; N a multiple of 64; both matrices below 2 GiB (32-bit buffer offsets).
 // Every wave executes exactly ceil(K / SK) + 1 workgroup barriers.
-template <typename Cfg, int MODE, typename Epi>
+// NT: the weight loads are non-temporal (weights_pass_by in hsd_api.hip says when).
+template <typename Cfg, int MODE, typename Epi, bool NT>
 __global__ void __launch_bounds__(Cfg::kThreads) k_gemm_mfma_r(int M, int N, int K, int m_base, const bf16 *__restrict__ A,
                                                                const bf16 *__restrict__ W, Epi epi) {
   static_assert(MODE == kModeNormal || MODE == kModeDual, "normal or dual mode");
@@ -98,7 +99,7 @@ __global__ void __launch_bounds__(Cfg::kThreads) k_gemm_mfma_r(int M, int N, int
     const LdsBytePtr dst = lds + (slot) * Cfg::kStageBytes;                                            \
     const int kv = (s) < nf ? 0 : (s) * RB, ks = (s) < nf ? (s) * RB : 0;                              \
     _Pragma("unroll") for (int j = 0; j < NLQ; ++j)                                                    \
-        lds_load16(rs_q, dst + (BP * RB + (4 * j + lw) * 1024), vq[j] + kv, ks);                       \
+        lds_load16<NT>(rs_q, dst + (BP * RB + (4 * j + lw) * 1024), vq[j] + kv, ks);                   \
     _Pragma("unroll") for (int j = 0; j < NLP; ++j)                                                    \
         lds_load16(rs_p, dst + (4 * j + lw) * 1024, vp[j] + kv, ks);                                   \
   }

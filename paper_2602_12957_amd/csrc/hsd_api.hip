@@ -234,13 +234,17 @@ int launch_gemm_mfma_d(hipStream_t st, int M, int N, int K, const void *A, const
 }
 
 template <typename Cfg, typename Epi>
-int launch_gemm_mfma_r(hipStream_t st, int M, int N, int K, const void *A, const void *W, Epi epi, int m_base = 0) {
+int launch_gemm_mfma_r(hipStream_t st, int M, int N, int K, const void *A, const void *W, Epi epi, int m_base = 0,
+                       bool pass_by = false) {
   constexpr int MODE = GemmModeOf<Epi>::value;
-  auto kern = k_gemm_mfma_r<Cfg, MODE, Epi>;
   constexpr int smem = Cfg::kSmemBytes + kRowScaleBytes;
+  auto kern = k_gemm_mfma_r<Cfg, MODE, Epi, false>, kern_nt = k_gemm_mfma_r<Cfg, MODE, Epi, true>;
   static const hipError_t attr_rc = hipFuncSetAttribute(reinterpret_cast<const void *>(kern),
                                                         hipFuncAttributeMaxDynamicSharedMemorySize, smem);
-  if (attr_rc != hipSuccess) return HSD_EHIP;
+  static const hipError_t attr_nt = hipFuncSetAttribute(reinterpret_cast<const void *>(kern_nt),
+                                                        hipFuncAttributeMaxDynamicSharedMemorySize, smem);
+  if (attr_rc != hipSuccess || attr_nt != hipSuccess) return HSD_EHIP;
+  if (pass_by) kern = kern_nt;
   const int tiles = (M - m_base + Cfg::BP - 1) / Cfg::BP * (N / Cfg::kCols / (MODE == kModeDual ? 1 : 2));
   hipLaunchKernelGGL(kern, dim3(tiles), dim3(Cfg::kThreads), smem, st, M, N, K, m_base, static_cast<const bf16 *>(A),
                      static_cast<const bf16 *>(W), epi);
@@ -359,7 +363,7 @@ int effective_gemm_cfg(const hsd_ctx *ctx, int site, int M, int N, int K) {
 
 template <typename T, typename Epi>
 int launch_gemm(const hsd_ctx *ctx, hipStream_t st, int site, int M, int N, int K, const void *A, const void *W,
-                const Epi &epi) {
+                const Epi &epi, bool pass_by) {
   // (the plain path's residual epilogue goes to the plain kernels only)
   if constexpr (std::is_same<T, bf16>::value && !std::is_same<Epi, EpiResidual>::value) {
     const int cfg = effective_gemm_cfg<T>(ctx, site, M, N, K);
@@ -426,7 +430,7 @@ int launch_gemm(const hsd_ctx *ctx, hipStream_t st, int site, int M, int N, int 
 #define HSD_CASE_R(c, cfg_t, ok)                                                                       \
   case c:                                                                                            \
     if constexpr (GemmModeOf<Epi>::value != kModeSwapLM && (ok))                                     \
-      return launch_gemm_mfma_r<cfg_t>(st, M, N, K, A, W, epi);                                      \
+      return launch_gemm_mfma_r<cfg_t>(st, M, N, K, A, W, epi, 0, pass_by);                          \
     break;
       // 14 to 17: the residual projections have epilogues of their own there (see residual_proj); 16 weight rows are not
       // enough for dual mode
@@ -626,6 +630,26 @@ int launch_attention(const hsd_ctx *ctx, hipStream_t st, const hsd_batch *b, con
   return HSD_OK;
 }
 
+// Whether a pass's layer weights are read past the memory-side cache (k_gemm_mfma_r, non-temporal loads; same bits).
+// One pass after the other walks the same layers.  Weights larger than the cache come from HBM each time whatever is done,
+// and push out what would have stayed there: the keys and values, and the LM head.  24-layer model (730 MB of layer
+// weights, 67 MB of LM head, 25 KB a key), us a pass with / without, sequences x keys: 1 x 1055 758 / 800, 2 x 300
+// 692 / 751, 7 x 1055 801 / 863, 16 x 200 752 / 779, 64 x 100 843 / 869; 4 x 1055 with 64 rows 904 / 958, with 128 1003 /
+// 1049, 16 x 64 with 128 rows 902 / 941 (attention 13.9 -> 12.9, LM head 24 -> 20).  8 x 1055 was even, 16 x 1055 (415 MB)
+// 900 / 885 and 16 steps of decoding 13.2 / 13.0 ms: nothing stays then, and part of the weights would have.  The lengths
+// are on the device, so the line is drawn by what the block tables can hold.  From 256 rows on several workgroups share a
+// weight row through L2: gate/up 12.4 -> 13.4, down 14.4 -> 14.2, LM head 34 -> 31, the pass even.
+constexpr int64_t kCacheBytes = int64_t{256} << 20;
+constexpr int kPassByRows = 128;
+bool weights_pass_by(const hsd_model_desc &d, const hsd_kv_pool *pool, const hsd_batch *b) {
+  if (pool == nullptr || b->total_q > kPassByRows) return false;
+  const int64_t qdim = d.n_q_heads * d.head_dim, kvdim = d.n_kv_heads * d.head_dim, dm = d.d_model;
+  const int64_t layers = 2 * d.n_layers * (dm * (qdim + 2 * kvdim) + qdim * dm + 3 * dm * d.d_ffn);
+  const int64_t blocks = std::min<int64_t>(pool->n_blocks, static_cast<int64_t>(b->n_seq) * b->max_blocks_per_seq);
+  const int64_t kept = blocks * HSD_KV_BLOCK_TOKENS * 2 * kvdim * 2 * d.n_layers + 2 * dm * d.vocab;
+  return layers > kCacheBytes && kept <= kCacheBytes;
+}
+
 template <typename T>
 int forward(hsd_ctx *ctx, hipStream_t st, const hsd_kv_pool *pool, const hsd_batch *b, void *ws_base, bool page_mode,
             bool with_head) {
@@ -637,6 +661,7 @@ int forward(hsd_ctx *ctx, hipStream_t st, const hsd_kv_pool *pool, const hsd_bat
   int rc;
 
   const AttnPlan plan = plan_attention<T>(ctx, b, page_mode);
+  const bool pass_by = weights_pass_by(d, pool, b);
   const bool dump = with_head && b->n_dump > 0 && b->logits_dump != nullptr;
   {
     ProfScope prof(ctx, st, HSD_PROF_RMSNORM);   // the pass's first norm is in here
@@ -682,16 +707,16 @@ int forward(hsd_ctx *ctx, hipStream_t st, const hsd_kv_pool *pool, const hsd_bat
           const EpiResidualQuarter e4{ws.x, d.d_model, next_gain, static_cast<bf16 *>(ws.h), ws.ss, ss2, plane};
           const EpiResidualNorm en{ws.x, d.d_model, next_gain, static_cast<bf16 *>(ws.h), ws.ss, nullptr, 0};
           switch (cfg) {   // narrow tiles
-            case 14: return launch_gemm_mfma_r<GemmCfgR11>(st, Tq, d.d_model, K, A, W, e4);
-            case 15: return launch_gemm_mfma_r<GemmCfgR21>(st, Tq, d.d_model, K, A, W, e4);
-            case 16: return launch_gemm_mfma_r<GemmCfgR22>(st, Tq, d.d_model, K, A, W, eh);
-            case 17: return launch_gemm_mfma_r<GemmCfgR42>(st, Tq, d.d_model, K, A, W, eh);
+            case 14: return launch_gemm_mfma_r<GemmCfgR11>(st, Tq, d.d_model, K, A, W, e4, 0, pass_by);
+            case 15: return launch_gemm_mfma_r<GemmCfgR21>(st, Tq, d.d_model, K, A, W, e4, 0, pass_by);
+            case 16: return launch_gemm_mfma_r<GemmCfgR22>(st, Tq, d.d_model, K, A, W, eh, 0, pass_by);
+            case 17: return launch_gemm_mfma_r<GemmCfgR42>(st, Tq, d.d_model, K, A, W, eh, 0, pass_by);
           }
-          return launch_gemm<T>(ctx, st, site, Tq, d.d_model, K, A, W, en);
+          return launch_gemm<T>(ctx, st, site, Tq, d.d_model, K, A, W, en, pass_by);
         }
       }
       EpiResidual er{ws.x, d.d_model};
-      if ((rc2 = launch_gemm<T>(ctx, st, site, Tq, d.d_model, K, A, W, er))) return rc2;
+      if ((rc2 = launch_gemm<T>(ctx, st, site, Tq, d.d_model, K, A, W, er, pass_by))) return rc2;
     }
     return next_gain != nullptr ? norm(next_gain) : HSD_OK;
   };
@@ -714,7 +739,8 @@ int forward(hsd_ctx *ctx, hipStream_t st, const hsd_kv_pool *pool, const hsd_bat
     EpiQKV<T> eq{d.n_q_heads, d.n_kv_heads, meta, kv, static_cast<T *>(ws.q), l == 0 ? rs_none : rs_down};
     {
       ProfScope ps(ctx, st, HSD_PROF_GEMM_QKV);
-      if ((rc = launch_gemm<T>(ctx, st, kSiteQKV, Tq, qdim + 2 * kvdim, d.d_model, ws.h, ctx->wqkv[l], eq))) return rc;
+      if ((rc = launch_gemm<T>(ctx, st, kSiteQKV, Tq, qdim + 2 * kvdim, d.d_model, ws.h, ctx->wqkv[l], eq, pass_by)))
+        return rc;
     }
     {
       ProfScope ps(ctx, st, HSD_PROF_ATTENTION);
@@ -724,7 +750,8 @@ int forward(hsd_ctx *ctx, hipStream_t st, const hsd_kv_pool *pool, const hsd_bat
     EpiSwiGLU<T> es{static_cast<T *>(ws.u), d.d_ffn, rs_o};
     {
       ProfScope ps(ctx, st, HSD_PROF_GEMM_GATE_UP);
-      if ((rc = launch_gemm<T>(ctx, st, kSiteGateUp, Tq, d.d_ffn, d.d_model, ws.h, ctx->w_gate_up[l], es))) return rc;
+      if ((rc = launch_gemm<T>(ctx, st, kSiteGateUp, Tq, d.d_ffn, d.d_model, ws.h, ctx->w_gate_up[l], es, pass_by)))
+        return rc;
     }
     // the norm that follows: next layer's attention norm, or the final norm before the LM head (none for prefill)
     const float *next_gain = (l + 1 < d.n_layers) ? ctx->attn_norm[l + 1] : (with_head ? ctx->final_norm : nullptr);
@@ -739,7 +766,7 @@ int forward(hsd_ctx *ctx, hipStream_t st, const hsd_kv_pool *pool, const hsd_bat
                relaxed ? ws.want_logit : nullptr, rs_down};
   {
     ProfScope ps(ctx, st, HSD_PROF_GEMM_LM_HEAD);
-    if ((rc = launch_gemm<T>(ctx, st, kSiteLM, Tq, d.vocab, d.d_model, ws.h, ctx->lm_head, el))) return rc;
+    if ((rc = launch_gemm<T>(ctx, st, kSiteLM, Tq, d.vocab, d.d_model, ws.h, ctx->lm_head, el, pass_by))) return rc;
   }
   // a batch of single rows needs no acceptance kernel: the reduction writes alpha = 0 and the bonus (and the stop rows are
   // the roots, which the tree kernel has to say)

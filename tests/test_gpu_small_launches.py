@@ -62,6 +62,23 @@ def test_16_row_tiles_match_the_general_tile(rows, d_model, d_ffn):
         np.testing.assert_array_equal(a, b)
 
 
+# one layer of 276 MB: more than the memory-side cache, so that passes of up to 128 rows read it past the caches
+WIDE_FFN = W.ModelDesc(1, 1024, 16, 4, 64, 44032, 512, "bf16")
+
+
+@pytest.fixture(scope="module")
+def wide_ffn():
+    return W.make_weights(WIDE_FFN, 37)
+
+
+@pytest.mark.parametrize("rows", [1, 17, 33, 128, 129])
+def test_weights_read_past_the_caches(wide_ffn, rows):
+    draft = np.random.default_rng(rows).integers(0, WIDE_FFN.vocab, size=rows - 1).astype(np.int32)
+    for a, b in zip(_round(WIDE_FFN, wide_ffn, 37, draft),
+                    _round(WIDE_FFN, wide_ffn, 37, draft, {"gemm_cfg": (2, 2, 2, 2, 0)})):
+        np.testing.assert_array_equal(a, b)
+
+
 LARGE_FP32 = W.ModelDesc(1, 1024, 16, 4, 64, 1024, 1024, "fp32")
 
 
