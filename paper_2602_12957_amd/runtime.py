@@ -135,7 +135,8 @@ class Engine:
         self.k_pool = torch.zeros(pool_elems, dtype=es, device=self.dev)
         self.v_pool = torch.zeros(pool_elems, dtype=es, device=self.dev)
         # all KV bookkeeping lives in one int32 buffer so that a snapshot/restore is a single device copy
-        # (the outputs the host reads back every round -- status, alpha, bonus, stop rows -- sit together at its end: one copy)
+        # (the outputs the host reads back every round -- status, alpha, bonus, stop rows -- sit together at its end: one copy;
+        # the stop rows come last and are not restored: a pass's stay readable until the next pass over trees)
         n_state = n_blocks + 1 + n_slots + n_slots * max_blocks_per_seq + 1 + 3 * n_slots
         self._state = torch.zeros(n_state, dtype=torch.int32, device=self.dev)
         o = 0
@@ -149,7 +150,8 @@ class Engine:
         self.bonus = self._state[o + 1 + n_slots:o + 1 + 2 * n_slots]
         self.stop_row = self._state[o + 1 + 2 * n_slots:o + 1 + 3 * n_slots]
         self._readback = self._state[o:o + 1 + 3 * n_slots]
-        self._snapshot = torch.zeros_like(self._state)
+        self._restored = self._state[:n_state - n_slots]
+        self._snapshot = torch.zeros_like(self._restored)
         self.cpool = B.hsd_kv_pool(_ptr(self.k_pool), _ptr(self.v_pool), n_blocks, _ptr(self.free_list),
                                    _ptr(self.free_count))
 
@@ -207,11 +209,12 @@ class Engine:
 
     def snapshot(self):
         """Remembers the KV bookkeeping (free stack, lengths, block tables); cached K/V data is not copied."""
-        self._snapshot.copy_(self._state)
+        self._snapshot.copy_(self._restored)
 
     def restore(self):
-        """Returns the bookkeeping to the last snapshot (one small device copy on the current stream)."""
-        self._state.copy_(self._snapshot)
+        """Returns the bookkeeping to the last snapshot (one small device copy on the current stream), and with it status,
+        accept_len and bonus; the other outputs of the last pass (arg-max, margins, gaps, stop rows, logits) stay."""
+        self._restored.copy_(self._snapshot)
 
     def profile(self, which: int, max_launches: int):
         B.hsd_profile_enable(self.ctx, which, max_launches)

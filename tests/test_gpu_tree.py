@@ -342,3 +342,25 @@ def test_malformed_tree_is_clamped_and_flagged():
     alpha, bonus, status = eng.read_acceptance(1)
     assert status == 0 and 0 <= out.stop_row.cpu().numpy()[0] < len(t)
     eng.close()
+
+
+def test_stop_rows_outlive_a_restore():
+    """verify hands out views of the engine's buffers; restore() returns the bookkeeping (with status, alpha and bonus) to
+    the snapshot and leaves a pass's stop rows, like its arg-max, to be read afterwards."""
+    from paper_2602_12957_amd.runtime import pack_prefix_tree
+    desc, seed = FP32, 5
+    sp = SequenceSpec(0, 20, 3, 40, 0.0)
+    eng = make_engine(desc, W.make_weights(desc, seed), [sp])
+    _, _, tok, emb, pending = prefix_rows(desc, seed, sp)
+    eng.prefill([0], [tok], [emb])
+    eng.snapshot()
+    first = int(eng.verify([0], [np.array([pending], np.int32)]).argmax[0])
+    eng.restore()
+    t, e, d = pack_prefix_tree(pending, [[(first + 1) % desc.vocab, 5], [first]])
+    out = eng.verify([0], [t], trees=[(e, d)])
+    alpha, _, status, stop = eng.read_acceptance(1, stop_rows=True)
+    assert status == 0 and alpha[0] == 1 and stop[0] == 3
+    eng.restore()
+    assert out.stop_row.cpu().numpy()[0] == 3 and out.argmax.cpu().numpy()[0] == first
+    assert eng.read_acceptance(1)[0][0] == 0 and int(eng.seq_len[0]) == len(tok)      # back at the snapshot
+    eng.close()
