@@ -80,13 +80,19 @@ class DraftTrees:
             np.fromiter((int(t) for t in d), dtype=np.int64, count=len(d))
 
     def tree(self, accepted: Sequence[int], n: int, pending: int, max_packed: int):
-        """(tokens, tree_end, tree_depth) of the capped, packed candidates that follow the last n accepted tokens."""
+        """(tokens, tree_end, tree_depth) of the capped, packed candidates that follow the last n accepted tokens.
+        max_packed is any number, as cap_candidates takes it: infinity cuts nothing."""
         window = np.asarray(accepted[-n:] if n > 0 else [], dtype=np.int64)
-        out = np.empty((3, max(min(max_packed, 4096), 1)), dtype=np.int32)
-        rc, rows = B.hsd_drafts_tree(self._set, window, int(pending), int(max_packed), out)
+        # ctypes hands the low 64 bits of an int to the library without a word: both numbers are brought into range here
+        pending, most = int(pending), 2 ** 31 - 1
+        if not -2 ** 63 <= pending < 2 ** 63:
+            raise OverflowError("the pending token does not fit 32 bits")
+        cap = int(max(max_packed, 0)) if max_packed < most else most
+        out = np.empty((3, max(min(cap, 4096), 1)), dtype=np.int32)
+        rc, rows = B.hsd_drafts_tree(self._set, window, pending, cap, out)
         if rc == B.HSD_ENOSPC and rows > out.shape[1]:
             out = np.empty((3, rows), dtype=np.int32)
-            rc, rows = B.hsd_drafts_tree(self._set, window, int(pending), int(max_packed), out)
+            rc, rows = B.hsd_drafts_tree(self._set, window, pending, cap, out)
         if rc == B.HSD_ERANGE:
             raise OverflowError("a token of the packed tree does not fit 32 bits")
         B.check("hsd_drafts_tree", rc)

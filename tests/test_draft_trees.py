@@ -43,6 +43,19 @@ def test_inputs_of_every_kind_and_long_drafts():
     assert DraftTrees([[2 ** 40, 5, 6]]).tree([5], 1, 0, 8)[0].tolist() == [0, 6]
 
 
+@pytest.mark.parametrize("cap", [float("inf"), float("-inf"), float("nan"), 4.5, -1, 0, 2 ** 31, 2 ** 63, 2 ** 64 + 2, -2 ** 70])
+def test_any_number_as_the_cap(cap):
+    drafts = [[1, 2, 3], [1, 5, 6]]
+    for a, b in zip(pack_prefix_tree(0, cap_candidates(match_candidates([], drafts, 3), cap)), DraftTrees(drafts).tree([], 3, 0, cap)):
+        np.testing.assert_array_equal(a, b)
+
+
+@pytest.mark.parametrize("pending", [2 ** 31, -2 ** 31 - 1, 2 ** 63, 2 ** 64 + 5])
+def test_a_pending_token_out_of_range_is_refused(pending):
+    with pytest.raises(OverflowError):
+        DraftTrees([[1, 2]]).tree([], 3, pending, 8)
+
+
 def test_bad_arguments_are_refused():
     out, n = C.c_void_p(), C.c_int32()
     off = np.array([0, 2, 1], np.int64)
