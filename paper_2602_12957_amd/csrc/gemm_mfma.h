@@ -116,7 +116,11 @@ __device__ __forceinline__ void gemm_epilogue(floatx16 (&acc)[Cfg::TM][Cfg::TN],
       // Top two of the lane's TM * 16 logits, whose ids ascend with e = 16 i + v: four instructions a value (the second
       // largest of three is their median) where comparing records took nine (the launch at 1856 rows 152 -> 131 us).
       auto id_of = [&](int e) { return n0 + wi * (BP / Cfg::WM) + (e >> 4) * 32 + 8 * ((e & 15) >> 2) + 4 * half + (e & 3); };
+      // With a NaN among its operands the instruction gives the smaller of the other two, which leaves m2 as it is.  The
+      // compiler does not keep to that: a median with a constant -inf it turns into a minimum, which for a NaN in second
+      // place is the first logit.  So it is not shown that m2 starts as a constant.
       float m1 = -INFINITY, m2 = -INFINITY;
+      asm volatile("" : "+v"(m2));
       int e1 = 0;
 #pragma unroll
       for (int e = 0; e < TM * 16; ++e) {

@@ -79,6 +79,33 @@ def test_weights_read_past_the_caches(wide_ffn, rows):
         np.testing.assert_array_equal(a, b)
 
 
+@pytest.mark.parametrize("rows", [1, 200])
+def test_lm_head_record_without_finite_logits(rows):
+    """The running top two of a lane whose logits are all -inf or NaN, and of one that meets some of them in any place.
+    A column of the LM head that is -inf (and 0 elsewhere) makes a token's logit -inf or +inf by the sign of the row's
+    operand there, a NaN makes it NaN.  The record: lowest id among the largest logits that are numbers, and its distance
+    to the second largest; both tile sizes of the LM head."""
+    desc, seed = W.ModelDesc(1, 128, 2, 1, 64, 128, 512, "bf16"), 47
+    weights = W.make_weights(desc, seed)
+    rng = np.random.default_rng(rows)
+    draft = rng.integers(0, desc.vocab, size=rows - 1).astype(np.int32)
+    ids = np.arange(desc.vocab)
+    none, half, every, thirds, scattered = ids < 0, ids < 256, ids >= 0, ids % 3, rng.integers(0, 3, size=desc.vocab)
+    for nan, inf, column in ((half, none, 0), (ids != 300, none, 0), (none, half, 3), (none, half, 4), (none, every, 3),
+                             (thirds == 1, thirds == 2, 3), (thirds == 0, none, 0), (scattered == 0, scattered == 1, 4)):
+        head = weights["lm_head"].copy()
+        head[inf] = 0.0
+        head[inf, column] = -np.inf
+        head[nan] = np.nan
+        argmax, margin, logits = _round(desc, {**weights, "lm_head": head}, seed, draft)
+        seen = np.where(np.isnan(logits), -np.inf, logits)
+        top = seen.max(axis=1)
+        np.testing.assert_array_equal(argmax, np.argmax((seen == top[:, None]) & ~np.isnan(logits), axis=1))
+        second = np.sort(seen, axis=1)[:, -2]
+        with np.errstate(invalid="ignore"):
+            np.testing.assert_array_equal(margin, top - second)
+
+
 LARGE_FP32 = W.ModelDesc(1, 1024, 16, 4, 64, 1024, 1024, "fp32")
 
 
