@@ -44,8 +44,8 @@ struct GemmCfgR {
   static constexpr int kThreads = 64 * (RT_ + kLoaders);
   static_assert(SK_ == 128 || SK_ == 256 || SK_ == 512, "16, 32 or 64 pieces a row");
   static_assert(BP * kRowBytes % (1024 * kLoaders) == 0 && BQ * kRowBytes % (1024 * kLoaders) == 0, "requests divide evenly over the waves");
-  static_assert(CW_ == 1 || CW_ == 2 || CW_ == 4 || CW_ == 8, "a quarter, half, whole 64-column group or two");
-  static_assert(STAGES_ >= 2 && (STAGES_ - 1) * (kLoadsP + kLoadsQ) < 64, "the load counter holds 63");
+  static_assert(CW_ == 1 || CW_ == 2 || CW_ == 4, "a quarter, half or whole 64-column group");
+  static_assert(STAGES_ >= 2 && STAGES_ <= 4 && (STAGES_ - 1) * (kLoadsP + kLoadsQ) < 64, "the load counter holds 63");
   static_assert(RT_ * 16 * kEpiStride * 4 <= kSmemBytes && kSmemBytes + kRowScaleBytes <= 160 * 1024, "LDS");
 };
 
@@ -67,14 +67,15 @@ __global__ void __launch_bounds__(Cfg::kThreads) k_gemm_mfma_r(int M, int N, int
   int ta, tw;
   xcd_tile(blockIdx.x, tiles_act, tiles_act * (N / (MODE == kModeDual ? COLS : 2 * COLS)), ta, tw);
   const int m0 = m_base + ta * BP;
-  constexpr int GR = CW > 4 ? 1 : 4 / CW;              // tiles of a 64-column group
-  const int n0 = (MODE == kModeDual) ? tw * COLS : (CW > 4 ? tw * (CW / 4) * 64 : tw / GR * 64 + tw % GR * COLS);
+  constexpr int GR = 4 / CW;                           // tiles of a 64-column group
+  const int n0 = (MODE == kModeDual) ? tw * COLS : tw / GR * 64 + tw % GR * COLS;
   const int nf = K / Cfg::SK, ns = (K + Cfg::SK - 1) / Cfg::SK;   // full stages; the last one may be partly filled
 
   if (wave >= Cfg::RT) {
     // ---- a requesting wave.  Rows from M on read as zero: the hardware checks the vector offset against the matrix's
     // size.  It does not check the scalar one, so a partly filled last stage, which reaches past the end of the last row,
-    // carries its K offset in the vector part.  Of the 1 KB pieces of a stage (activation rows, then weight rows), piece 4 j + lw
+    // carries its K offset in the vector part.  Of the 1 KB pieces of a stage's activation rows, and of its weight rows,
+    // requesting wave lw fetches pieces 4 j + lw.
     constexpr int LPR = RB / 16;                       // lanes of a row
     const int lw = wave - Cfg::RT;
     const LdsBytePtr lds = (LdsBytePtr)smem_raw;
@@ -89,9 +90,7 @@ __global__ void __launch_bounds__(Cfg::kThreads) k_gemm_mfma_r(int M, int N, int
 #pragma unroll
     for (int j = 0; j < NLQ; ++j) {
       const int r = (4 * j + lw) * (64 / LPR) + lane / LPR;
-      // 64 rows a group at most: COLS (or 32) output columns, then their partners
-      constexpr int HC = COLS < 32 ? COLS : 32;
-      const int row = n0 + r / (2 * HC) * (MODE == kModeDual ? HC : 64) + r % HC + r / HC % 2 * (MODE == kModeDual ? N : 32);
+      const int row = n0 + r % COLS + r / COLS * (MODE == kModeDual ? N : 32);   // COLS output columns, then their partners
       vq[j] = (row * K + ((lane % LPR) ^ (r & 15)) * 8) * 2;
     }
 #define HSD_GR_ISSUE(slot, s)                                                                          \
@@ -111,7 +110,7 @@ __global__ void __launch_bounds__(Cfg::kThreads) k_gemm_mfma_r(int M, int N, int
       // stage s has landed; stages s + 1 .. s + S - 2 (requested so far) may stay in flight
       const int ahead = min(ns - 1 - s, S - 2);
 #define HSD_GR_WAIT(n) case n: HSD_VMCNT((n) * NL < 63 ? (n) * NL : 63); break;
-      switch (ahead) { HSD_GR_WAIT(0) HSD_GR_WAIT(1) HSD_GR_WAIT(2) HSD_GR_WAIT(3) HSD_GR_WAIT(4) default: HSD_VMCNT(0); }
+      switch (ahead) { HSD_GR_WAIT(0) HSD_GR_WAIT(1) HSD_GR_WAIT(2) default: HSD_VMCNT(0); }
 #undef HSD_GR_WAIT
       __builtin_amdgcn_s_barrier();
       if (s + S - 1 < ns) HSD_GR_ISSUE(slot, s + S - 1)
@@ -185,8 +184,7 @@ __global__ void __launch_bounds__(Cfg::kThreads) k_gemm_mfma_r(int M, int N, int
 
   // Result layout: lane l holds column l % 16 (of sub-tile c) and rows 4 (l / 16) + v.  Through LDS to row pieces of
   // PC = Epi::kPiece columns and their partners, as gemm_epilogue does; LPR lanes own a row.
-  constexpr int HC = COLS < 32 ? COLS : 32, JG = COLS / HC;
-  constexpr int ST = Cfg::kEpiStride, PC = Epi::kPiece, LPR = HC / PC, RPI = 64 / LPR;
+  constexpr int ST = Cfg::kEpiStride, PC = Epi::kPiece, LPR = COLS / PC, RPI = 64 / LPR;
   float *wst = reinterpret_cast<float *>(smem_raw) + wave * 16 * ST;
   const float *rsl = reinterpret_cast<const float *>(smem_raw + Cfg::kSmemBytes) + wave * 16;
 #pragma unroll
@@ -202,18 +200,15 @@ __global__ void __launch_bounds__(Cfg::kThreads) k_gemm_mfma_r(int M, int N, int
     const int m = m0 + wave * 16 + r;
     if (r >= 16 || m >= M) continue;
     const float rsc = Epi::kRowScale ? rsl[r] : 1.0f;
+    float lo[PC], hi[PC];
+    const float *src = wst + r * ST + PC * pc;
 #pragma unroll
-    for (int jg = 0; jg < JG; ++jg) {
-      float lo[PC], hi[PC];
-      const float *src = wst + r * ST + jg * 2 * HC + PC * pc;
-#pragma unroll
-      for (int e = 0; e < PC; ++e) {
-        lo[e] = Epi::kRowScale ? src[e] * rsc : src[e];
-        hi[e] = Epi::kRowScale ? src[HC + e] * rsc : src[HC + e];
-      }
-      if constexpr (MODE == kModeDual) epi.piece_dual(m, n0 + jg * HC + PC * pc, lo, hi);
-      else epi.piece(m, n0 + jg * 64 + PC * pc, lo, hi);
+    for (int e = 0; e < PC; ++e) {
+      lo[e] = Epi::kRowScale ? src[e] * rsc : src[e];
+      hi[e] = Epi::kRowScale ? src[COLS + e] * rsc : src[COLS + e];
     }
+    if constexpr (MODE == kModeDual) epi.piece_dual(m, n0 + PC * pc, lo, hi);
+    else epi.piece(m, n0 + PC * pc, lo, hi);
   }
 }
 

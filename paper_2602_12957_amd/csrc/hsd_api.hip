@@ -233,18 +233,25 @@ int launch_gemm_mfma_d(hipStream_t st, int M, int N, int K, const void *A, const
   return HSD_OK;
 }
 
+// pass_by: the weights are read past the memory-side cache, see weights_pass_by, in passes of up to kPassByRows rows (tiles of
+// more rows have no such form: one row tile of 128 x 64 always precedes them)
+constexpr int kPassByRows = 128;
 template <typename Cfg, typename Epi>
 int launch_gemm_mfma_r(hipStream_t st, int M, int N, int K, const void *A, const void *W, Epi epi, int m_base = 0,
                        bool pass_by = false) {
   constexpr int MODE = GemmModeOf<Epi>::value;
   constexpr int smem = Cfg::kSmemBytes + kRowScaleBytes;
-  auto kern = k_gemm_mfma_r<Cfg, MODE, Epi, false>, kern_nt = k_gemm_mfma_r<Cfg, MODE, Epi, true>;
+  auto kern = k_gemm_mfma_r<Cfg, MODE, Epi, false>;
   static const hipError_t attr_rc = hipFuncSetAttribute(reinterpret_cast<const void *>(kern),
                                                         hipFuncAttributeMaxDynamicSharedMemorySize, smem);
-  static const hipError_t attr_nt = hipFuncSetAttribute(reinterpret_cast<const void *>(kern_nt),
-                                                        hipFuncAttributeMaxDynamicSharedMemorySize, smem);
-  if (attr_rc != hipSuccess || attr_nt != hipSuccess) return HSD_EHIP;
-  if (pass_by) kern = kern_nt;
+  if (attr_rc != hipSuccess) return HSD_EHIP;
+  if constexpr (Cfg::BP <= kPassByRows) {
+    auto kern_nt = k_gemm_mfma_r<Cfg, MODE, Epi, true>;
+    static const hipError_t attr_nt = hipFuncSetAttribute(reinterpret_cast<const void *>(kern_nt),
+                                                          hipFuncAttributeMaxDynamicSharedMemorySize, smem);
+    if (attr_nt != hipSuccess) return HSD_EHIP;
+    if (pass_by) kern = kern_nt;
+  }
   const int tiles = (M - m_base + Cfg::BP - 1) / Cfg::BP * (N / Cfg::kCols / (MODE == kModeDual ? 1 : 2));
   hipLaunchKernelGGL(kern, dim3(tiles), dim3(Cfg::kThreads), smem, st, M, N, K, m_base, static_cast<const bf16 *>(A),
                      static_cast<const bf16 *>(W), epi);
@@ -640,7 +647,6 @@ int launch_attention(const hsd_ctx *ctx, hipStream_t st, const hsd_batch *b, con
 // are on the device, so the line is drawn by what the block tables can hold.  From 256 rows on several workgroups share a
 // weight row through L2: gate/up 12.4 -> 13.4, down 14.4 -> 14.2, LM head 34 -> 31, the pass even.
 constexpr int64_t kCacheBytes = int64_t{256} << 20;
-constexpr int kPassByRows = 128;
 bool weights_pass_by(const hsd_model_desc &d, const hsd_kv_pool *pool, const hsd_batch *b) {
   if (pool == nullptr || b->total_q > kPassByRows) return false;
   const int64_t qdim = d.n_q_heads * d.head_dim, kvdim = d.n_kv_heads * d.head_dim, dm = d.d_model;
