@@ -1,6 +1,7 @@
-"""What the compiler made of the residual projections' GEMM kernels, read from the built library's own metadata: none
-may spill vector registers.  Their epilogue runs once per tile with the accumulators live, so state that only the narrow
-tiles need has to stay out of the wide ones (a run-time choice there cost the persistent 256x256 kernel two spills)."""
+"""What the compiler made of the residual projections' GEMM kernels and of the attention spread over a workgroup's waves, read
+from the built library's own metadata: none may spill vector registers.  The GEMM epilogue runs once per tile with the
+accumulators live, so state that only the narrow tiles need has to stay out of the wide ones (a run-time choice there cost
+the persistent 256x256 kernel two spills); k_attn_wide has 128 registers, so that two workgroups fit a compute unit."""
 import os
 import shutil
 import subprocess
@@ -29,6 +30,11 @@ def _kernels(tmp_path):
 
 def test_residual_gemm_kernels_do_not_spill(tmp_path):
     gemms = {k[".name"]: k[".vgpr_spill_count"] for k in _kernels(tmp_path) if "k_gemm_mfma" in k[".name"] and "EpiResidual" in k[".name"]}
-    for form in ("k_gemm_mfma8", "k_gemm_mfma8p", "k_gemm_mfma_ws", "k_gemm_mfma_d"):
+    for form in ("k_gemm_mfma8", "k_gemm_mfma8p", "k_gemm_mfma_ws", "k_gemm_mfma_d", "k_gemm_mfma_r"):
         assert any(f"{len(form)}{form}I" in name for name in gemms), form
     assert {n: s for n, s in gemms.items() if s} == {}
+
+
+def test_wide_attention_does_not_spill(tmp_path):
+    forms = {k[".name"]: k[".vgpr_spill_count"] + k[".private_segment_fixed_size"] for k in _kernels(tmp_path) if "11k_attn_wideI" in k[".name"]}
+    assert len(forms) == 4 and {n: s for n, s in forms.items() if s} == {}

@@ -1,7 +1,8 @@
 """k_attn_wide (passes of few query sets) against k_attn_mfma, bit for bit: the same blocks scored alone and in one
 batch with a block so long that the pass takes the general kernel.  Both kernels run the same instructions on a row's
 keys in the same order, so the tolerance is zero.  Block lengths around the set sizes (8, 16, 32 rows), cached lengths
-around the 64-key groups and the 256-key steps, chains and packed trees, every grouping of query heads."""
+around the 64-key groups, the 256-key steps and the 2048 and 4096 keys after which a wave fetches page ids again, chains and
+packed trees, every grouping of query heads.  And batches whose tasks are dealt one group after the other."""
 import numpy as np
 import pytest
 import torch
@@ -11,7 +12,8 @@ from paper_2602_12957_amd.runtime import Engine
 
 pytestmark = pytest.mark.gpu
 
-BLOCKS = [(0, 1), (1, 8), (55, 9), (63, 1), (64, 16), (191, 65), (192, 17), (255, 1), (256, 7), (511, 33), (513, 2), (1300, 32)]
+BLOCKS = [(0, 1), (1, 8), (55, 9), (63, 1), (64, 16), (191, 65), (192, 17), (255, 1), (256, 7), (511, 33), (513, 2), (1300, 32),
+          (2040, 20), (2049, 5), (4090, 7), (4097, 33), (8200, 9)]
 
 
 def _tree(rng, rows):
@@ -64,5 +66,41 @@ def test_wide_attention_matches_the_general_kernel(n_q, n_kv, tree):
         out = eng.verify([i], [blocks[i]], "region", dump_rows=np.arange(len(blocks[i])), log_tau=-0.3, trees=[trees[i]] if tree else None)
         np.testing.assert_array_equal(general[0][at:at + len(blocks[i])], out.logits.cpu().numpy(), err_msg=str(BLOCKS[i]))
         at += len(blocks[i])
+    assert int(eng.status.item()) == 0
+    eng.close()
+
+
+# Rows and cached keys of uneven batches in which a list of the task table comes near its length on 256 compute units, so that
+# groups are dealt singly; in all but the first the list with the least work is full at least once.
+UNEVEN = {
+    "wide": (4, 4, "region", [220, 46, 32], [100, 0, 0]),
+    "wide_full": (8, 2, "page", [263, 454, 133, 277, 451], [8000, 100, 100, 2000, 0]),
+    "region_full": (16, 4, "region", [33, 185, 399, 539, 424, 471], [547, 2774, 695, 123, 433, 2182]),
+    "page_full": (4, 1, "page", [216, 527, 110, 587, 385, 8, 585, 344, 399, 319, 22, 373, 3, 190, 411, 181],
+                  [1210, 1688, 1395, 427, 207, 2158, 1351, 2924, 3266, 1668, 1459, 3651, 3967, 3781, 3820, 989]),
+}
+
+
+@pytest.mark.parametrize("name", UNEVEN)
+def test_uneven_batches_match_their_members(name):
+    """A task that is dealt twice or not at all, or past the end of its list, would leave rows unwritten."""
+    n_q, n_kv, mode, rows, cached = UNEVEN[name]
+    desc = W.tiny_model(2, 128, n_q, n_kv, 64, 128, 256, "bf16")
+    rng = np.random.default_rng(len(rows))
+    blocks = [rng.integers(0, desc.vocab, size=r).astype(np.int32) for r in rows]
+    total, n = sum(rows), len(rows)
+    eng = Engine(desc, W.make_weights(desc, 43), sum((r + c) // 16 + 2 for r, c in zip(rows, cached)), n,
+                 max((r + c) // 16 + 2 for r, c in zip(rows, cached)), total, total)
+    have = [i for i in range(n) if cached[i]]
+    eng.prefill(have, [rng.integers(0, desc.vocab, size=cached[i]).astype(np.int32) for i in have])
+    eng.snapshot()
+    eng.ws.zero_()
+    batch = eng.verify(list(range(n)), blocks, mode, dump_rows=np.arange(total)).logits.cpu().numpy().copy()
+    at = 0
+    for i in range(n):
+        eng.restore()
+        out = eng.verify([i], [blocks[i]], mode, dump_rows=np.arange(rows[i]))
+        np.testing.assert_array_equal(batch[at:at + rows[i]], out.logits.cpu().numpy(), err_msg=str(i))
+        at += rows[i]
     assert int(eng.status.item()) == 0
     eng.close()

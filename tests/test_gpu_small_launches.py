@@ -53,7 +53,7 @@ def test_row_sums_of_a_wide_model_with_one_head(rows, d_model):
 @pytest.mark.parametrize("rows", [16, 17, 129, 257, 513, 700, 1025, 2049, 4097])
 @pytest.mark.parametrize("d_model, d_ffn", [(256, 512), (384, 640)])
 def test_16_row_tiles_match_the_general_tile(rows, d_model, d_ffn):
-    """Row counts on both sides of the lines between the 16-row kernel's tiles (16 x 16 to 144 x 64) for these widths,
+    """Row counts on both sides of the lines between the 16-row kernel's tiles from 16 x 16 to 128 x 64 for these widths,
     and contraction lengths that are whole stages of 512 or 256 (256, 512) or leave a partly filled one (384, 640)."""
     desc, seed = W.ModelDesc(2, d_model, 8, 2, 64, d_ffn, 512, "bf16"), 31
     weights = W.make_weights(desc, seed)
@@ -62,20 +62,55 @@ def test_16_row_tiles_match_the_general_tile(rows, d_model, d_ffn):
         np.testing.assert_array_equal(a, b)
 
 
-# one layer of 276 MB: more than the memory-side cache, so that passes of up to 128 rows read it past the caches
-WIDE_FFN = W.ModelDesc(1, 1024, 16, 4, 64, 44032, 512, "bf16")
+@pytest.mark.parametrize("heads, d_model, d_ffn, cols", [((8, 2), 256, 512, 768), ((8, 2), 384, 640, 384), ((9, 9), 384, 512, 384)])
+@pytest.mark.parametrize("end", ["first", "last", "past"])
+def test_144_row_tiles_match_the_general_tile(heads, d_model, d_ffn, cols, end):
+    """The widest tile, 144 x 64, at the projection with `cols` outputs (QKV, or output and down): taken from the first row
+    count at which 128 x 64 tiles outnumber the compute units to the last at which its own do not.  Nine heads: the output
+    projection's contraction (576) leaves a stage of 128 half filled."""
+    n_cu = torch.cuda.get_device_properties(0).multi_processor_count
+    first, last = n_cu // (cols // 64) * 128 + 1, n_cu // (cols // 64) * 144
+    rows = {"first": first, "last": last, "past": last + 1}[end]
+    assert -(-first // 128) * (cols // 64) > n_cu >= -(-last // 144) * (cols // 64) and -(-(last + 1) // 144) * (cols // 64) > n_cu
+    assert last < 6144                       # from there on 256 x 256 tiles
+    desc, seed = W.ModelDesc(1, d_model, *heads, 64, d_ffn, 512, "bf16"), 31
+    weights = W.make_weights(desc, seed)
+    draft = np.random.default_rng(rows).integers(0, desc.vocab, size=rows - 1).astype(np.int32)
+    for a, b in zip(_round(desc, weights, seed, draft), _round(desc, weights, seed, draft, {"gemm_cfg": (2, 2, 2, 2, 0)})):
+        np.testing.assert_array_equal(a, b)
+
+
+# nine layers of 31 MB: more than the memory-side cache, so that passes of up to 128 rows read them past the caches.  On 256
+# compute units every projection takes the 16-row kernel at the rows tested: gate/up 32 x 32, 32 x 64 and 64 x 64 tiles.
+DEEP = W.ModelDesc(9, 1024, 16, 4, 64, 4096, 512, "bf16")
 
 
 @pytest.fixture(scope="module")
-def wide_ffn():
-    return W.make_weights(WIDE_FFN, 37)
+def deep_engines():
+    d = DEEP
+    assert 2 * d.n_layers * d.d_model * ((d.n_q_heads + 2 * d.n_kv_heads + d.n_q_heads) * 64 + 3 * d.d_ffn) > 256 << 20
+    weights, spec = W.make_weights(d, 37), SequenceSpec(0, 37, 3, 128, 0.0)
+    _, _, tok, emb, pending = prefix_rows(d, 37, spec)
+    engines = []
+    for debug in (None, {"gemm_cfg": (2, 2, 2, 2, 0)}):
+        engines.append(make_engine(d, weights, [spec], max_total_q=160, max_dump=160, debug=debug))
+        engines[-1].prefill([0], [tok], [emb])
+        engines[-1].snapshot()
+    yield engines, pending
+    for eng in engines:
+        eng.close()
 
 
-@pytest.mark.parametrize("rows", [1, 17, 33, 128, 129])
-def test_weights_read_past_the_caches(wide_ffn, rows):
-    draft = np.random.default_rng(rows).integers(0, WIDE_FFN.vocab, size=rows - 1).astype(np.int32)
-    for a, b in zip(_round(WIDE_FFN, wide_ffn, 37, draft),
-                    _round(WIDE_FFN, wide_ffn, 37, draft, {"gemm_cfg": (2, 2, 2, 2, 0)})):
+@pytest.mark.parametrize("rows", [1, 17, 33, 65, 128, 129])
+def test_weights_read_past_the_caches(deep_engines, rows):
+    engines, pending = deep_engines
+    draft = np.random.default_rng(rows).integers(0, DEEP.vocab, size=rows - 1).astype(np.int32)
+    res = []
+    for eng in engines:
+        eng.restore()
+        out = eng.verify([0], [np.concatenate([[pending], draft]).astype(np.int32)], dump_rows=np.arange(rows))
+        res.append([x.cpu().numpy().copy() for x in (out.argmax, out.margin, out.logits)])
+    for a, b in zip(*res):
         np.testing.assert_array_equal(a, b)
 
 

@@ -364,3 +364,100 @@ def test_stop_rows_outlive_a_restore():
     assert out.stop_row.cpu().numpy()[0] == 3 and out.argmax.cpu().numpy()[0] == first
     assert eng.read_acceptance(1)[0][0] == 0 and int(eng.seq_len[0]) == len(tok)      # back at the snapshot
     eng.close()
+
+
+def _path_beside_decoys(pending, path, decoy, decoy_first):
+    """A packed tree of `path` and a chain of `decoy` other tokens under the root, with a leaf beside every seventh node
+    of the path.  Returns (tokens, end, depth, packed row of every depth of the path)."""
+    toks, deps, rows = [pending], [0], [0]
+    if decoy_first:
+        toks += decoy
+        deps += range(1, len(decoy) + 1)
+    for k, t in enumerate(path):
+        if k % 7 == 3:
+            toks.append(t + 1 if t == 0 else t - 1), deps.append(k + 1)
+        rows.append(len(toks))
+        toks.append(t), deps.append(k + 1)
+    if not decoy_first:
+        toks += decoy
+        deps += range(1, len(decoy) + 1)
+    end, open_nodes = [0] * len(toks), []
+    for i, d in enumerate(deps):
+        while open_nodes and deps[open_nodes[-1]] >= d:
+            end[open_nodes.pop()] = i
+        open_nodes.append(i)
+    for i in open_nodes:
+        end[i] = len(toks)
+    return np.asarray(toks, np.int32), np.asarray(end, np.int32), np.asarray(deps, np.int32), rows
+
+
+def _cached(eng, desc, slots):
+    """K and V of sequence 0 at the given cache slots, [layer, kv head, slot, dim]."""
+    table = eng.block_table[0].cpu().numpy()
+    shape = (desc.n_layers, eng.n_blocks, desc.n_kv_heads, 1024)
+    k = eng.k_pool.view(*shape).cpu().numpy().reshape(*shape[:3], 16, 64)
+    v = eng.v_pool.view(*shape).cpu().numpy().reshape(*shape[:3], 64, 16)
+    slots = np.asarray(slots)
+    b, t = table[slots // 16], slots % 16
+    place = 8 * ((t >> 2) & 1) + 4 * (t >> 3) + (t & 3)              # of a token within a V page
+    return np.moveaxis(k[:, b, :, t], 0, 2), np.moveaxis(v[:, b, :, :, place], 0, 2)
+
+
+# (rows of the tree, levels of the path, decoy first).  64 levels are found and moved at a time; trees of up to 2048 rows are
+# walked in LDS by the acceptance, and by the commit where the stop node lies in the first 2048 rows.
+@pytest.mark.parametrize("rows, levels, decoy_first", [
+    (100, 63, True), (140, 64, True), (140, 65, True), (300, 128, True), (300, 129, True), (300, 129, False),
+    (2048, 150, True), (2049, 150, True), (2050, 150, True), (2600, 150, True), (2600, 150, False)])
+@pytest.mark.parametrize("desc", [FP32, BF16], ids=["fp32", "bf16"])
+def test_deep_paths_and_long_trees(desc, rows, levels, decoy_first):
+    """Acceptance against the numpy walk over the GPU's own rows (exact and relaxed rule); after the commit of the whole
+    path its K/V lie in the slots behind the prefix, bit for bit, and the round that follows agrees with the one behind
+    the same tokens committed as a chain."""
+    seed = 7
+    sp = SequenceSpec(0, 30, 3, rows + levels, 0.0)
+    eng = make_engine(desc, W.make_weights(desc, seed), [sp], max_total_q=rows, max_dump=rows)
+    _, _, tok, emb, pending = prefix_rows(desc, seed, sp)
+    eng.prefill([0], [tok], [emb])
+    eng.snapshot()
+    S = len(tok)
+    path = eng.greedy_decode([0], [pending], levels)[0].tolist()
+    leaves = len(range(3, levels, 7))
+    decoy = np.random.default_rng(rows).integers(0, desc.vocab, size=rows - 1 - levels - leaves).tolist()
+    decoy[0] = (path[0] + 1) % desc.vocab
+    t, e, d, at = _path_beside_decoys(pending, path, decoy, decoy_first)
+    assert len(t) == rows and at != list(range(levels + 1))
+    parent = [0] * rows
+    for c in range(1, rows):
+        p = c - 1
+        while not (d[p] == d[c] - 1):
+            p -= 1
+        parent[c] = p
+    for log_tau in (math.log(0.75), 0.0):
+        eng.restore()
+        out = eng.verify([0], [t], dump_rows=np.arange(rows), log_tau=log_tau, trees=[(e, d)])
+        alpha, bonus, status, stop = eng.read_acceptance(1, stop_rows=True)
+        assert status == 0
+        logits, arg = out.logits.cpu().numpy(), out.argmax.cpu().numpy()
+        gap = out.gap.cpu().numpy() if log_tau < 0 else None
+        want = np.array([logits[parent[c], t[c]] if c else -np.inf for c in range(rows)])
+        assert (alpha[0], bonus[0], stop[0]) == _walk(arg, t, e, gap, want, log_tau)
+        if desc is FP32:                       # (bf16: a tie may part the walk from the path)
+            assert alpha[0] == levels and stop[0] == at[-1]
+    moved_k, moved_v = _cached(eng, desc, S + np.asarray(at))
+    eng.override_acceptance(np.array([levels]), np.array([5]), np.array([at[-1]]))
+    eng.commit()
+    assert int(eng.seq_len[0]) == S + 1 + levels
+    k, v = _cached(eng, desc, S + np.arange(levels + 1))
+    np.testing.assert_array_equal(k, moved_k)
+    np.testing.assert_array_equal(v, moved_v)
+    block = np.arange(5, 12, dtype=np.int32)
+    got = eng.verify([0], [block], dump_rows=np.arange(7)).logits.cpu().numpy().copy()
+    eng.restore()
+    eng.verify([0], [np.asarray([pending] + path, np.int32)])
+    eng.override_acceptance(np.array([levels]), np.array([5]))
+    eng.commit()
+    ref = eng.verify([0], [block], dump_rows=np.arange(7)).logits.cpu().numpy()
+    assert int(eng.status.item()) == 0
+    # the two differ in how the attention sums of the path's rows group their keys, as the GPU and the oracle do
+    assert float(np.abs(got - ref).max()) <= TOL[desc.dtype]
+    eng.close()
