@@ -1,7 +1,8 @@
-"""Kernels chosen for launches of few rows against the general ones, bit for bit: the narrow (32-column) tiles of the
-bf16 projections against a tile set by hand, the 16-row tiles of the fp32 path against the 64-row ones that a block
-with enough rows takes at every projection.  Every output sums its products in one fixed order in all of them, so the
-tolerance is zero.  And the plain kernels on a bf16 model against the oracle, with the bar of the bf16 parity tests."""
+"""Kernels chosen for launches of few rows against the general ones, bit for bit: the 16-row kernel's tiles for the bf16
+projections, and its weights read past the caches, against a tile set by hand; the 16-row tiles of the fp32 path against
+the 64-row ones that a block with enough rows takes at every projection.  Every output sums its products in one fixed
+order in all of them, so the tolerance is zero.  The LM head's record where logits are not finite.  And the plain kernels
+on a bf16 model against the oracle, with the bar of the bf16 parity tests."""
 import numpy as np
 import pytest
 import torch
@@ -39,10 +40,11 @@ def test_narrow_tiles_match_the_general_tile(rows):
 
 
 @pytest.mark.parametrize("rows", [1, 33])
-@pytest.mark.parametrize("d_model", [2048, 2176])
+@pytest.mark.parametrize("d_model", [640, 768, 2048, 2176])
 def test_row_sums_of_a_wide_model_with_one_head(rows, d_model):
-    """One head of 64: the narrow tiles' second plane of row sums (d_model / 64 floats a row) fills q and the attention
-    output exactly at d_model 2048 and does not fit at 2176, where the wider tile has to be taken."""
+    """One head of 64: the further planes of row sums (d_model / 64 floats a row each) lie in q and the attention output.  The
+    three planes of 16-column tiles fit up to d_model 640, the one of 32-column tiles fills them exactly at 2048; at 768 and
+    2176 the next wider tile has to be taken."""
     desc, seed = W.ModelDesc(2, d_model, 1, 1, 64, 128, 512, "bf16"), 23
     weights = W.make_weights(desc, seed)
     draft = np.random.default_rng(rows).integers(0, desc.vocab, size=rows - 1).astype(np.int32)
