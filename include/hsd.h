@@ -224,6 +224,9 @@ int hsd_prefill(hsd_ctx *ctx, void *stream, const hsd_kv_pool *pool, const hsd_b
  * verify call is bracketed by a pair of HIP events recorded on the caller's stream (at most max_launches
  * pairs; later launches are not timed).  hsd_profile_read waits for the recorded events, returns the number
  * of timed launches and the sum of their durations in milliseconds, and clears the record.
+ * HSD_PROF_RMSNORM is the launch that opens a pass (block reservation and row places, attention task table, row metadata,
+ * embeddings and the first norm) and, where the plain kernels run, the norms after it; the MFMA path folds those into the
+ * projections.
  * hsd_profile_enable(ctx, HSD_PROF_NONE, 0) switches timing off and releases the events. */
 enum {
   HSD_PROF_NONE = 0,

@@ -309,6 +309,8 @@ int effective_gemm_cfg(const hsd_ctx *ctx, int site, int M, int N, int K) {
     //   O                1 row 8.6 / 7.2, 128 9.2 / 8.3, 512 11.9 / 10.2, 1008 12.9 / 12.2, 1856 16.2 / 15.2
     //   QKV              1 row 9.8 / 8.8, 64 11.2 / 10.8, 320 12.0 / 11.3, 512 12.8 / 12.5, 1008 15.0 / 14.5, 1280 18.6 / 14.9
     //   gate/up          32 rows 12.0 / 11.0 (32 x 32), 64 12.0 / 11.4 (32 x 64), 128 13.8 / 13.2, 256 15.0 / 14.3
+    //   144 x 64         QKV 1281 rows 16.7 / 14.1, 1440 16.8 / 14.1; O 2049 19.0 / 15.6, 2304 21.2 / 16.5; down 2049 44.5 / 32.2,
+    //                    2304 46.7 / 36.1
     // The other side of the line: gate/up 320 rows 17.7 / 21.4 (128 x 64, 384 tiles), QKV 1856 20.3 / 24.0 (360).
     // Gate/up beyond: 128x128 tiles (7) while they fit one round (512 rows: 18.3; 256x128 23.4), then 256x128 (6; 768 rows
     // 26.2 / 23.7, 1008 27.9 / 26.1), then 256x256 (1280 rows 33.1; 256x128 42.7).
