@@ -8,7 +8,7 @@ LIB_PATH = os.path.join(PKG_DIR, "libhsd.so")
 
 HIPCC_FLAGS = [
     "-O3", "--offload-arch=gfx950", "-std=c++17", "-shared", "-fPIC",
-    # hipcc -O3 must not form packed-fp32 instructions on the test machines
+    # hipcc -O3 must not form packed-fp32 instructions: some of their forms have given wrong results on this hardware
     "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
     # the command processor hands the first kernel arguments to a wave in registers instead of the wave reading them from
     # memory before it can form its first address

@@ -450,3 +450,40 @@ def test_tile_configurations_agree_bitwise():
     for other in results[1:]:
         np.testing.assert_array_equal(results[0][0], other[0])
         np.testing.assert_array_equal(results[0][1], other[1])
+
+
+@pytest.mark.parametrize("dtype", ["fp32", "bf16"])
+def test_embedding_inputs_need_no_more_than_their_elements_alignment(dtype):
+    """The embedding table and the caller's embedding rows, one element past a 16-byte boundary (a slice of a larger
+    buffer), give the bits of aligned ones."""
+    import paper_2602_12957_amd.binding as B
+    from paper_2602_12957_amd.runtime import Engine, _ptr
+    desc, seed = W.ModelDesc(1, 256, 4, 2, 64, 256, 512, dtype), 11
+    weights = W.make_weights(desc, seed)
+
+    def shifted(t):
+        buf = torch.zeros(t.numel() + 1, dtype=t.dtype, device=t.device)
+        buf[1:] = t.reshape(-1)
+        return buf[1:].view(t.shape)
+
+    class ShiftedTable(Engine):
+        def _up_mat(self, a):
+            p = super()._up_mat(a)
+            if a is not weights["tok_embed"]:
+                return p
+            self._keep.append(shifted(self._keep[-1]))
+            return self._keep[-1].data_ptr()
+
+    rng = np.random.default_rng(3)
+    tok = np.where(np.arange(37) % 3 == 0, -1, rng.integers(0, desc.vocab, size=37)).astype(np.int32)
+    emb = torch.from_numpy(rng.standard_normal((37, desc.d_model)).astype(np.float32)).cuda()
+    res = []
+    for cls, e in ((Engine, emb), (ShiftedTable, shifted(emb))):
+        eng = cls(desc, weights, 16, 1, 8, 64, 37)
+        b = eng._make_batch([0], [tok], dump_rows=np.arange(37), embeds=e)
+        assert (b.embeds % 16 == 0) == (cls is Engine) and (eng._cw.tok_embed % 16 == 0) == (cls is Engine)
+        B.hsd_verify_region_batch(eng.ctx, eng.stream, eng.cpool, b, _ptr(eng.ws), eng.ws_bytes)
+        res.append(eng.logits_dump[:37].cpu().numpy().copy())
+        assert int(eng.status.item()) == 0
+        eng.close()
+    np.testing.assert_array_equal(*res)
