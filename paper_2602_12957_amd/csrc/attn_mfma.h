@@ -4,29 +4,38 @@
 // sequence s at absolute position p attends to the cached positions 0..p of s -- the accepted prefix plus
 // the rows before it in its own block, which the QKV epilogue appended to the pages just before.
 //
-// Work split.  A workgroup owns one (sequence, kv head, tile of query rows).  Its waves come in pairs: the two
-// waves of a pair hold the same 32 queries of one query head (lane l <-> query l % 32) and share every
-// 128-key stage between them, the first taking keys 0-63 of the stage and the second keys 64-127 ("parity").
-// The pairs of a workgroup are the query heads that share the kv head (GQA) and/or further 32-row sub-tiles,
-// so every K/V stage in LDS is used by all of them: 4 pairs per workgroup for region-level batches (many short
-// blocks, Eq. 2), 8 pairs for page-level ones (few long blocks, Eq. 4: twice the reuse of each stage).
+// Work split.  A workgroup owns one (sequence, kv head, tile of query rows).  A wave holds 32 queries of one query head
+// (lane l <-> query l % 32); the waves of a workgroup are the query heads that share the kv head (GQA) and/or further 32-row
+// sub-tiles, so every 128-key K/V stage in LDS is used by all of them: 4 waves for region-level batches (many short
+// blocks, Eq. 2), 8 for page-level ones (few long blocks, Eq. 4: twice the reuse of each stage).
 //
 // One row's arithmetic is the same in every variant and every batch: its keys are visited in 64-key groups at
-// absolute positions, even groups by one accumulator set and odd groups by another, in ascending order, and the
+// absolute positions, even groups by one accumulator set and odd groups by another ("parity"), in ascending order, and the
 // two sets are folded at the end (even first).  Verification of a block and token-by-token decoding therefore give
 // the same bits.
 //
 // Orientation.  Both products are computed transposed so that a lane owns ONE query:
-//   S^T = K Q^T   (MFMA i = key, j = query)  -> the lane's 32 registers per step are 32 keys of its query:
-//                 row max / row sum are in-register plus one exchange between the two lane halves;
-//   O^T = V^T P^T (MFMA i = head dim, j = query) -> rescaling by the softmax correction is a per-lane scalar.
+//   S^T = K Q^T   (MFMA i = key, j = query)  -> the lane's 32 registers per step are 32 keys of its query;
+//   O^T = V^T P^T (MFMA i = head dim, j = query) -> a correction factor is a per-lane scalar.
 // P^T is fed straight from the S^T registers as the B operand.  Register v of lane half h holds key
 // 8*(v/4) + 4h + v%4, so the contraction slots of a 16-key step are keys {4h..4h+3, 8+4h..8+4h+3}; the V
 // pages are stored transposed and in exactly that token order ([dim][perm(token)], see kv_v_slot), hence the
 // A operand of the second product is one 16-byte LDS read per lane and no transpose is ever done here.
 //
+// What bounds it, and why a wave holds both parities.  A group of 64 keys is 16 matrix instructions (32 cycles each) and 32
+// exponentials, 16 conversions and 32 additions per lane.  The matrix pipe and the vector unit run side by side only if
+// independent work of both kinds is in the instruction stream: microbenchmark, one wave per SIMD, ns per group: products
+// alone 225, vector part alone 190, both interleaved 230 to 260.  With one parity to a wave, four waves per SIMD in step behind a
+// barrier a stage, each waited for its own chain of reads, products, maximum, exponentials and products: 577 ns a group (four pages
+// of 8193 rows: 1907 us a layer).  Here, in every turn, the exponentials of one parity run beside the products of the other, in
+// an order fixed by hand; what the exponentials need beside (maximum, subtraction, rescaling) is taken out of the common case
+// (attn_reference), and the keys and values are requested by LDS-direct loads, so that staging takes no registers and no store
+// instructions.  On the way (us a layer at that size): no running maximum 1757; both parities in a wave 1779; row sums
+// off the matrix pipe (attn_page_sum) and the order pinned 1594.  16 regions of 17 to 257 rows on 1055 keys: 29.7 -> 26.2.
+// What is left there: 10 % of the launch is its last tasks; a third of a wave's time are waits for LDS reads and at barriers.
+//
 // The key loop has two forms.  Stages whose every key is visible to every query of the workgroup (the bulk of a
-// cached prefix) run with no mask, no validity checks and no special cases; the last one or two stages of a
+// cached prefix) run with no mask and no validity checks; the last one or two stages of a
 // workgroup (the diagonal of the causal mask, the tree-ancestry mask, the partly filled last page) run the
 // checked form.
 #pragma once
@@ -37,18 +46,12 @@
 
 namespace hsd {
 
-constexpr int kAttnKeys = 128;            // keys per LDS stage: 8 pages; keys 0-63 for parity 0, 64-127 for parity 1
-constexpr int kKsStride = kHd + 8;        // bf16 per K row in LDS (16 B pad: conflict-free 128-bit reads)
-constexpr int kVtStride = kAttnKeys + 8;  // bf16 per V^T row (one head dim, the 8 pages' token slots side by side;
-                                          // 16 B pad: a row is 68 dwords, so the 128-bit reads of 16 consecutive
-                                          // dims, and the stores of 16 consecutive dims, cover all 64 banks once)
-constexpr int kAttnStage = kAttnKeys * kKsStride + kHd * kVtStride;   // bf16 elements per stage: K rows, then V^T rows
-// Dynamic LDS of k_attn_mfma: two stages, reused after the key loop for handing the odd-parity partial results of
-// each of the QS query sets (34 floats per lane) to their even-parity partners.
-constexpr size_t attn_smem_bytes(int qs) {
-  const size_t stages = 2 * static_cast<size_t>(kAttnStage) * 2, merge = static_cast<size_t>(qs) * 34 * 64 * 4;
-  return stages > merge ? stages : merge;
-}
+constexpr int kAttnKeys = 128;            // keys per LDS stage: 8 pages; keys 0-63 are parity 0's, 64-127 parity 1's
+// LDS: three stages of K rows, then two of V^T pages (a stage's V is wanted half a stage after its K, and its K may have to be
+// read a second time); 80 KB, two workgroups a compute unit
+constexpr int kAttnHalfStage = kAttnKeys * kHd * 2;
+constexpr int kAttnKStages = 3, kAttnVStages = 2;
+constexpr size_t kAttnLdsBytes = (kAttnKStages + kAttnVStages) * kAttnHalfStage;
 
 // What a workgroup needs to know about its task -- one (query tile, kv head group) -- resolved once per pass instead
 // of by every workgroup of every layer (a binary search and four dependent reads before the first K/V request
@@ -249,22 +252,72 @@ union Frag8 {
   uint16_t h[8];
 };
 
-// QS = query sets (pairs of waves; 32 queries x one head each) per workgroup: 4 (region-level) or 8 (page-level).
+// Softmax.  q comes scaled by log2(e) / sqrt(64) (EpiQKV::kQScale), so a score is an exponent of two and a probability is
+// exp2(score - m) with a reference point m of the query.  m needs to keep sums and probabilities in range, no more: fp32 and
+// bf16 are as precise at 2^40 as at 1.  It is an INTEGER, so that every correction factor is an exact power of two, and 0
+// unless the scores ask for another: it is set at the first group of 64 keys that holds a visible one, to 0 where that
+// group's largest score lies within +-kAttnZeroRange and to the score rounded up otherwise, and moves (to a group's largest
+// score rounded up) only at a group with a score kAttnMoveAt above it.  Largest probability of the first group: 2^-33 at
+// least, 2^32 at most; of any: 2^64.  So the common group needs no maximum, no subtraction and no rescaling, and its test is
+// one comparison: a probability of 2^64 or more makes the row sum as large.
+// Each kernel applies the rule group by group, in ascending order within a parity: a row's numbers do not depend on the
+// kernel.
+constexpr float kAttnZeroRange = 32.f, kAttnMoveAt = 64.f;
+constexpr float kAttnSumLimit = 0x1p63f;   // below 2^kAttnMoveAt by more than the exponential's error
+__device__ __forceinline__ float attn_reference(float m, float mx) {
+  if (m == -INFINITY) {
+    const float c = ceilf(mx);
+    return fabsf(c) <= kAttnZeroRange ? 0.f : c;   // -inf while no key is visible
+  }
+  return mx - m >= kAttnMoveAt ? ceilf(mx) : m;
+}
+
+// Row sums are fp32 sums of the probabilities before they are rounded for the second product: of the 16 keys of a page that a
+// lane half holds (8) as a tree, the group's four pages as a tree, the groups one after the other.  (Adding the rounded pairs
+// with v_dot2_f32_bf16 is half the instructions, but it runs on the matrix pipe: 16 products and the exponentials of a group
+// take 260 ns together, 500 with the 16 dot products among them.)
+__device__ __forceinline__ float attn_page_sum(const floatx8 &p) { return ((p[0] + p[1]) + (p[2] + p[3])) + ((p[4] + p[5]) + (p[6] + p[7])); }
+
+typedef __attribute__((address_space(3))) unsigned char *AttnLds;
+// s_waitcnt vmcnt(N) with the other counters left alone (N < 64), also for the compiler's eyes: no LDS access moves across it
+#define HSD_ATTN_VMCNT(N)                                                                             \
+  do {                                                                                               \
+    asm volatile("" ::: "memory");                                                                   \
+    __builtin_amdgcn_s_waitcnt(((N) & 15) | (7 << 4) | (15 << 8) | (((N) >> 4) << 14));              \
+    asm volatile("" ::: "memory");                                                                   \
+  } while (0)
+// A page of 2 KB (uniform address) to LDS (uniform) in two LDS-direct loads: lane l's 16 bytes at byte off0 of the page go to
+// dst + 16 l, those at off1 to dst + 1024 + 16 l.  In asm: the compiler would otherwise wait for every load in flight before
+// each LDS read.  No register is written; the reads wait by HSD_ATTN_VMCNT and a barrier.
+__device__ __forceinline__ void attn_load_page(const bf16 *page, AttnLds dst, int off0, int off1) {
+  const uint32_t d = __builtin_amdgcn_readfirstlane(static_cast<uint32_t>(reinterpret_cast<uintptr_t>(dst)));
+  const uint64_t p = reinterpret_cast<uint64_t>(page);
+  const uint64_t up = (static_cast<uint64_t>(__builtin_amdgcn_readfirstlane(static_cast<uint32_t>(p >> 32))) << 32) |
+                      static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(static_cast<uint32_t>(p)));
+  asm volatile(
+      "s_mov_b32 m0, %0\n\t"
+      "s_nop 0\n\t"
+      "global_load_lds_dwordx4 %1, %3\n\t"
+      "s_add_u32 m0, m0, 0x400\n\t"
+      "s_nop 0\n\t"
+      "global_load_lds_dwordx4 %2, %3"
+      :
+      : "s"(d), "v"(off0), "v"(off1), "s"(up)
+      : "memory", "scc", "m0");
+}
+
+// QS = query sets (waves; 32 queries x one head each) per workgroup: 4 (region-level) or 8 (page-level).
 // G4 = query heads of one kv head among them (1, 2 or 4); QS/G4 row sub-tiles of 32 queries.
-// Waves w and w + QS form a pair: same queries, parity 0 / 1 of every stage.  Their partial (reference point, sum,
-// O^T) are folded through LDS at the end, always in the same order, so results do not depend on timing.
 // TREE selects the tree-ancestry mask (row_end = packed index one past each row's subtree) instead of the causal one.
 // SPLIT: grid z = key chunk (see AttnSplit); results go to the partial buffers instead of `out`.
-// grid: (attn_grid_size(...) tasks, 1, chunks), block 128*QS, dynamic LDS attn_smem_bytes(QS).
+// grid: (attn_grid_size(...) tasks, 1, chunks), block 64*QS, dynamic LDS kAttnLdsBytes.
 template <int G4, int QS, bool TREE, bool SPLIT>
-__global__ void __launch_bounds__(128 * QS) k_attn_mfma(int n_q_heads, const AttnTile *__restrict__ tiles, PagedKV kv,
-                                                        const bf16 *__restrict__ q, bf16 *__restrict__ out,
-                                                        const int32_t *__restrict__ row_end, AttnSplit sp) {
-  // staging: the 8 pages of a stage are spread over the 2*QS waves; a page's K is 128 16-byte pieces, its V^T too
-  constexpr int NS = 8 / QS;                      // K pieces (and V^T pieces) per lane and stage: 2 or 1
-  static_assert(QS == 4 || QS == 8, "a stage's 8 pages are staged by 8 or 16 waves");
+__global__ void __launch_bounds__(64 * QS, 2) k_attn_mfma(int n_q_heads, const AttnTile *__restrict__ tiles, PagedKV kv,
+                                                               const bf16 *__restrict__ q, bf16 *__restrict__ out,
+                                                               const int32_t *__restrict__ row_end, AttnSplit sp) {
+  constexpr int NP = 8 / QS;                      // pages of a stage that a wave requests: 2 or 1
+  static_assert(QS == 4 || QS == 8, "a stage's 8 pages are requested by 4 or 8 waves");
   extern __shared__ __attribute__((aligned(16))) unsigned char smem_raw[];
-  uint16_t *smem = reinterpret_cast<uint16_t *>(smem_raw);
   constexpr int SUB = QS / G4, QT = 32 * SUB;
 
   // the tile's descriptor comes through the scalar unit in one read (constant address space: written by an
@@ -278,8 +331,7 @@ __global__ void __launch_bounds__(128 * QS) k_attn_mfma(int n_q_heads, const Att
   const int group = n_q_heads / kv.n_kv_heads, hb = (group + G4 - 1) / G4;
   const int kvh = ty / hb, hgrp = ty % hb;
   const int t = threadIdx.x, lane = t & 63, half = lane >> 5, qj = lane & 31;
-  const int wave = __builtin_amdgcn_readfirstlane(t >> 6);
-  const int wq = wave % QS, par = wave / QS;                       // query-set index, parity of the wave
+  const int wq = __builtin_amdgcn_readfirstlane(t >> 6);           // query-set index
   const int head = kvh * group + hgrp * G4 + (wq % G4);
   const int row0_wg = tile_in_seq * QT;
   const int row0 = row0_wg + (wq / G4) * 32;                       // first query row (within the block) of this wave
@@ -302,6 +354,55 @@ __global__ void __launch_bounds__(128 * QS) k_attn_mfma(int n_q_heads, const Att
   const int kt_plain = min(kt1, (TREE ? S : S + row0_wg + 1) / kAttnKeys);
   const int qdim = n_q_heads * kHd;
 
+  // ---- requests.  Page pg of a stage is fetched by wave pg % QS, K and V in two loads of 1 KB each that write LDS directly:
+  // lane l's 16 bytes land at 16 l.  K (16 rows of 128 bytes): the 16-byte piece p of row r lies at position
+  // p ^ ((r >> 1) & 7) of its row; V^T (64 dims of 32 bytes): half h of dim d lies at h ^ ((d >> 3) & 1): the reads of 16
+  // rows, or dims, cover all 64 banks once.  The page ids of many stages are read at once, a lane each.
+  // An id that is out of range (a page beyond the data of this round, a damaged table) reads block 0 instead; every
+  // position such a page could stand for is masked (and its V zeroed) by the checked form of the loop, and the plain form
+  // only sees pages of the cached prefix.
+  const AttnLds lds = (AttnLds)smem_raw;
+  int vk[2], vv;   // byte offsets of a lane in a page: K rows 8 c + l / 8, V dims 32 c + l / 2 (+ 1024 c)
+#pragma unroll
+  for (int c = 0; c < 2; ++c) vk[c] = (8 * c + (lane >> 3)) * 128 + (((lane & 7) ^ ((4 * c + (lane >> 4)) & 7)) << 4);
+  vv = (lane >> 1) * 32 + (((lane & 1) ^ ((lane >> 4) & 1)) << 4);
+  const int32_t *table_row = kv.block_table + static_cast<size_t>(slot) * kv.max_blocks_per_seq;
+  const int last_entry = kv.max_blocks_per_seq - 1;
+  // ids: lane NP j + i holds that of page wq + QS i of stage id0 + j
+  int ids, id0;
+  auto fetch_ids = [&](int kt) {
+    id0 = kt;
+    const int id = table_row[min((kt + lane / NP) * (kAttnKeys / kBlk) + wq + QS * (lane % NP), last_entry)];
+    ids = (id >= 0 && id < kv.n_blocks) ? id : 0;
+  };
+  auto page = [&](int kt, int i) { return kv_block_offset(kv, __builtin_amdgcn_readlane(ids, (kt - id0) * NP + i), kvh); };
+  // K is requested a stage ahead of V: next_k and next_v are the stages to come, k_put the K slot of the former
+  int next_k = kt0, next_v = kt0, k_put = 0;
+  auto issue_k = [&]() {
+    if (next_k - id0 == 64 / NP) fetch_ids(next_v);   // V is behind and still needs its own
+#pragma unroll
+    for (int i = 0; i < NP; ++i)
+      attn_load_page(static_cast<const bf16 *>(kv.k_pool) + page(next_k, i), lds + k_put * kAttnHalfStage + (wq + QS * i) * 2048, vk[0], vk[1]);
+    ++next_k;
+    k_put = k_put + 1 == kAttnKStages ? 0 : k_put + 1;
+  };
+  auto issue_v = [&]() {
+#pragma unroll
+    for (int i = 0; i < NP; ++i)
+      attn_load_page(static_cast<const bf16 *>(kv.v_pool) + page(next_v, i),
+                     lds + (kAttnKStages + (next_v & 1)) * kAttnHalfStage + (wq + QS * i) * 2048, vv, vv + 1024);
+    ++next_v;
+  };
+  // Everything requested so far has landed, in every wave, and every wave is done with what it read.
+  auto landed = [&]() {
+    HSD_ATTN_VMCNT(0);
+    __syncthreads();
+  };
+  fetch_ids(kt0);
+  issue_k();
+  issue_v();
+  if (next_k < kt1) issue_k();
+
   // ---- query fragments (B operand of S^T): lane holds dims 16*kk + 8*half .. +7 of its query
   Frag8 qf[4];
   {
@@ -309,92 +410,77 @@ __global__ void __launch_bounds__(128 * QS) k_attn_mfma(int n_q_heads, const Att
 #pragma unroll
     for (int kk = 0; kk < 4; ++kk) qf[kk].u = *reinterpret_cast<const uint4 *>(qp + kk * 16);
   }
+  int ka[4];   // K fragment kk of a block of 32 keys: byte offset in the block
+#pragma unroll
+  for (int kk = 0; kk < 4; ++kk) ka[kk] = qj * 128 + (((2 * kk + half) ^ ((qj >> 1) & 7)) << 4);
+  const int va = qj * 32 + ((half ^ ((qj >> 3) & 1)) << 4);
 
-  const bf16 *kpool = static_cast<const bf16 *>(kv.k_pool);
-  const bf16 *vpool = static_cast<const bf16 *>(kv.v_pool);
-  // Staging.  A wave stages (QS = 4) one whole page of every stage or (QS = 8) half a page: piece c of a page is
-  // 16 bytes at byte offset 16*c of the K page (key c/8, dims 8*(c%8)..) and of the V^T page (dim c/2, token slots
-  // 8*(c%2)..).  For V^T a lane takes piece cv = 2*(c%32) + c/32 of its 64-piece group instead of piece c, so that 16
-  // consecutive lanes write 16 consecutive dims (LDS rows) and never two halves of one row.  The page id is therefore uniform per wave: it is read through the scalar unit (constant address
-  // space: the table is not written while this kernel runs), one stage ahead of the data it addresses, and the page
-  // offset is scalar arithmetic.
-  const int pgw = (QS == 4) ? wave : (wave >> 1);                  // page of the stage this wave stages
-  const int c0 = (QS == 4) ? lane : ((wave & 1) * 64 + lane);      // first K piece of the lane; piece i is c0 + 64*i
-  const int cv0 = c0 - lane + 2 * (lane & 31) + (lane >> 5);       // first V^T piece
-  u32x4 rk[NS], rv[NS];
-  int bid;
-  typedef const int32_t __attribute__((address_space(4))) *TablePtr;
-  const TablePtr table_row = (TablePtr)(kv.block_table + static_cast<size_t>(slot) * kv.max_blocks_per_seq);
-  const int last_entry = kv.max_blocks_per_seq - 1;
-  // fetch_id only ISSUES the read (index clamped to the table row); examining the id here would stall the wave
-  // for a memory latency every iteration
-  auto fetch_id = [&](int kt) { bid = table_row[min(kt * (kAttnKeys / kBlk) + pgw, last_entry)]; };
-  // prefetch only ISSUES the loads.  They are unconditional: an id that is out of range (a page beyond the data of
-  // this round, a damaged table) reads block 0 instead; every position such a page could stand for is masked (and
-  // its V zeroed) by the checked form of the loop, and the plain form only sees pages of the cached prefix.
-  auto prefetch = [&]() {
-    const int b = (bid >= 0 && bid < kv.n_blocks) ? bid : 0;
-    const size_t off = kv_block_offset(kv, b, kvh);
-#pragma unroll
-    for (int i = 0; i < NS; ++i) {
-      rk[i] = *reinterpret_cast<const u32x4 *>(kpool + off + (c0 + 64 * i) * 8);
-      rv[i] = *reinterpret_cast<const u32x4 *>(vpool + off + (cv0 + 64 * i) * 8);
-    }
-  };
-  // kt = stage the staged registers belong to
-  auto store_lds = [&](int stage, int kt, bool checked) {
-    uint16_t *ks = smem + stage * kAttnStage, *vt = ks + kAttnKeys * kKsStride;
-#pragma unroll
-    for (int i = 0; i < NS; ++i) {
-      const int c = c0 + 64 * i;
-      *reinterpret_cast<u32x4 *>(ks + (pgw * kBlk + (c >> 3)) * kKsStride + (c & 7) * 8) = rk[i];
-      u32x4 f = rv[i];
-      const int cv = cv0 + 64 * i;
-      const int p0 = kt * kAttnKeys + pgw * kBlk;
-      if (checked && p0 + kBlk > n_valid) {
-        // partly filled (or absent) page: slots of positions that hold no data of this sequence must read as 0
-        // (their probability is 0, but 0 * stale-NaN would poison the product).  Element e of the piece is
-        // token 4*hf + e (e < 4) or 8 + 4*hf + e - 4; two elements per 32-bit word.
-        const int hf = cv & 1;
-#pragma unroll
-        for (int w = 0; w < 4; ++w) {
-          const int tok0 = (w < 2) ? 4 * hf + 2 * w : 8 + 4 * hf + 2 * (w - 2);
-          uint32_t keep = 0;
-          if (p0 + tok0 < n_valid) keep |= 0x0000ffffu;
-          if (p0 + tok0 + 1 < n_valid) keep |= 0xffff0000u;
-          f[w] &= keep;
-        }
-      }
-      *reinterpret_cast<u32x4 *>(vt + (cv >> 1) * kVtStride + pgw * kBlk + (cv & 1) * 8) = f;
-    }
-  };
-
-  floatx16 o[2];
-#pragma unroll
-  for (int i = 0; i < 2; ++i)
-#pragma unroll
-    for (int v = 0; v < 16; ++v) o[i][v] = 0.f;
-  float m_run = -INFINITY, l_run = 0.f;
-  const float sc = 0.125f * 1.4426950408889634f;  // 1/sqrt(64) * log2(e): softmax in base 2
-
-  // One stage of this wave: its 64 keys (parity `par`) against its 32 queries.  CHECKED adds the masks.
-  auto step = [&](int kt, auto checked_tag) {
-    constexpr bool CHECKED = decltype(checked_tag)::value;
-    const int kb = kt * kAttnKeys + par * 64;   // first key of this wave's part of the stage
-    if (CHECKED && !(wave_active && kb < wave_keys)) return;
-    const uint16_t *ks = smem + (kt & 1) * kAttnStage, *vt = ks + kAttnKeys * kKsStride;
+  // What a parity has summed: O^T, reference point of the lane's query (-inf: no visible key so far), row sum; whether every
+  // reference point of the wave is 0 (wave-uniform); the probabilities of its current group
+  struct Half {
+    floatx16 o[2];
+    float m, l;
+    bool at_zero;
     floatx16 st[2];
+    bf16x8 pf[4];
+  };
+  Half he, ho;
+  auto init = [](Half &h) {
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+      for (int v = 0; v < 16; ++v) h.o[i][v] = 0.f;
+    h.m = -INFINITY;
+    h.l = 0.f;
+    h.at_zero = false;
+#pragma unroll
+    for (int pg = 0; pg < 4; ++pg)
+#pragma unroll
+      for (int e = 0; e < 8; ++e) h.pf[pg][e] = static_cast<__bf16>(0.0f);
+  };
+  init(he);
+  init(ho);
+  typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+  // K and V of the 64 keys of parity `par` of a stage: of K in the given slot, of V by the stage's number
+  auto k_half = [&](int slot_k, int par) { return smem_raw + slot_k * kAttnHalfStage + par * 8192; };
+  auto v_half = [&](int kt, int par) { return smem_raw + (kAttnKStages + (kt & 1)) * kAttnHalfStage + par * 8192; };
+  // S^T of a group
+  auto products = [&](Half &h, const unsigned char *ks) {
 #pragma unroll
     for (int b = 0; b < 2; ++b) {
 #pragma unroll
-      for (int v = 0; v < 16; ++v) st[b][v] = 0.f;
+      for (int v = 0; v < 16; ++v) h.st[b][v] = 0.f;
 #pragma unroll
-      for (int kk = 0; kk < 4; ++kk) {
-        bf16x8 a = *reinterpret_cast<const bf16x8 *>(ks + (par * 64 + b * 32 + qj) * kKsStride + kk * 16 + half * 8);
-        st[b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, qf[kk].v, st[b], 0, 0, 0);
-      }
+      for (int kk = 0; kk < 4; ++kk)
+        h.st[b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(*reinterpret_cast<const bf16x8 *>(ks + b * 4096 + ka[kk]), qf[kk].v, h.st[b], 0, 0, 0);
     }
-    // scores stay unscaled; the softmax scale rides in the exponent's fused multiply-add
+  };
+  // O^T += V^T P^T.  CHECKED: slots of positions that hold no data of this sequence must read as 0 (their probability is 0,
+  // but 0 * stale-NaN would poison the product); slot order of a V page: see kv_v_slot
+  auto accumulate = [&](Half &h, int kt, int par, auto checked_tag) {
+    const unsigned char *vs = v_half(kt, par);
+#pragma unroll
+    for (int pg = 0; pg < 4; ++pg)
+#pragma unroll
+      for (int i = 0; i < 2; ++i) {
+        Frag8 f;
+        f.v = *reinterpret_cast<const bf16x8 *>(vs + pg * 2048 + i * 1024 + va);
+        if constexpr (decltype(checked_tag)::value) {
+          const int p0 = kt * kAttnKeys + par * 64 + pg * kBlk;
+          if (p0 + kBlk > n_valid) {
+#pragma unroll
+            for (int e = 0; e < 8; ++e)
+              if (p0 + (e < 4 ? 0 : 4) + 4 * half + e >= n_valid) f.h[e] = 0;
+          }
+        }
+        h.o[i] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f.v, h.pf[pg], h.o[i], 0, 0, 0);
+      }
+  };
+  // The probabilities of a group by the general rule: masks (checked form), the largest score, a reference point set or
+  // moved where it has to be.
+  auto general = [&](Half &h, const unsigned char *ks, int kb, auto checked_tag) {   // kb: first key
+    constexpr bool CHECKED = decltype(checked_tag)::value;
+    products(h, ks);
     if constexpr (CHECKED) {
       if constexpr (TREE) {
         // packed prefix tree (tree-ancestry mask): inside the block, the key in slot S + p is visible to local
@@ -416,7 +502,7 @@ __global__ void __launch_bounds__(128 * QS) k_attn_mfma(int n_q_heads, const Att
             for (int v = 0; v < 16; ++v) {
               const int kpos = kb + 32 * b + 8 * (v >> 2) + 4 * half + (v & 3);
               const bool vis = (kpos <= pos_j) & ((kpos < S) | (e_sub[b][v] > base + my_row));
-              st[b][v] = vis ? st[b][v] : -INFINITY;
+              h.st[b][v] = vis ? h.st[b][v] : -INFINITY;
             }
         }
       } else if (kb + 63 > S + row0) {  // the wave's keys reach past its first query: causal mask (wave-uniform)
@@ -425,158 +511,176 @@ __global__ void __launch_bounds__(128 * QS) k_attn_mfma(int n_q_heads, const Att
 #pragma unroll
           for (int v = 0; v < 16; ++v) {
             const int kpos = kb + 32 * b + 8 * (v >> 2) + 4 * half + (v & 3);
-            if (kpos > pos_j) st[b][v] = -INFINITY;
+            if (kpos > pos_j) h.st[b][v] = -INFINITY;
           }
       }
     }
-    float mx = fmaxf(st[0][0], st[1][0]);
+    float mx = fmaxf(h.st[0][0], h.st[1][0]);
 #pragma unroll
-    for (int v = 1; v < 16; ++v) mx = fmaxf(fmaxf(mx, st[0][v]), st[1][v]);
-    mx = half_max(mx);
-    // The running reference point is kept as an INTEGER in the base-2 exponent domain (the smallest integer
-    // >= max score * scale seen so far).  Every correction factor is then an exact power of two, and the bf16
-    // rounding of a probability no longer depends on which stage it was computed in: rounding commutes with
-    // powers of two.  Probabilities lie in (0, 1].
-    const float m_new = fmaxf(m_run, ceilf(mx * sc));
-    // a query that has seen no visible key yet keeps -inf (checked form only: its first keys lie in the other
-    // parity); the reference point 0 then yields p = 0 and corr = 0 without producing inf - inf
-    const float msc = (CHECKED && m_new == -INFINITY) ? 0.f : m_new;
-    // the reference point is an integer and seldom moves after the first stages; when it moved for no lane
-    // every factor is exactly 1 and the rescale is skipped (wave-uniform branch, same bits either way)
-    if (__any(m_new != m_run)) {
-      const float corr = (m_run == -INFINITY) ? 0.f : ldexpf(1.0f, static_cast<int>(m_run - msc));
-      l_run *= corr;
+    for (int v = 1; v < 16; ++v) mx = fmaxf(fmaxf(mx, h.st[0][v]), h.st[1][v]);
+    const float m_new = attn_reference(h.m, half_max(mx));
+    // when no reference point moved every factor is exactly 1 and the rescale is skipped (wave-uniform branch, same bits
+    // either way)
+    if (__any(m_new != h.m)) {
+      const float corr = (h.m == -INFINITY) ? 0.f : ldexpf(1.0f, static_cast<int>(h.m - m_new));
+      h.l *= corr;
 #pragma unroll
       for (int i = 0; i < 2; ++i)
 #pragma unroll
-        for (int v = 0; v < 16; ++v) o[i][v] *= corr;
+        for (int v = 0; v < 16; ++v) h.o[i][v] *= corr;
+      h.m = m_new;
+      h.at_zero = __all(h.m == 0.f);
     }
-    m_run = m_new;
-    bf16x8 pf[4];
-    typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
-    const bf16x2 ones = {static_cast<__bf16>(1.0f), static_cast<__bf16>(1.0f)};
+    const float msub = h.m == -INFINITY ? 0.f : h.m;   // no visible key yet: p = 0 without producing inf - inf
+    float ps[4];
 #pragma unroll
     for (int pg = 0; pg < 4; ++pg) {
       floatx8 pv;
 #pragma unroll
-      for (int e = 0; e < 8; ++e) {
-        // bare hardware exponential: arguments are <= 0 and results below 2^-126 may flush to zero, far
-        // beneath half a bf16 unit of any probability that matters
-        pv[e] = __builtin_amdgcn_exp2f(fmaf(st[pg >> 1][8 * (pg & 1) + e], sc, -msc));
-      }
-      pf[pg] = __builtin_convertvector(pv, bf16x8);
-      // the row sum takes the probabilities as the second product will see them (rounded to bf16), two per
-      // instruction: l += p0 * 1 + p1 * 1
-      l_run = __builtin_amdgcn_fdot2_f32_bf16(__builtin_shufflevector(pf[pg], pf[pg], 0, 1), ones, l_run, false);
-      l_run = __builtin_amdgcn_fdot2_f32_bf16(__builtin_shufflevector(pf[pg], pf[pg], 2, 3), ones, l_run, false);
-      l_run = __builtin_amdgcn_fdot2_f32_bf16(__builtin_shufflevector(pf[pg], pf[pg], 4, 5), ones, l_run, false);
-      l_run = __builtin_amdgcn_fdot2_f32_bf16(__builtin_shufflevector(pf[pg], pf[pg], 6, 7), ones, l_run, false);
+      for (int e = 0; e < 8; ++e) pv[e] = __builtin_amdgcn_exp2f(h.st[pg >> 1][8 * (pg & 1) + e] - msub);
+      h.pf[pg] = __builtin_convertvector(pv, bf16x8);
+      ps[pg] = attn_page_sum(pv);
     }
+    h.l += (ps[0] + ps[1]) + (ps[2] + ps[3]);
+  };
+  // A turn: the products of half x -- V^T P^T of one group, K Q^T of the next but one -- beside the
+  // exponentials of half y, whose scores are there and whose reference points are taken for 0.  Returns whether y's
+  // probabilities stand (wave-uniform); l is its row sum then.
+  // The order is fixed by hand: a matrix instruction, the fragment read of one further on, two exponentials, and what follows
+  // from those of the slot before, so that neither pipe waits for the other.  The V fragments of the first four slots
+  // are there (pre); those of the following turn are read from vn, if it is given, before this one's result is looked at.
+  bf16x8 pre[4];
+  auto read_v = [&](const unsigned char *vs, int i) { return *reinterpret_cast<const bf16x8 *>(vs + (i >> 1) * 2048 + (i & 1) * 1024 + va); };
+  auto read_pre = [&](const unsigned char *vs) {
+#pragma unroll
+    for (int i = 0; i < 4; ++i) pre[i] = read_v(vs, i);
+  };
+  auto turn = [&](Half &x, const unsigned char *vs, const unsigned char *ks, Half &y, float &l, const unsigned char *vn) {
+    constexpr int kAhead = 5;
+    // slot: 0 to 7 = V fragment (page s / 2, dims 32 (s % 2) ..), 8 + = K fragment (block s % 2, k-step (s - 8) / 2)
+    constexpr int kSeq[16] = {0, 1, 2, 3, 8, 9, 4, 5, 10, 11, 6, 7, 12, 13, 14, 15};
+    auto read = [&](int j) {
+      const int f = kSeq[j];
+      return f < 8 ? read_v(vs, f) : *reinterpret_cast<const bf16x8 *>(ks + (f & 1) * 4096 + ka[(f - 8) >> 1]);
+    };
+    bf16x8 fr[16];
+    float e0[16], e1[16];
+    bf16x2 pw[16];
+    float sum[16];   // by pairs, then a page's in its last, then all in the last
+    auto pack = [&](int j) { pw[j] = __builtin_convertvector((floatx2){e0[j], e1[j]}, bf16x2); };
+    auto add = [&](int j) {   // attn_page_sum, and the pages' tree
+      sum[j] = e0[j] + e1[j];
+      if (j & 1) sum[j] = sum[j - 1] + sum[j];
+      if ((j & 3) == 3) sum[j] = sum[j - 2] + sum[j];
+      if ((j & 7) == 7) sum[j] = sum[j - 4] + sum[j];
+      if (j == 15) sum[j] = sum[j - 8] + sum[j];
+    };
+#pragma unroll
+    for (int j = 0; j < kAhead; ++j) fr[j] = j < 4 ? pre[j] : read(j);
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int j = 0; j < 16; ++j) {
+      const int f = kSeq[j], c = f & 1;
+      if (f < 8) {
+        x.o[c] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fr[j], x.pf[f >> 1], x.o[c], 0, 0, 0);
+      } else {
+        const floatx16 zero = {};
+        x.st[c] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fr[j], qf[(f - 8) >> 1].v, f < 10 ? zero : x.st[c], 0, 0, 0);
+      }
+      if (j + kAhead < 16) fr[j + kAhead] = read(j + kAhead);
+      // bare hardware exponential: results below 2^-126 may flush to zero, far beneath half a bf16 unit of any
+      // probability that matters
+      e0[j] = __builtin_amdgcn_exp2f(y.st[j >> 3][2 * (j & 7)]);
+      e1[j] = __builtin_amdgcn_exp2f(y.st[j >> 3][2 * (j & 7) + 1]);
+      asm volatile("" : "+v"(e0[j]), "+v"(e1[j]));   // computed here: pure instructions are moved across scheduling barriers
+      if (j >= 1) {
+        pack(j - 1), add(j - 1);
+        asm volatile("" : "+v"(sum[j - 1]), "+v"(pw[j - 1]));
+      }
+      __builtin_amdgcn_sched_barrier(0);
+    }
+    if (vn != nullptr) read_pre(vn);
+    pack(15);
+    add(15);
+    l = y.l + sum[15];
 #pragma unroll
     for (int pg = 0; pg < 4; ++pg)
-#pragma unroll
-      for (int i = 0; i < 2; ++i) {
-        bf16x8 a = *reinterpret_cast<const bf16x8 *>(vt + (i * 32 + qj) * kVtStride + (par * 4 + pg) * kBlk + half * 8);
-        o[i] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, pf[pg], o[i], 0, 0, 0);
-      }
+      y.pf[pg] = __builtin_shufflevector(__builtin_shufflevector(pw[4 * pg], pw[4 * pg + 1], 0, 1, 2, 3),
+                                         __builtin_shufflevector(pw[4 * pg + 2], pw[4 * pg + 3], 0, 1, 2, 3), 0, 1, 2, 3, 4, 5, 6, 7);
+    return static_cast<int>(y.at_zero) & __all(l < kAttnSumLimit);
   };
+  const auto plain = std::false_type{};
+  const auto checked = std::true_type{};
 
-  // Pipeline: K/V of stage kt+2 and the page id of stage kt+3 are requested at the top of iteration kt, right after
-  // the staging registers (stage kt+1, requested one whole iteration earlier, so long since arrived) were written to
-  // the LDS stage that iteration kt-1 finished reading.  No wave ever waits for a load it has just issued, and the
-  // LDS stores run ahead of the stage's arithmetic instead of between it and the barrier.
-  fetch_id(kt0);
-  prefetch();
-  if (kt0 + 1 < kt1) fetch_id(kt0 + 1);
-  store_lds(kt0 & 1, kt0, kt0 >= kt_plain);
-  if (kt0 + 1 < kt1) {
-    prefetch();
-    if (kt0 + 2 < kt1) fetch_id(kt0 + 2);
-  }
-  __syncthreads();
-  int kt = kt0;
-  // plain stages: stage kt+1 may already be a checked one (its store then needs the zeroing of absent positions)
-  for (; kt < kt_plain; ++kt) {
-    if (kt + 1 < kt1) {
-      if (kt + 1 < kt_plain) store_lds((kt + 1) & 1, kt + 1, false);
-      else store_lds((kt + 1) & 1, kt + 1, true);
-      if (kt + 2 < kt1) {
-        prefetch();
-        if (kt + 3 < kt1) fetch_id(kt + 3);
-      }
+  // ---- plain stages.  Beside the exponentials of one parity run the products of the other: its last group's V^T P^T and its
+  // next group's K Q^T.
+  landed();
+  int kt = kt0, k_at = 0;   // k_at: K slot of stage kt
+  auto next_slot = [](int k) { return k + 1 == kAttnKStages ? 0 : k + 1; };
+  if (kt < kt_plain) {
+    products(he, k_half(k_at, 0));
+    read_pre(v_half(kt, 1));
+    for (; kt < kt_plain; ++kt) {
+      float l;
+      // first turn: o's probabilities are 0, any V will do
+      const int ok_e = turn(ho, v_half(max(kt - 1, kt0), 1), k_half(k_at, 1), he, l, nullptr);
+      if (ok_e) he.l = l;
+      else general(he, k_half(k_at, 0), kt * kAttnKeys, plain);
+      landed();                                     // K of stage kt + 1, V of stage kt
+      read_pre(v_half(kt, 0));
+      if (next_k < kt1) issue_k();                  // K of stage kt + 2, over that of kt - 1
+      if (next_v < kt1) issue_v();                  // V of stage kt + 1, over that of kt - 1
+      const int k_next = next_slot(k_at);
+      const int ok_o = turn(he, v_half(kt, 0), k_half(k_next, 0), ho, l, v_half(kt, 1));   // last turn: the scores are not used
+      if (ok_o) ho.l = l;
+      else general(ho, k_half(k_at, 1), kt * kAttnKeys + 64, plain);
+      k_at = k_next;
     }
-    step(kt, std::false_type{});
-    __syncthreads();
+    accumulate(ho, kt - 1, 1, plain);
   }
   for (; kt < kt1; ++kt) {
-    if (kt + 1 < kt1) {
-      store_lds((kt + 1) & 1, kt + 1, true);
-      if (kt + 2 < kt1) {
-        prefetch();
-        if (kt + 3 < kt1) fetch_id(kt + 3);
-      }
+    if (kt > kt0) landed();
+    if (next_k < kt1 && next_k <= kt + 1) issue_k();
+    if (next_v < kt1 && next_v <= kt + 1) issue_v();
+    if (wave_active && kt * kAttnKeys < wave_keys) {
+      general(he, k_half(k_at, 0), kt * kAttnKeys, checked);
+      accumulate(he, kt, 0, checked);
     }
-    step(kt, std::true_type{});
-    __syncthreads();
+    if (wave_active && kt * kAttnKeys + 64 < wave_keys) {
+      general(ho, k_half(k_at, 1), kt * kAttnKeys + 64, checked);
+      accumulate(ho, kt, 1, checked);
+    }
+    k_at = next_slot(k_at);
   }
 
-  // ---- fold the two parities of each query set through LDS (stage memory is free after the last barrier):
-  // parity 0 takes in parity 1
-  float *mrg = reinterpret_cast<float *>(smem_raw);   // [QS query sets][34][64 lanes]
-  l_run = half_sum(l_run);
-  if (par == 1) {
-    float *dst = mrg + wq * 34 * 64 + lane;
+  // ---- fold the two parities, even first.  Integer exponents: exact powers of two.  Unsplit, parity 0 is never empty (key 0
+  // is in its first stage); a chunk of a split pass may hold no visible key for a row in either parity
+  if (!wave_active || row0 + qj >= Lq) return;
+  const float l_a = half_sum(he.l), l_b = half_sum(ho.l);
+  const float m_tot = fmaxf(he.m, ho.m);
+  const float ca = (he.m > -INFINITY) ? ldexpf(1.0f, static_cast<int>(he.m - m_tot)) : 0.f;
+  const float cb = (ho.m > -INFINITY) ? ldexpf(1.0f, static_cast<int>(ho.m - m_tot)) : 0.f;
+  const float l_tot = l_a * ca + l_b * cb;
+  const float inv = SPLIT ? 1.0f : 1.0f / l_tot;
+  const size_t rh = (static_cast<size_t>(blockIdx.z) * n_q_heads + head) * sp.total_q + base + row0 + qj;
 #pragma unroll
-    for (int i = 0; i < 2; ++i)
+  for (int i = 0; i < 2; ++i)
 #pragma unroll
-      for (int v = 0; v < 16; ++v) dst[(i * 16 + v) * 64] = o[i][v];
-    dst[32 * 64] = m_run;
-    dst[33 * 64] = l_run;
-  }
-  __syncthreads();
-  if (par == 0 && wave_active && row0 + qj < Lq) {
-    {
-      const float *src = mrg + wq * 34 * 64 + lane;
-      const float m_b = src[32 * 64], l_b = src[33 * 64];
-      // integer exponents: exact powers of two.  Unsplit, parity 0 is never empty (key 0 is in its first stage); a
-      // chunk of a split pass may hold no visible key for a row in either parity
-      const float m_tot = fmaxf(m_run, m_b);
-      const float ca = (m_run > -INFINITY) ? ldexpf(1.0f, static_cast<int>(m_run - m_tot)) : 0.f;
-      const float cb = (m_b > -INFINITY) ? ldexpf(1.0f, static_cast<int>(m_b - m_tot)) : 0.f;
-      l_run = l_run * ca + l_b * cb;
-      m_run = m_tot;
+    for (int g = 0; g < 4; ++g) {
+      floatx4 ov;
 #pragma unroll
-      for (int i = 0; i < 2; ++i)
+      for (int e = 0; e < 4; ++e) ov[e] = he.o[i][4 * g + e] * ca + ho.o[i][4 * g + e] * cb;
+      if constexpr (SPLIT) {
+        *reinterpret_cast<floatx4 *>(sp.part_o + rh * kHd + i * 32 + 8 * g + 4 * half) = ov;
+      } else {
 #pragma unroll
-        for (int v = 0; v < 16; ++v) o[i][v] = o[i][v] * ca + src[(i * 16 + v) * 64] * cb;
+        for (int e = 0; e < 4; ++e) ov[e] *= inv;
+        *reinterpret_cast<bf16x4 *>(out + static_cast<size_t>(base + row0 + qj) * qdim + head * kHd + i * 32 + 8 * g + 4 * half) =
+            __builtin_convertvector(ov, bf16x4);
+      }
     }
-    if constexpr (SPLIT) {
-      const size_t rh = (static_cast<size_t>(blockIdx.z) * n_q_heads + head) * sp.total_q + base + row0 + qj;
-      float *po = sp.part_o + rh * kHd;
-#pragma unroll
-      for (int i = 0; i < 2; ++i)
-#pragma unroll
-        for (int g = 0; g < 4; ++g) {
-          floatx4 ov;
-#pragma unroll
-          for (int e = 0; e < 4; ++e) ov[e] = o[i][4 * g + e];
-          *reinterpret_cast<floatx4 *>(po + i * 32 + 8 * g + 4 * half) = ov;
-        }
-      if (half == 0) sp.part_ml[rh] = make_float2(m_run, l_run);
-    } else {
-      const float inv = 1.0f / l_run;
-      bf16 *op = out + static_cast<size_t>(base + row0 + qj) * qdim + head * kHd;
-#pragma unroll
-      for (int i = 0; i < 2; ++i)
-#pragma unroll
-        for (int g = 0; g < 4; ++g) {
-          floatx4 ov;
-#pragma unroll
-          for (int e = 0; e < 4; ++e) ov[e] = o[i][4 * g + e] * inv;
-          *reinterpret_cast<bf16x4 *>(op + i * 32 + 8 * g + 4 * half) = __builtin_convertvector(ov, bf16x4);
-        }
-    }
-  }
+  if constexpr (SPLIT)
+    if (half == 0) sp.part_ml[rh] = make_float2(m_tot, l_tot);
 }
 
 // Folds the key chunks of a split pass: row r (cache slot row_slot[r]) has chunks 0 .. min(kAttnMaxChunks - 1,

@@ -43,7 +43,8 @@ __global__ void __launch_bounds__(256) k_attn_simple(int n_q_heads, RowMeta meta
       for (int e = 0; e < 4; ++e) v[i + e] = x[e];
     }
   };
-  const float scale = 0.125f;  // 1/sqrt(64)
+  // 1/sqrt(64); bf16 query rows carry it, with a log2(e) (EpiQKV::kQScale)
+  const float scale = std::is_same<T, float>::value ? 0.125f : 0.69314718056f;
   float m = -INFINITY, l = 0.f, acc = 0.f;
   int id = lane < n_keys ? kv_lookup_block(kv, s, lane) : -1;   // block of the lane's key
   for (int j0 = 0; j0 < n_keys; j0 += kWave) {

@@ -2,18 +2,17 @@
 // workgroup.
 //
 // Why.  k_attn_mfma gives a wave 32 queries and lets it walk every second 64-key group of the sequence on its own:
-// products, maximum, exponentials and products again in one dependent chain per group.  A pass with few rows has few such
-// walks (one token of one sequence: 4 workgroups on 256 compute units), so the launch lasts as long as one of them:
-// 15 us at 1055 keys, most of it latency.  What truly depends on the previous group is little: the running maximum (one
-// number per query) and the accumulation of O and of the row sum.  Here the scoring waves take one 64-key group each
-// (S^T = K Q^T, maximum, probabilities), exchange their maxima through LDS, so
-// that each knows the reference point the serial walk would have had at its group, and leave their probabilities in LDS.
+// 64 keys after 64 keys.  A pass with few rows has few such
+// walks (one token of one sequence: 4 workgroups on 256 compute units), so the launch lasts as long as one of them,
+// most of it latency.  What truly depends on the previous group is little: the accumulation of O and of the row sum, and a
+// reference point that hardly ever moves.  Here the scoring waves take one 64-key group each (S^T = K Q^T,
+// probabilities) and leave their probabilities and row sums in LDS.
 // Four accumulating waves -- (key parity, half of the head dimension) -- walk the groups in order and add V^T P^T: a chain
 // of four matrix instructions a group, with V straight from memory to registers (a V page is stored as the operand).
 //
 // Every number is formed by the same instructions on the same operands in the same order as in k_attn_mfma (groups at
-// absolute positions, even and odd groups in separate sums, the reference point of a group = the largest seen so far in
-// its parity), so the two kernels give the same bits and the choice between them may follow the batch.
+// absolute positions, even and odd groups in separate sums, reference points by attn_reference group by group within a
+// parity), so the two kernels give the same bits and the choice between them may follow the batch.
 //
 // Query sets.  A set is QW = 32 columns: 32 rows of one query head, or, where a sequence has few rows, the rows of several
 // query heads of one kv head (16 rows of two heads, 8 rows of four), so that K and V are read once for all of them.  The
@@ -26,15 +25,20 @@
 
 namespace hsd {
 
-// LDS: probabilities of two steps of four groups (4 KB a group: [page][lane][8 bf16]), the groups' maxima of two steps, and
-// the odd parity's (O, reference point, sum) for the final fold
+// LDS: probabilities of two steps of four groups (4 KB a group: [page][lane][8 bf16]), the reference points they are relative
+// to, whether a scoring wave's group moves one, and the odd parity's (O, reference point, sum) for the final fold
 constexpr int kAttnWideScorers = 4;
+constexpr int kKsStride = kHd + 8;   // bf16 per K row in LDS
 template <int QW>
 struct AttnWideLds {
   uint4 p[2][kAttnWideScorers][QW / 8][64];
   float mg[2][kAttnWideScorers][QW];
-  uint16_t k[kAttnWideScorers][64 * kKsStride];   // a scoring wave's own 64 keys (see k_row)
-  float fold[2][QW / 2 + 2][64];
+  float sum[2][kAttnWideScorers][64];             // a lane's row sum over its group
+  int moves[2][kAttnWideScorers];
+  union {
+    uint16_t k[kAttnWideScorers][64 * kKsStride];   // a scoring wave's own 64 keys (see k_row)
+    float fold[2][QW / 2 + 2][64];                  // after the last products
+  };
 };
 // Offset of a key's row in AttnWideLds::k: rows 144 B apart, those of odd pages 16 B further, so that the fragment reads of
 // 16 rows (16 keys in a row, or 8 of a page and the same 8 of the next) cover all 64 banks once.
@@ -49,22 +53,16 @@ __device__ __forceinline__ float quarter_sum(float x) {
   const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(x), false, false);
   return __uint_as_float(r[0]) + __uint_as_float(r[1]);
 }
-// Value of the other lane half
-__device__ __forceinline__ float other_half(float x, int half) {
-  const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
-  return __uint_as_float(half ? r[0] : r[1]);
-}
-
 // NS scoring waves and four accumulating ones; a step covers NS 64-key groups.
 // grid: attn_grid_size(...) tasks, block 64 * (NS + 4), dynamic LDS sizeof(AttnWideLds).
-// Two barriers a step, executed by every wave: behind the first the maxima of the step's groups are in LDS, behind the
-// second its probabilities.  The accumulating waves work on a step between its second barrier and that of the next step.
-// What bounds it (in-kernel timestamps, one token at 1055 keys, 10.2 us): 2.6 us until the first scores (descriptor, page
-// ids, keys: three dependent reads), five steps of 1.1 us -- the unit's load path takes 64 KB a step at 64 B a cycle, and a
-// scoring wave stalls in the issue of its requests -- and 1 us of last accumulation, fold and store.  On the way here: 12.3
-// us with 32 columns, 11.5 with 16, 10.2 with pages numbered once per 16 steps instead of a 64-bit product per page and
-// use.  Tried on top: eight scoring waves (32 columns: 13.4 us against 12.1), keys and values two steps ahead (13.8), the
-// next step's products under the exponentials and all LDS reads of a step up front (10.7).
+// One barrier a step, executed by every wave: behind it the step's probabilities are in LDS.  A step in which a group sets or
+// moves a reference point (the first takes it for 0) takes NS / 2 more, the same for every wave.
+// What bounds it (one token at 1055 keys, 8.5 us): 2.6 us until the first scores (descriptor, page
+// ids, keys: three dependent reads), then the 270 KB of a kv head through one unit's load path (a bare read of 256 KB by a
+// workgroup takes 5 us with its launch), 1 us of last accumulation, fold and store.  Tried: eight scoring waves (32 columns: 13.4
+// us against 12.1); keys and values two steps ahead in registers (16 tokens a step 13.58 ms against 13.15); four more waves that
+// only request the keys into a ring of three or four steps (13.66; 64 tokens 9.05 ms against 8.62, one workgroup a unit).
+static_assert(2 * sizeof(AttnWideLds<32>) <= 160 * 1024, "two workgroups a compute unit");
 template <int QW, bool TREE>
 __global__ void __launch_bounds__(64 * (kAttnWideScorers + 4), 4) k_attn_wide(int n_q_heads, int g4, const AttnTile *__restrict__ tiles,
                                                                            PagedKV kv, const bf16 *__restrict__ q,
@@ -94,7 +92,6 @@ __global__ void __launch_bounds__(64 * (kAttnWideScorers + 4), 4) k_attn_wide(in
   const int n_keys = S + min(row0 + (1 << rshift), Lq);            // keys any query of the set can see
   const int n_groups = (n_keys + 63) >> 6, n_steps = (n_groups + NS - 1) / NS;
   const int qdim = n_q_heads * kHd;
-  const float sc = 0.125f * 1.4426950408889634f;
 
   const int32_t *table_row = kv.block_table + static_cast<size_t>(slot) * kv.max_blocks_per_seq;
   const int last_entry = kv.max_blocks_per_seq - 1;
@@ -108,6 +105,13 @@ __global__ void __launch_bounds__(64 * (kAttnWideScorers + 4), 4) k_attn_wide(in
   // element offset of the page whose number lane `src` of `pages` holds
   auto page_off = [&](int pages, int src) {
     return static_cast<size_t>(static_cast<uint32_t>(__builtin_amdgcn_readlane(pages, src))) * (kBlk * kHd);
+  };
+  auto any_moves = [&](int s) {
+    const int *f = sm.moves[s & 1];
+    int m = 0;
+#pragma unroll
+    for (int k = 0; k < NS; ++k) m |= f[k];
+    return __builtin_amdgcn_readfirstlane(m) != 0;
   };
   if (wave >= 4) {
     // ---- a scoring wave: groups w, w + NS, w + 2 NS, ...
@@ -144,46 +148,135 @@ __global__ void __launch_bounds__(64 * (kAttnWideScorers + 4), 4) k_attn_wide(in
       __builtin_amdgcn_wave_barrier();
       __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
     };
+    constexpr int NB = QW == 32 ? 2 : 4, NV = QW == 32 ? 16 : 4;
+    // Scores of 64 keys x QW queries: register v of block b is key_of(b, v) of the group.  QW = 16: blocks 2 p and 2 p + 1
+    // cover pages 2 p and 2 p + 1, the keys dealt to the operand rows so that a lane's eight registers of the two are the
+    // eight contraction slots that the second product takes from it.
+    auto key_of = [&](int b, int v) {
+      return QW == 32 ? 32 * b + 8 * (v >> 2) + 4 * half + (v & 3) : 32 * (b >> 1) + 8 * (b & 1) + 16 * (kg >> 1) + 4 * (kg & 1) + v;
+    };
+    float st[NB][NV];
+    // The wave's group of a step: products, then masks and the lane's largest score
+    // (with 16 columns the first half's fragments are read ahead, while the wave learns whether the step before stands)
+    bf16x8 first[4];
+    auto fragment = [&](int j) {   // QW = 32: block j / 4, k-step j % 4; QW = 16: j / 2, j % 2
+      if constexpr (QW == 32) {
+        return *reinterpret_cast<const bf16x8 *>(ks + k_row((j >> 2) * 32 + qj) + (j & 3) * 16 + half * 8);
+      } else {
+        const int b = j >> 1, key = 32 * (b >> 1) + 8 * (b & 1) + 16 * (qj >> 3) + 4 * ((qj >> 2) & 1) + (qj & 3);
+        return *reinterpret_cast<const bf16x8 *>(ks + k_row(key) + (j & 1) * 32 + kg * 8);
+      }
+    };
+    auto read_first = [&]() {
+#pragma unroll
+      for (int j = 0; j < 4; ++j) first[j] = fragment(j);
+    };
+    auto products = [&]() {
+#pragma unroll
+      for (int b = 0; b < NB; ++b) {
+        if constexpr (QW == 32) {
+          floatx16 acc;
+#pragma unroll
+          for (int v = 0; v < 16; ++v) acc[v] = 0.f;
+#pragma unroll
+          for (int kk = 0; kk < 4; ++kk)
+            acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fragment(4 * b + kk), qf[kk].v, acc, 0, 0, 0);
+#pragma unroll
+          for (int v = 0; v < NV; ++v) st[b][v] = acc[v];
+        } else {
+          floatx4 acc = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+          for (int kk = 0; kk < 2; ++kk)
+            acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(b < 2 ? first[2 * b + kk] : fragment(2 * b + kk), qf[kk].v, acc, 0, 0, 0);
+#pragma unroll
+          for (int v = 0; v < NV; ++v) st[b][v] = acc[v];
+        }
+      }
+    };
+    auto mask = [&](int kb) {
+      if constexpr (TREE) {
+        if (kb + 63 >= S) {  // the group reaches into the block: tree-ancestry mask (see k_attn_mfma)
+#pragma unroll
+          for (int b = 0; b < NB; ++b) {
+            int e_sub[NV];   // a block at a time: the registers of all would decide between one and two workgroups a unit
+#pragma unroll
+            for (int v = 0; v < NV; ++v) e_sub[v] = row_end[base + min(max(kb + key_of(b, v) - S, 0), Lq - 1)];
+#pragma unroll
+            for (int v = 0; v < NV; ++v) {
+              const int kpos = kb + key_of(b, v);
+              const bool vis = (kpos <= pos_j) & ((kpos < S) | (e_sub[v] > base + my_row));
+              st[b][v] = vis ? st[b][v] : -INFINITY;
+            }
+          }
+        }
+      } else if (kb + 63 > S + row0) {  // the group reaches past the first query: causal mask
+#pragma unroll
+        for (int b = 0; b < NB; ++b)
+#pragma unroll
+          for (int v = 0; v < NV; ++v)
+            if (kb + key_of(b, v) > pos_j) st[b][v] = -INFINITY;
+      }
+    };
+    auto query_max = [&]() {   // the group's largest score of the lane's query
+      float mx = st[0][0];
+#pragma unroll
+      for (int b = 0; b < NB; ++b)
+#pragma unroll
+        for (int v = 0; v < NV; ++v) mx = fmaxf(mx, st[b][v]);
+      mx = half_max(mx);
+      return QW == 16 ? quarter_max(mx) : mx;
+    };
+    // Reference point of the lane's query in this wave's parity (attn_reference).  The first step takes it for 0, which it is
+    // unless the scores are extreme, so that its four groups need not wait for one another either.
+    float m_run = 0.f;
+    // the group's probabilities and the reference points they are relative to; returns the lane's row sum
+    auto probs = [&](int s) {
+      const float msub = m_run == -INFINITY ? 0.f : m_run;
+      float ps[QW / 8];
+#pragma unroll
+      for (int f = 0; f < QW / 8; ++f) {   // operand f: page f of the group, or pages 2 f and 2 f + 1
+        floatx8 pv;
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+          const float x = QW == 32 ? st[f >> 1][8 * (f & 1) + e] : st[2 * f + (e >> 2)][e & 3];
+          pv[e] = __builtin_amdgcn_exp2f(x - msub);
+        }
+        Frag8 pf;
+        pf.v = __builtin_convertvector(pv, bf16x8);
+        sm.p[s & 1][w][f][lane] = pf.u;
+        ps[f] = attn_page_sum(pv);
+        // QW = 16: this lane's page and the other half's
+        if constexpr (QW == 16) ps[f] = half_sum(ps[f]);
+      }
+      const float sum = QW == 32 ? (ps[0] + ps[1]) + (ps[2] + ps[3]) : ps[0] + ps[1];
+      sm.sum[s & 1][w][lane] = sum;
+      if (kg == 0) sm.mg[s & 1][w][qj] = m_run;
+      return sum;
+    };
     load_k(0);
     store_k();
     if (n_steps > 1) load_k(1);
-    float m_run = -INFINITY;   // largest reference point of this wave's parity in the steps so far
+    // Behind a step's barrier: if a group of it sets or moves a reference point, the groups of a parity one after the other, each
+    // from the reference point its predecessor left.
+    auto settle = [&](int s) {
+      if (!any_moves(s)) return;
+      if (s == 0) m_run = -INFINITY;
+      for (int k = 0; k < NS / 2; ++k) {
+        if ((w >> 1) == k && s * NS + w < n_groups) {
+          m_run = attn_reference(m_run, query_max());
+          probs(s);
+        }
+        __syncthreads();
+        const int last = 2 * k + (w & 1);
+        if (s * NS + last < n_groups) m_run = sm.mg[s & 1][last][qj];
+      }
+    };
     for (int s = 0; s < n_steps; ++s) {
       const int g = s * NS + w, kb = g * 64;
-      // Scores of 64 keys x QW queries: register v of block b is key_of(b, v) of the group.  QW = 16: blocks 2 p and 2 p + 1
-      // cover pages 2 p and 2 p + 1, the keys dealt to the operand rows so that a lane's eight registers of the two are the
-      // eight contraction slots that the second product takes from it.
-      constexpr int NB = QW == 32 ? 2 : 4, NV = QW == 32 ? 16 : 4;
-      auto key_of = [&](int b, int v) {
-        return QW == 32 ? 32 * b + 8 * (v >> 2) + 4 * half + (v & 3) : 32 * (b >> 1) + 8 * (b & 1) + 16 * (kg >> 1) + 4 * (kg & 1) + v;
-      };
-      float st[NB][NV];
-      float mi = -INFINITY;
-      if (g < n_groups) {
-#pragma unroll
-        for (int b = 0; b < NB; ++b) {
-          if constexpr (QW == 32) {
-            floatx16 acc;
-#pragma unroll
-            for (int v = 0; v < 16; ++v) acc[v] = 0.f;
-#pragma unroll
-            for (int kk = 0; kk < 4; ++kk)
-              acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(*reinterpret_cast<const bf16x8 *>(ks + k_row(b * 32 + qj) + kk * 16 + half * 8),
-                                                            qf[kk].v, acc, 0, 0, 0);
-#pragma unroll
-            for (int v = 0; v < NV; ++v) st[b][v] = acc[v];
-          } else {
-            const int key = 32 * (b >> 1) + 8 * (b & 1) + 16 * (qj >> 3) + 4 * ((qj >> 2) & 1) + (qj & 3);
-            floatx4 acc = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-            for (int kk = 0; kk < 2; ++kk)
-              acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(*reinterpret_cast<const bf16x8 *>(ks + k_row(key) + kk * 32 + kg * 8),
-                                                            qf[kk].v, acc, 0, 0, 0);
-#pragma unroll
-            for (int v = 0; v < NV; ++v) st[b][v] = acc[v];
-          }
-        }
-      }
+      bool moves = false;
+      if constexpr (QW == 16) read_first();
+      if (s > 0) settle(s - 1);
+      if (g < n_groups) products();
       if (s + 1 < n_steps) {
         store_k();
         if (s + 2 < n_steps) {
@@ -192,66 +285,17 @@ __global__ void __launch_bounds__(64 * (kAttnWideScorers + 4), 4) k_attn_wide(in
         }
       }
       if (g < n_groups) {
-        if constexpr (TREE) {
-          if (kb + 63 >= S) {  // the group reaches into the block: tree-ancestry mask (see k_attn_mfma)
-#pragma unroll
-            for (int b = 0; b < NB; ++b) {
-              int e_sub[NV];   // a block at a time: the registers of all would decide between one and two workgroups a unit
-#pragma unroll
-              for (int v = 0; v < NV; ++v) e_sub[v] = row_end[base + min(max(kb + key_of(b, v) - S, 0), Lq - 1)];
-#pragma unroll
-              for (int v = 0; v < NV; ++v) {
-                const int kpos = kb + key_of(b, v);
-                const bool vis = (kpos <= pos_j) & ((kpos < S) | (e_sub[v] > base + my_row));
-                st[b][v] = vis ? st[b][v] : -INFINITY;
-              }
-            }
-          }
-        } else if (kb + 63 > S + row0) {  // the group reaches past the first query: causal mask
-#pragma unroll
-          for (int b = 0; b < NB; ++b)
-#pragma unroll
-            for (int v = 0; v < NV; ++v)
-              if (kb + key_of(b, v) > pos_j) st[b][v] = -INFINITY;
-        }
-        float mx = st[0][0];
-#pragma unroll
-        for (int b = 0; b < NB; ++b)
-#pragma unroll
-          for (int v = 0; v < NV; ++v) mx = fmaxf(mx, st[b][v]);
-        mx = half_max(mx);
-        if constexpr (QW == 16) mx = quarter_max(mx);
-        mi = ceilf(mx * sc);   // integer reference point in the base-2 exponent domain (see k_attn_mfma)
+        mask(kb);
+        const float sum = probs(s);
+        // A parity's first group, or a query without a visible key so far; elsewhere a score that moves a reference point
+        // shows in the row sum (kAttnSumLimit)
+        if (g < 2 || !__all(sum < kAttnSumLimit && m_run > -INFINITY))
+          moves = __any(attn_reference(g < 2 ? -INFINITY : m_run, query_max()) != m_run);
       }
-      if (kg == 0) sm.mg[s & 1][w][qj] = mi;
-      __syncthreads();
-      // the reference point at this group: the largest of the parity's groups up to and including it
-      float m_new = m_run;
-#pragma unroll
-      for (int k = 0; k < NS / 2; ++k) {
-        const int w2 = 2 * k + (w & 1);
-        const float v = sm.mg[s & 1][w2][qj];
-        if (w2 <= w) m_new = fmaxf(m_new, v);
-        m_run = fmaxf(m_run, v);
-      }
-      if (g < n_groups) {
-        // a query that has seen no visible key yet: reference point 0 yields p = 0 without producing inf - inf
-        const float msc = m_new == -INFINITY ? 0.f : m_new;
-#pragma unroll
-        for (int f = 0; f < QW / 8; ++f) {   // operand f: page f of the group, or pages 2 f and 2 f + 1
-          floatx8 pv;
-#pragma unroll
-          for (int e = 0; e < 8; ++e) {
-            const float x = QW == 32 ? st[f >> 1][8 * (f & 1) + e] : st[2 * f + (e >> 2)][e & 3];
-            pv[e] = __builtin_amdgcn_exp2f(fmaf(x, sc, -msc));
-          }
-          Frag8 pf;
-          pf.v = __builtin_convertvector(pv, bf16x8);
-          sm.p[s & 1][w][f][lane] = pf.u;
-        }
-      }
-      __syncthreads();
+      if (lane == 0) sm.moves[s & 1][w] = moves;
+      __syncthreads();   // the step's probabilities
     }
+    settle(n_steps - 1);
     __syncthreads();   // the fold below
     return;
   }
@@ -295,16 +339,15 @@ __global__ void __launch_bounds__(64 * (kAttnWideScorers + 4), 4) k_attn_wide(in
 #pragma unroll
   for (int v = 0; v < 8; ++v) o16[v >> 2][v & 3] = 0.f;
   float m_run = -INFINITY, l_run = 0.f;
-  typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
-  const bf16x2 ones = {static_cast<__bf16>(1.0f), static_cast<__bf16>(1.0f)};
-  // the row sum of a lane's eight slots, two per instruction, in ascending order (as in k_attn_mfma)
-  auto add8 = [&](float l, const bf16x8 &x) {
-    l = __builtin_amdgcn_fdot2_f32_bf16(__builtin_shufflevector(x, x, 0, 1), ones, l, false);
-    l = __builtin_amdgcn_fdot2_f32_bf16(__builtin_shufflevector(x, x, 2, 3), ones, l, false);
-    l = __builtin_amdgcn_fdot2_f32_bf16(__builtin_shufflevector(x, x, 4, 5), ones, l, false);
-    return __builtin_amdgcn_fdot2_f32_bf16(__builtin_shufflevector(x, x, 6, 7), ones, l, false);
+  Frag8 pf[KG][QW / 8];
+  float mg[KG], rs[KG];
+  auto read_group = [&](int s, int k) {   // what the scoring wave left; with 16 columns ahead of the barriers' outcome
+    const int w = 2 * k + par;
+    mg[k] = sm.mg[s & 1][w][qj];
+#pragma unroll
+    for (int f = 0; f < QW / 8; ++f) pf[k][f].u = sm.p[s & 1][w][f][lane];
+    rs[k] = sm.sum[s & 1][w][lane];
   };
-
   auto accumulate = [&](int s, int k) {
     const int w = 2 * k + par, g = s * NS + w;
     if (g >= n_groups) return;
@@ -320,7 +363,8 @@ __global__ void __launch_bounds__(64 * (kAttnWideScorers + 4), 4) k_attn_wide(in
           if (g * 64 + page * kBlk + tok >= n_valid) vf[k][f].h[e] = 0;
         }
     }
-    const float m_new = fmaxf(m_run, sm.mg[s & 1][w][qj]);
+    if constexpr (QW == 32) read_group(s, k);
+    const float m_new = mg[k];
     if (__any(m_new != m_run)) {
       const float corr = (m_run == -INFINITY) ? 0.f : ldexpf(1.0f, static_cast<int>(m_run - m_new));
       l_run *= corr;
@@ -333,49 +377,47 @@ __global__ void __launch_bounds__(64 * (kAttnWideScorers + 4), 4) k_attn_wide(in
       }
     }
     m_run = m_new;
-    Frag8 pf[QW / 8];
-#pragma unroll
-    for (int f = 0; f < QW / 8; ++f) pf[f].u = sm.p[s & 1][w][f][lane];
+    l_run += rs[k];
     if constexpr (QW == 32) {
 #pragma unroll
-      for (int f = 0; f < 4; ++f) {
-        o32 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf[k][f].v, pf[f].v, o32, 0, 0, 0);
-        l_run = add8(l_run, pf[f].v);
-      }
+      for (int f = 0; f < 4; ++f) o32 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf[k][f].v, pf[k][f].v, o32, 0, 0, 0);
     } else {
-      // the lower lane half holds page 2 p, the upper page 2 p + 1: the sum passes through both in turn and is kept in
-      // the lower half
 #pragma unroll
-      for (int p = 0; p < 2; ++p) {
+      for (int p = 0; p < 2; ++p)
 #pragma unroll
-        for (int d = 0; d < 2; ++d) o16[d] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(vf[k][2 * p + d].v, pf[p].v, o16[d], 0, 0, 0);
-        l_run = other_half(add8(l_run, pf[p].v), half);
-        l_run = other_half(add8(l_run, pf[p].v), half);
-      }
+        for (int d = 0; d < 2; ++d) o16[d] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(vf[k][2 * p + d].v, pf[k][p].v, o16[d], 0, 0, 0);
     }
   };
 
-  __syncthreads();   // first step: maxima
-  __syncthreads();   // first step: probabilities
+  auto wait_step = [&](int s) {   // the barriers of the scoring waves' step
+    __syncthreads();
+    if constexpr (QW == 16) {
+#pragma unroll
+      for (int k = 0; k < KG; ++k) read_group(s, k);
+    }
+    if (any_moves(s)) {
+      for (int k = 0; k < NS / 2; ++k) __syncthreads();
+      if constexpr (QW == 16) {
+#pragma unroll
+        for (int k = 0; k < KG; ++k) read_group(s, k);
+      }
+    }
+  };
+  wait_step(0);
   for (int s = 0; s + 1 < n_steps; ++s) {
     if ((s + 1) % SPF == 0) pages = fetch_pages(s + 1);
 #pragma unroll
     for (int k = 0; k < KG; ++k) {
       accumulate(s, k);
       load_v(s + 1, k);
-      if (k == KG / 2 - 1) __syncthreads();   // step s + 1: maxima
     }
-    __syncthreads();                          // step s + 1: probabilities
+    wait_step(s + 1);
   }
 #pragma unroll
   for (int k = 0; k < KG; ++k) accumulate(n_steps - 1, k);
 
   // ---- fold the two parities (even first), as k_attn_mfma does
   l_run = QW == 32 ? half_sum(l_run) : quarter_sum(l_run);
-  if constexpr (QW == 16) {
-    const float lower = other_half(l_run, half);
-    l_run = half ? lower : l_run;
-  }
   float o[NO];
 #pragma unroll
   for (int v = 0; v < NO; ++v) o[v] = QW == 32 ? o32[v] : o16[(v >> 2) & 1][v & 3];

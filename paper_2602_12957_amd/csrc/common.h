@@ -11,10 +11,12 @@ namespace hsd {
 constexpr int kWave = 64;        // CDNA wavefront width
 constexpr int kHd = HSD_HEAD_DIM;
 constexpr int kBlk = HSD_KV_BLOCK_TOKENS;
+constexpr float kSoftmaxScale = 0.125f * 1.4426950408889634f;   // log2(e) / sqrt(64): softmax in base 2
 
 // native vector types (kept in VGPRs as whole registers; HIP's uint4 / float4 structs are not)
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
+typedef float floatx2 __attribute__((ext_vector_type(2)));
 typedef float floatx4 __attribute__((ext_vector_type(4)));
 typedef float floatx8 __attribute__((ext_vector_type(8)));
 typedef float floatx16 __attribute__((ext_vector_type(16)));

@@ -69,6 +69,9 @@ struct EpiQKV {
   PagedKV kv;
   T *q_out;  // [T, n_q_heads*64]
   RowScale rs;
+  // Factor of the query rows: in bf16 the softmax scale in base 2, so that the matrix-core attention's scores are exponents
+  // as they come out of the products (bf16 rounds either way alike); the plain kernel follows suit.
+  static constexpr float kQScale = std::is_same<T, float>::value ? 1.0f : kSoftmaxScale;
 
   // One (row, column pair) at a time, given the row's rotary pair cs = rope_cs[m][n & 31] and cache destination
   // kvd = row_kv[m].
@@ -82,8 +85,8 @@ struct EpiQKV {
     }
     if (head < n_q_heads) {
       T *dst = q_out + static_cast<size_t>(m) * (n_q_heads * kHd) + head * kHd + dim;
-      dst[0] = from_f32<T>(lo);
-      dst[32] = from_f32<T>(hi);
+      dst[0] = from_f32<T>(lo * kQScale);
+      dst[32] = from_f32<T>(hi * kQScale);
       return;
     }
     if (kvd < 0) return;
@@ -120,6 +123,8 @@ struct EpiQKV {
       }
     }
     if (head < n_q_heads) {
+#pragma unroll
+      for (int e = 0; e < 8; ++e) lo[e] *= kQScale, hi[e] *= kQScale;
       T *dst = q_out + static_cast<size_t>(m) * (n_q_heads * kHd) + head * kHd + dim;
       store_row(dst, lo);
       store_row(dst + 32, hi);

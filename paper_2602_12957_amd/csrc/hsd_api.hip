@@ -497,22 +497,14 @@ constexpr size_t kLdsExclusive = 84 * 1024;
 template <int G4, int QS, bool TREE, bool SPLIT>
 int launch_attn_mfma(hipStream_t st, dim3 grid, int n_cu, int n_q_heads, const AttnTile *tiles, const PagedKV &kv,
                      const bf16 *q, bf16 *o, const int32_t *row_end, const AttnSplit &sp) {
-  constexpr size_t smem = attn_smem_bytes(QS);
   auto kern = k_attn_mfma<G4, QS, TREE, SPLIT>;
   // set once per instantiation (initialisation of a function-local static is thread safe)
-  static const hipError_t attr_rc =
-      hipFuncSetAttribute(reinterpret_cast<const void *>(kern), hipFuncAttributeMaxDynamicSharedMemorySize,
-                          smem > kLdsExclusive ? smem : kLdsExclusive);
+  static const hipError_t attr_rc = hipFuncSetAttribute(reinterpret_cast<const void *>(kern),
+                                                        hipFuncAttributeMaxDynamicSharedMemorySize, kLdsExclusive);
   if (attr_rc != hipSuccess) return HSD_EHIP;
-  // Two workgroups fit a compute unit, and the dispatcher does pair them up while other units are still empty:
-  // with about one workgroup per unit (measured on the 16-region workload: 30 of 256 units held two, 30 none) the
-  // paired ones run 1.7 times as long and set the launch's duration (31 us against 22 us).  A launch with no more
-  // workgroups than the chip has units therefore asks for more LDS than half a unit has, which spreads it one
-  // workgroup per unit.  (With a few more workgroups than units pairing is the better deal: a second round would
-  // cost more.)  Scheduling only: no result depends on it.
   const size_t n_wg = static_cast<size_t>(grid.x) * grid.y * grid.z;
-  const size_t lds = (n_cu > 0 && n_wg <= static_cast<size_t>(n_cu) && smem < kLdsExclusive) ? kLdsExclusive : smem;
-  hipLaunchKernelGGL(kern, grid, dim3(128 * QS), lds, st, n_q_heads, tiles, kv, q, o, row_end, sp);
+  const size_t lds = (n_cu > 0 && n_wg <= static_cast<size_t>(n_cu)) ? kLdsExclusive : kAttnLdsBytes;
+  hipLaunchKernelGGL(kern, grid, dim3(64 * QS), lds, st, n_q_heads, tiles, kv, q, o, row_end, sp);
   HSD_LAUNCH_CHECK();
   return HSD_OK;
 }

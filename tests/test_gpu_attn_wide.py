@@ -104,3 +104,48 @@ def test_uneven_batches_match_their_members(name):
         at += rows[i]
     assert int(eng.status.item()) == 0
     eng.close()
+
+
+# Scores far from 0: a reference point other than 0 is set at a parity's first group (beyond +-32 binary orders of magnitude) and
+# moves where a later score lies 64 above it.  Queries and keys are `factor` times the usual, so that the scores' standard
+# deviation is 0.6 factor^2 binary orders.
+@pytest.mark.parametrize("tree", [False, True])
+@pytest.mark.parametrize("factor", [4, 8, 16])
+def test_extreme_scores(factor, tree):
+    """Both kernels alike bit for bit, and near the plain kernels, which take a running maximum.  One layer, so that the two paths
+    store the same queries and keys but for roundings to bf16 that fall the other way: one in a term of a score moves it by
+    2^-8 of the term, at the largest factor (terms of standard deviation 2.3, the largest of 64 about 8) by 0.03, a
+    probability by 2 %, an attention output by less than 2 % of a value; the bar is the one of all shallow bf16 models, 2e-2 of
+    a logit.  (A second layer's scores would carry the roundings of all its inputs: 2.1e-2 at factor 16.)"""
+    desc = W.tiny_model(1, 128, 16, 4, 64, 128, 256, "bf16")
+    weights = W.make_weights(desc, 47)
+    qk = (desc.n_q_heads + desc.n_kv_heads) * 64
+    for layer in weights["layers"]:
+        layer["wqkv"] = np.concatenate([layer["wqkv"][:qk] * np.float32(factor), layer["wqkv"][qk:]]).astype(layer["wqkv"].dtype)
+    rng = np.random.default_rng(factor)
+    n_cu = torch.cuda.get_device_properties(0).multi_processor_count
+    shapes = [(0, 1), (40, 3), (63, 70), (300, 1), (700, 33), (1300, 5), (0, 32 * (3 * n_cu // 16 + 1))]
+    n, rows = len(shapes), sum(r for _, r in shapes[:-1])
+    blocks, trees = [], []
+    for i, (_, r) in enumerate(shapes):
+        if tree and i < n - 1:
+            tok, end, dep = _tree(rng, r)
+        else:
+            tok, end, dep = rng.integers(0, 256, size=r).astype(np.int32), np.full(r, r, np.int32), np.arange(r, dtype=np.int32)
+        blocks.append(tok)
+        trees.append((end, dep))
+    prefix = {i: rng.integers(0, 256, size=s).astype(np.int32) for i, (s, _) in enumerate(shapes) if s}
+
+    def score(members, debug=None):
+        eng = Engine(desc, weights, sum((s + r) // 16 + 2 for s, r in shapes), n, max((s + r) // 16 + 2 for s, r in shapes),
+                     sum(r for _, r in shapes), rows, debug=debug)
+        eng.prefill(list(prefix), list(prefix.values()))
+        out = eng.verify(members, [blocks[i] for i in members], "region", dump_rows=np.arange(rows),
+                         trees=[trees[i] for i in members] if tree else None).logits.cpu().numpy().copy()
+        assert int(eng.status.item()) == 0
+        eng.close()
+        return out
+
+    general, wide, plain = score(range(n)), score(range(n - 1)), score(range(n - 1), {"force_simple": 1})
+    np.testing.assert_array_equal(general, wide)
+    assert np.abs(wide - plain).max() <= 2e-2
