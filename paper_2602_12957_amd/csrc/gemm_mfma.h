@@ -63,6 +63,39 @@ __device__ __forceinline__ void gemm_tile_of(int pid, int M, int w_rows, int til
   else xcd_tile(pid, tiles_act, tiles_act * tiles_w, ta, tw);
 }
 
+// Bands.  With one to two thousand rows a one-round launch has about as many activation tiles as weight tiles, and a run of
+// the plain order gives each XCD every activation tile: eight times the activations from the memory-side cache, which bounds such
+// launches (the units ask L2 for 12 to 14 TB/s, a third of it missed).  So the tiles are cut into 2 or 4 bands of activation
+// tiles by 4 or 2 bands of weight tiles, a rectangle to each XCD (workgroup i runs on XCD i % 8).  band = log2 of the activation
+// bands; rectangles of uneven cuts leave workgroups without a tile (false).
+__device__ __forceinline__ bool band_tile(int pid, int tiles_act, int tiles_w, int band, int &ta, int &tw) {
+  const int x = pid & 7, j = pid >> 3, xa = x & ((1 << band) - 1), xw = x >> band, wlog = 3 - band;
+  const int a0 = (tiles_act * xa) >> band, na = ((tiles_act * (xa + 1)) >> band) - a0;
+  const int w0 = (tiles_w * xw) >> wlog, nw = ((tiles_w * (xw + 1)) >> wlog) - w0;
+  if (j >= na * nw) return false;
+  ta = a0 + j % na;
+  tw = w0 + j / na;
+  return true;
+}
+inline int band_grid(int tiles_act, int tiles_w, int band) {
+  const int a = 1 << band, w = 8 >> band;
+  return 8 * ((tiles_act + a - 1) / a) * ((tiles_w + w - 1) / w);
+}
+// The bands of a launch of tiles_act x tiles_w tiles of bp x bq rows, or -1: the plain order.  Bands where they still give at
+// most one workgroup per unit and an XCD reads less than 0.8 of what it reads in the plain order.  us, plain / bands (launches in
+// a row, d 1024): O at 1856 rows 13.2 / 9.7, 2304 15.1 / 12.0; down 1280 rows 21.3 / 19.7, 1856 25.1 / 23.8, 2304 30.9 / 29.1; QKV
+// 1856 14.0 / 13.1, 2304 14.8 / 13.8.  Below the line: O at 768 rows 6.7 / 6.7, QKV 1016 7.6 / 7.6, gate/up 168 8.5 / 9.5.
+inline int gemm_bands(int tiles_act, int tiles_w, int bp, int bq, int n_cu) {
+  int best = -1;
+  int64_t least = int64_t{8} * (int64_t{tiles_act} * bp + int64_t{(tiles_w + 7) / 8} * bq) / 10;
+  for (int band = 1; band <= 2; ++band) {
+    const int a = 1 << band, w = 8 >> band;
+    const int64_t reads = int64_t{(tiles_act + a - 1) / a} * bp + int64_t{(tiles_w + w - 1) / w} * bq;
+    if (tiles_act >= a && tiles_w >= w && band_grid(tiles_act, tiles_w, band) <= n_cu && reads < least) best = band, least = reads;
+  }
+  return best;
+}
+
 // Tile counts for (M, N) in a mode: activation tiles first, weight tiles second.
 template <typename Cfg, int MODE>
 __host__ __device__ inline void gemm_tiles(int M, int N, int &tiles_act, int &tiles_w) {

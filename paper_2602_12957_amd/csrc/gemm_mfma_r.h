@@ -51,10 +51,11 @@ struct GemmCfgR {
 
 // grid: ceil((M - m_base) / BP) * (N / kCols / (dual ? 1 : 2)) workgroups of Cfg::kThreads threads, Cfg::kSmemBytes +
 // kRowScaleBytes dynamic LDS; the tiles cover rows m_base .. M-1 (see k_gemm_mfma_d).  K a multiple of 32; N a multiple of 64; both matrices below 2 GiB (32-bit buffer offsets).
-// Every wave executes exactly ceil(K / SK) + 1 workgroup barriers.
+// band >= 0: band_grid workgroups in the order of band_tile.
+// Every wave executes exactly ceil(K / SK) + 1 workgroup barriers (none in a workgroup without a tile).
 // NT: the weight loads are non-temporal (weights_pass_by in hsd_api.hip says when).
 template <typename Cfg, int MODE, typename Epi, bool NT>
-__global__ void __launch_bounds__(Cfg::kThreads) k_gemm_mfma_r(int M, int N, int K, int m_base, const bf16 *__restrict__ A,
+__global__ void __launch_bounds__(Cfg::kThreads) k_gemm_mfma_r(int M, int N, int K, int m_base, int band, const bf16 *__restrict__ A,
                                                                const bf16 *__restrict__ W, Epi epi) {
   static_assert(MODE == kModeNormal || MODE == kModeDual, "normal or dual mode");
   constexpr int BP = Cfg::BP, CW = Cfg::CW, S = Cfg::kStages, RB = Cfg::kRowBytes, COLS = Cfg::kCols;
@@ -65,7 +66,9 @@ __global__ void __launch_bounds__(Cfg::kThreads) k_gemm_mfma_r(int M, int N, int
   const int tiles_act = (M - m_base + BP - 1) / BP;
   // (the grid is computed, not read: gridDim lies behind the kernel arguments in memory, a read on the way to the first load)
   int ta, tw;
-  xcd_tile(blockIdx.x, tiles_act, tiles_act * (N / (MODE == kModeDual ? COLS : 2 * COLS)), ta, tw);
+  const int tiles_w = N / (MODE == kModeDual ? COLS : 2 * COLS);
+  if (band < 0) xcd_tile(blockIdx.x, tiles_act, tiles_act * tiles_w, ta, tw);
+  else if (!band_tile(blockIdx.x, tiles_act, tiles_w, band, ta, tw)) return;   // the whole workgroup
   const int m0 = m_base + ta * BP;
   constexpr int GR = 4 / CW;                           // tiles of a 64-column group
   const int n0 = (MODE == kModeDual) ? tw * COLS : tw / GR * 64 + tw % GR * COLS;

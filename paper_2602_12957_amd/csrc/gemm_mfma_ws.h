@@ -23,9 +23,9 @@ using GemmCfgWS = GemmCfg<128, 128, 64, 2, 2>;
 using GemmCfgWS64 = GemmCfg<64, 128, 64, 2, 2>;
 
 // Cfg: a configuration with four (multiplying) waves.
-// grid: 1-D, tiles_act * tiles_w workgroups of 512 threads, Cfg::kSmemBytes + kRowScaleBytes dynamic LDS.
+// grid: 1-D, tiles_act * tiles_w workgroups (band >= 0: band_grid, in the order of band_tile) of 512 threads, Cfg::kSmemBytes + kRowScaleBytes dynamic LDS.
 template <typename Cfg, int MODE, typename Epi>
-__global__ void __launch_bounds__(512) k_gemm_mfma_ws(int M, int N, int K, const bf16 *__restrict__ A,
+__global__ void __launch_bounds__(512) k_gemm_mfma_ws(int M, int N, int K, int band, const bf16 *__restrict__ A,
                                                       const bf16 *__restrict__ W, Epi epi) {
   static_assert(Cfg::kThreads == 256 && Cfg::BK == 64, "four multiplying waves, 64-wide K slices");
   static_assert(MODE == kModeNormal || MODE == kModeDual, "normal or dual mode");
@@ -38,7 +38,8 @@ __global__ void __launch_bounds__(512) k_gemm_mfma_ws(int M, int N, int K, const
   const bool mover = wave >= 4;
   int tiles_act, tiles_w, ta, tw;
   gemm_tiles<Cfg, MODE>(M, N, tiles_act, tiles_w);
-  gemm_tile_of(blockIdx.x, M, (MODE == kModeDual) ? 2 * N : N, tiles_act, tiles_w, ta, tw);
+  if (band < 0) gemm_tile_of(blockIdx.x, M, (MODE == kModeDual) ? 2 * N : N, tiles_act, tiles_w, ta, tw);
+  else if (!band_tile(blockIdx.x, tiles_act, tiles_w, band, ta, tw)) return;   // the whole workgroup
   const int m0 = ta * BP, n0 = tw * ((MODE == kModeDual) ? BQ / 2 : BQ);
   const int nk = K / BK;
 

@@ -202,7 +202,7 @@ int launch_gemm_mfma8(hipStream_t st, int M, int N, int K, const void *A, const 
 }
 
 template <typename Cfg, typename Epi>
-int launch_gemm_mfma_ws(hipStream_t st, int M, int N, int K, const void *A, const void *W, Epi epi) {
+int launch_gemm_mfma_ws(hipStream_t st, int M, int N, int K, const void *A, const void *W, Epi epi, int n_cu) {
   constexpr int MODE = GemmModeOf<Epi>::value;
   auto kern = k_gemm_mfma_ws<Cfg, MODE, Epi>;
   constexpr int smem = Cfg::kSmemBytes + kRowScaleBytes;
@@ -211,7 +211,8 @@ int launch_gemm_mfma_ws(hipStream_t st, int M, int N, int K, const void *A, cons
   if (attr_rc != hipSuccess) return HSD_EHIP;
   int tiles_act, tiles_w;
   gemm_tiles<Cfg, MODE>(M, N, tiles_act, tiles_w);
-  hipLaunchKernelGGL(kern, dim3(tiles_act * tiles_w), dim3(512), smem, st, M, N, K, static_cast<const bf16 *>(A),
+  const int band = gemm_bands(tiles_act, tiles_w, Cfg::BP, Cfg::BQ, n_cu);
+  hipLaunchKernelGGL(kern, dim3(band < 0 ? tiles_act * tiles_w : band_grid(tiles_act, tiles_w, band)), dim3(512), smem, st, M, N, K, band, static_cast<const bf16 *>(A),
                      static_cast<const bf16 *>(W), epi);
   HSD_LAUNCH_CHECK();
   return HSD_OK;
@@ -237,8 +238,8 @@ int launch_gemm_mfma_d(hipStream_t st, int M, int N, int K, const void *A, const
 // more rows have no such form: one row tile of 128 x 64 always precedes them)
 constexpr int kPassByRows = 128;
 template <typename Cfg, typename Epi>
-int launch_gemm_mfma_r(hipStream_t st, int M, int N, int K, const void *A, const void *W, Epi epi, int m_base = 0,
-                       bool pass_by = false) {
+int launch_gemm_mfma_r(hipStream_t st, int M, int N, int K, const void *A, const void *W, Epi epi, int n_cu,
+                       int m_base = 0, bool pass_by = false) {
   constexpr int MODE = GemmModeOf<Epi>::value;
   constexpr int smem = Cfg::kSmemBytes + kRowScaleBytes;
   auto kern = k_gemm_mfma_r<Cfg, MODE, Epi, false>;
@@ -252,8 +253,10 @@ int launch_gemm_mfma_r(hipStream_t st, int M, int N, int K, const void *A, const
     if (attr_nt != hipSuccess) return HSD_EHIP;
     if (pass_by) kern = kern_nt;
   }
-  const int tiles = (M - m_base + Cfg::BP - 1) / Cfg::BP * (N / Cfg::kCols / (MODE == kModeDual ? 1 : 2));
-  hipLaunchKernelGGL(kern, dim3(tiles), dim3(Cfg::kThreads), smem, st, M, N, K, m_base, static_cast<const bf16 *>(A),
+  const int tiles_act = (M - m_base + Cfg::BP - 1) / Cfg::BP, tiles_w = N / Cfg::kCols / (MODE == kModeDual ? 1 : 2);
+  const int band = gemm_bands(tiles_act, tiles_w, Cfg::BP, Cfg::BQ, n_cu);
+  hipLaunchKernelGGL(kern, dim3(band < 0 ? tiles_act * tiles_w : band_grid(tiles_act, tiles_w, band)), dim3(Cfg::kThreads), smem, st, M, N, K,
+                     m_base, band, static_cast<const bf16 *>(A),
                      static_cast<const bf16 *>(W), epi);
   HSD_LAUNCH_CHECK();
   return HSD_OK;
@@ -403,9 +406,9 @@ int launch_gemm(const hsd_ctx *ctx, hipStream_t st, int site, int M, int N, int 
             // the tile that reads least among those that stay within one workgroup per compute unit, as in
             // effective_gemm_cfg, from 64 weight rows on: the main launch and every reader work with one sum per piece
             const int64_t cols64 = w_cols / 64;
-            if (((rem + 31) / 32) * cols64 <= cu) return launch_gemm_mfma_r<GemmCfgR24>(st, M, N, K, A, W, epi, m_main);
-            if (((rem + 63) / 64) * cols64 <= cu) return launch_gemm_mfma_r<GemmCfgR44>(st, M, N, K, A, W, epi, m_main);
-            if (((rem + 127) / 128) * cols64 <= cu) return launch_gemm_mfma_r<GemmCfgR84>(st, M, N, K, A, W, epi, m_main);
+            if (((rem + 31) / 32) * cols64 <= cu) return launch_gemm_mfma_r<GemmCfgR24>(st, M, N, K, A, W, epi, ctx->n_cu, m_main);
+            if (((rem + 63) / 64) * cols64 <= cu) return launch_gemm_mfma_r<GemmCfgR44>(st, M, N, K, A, W, epi, ctx->n_cu, m_main);
+            if (((rem + 127) / 128) * cols64 <= cu) return launch_gemm_mfma_r<GemmCfgR84>(st, M, N, K, A, W, epi, ctx->n_cu, m_main);
             return launch_gemm_mfma_d<GemmCfgD64>(st, M, N, K, A, W, epi, m_main);
           }
         }
@@ -421,11 +424,11 @@ int launch_gemm(const hsd_ctx *ctx, hipStream_t st, int site, int M, int N, int 
       case 6: return launch_gemm_mfma<GemmCfg6>(st, M, N, K, A, W, epi);
       case 7:
         if constexpr (GemmModeOf<Epi>::value != kModeSwapLM)
-          return launch_gemm_mfma_ws<GemmCfgWS>(st, M, N, K, A, W, epi);
+          return launch_gemm_mfma_ws<GemmCfgWS>(st, M, N, K, A, W, epi, ctx->n_cu);
         break;
       case 9:
         if constexpr (GemmModeOf<Epi>::value != kModeSwapLM)
-          return launch_gemm_mfma_ws<GemmCfgWS64>(st, M, N, K, A, W, epi);
+          return launch_gemm_mfma_ws<GemmCfgWS64>(st, M, N, K, A, W, epi, ctx->n_cu);
         break;
       case 8: return launch_gemm_mfma8(st, M, N, K, A, W, epi, ctx->n_cu);
       case 10:
@@ -439,7 +442,7 @@ int launch_gemm(const hsd_ctx *ctx, hipStream_t st, int site, int M, int N, int 
 #define HSD_CASE_R(c, cfg_t, ok)                                                                       \
   case c:                                                                                            \
     if constexpr (GemmModeOf<Epi>::value != kModeSwapLM && (ok))                                     \
-      return launch_gemm_mfma_r<cfg_t>(st, M, N, K, A, W, epi, 0, pass_by);                          \
+      return launch_gemm_mfma_r<cfg_t>(st, M, N, K, A, W, epi, ctx->n_cu, 0, pass_by);                          \
     break;
       // 14 to 17: the residual projections have epilogues of their own there (see residual_proj); 16 weight rows are not
       // enough for dual mode
@@ -707,10 +710,10 @@ int forward(hsd_ctx *ctx, hipStream_t st, const hsd_kv_pool *pool, const hsd_bat
           const EpiResidualQuarter e4{ws.x, d.d_model, next_gain, static_cast<bf16 *>(ws.h), ws.ss, ss2, plane};
           const EpiResidualNorm en{ws.x, d.d_model, next_gain, static_cast<bf16 *>(ws.h), ws.ss, nullptr, 0};
           switch (cfg) {   // narrow tiles
-            case 14: return launch_gemm_mfma_r<GemmCfgR11>(st, Tq, d.d_model, K, A, W, e4, 0, pass_by);
-            case 15: return launch_gemm_mfma_r<GemmCfgR21>(st, Tq, d.d_model, K, A, W, e4, 0, pass_by);
-            case 16: return launch_gemm_mfma_r<GemmCfgR22>(st, Tq, d.d_model, K, A, W, eh, 0, pass_by);
-            case 17: return launch_gemm_mfma_r<GemmCfgR42>(st, Tq, d.d_model, K, A, W, eh, 0, pass_by);
+            case 14: return launch_gemm_mfma_r<GemmCfgR11>(st, Tq, d.d_model, K, A, W, e4, ctx->n_cu, 0, pass_by);
+            case 15: return launch_gemm_mfma_r<GemmCfgR21>(st, Tq, d.d_model, K, A, W, e4, ctx->n_cu, 0, pass_by);
+            case 16: return launch_gemm_mfma_r<GemmCfgR22>(st, Tq, d.d_model, K, A, W, eh, ctx->n_cu, 0, pass_by);
+            case 17: return launch_gemm_mfma_r<GemmCfgR42>(st, Tq, d.d_model, K, A, W, eh, ctx->n_cu, 0, pass_by);
           }
           return launch_gemm<T>(ctx, st, site, Tq, d.d_model, K, A, W, en, pass_by);
         }
