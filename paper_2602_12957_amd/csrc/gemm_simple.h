@@ -1,5 +1,5 @@
 // Plain LDS-tiled GEMM with fp32 FMA accumulation: C[m,n] = sum_k A[m,k] * W[n,k].
-// This is the fp32 debug path (model dtype fp32) and the cross-check for the bf16 MFMA kernel.
+// The cross-check for the bf16 MFMA kernels (the fp32 path has k_gemm_f32).
 // Tile 64x64x32 or 16x64x32, 256 threads; thread (ty, tx) owns TR rows from ty*TR and the column pair (tx, tx+32).
 #pragma once
 

@@ -24,6 +24,7 @@
 #include "gemm_mfma_d.h"
 #include "gemm_mfma_r.h"
 #include "probes.h"
+#include "gemm_f32.h"
 #include "gemm_simple.h"
 #include "misc_kernels.h"
 #include "pass_setup.h"
@@ -461,14 +462,29 @@ int launch_gemm(const hsd_ctx *ctx, hipStream_t st, int site, int M, int N, int 
   if constexpr (std::is_same<Epi, EpiResidualNorm>::value) {
     return HSD_EINVAL;   // this epilogue exists for the MFMA kernels only (the caller never gets here with it)
   } else {
-    // 16-row tiles while 64-row ones would not give every compute unit a workgroup: a workgroup's walk over K sets the
-    // launch's time then, and it is shorter with fewer rows, although each multiply-add takes more LDS reads.  Same bits
-    // either way.  16-row / 64-row tiles in us, by the number of 64-row tiles: 32 (down, d_model 256) 24 / 52; 240 to
-    // 252, just below the line, gate/up 24 / 29, QKV 18 / 23, down 50 / 56, QKV of d_model 1024 47 / 58; 256 to 384 gate/up
-    // 30 / 36 and 33 / 36, at d_model 1024 77 / 99 and 110 / 124; 512 gate/up 42 / 38, at d_model 1024 143 / 127, LM head
-    // 31 / 30; 1024 LM head 52 / 44.  They cross between 1.5 and 2 tiles per unit: the line is on the safe side of it.
+    // fp32: k_gemm_f32, by tiles of one 64-column group.  Half a group and 16 rows while whole ones fill at most half of the
+    // units, 16 rows up to one tile a unit, 32 up to two, 64 beyond.  us, the vector-unit kernel / this one: 132 rows of d_model
+    // 256: down 23.1 / 10.5 (whole groups 16.5), QKV 8.3 / 5.7 (7.4), O 7.2 / 5.0 (6.0), gate/up 11.3 / 8.6; 1024 rows: gate/up 27.7 /
+    // 18.6, down 25.3 / 17.5, QKV 13.5 / 16.6, LM head 43.7 / 47.9, the pass 423 / 405.  The other end: at 2064 rows gate/up 45.8 /
+    // 48.1, down 38.4 / 40.3, LM head 84 / 94, the pass 1235 / 1265 (one kernel for all row counts, since the order of a row's sums
+    // must not follow the batch).
+    // bf16 (cross-check only): 16-row tiles while 64-row ones would not give every compute unit a workgroup; same bits.
     const int64_t n64 = static_cast<int64_t>(N / 64) * ((M + 63) / 64);
-    if (n64 < (ctx->n_cu > 0 ? ctx->n_cu : 256)) {
+    const bool few = n64 < (ctx->n_cu > 0 ? ctx->n_cu : 256);
+    if constexpr (std::is_same<T, float>::value) {
+      const float *a = static_cast<const float *>(A), *w = static_cast<const float *>(W);
+      const int cu = ctx->n_cu > 0 ? ctx->n_cu : 256, t16 = N / 64 * ((M + 15) / 16), t32 = N / 64 * ((M + 31) / 32);
+      if constexpr (GemmModeOf<Epi>::value != kModeSwapLM) {
+        if (2 * t16 <= cu) {
+          hipLaunchKernelGGL((k_gemm_f32<Epi, 1, 2>), dim3(N / 32, (M + 15) / 16), dim3(128), 0, st, M, N, K, a, w, epi);
+          HSD_LAUNCH_CHECK();
+          return HSD_OK;
+        }
+      }
+      if (t16 <= cu) hipLaunchKernelGGL((k_gemm_f32<Epi, 1, 4>), dim3(N / 64, (M + 15) / 16), dim3(256), 0, st, M, N, K, a, w, epi);
+      else if (t32 <= 2 * cu) hipLaunchKernelGGL((k_gemm_f32<Epi, 2, 4>), dim3(N / 64, (M + 31) / 32), dim3(256), 0, st, M, N, K, a, w, epi);
+      else hipLaunchKernelGGL((k_gemm_f32<Epi, 4, 4>), dim3(N / 64, (M + 63) / 64), dim3(256), 0, st, M, N, K, a, w, epi);
+    } else if (few) {
       hipLaunchKernelGGL((k_gemm_simple<T, Epi, 2>), dim3(N / 64, (M + 15) / 16), dim3(256), 0, st, M, N, K,
                          static_cast<const T *>(A), static_cast<const T *>(W), epi);
     } else {
