@@ -22,8 +22,8 @@
 // pages are stored transposed and in exactly that token order ([dim][perm(token)], see kv_v_slot), hence the
 // A operand of the second product is one 16-byte LDS read per lane and no transpose is ever done here.
 //
-// What bounds it, and why a wave holds both parities.  A group of 64 keys is 16 matrix instructions (32 cycles each) and 32
-// exponentials, 16 conversions and 32 additions per lane.  The matrix pipe and the vector unit run side by side only if
+// What bounds it, and why a wave holds both parities.  A group of 64 keys is 16 matrix instructions (32 cycles each), eight
+// small ones (8 cycles) for the row sums, and 32 exponentials and 16 conversions per lane.  The matrix pipe and the vector unit run side by side only if
 // independent work of both kinds is in the instruction stream: microbenchmark, one wave per SIMD, ns per group: products
 // alone 225, vector part alone 190, both interleaved 230 to 260.  With one parity to a wave, four waves per SIMD in step behind a
 // barrier a stage, each waited for its own chain of reads, products, maximum, exponentials and products: 577 ns a group (four pages
@@ -272,11 +272,24 @@ __device__ __forceinline__ float attn_reference(float m, float mx) {
   return mx - m >= kAttnMoveAt ? ceilf(mx) : m;
 }
 
-// Row sums are fp32 sums of the probabilities before they are rounded for the second product: of the 16 keys of a page that a
-// lane half holds (8) as a tree, the group's four pages as a tree, the groups one after the other.  (Adding the rounded pairs
-// with v_dot2_f32_bf16 is half the instructions, but it runs on the matrix pipe: 16 products and the exponentials of a group
-// take 260 ns together, 500 with the 16 dot products among them.)
-__device__ __forceinline__ float attn_page_sum(const floatx8 &p) { return ((p[0] + p[1]) + (p[2] + p[3])) + ((p[4] + p[5]) + (p[6] + p[7])); }
+// Row sums are fp32 sums of the probabilities as the second product sees them, ROUNDED to bf16: the rounding then cancels in
+// the quotient, and a row whose probability lies on one key gets that key's value to the last bit.  (Sums of the unrounded
+// values hold more bits, but the quotient loses: a row with one key is off by up to 2^-8.)  They are taken by
+// v_mfma_f32_4x4x4_16b_bf16 with ones as A: every lane is a column of its own, so four of its probabilities are added to its
+// accumulator and no row sees another's infinities or NaN.  Order: a lane half's eight keys of a page, the group's pages 0 and
+// 2 in one chain, 1 and 3 in another, their sum, then the groups one after the other.
+// ns a group beside the 16 products and the exponentials, one / two waves a SIMD (microbenchmark): no sums 306 / 236; 32 fp32
+// additions of the unrounded values 358 / 282; these 331 / 299; the rounded values unpacked and added 461 / 336; 16
+// v_dot2_f32_bf16 about 500.
+__device__ __forceinline__ floatx4 attn_add_4(uint2 p, floatx4 sum) {
+  typedef short short4v __attribute__((ext_vector_type(4)));
+  const short4v ones = {0x3f80, 0x3f80, 0x3f80, 0x3f80};
+  return __builtin_amdgcn_mfma_f32_4x4x4bf16_1k(ones, __builtin_bit_cast(short4v, p), sum, 0, 0, 0);
+}
+__device__ __forceinline__ floatx4 attn_add_page(const bf16x8 &p, floatx4 sum) {
+  const uint4 w = __builtin_bit_cast(uint4, p);
+  return attn_add_4(make_uint2(w.z, w.w), attn_add_4(make_uint2(w.x, w.y), sum));
+}
 
 typedef __attribute__((address_space(3))) unsigned char *AttnLds;
 // s_waitcnt vmcnt(N) with the other counters left alone (N < 64), also for the compiler's eyes: no LDS access moves across it
@@ -532,16 +545,16 @@ __global__ void __launch_bounds__(64 * QS, 2) k_attn_mfma(int n_q_heads, const A
       h.at_zero = __all(h.m == 0.f);
     }
     const float msub = h.m == -INFINITY ? 0.f : h.m;   // no visible key yet: p = 0 without producing inf - inf
-    float ps[4];
+    floatx4 ps[2] = {};
 #pragma unroll
     for (int pg = 0; pg < 4; ++pg) {
       floatx8 pv;
 #pragma unroll
       for (int e = 0; e < 8; ++e) pv[e] = __builtin_amdgcn_exp2f(h.st[pg >> 1][8 * (pg & 1) + e] - msub);
       h.pf[pg] = __builtin_convertvector(pv, bf16x8);
-      ps[pg] = attn_page_sum(pv);
+      ps[pg & 1] = attn_add_page(h.pf[pg], ps[pg & 1]);
     }
-    h.l += (ps[0] + ps[1]) + (ps[2] + ps[3]);
+    h.l += ps[0][0] + ps[1][0];
   };
   // A turn: the products of half x -- V^T P^T of one group, K Q^T of the next but one -- beside the
   // exponentials of half y, whose scores are there and whose reference points are taken for 0.  Returns whether y's
@@ -566,14 +579,10 @@ __global__ void __launch_bounds__(64 * QS, 2) k_attn_mfma(int n_q_heads, const A
     bf16x8 fr[16];
     float e0[16], e1[16];
     bf16x2 pw[16];
-    float sum[16];   // by pairs, then a page's in its last, then all in the last
+    floatx4 ps[2] = {};
     auto pack = [&](int j) { pw[j] = __builtin_convertvector((floatx2){e0[j], e1[j]}, bf16x2); };
-    auto add = [&](int j) {   // attn_page_sum, and the pages' tree
-      sum[j] = e0[j] + e1[j];
-      if (j & 1) sum[j] = sum[j - 1] + sum[j];
-      if ((j & 3) == 3) sum[j] = sum[j - 2] + sum[j];
-      if ((j & 7) == 7) sum[j] = sum[j - 4] + sum[j];
-      if (j == 15) sum[j] = sum[j - 8] + sum[j];
+    auto add = [&](int i) {   // words 2 i and 2 i + 1: half of page i / 2
+      ps[(i >> 1) & 1] = attn_add_4(make_uint2(__builtin_bit_cast(uint32_t, pw[2 * i]), __builtin_bit_cast(uint32_t, pw[2 * i + 1])), ps[(i >> 1) & 1]);
     };
 #pragma unroll
     for (int j = 0; j < kAhead; ++j) fr[j] = j < 4 ? pre[j] : read(j);
@@ -594,15 +603,16 @@ __global__ void __launch_bounds__(64 * QS, 2) k_attn_mfma(int n_q_heads, const A
       e1[j] = __builtin_amdgcn_exp2f(y.st[j >> 3][2 * (j & 7) + 1]);
       asm volatile("" : "+v"(e0[j]), "+v"(e1[j]));   // computed here: pure instructions are moved across scheduling barriers
       if (j >= 1) {
-        pack(j - 1), add(j - 1);
-        asm volatile("" : "+v"(sum[j - 1]), "+v"(pw[j - 1]));
+        pack(j - 1);
+        asm volatile("" : "+v"(pw[j - 1]));
       }
+      if (j >= 3 && (j & 1)) add((j - 3) >> 1);
       __builtin_amdgcn_sched_barrier(0);
     }
     if (vn != nullptr) read_pre(vn);
     pack(15);
-    add(15);
-    l = y.l + sum[15];
+    add(7);
+    l = y.l + (ps[0][0] + ps[1][0]);
 #pragma unroll
     for (int pg = 0; pg < 4; ++pg)
       y.pf[pg] = __builtin_shufflevector(__builtin_shufflevector(pw[4 * pg], pw[4 * pg + 1], 0, 1, 2, 3),

@@ -232,7 +232,7 @@ __global__ void __launch_bounds__(64 * (kAttnWideScorers + 4), 4) k_attn_wide(in
     // the group's probabilities and the reference points they are relative to; returns the lane's row sum
     auto probs = [&](int s) {
       const float msub = m_run == -INFINITY ? 0.f : m_run;
-      float ps[QW / 8];
+      floatx4 ps[2] = {};   // QW = 16: a lane holds even pages or odd ones, in ps[0]
 #pragma unroll
       for (int f = 0; f < QW / 8; ++f) {   // operand f: page f of the group, or pages 2 f and 2 f + 1
         floatx8 pv;
@@ -244,11 +244,9 @@ __global__ void __launch_bounds__(64 * (kAttnWideScorers + 4), 4) k_attn_wide(in
         Frag8 pf;
         pf.v = __builtin_convertvector(pv, bf16x8);
         sm.p[s & 1][w][f][lane] = pf.u;
-        ps[f] = attn_page_sum(pv);
-        // QW = 16: this lane's page and the other half's
-        if constexpr (QW == 16) ps[f] = half_sum(ps[f]);
+        ps[QW == 32 ? f & 1 : 0] = attn_add_page(pf.v, ps[QW == 32 ? f & 1 : 0]);
       }
-      const float sum = QW == 32 ? (ps[0] + ps[1]) + (ps[2] + ps[3]) : ps[0] + ps[1];
+      const float sum = QW == 32 ? ps[0][0] + ps[1][0] : half_sum(ps[0][0]);
       sm.sum[s & 1][w][lane] = sum;
       if (kg == 0) sm.mg[s & 1][w][qj] = m_run;
       return sum;

@@ -149,3 +149,52 @@ def test_extreme_scores(factor, tree):
     general, wide, plain = score(range(n)), score(range(n - 1)), score(range(n - 1), {"force_simple": 1})
     np.testing.assert_array_equal(general, wide)
     assert np.abs(wide - plain).max() <= 2e-2
+
+
+# A row that sees one key gets that key's value, to the last bit: the probability, whatever its rounding to bf16, cancels in the
+# quotient.  mode, sequences, rows of a further sequence, key chunk: 16 and 32 columns of k_attn_wide, k_attn_mfma with 4 and 8
+# query sets and with a key split.
+ONE_KEY = {"wide_16": ("region", 8, 0, 0), "wide_32": ("region", 8, 9, 0), "general": ("region", 0, 0, 0), "general_page": ("page", 0, 0, 0),
+           "split": ("page", 8, 9, 128)}
+
+
+@pytest.mark.parametrize("name", ONE_KEY)
+@pytest.mark.parametrize("n_q, n_kv", [(16, 4), (16, 8), (16, 16)])
+def test_one_key_gives_its_value(n_q, n_kv, name):
+    """One layer in which every number but the probability is exact.  Embeddings are +-V with V the largest mantissa (an error of
+    2^-9 is a whole unit of it), so that norms make them +-1; the values are the embeddings again; the output projection takes the
+    attention's output off the residual: what is left is 0, and so are the logits (one-hot rows of the LM head), in every
+    column whose value came back whole.  The last head's columns stay, to keep the last norm finite.  Scores: q = a number per
+    head, k = a random sum of signs, so that the probabilities' mantissas are spread."""
+    mode, n, more, chunk = ONE_KEY[name]
+    n_cu = torch.cuda.get_device_properties(0).multi_processor_count
+    if n == 0:
+        n = 9 * n_cu // (4 * n_kv) + 1                  # more than 2.25 query sets per compute unit: the general kernel
+    d, group, big = n_q * 64, n_q // n_kv, 255 / 128
+    desc = W.ModelDesc(1, d, n_q, n_kv, 64, 128, 1024, "bf16")
+    rng = np.random.default_rng(n_q + n_kv)
+    sign = rng.choice([-1.0, 1.0], (desc.vocab, n_kv, 64)).astype(np.float32)
+    wqkv = np.zeros(((n_q + 2 * n_kv) * 64, d), np.float32)
+    at = lambda h, i: h * 64 + i
+    for h in range(n_q):
+        wqkv[at(h, 0), at(group * (h // group), 0)] = rng.uniform(2, 20)          # q . k = q_0 k_0
+    for g in range(n_kv):
+        wqkv[at(n_q + g, 0), [at(group * g, i) for i in range(64)]] = rng.normal(0, 0.25, 64)
+        for i in range(64):
+            wqkv[at(n_q + n_kv + g, i), at(group * g, i)] = big
+    wo = -np.eye(d, dtype=np.float32)
+    wo[d - 64:] = 0
+    ones = np.ones(d, np.float32)
+    weights = dict(tok_embed=big * np.repeat(sign, group, axis=1).reshape(desc.vocab, d), lm_head=np.eye(desc.vocab, d, dtype=np.float32),
+                   final_norm=ones, layers=[dict(attn_norm=ones, wqkv=wqkv, wo=wo, ffn_norm=ones,
+                                                 w_gate_up=np.zeros((256, d), np.float32), w_down=np.zeros((d, 128), np.float32))])
+    blocks = [rng.integers(0, desc.vocab, 1).astype(np.int32) for _ in range(n)]
+    if more:
+        blocks.append(rng.integers(0, desc.vocab, more).astype(np.int32))
+    first = np.cumsum([0] + [len(b) for b in blocks[:-1]]).astype(np.int32)
+    eng = Engine(desc, weights, len(blocks) + 1, len(blocks), 1, n + more, len(blocks), attn_key_chunk=chunk)
+    logits = eng.verify(list(range(len(blocks))), blocks, mode, dump_rows=first).logits.cpu().numpy().copy()
+    assert int(eng.status.item()) == 0
+    eng.close()
+    assert np.isfinite(logits).all() and (np.abs(logits[:, d - 64:]) > 0.5).all()
+    np.testing.assert_array_equal(logits[:, :d - 64], 0)
