@@ -29,7 +29,8 @@
 // barrier a stage, each waited for its own chain of reads, products, maximum, exponentials and products: 577 ns a group (four pages
 // of 8193 rows: 1907 us a layer).  Here, in every turn, the exponentials of one parity run beside the products of the other, in
 // an order fixed by hand; what the exponentials need beside (maximum, subtraction, rescaling) is taken out of the common case
-// (attn_reference), and the keys and values are requested by LDS-direct loads, so that staging takes no registers and no store
+// (attn_reference; a pass over those pages takes 65 ms, and 72 with queries and keys scaled by 8, where most points are not 0:
+// 105 when such groups had to subtract and went through the general rule), and the keys and values are requested by LDS-direct loads, so that staging takes no registers and no store
 // instructions.  On the way (us a layer at that size): no running maximum 1757; both parities in a wave 1779; row sums
 // off the matrix pipe (attn_page_sum) and the order pinned 1594.  16 regions of 17 to 257 rows on 1055 keys: 29.7 -> 26.2.
 // What is left there: 10 % of the launch is its last tasks; a third of a wave's time are waits for LDS reads and at barriers.
@@ -254,16 +255,19 @@ union Frag8 {
 
 // Softmax.  q comes scaled by log2(e) / sqrt(64) (EpiQKV::kQScale), so a score is an exponent of two and a probability is
 // exp2(score - m) with a reference point m of the query.  m needs to keep sums and probabilities in range, no more: fp32 and
-// bf16 are as precise at 2^40 as at 1.  It is an INTEGER, so that every correction factor is an exact power of two, and 0
-// unless the scores ask for another: it is set at the first group of 64 keys that holds a visible one, to 0 where that
-// group's largest score lies within +-kAttnZeroRange and to the score rounded up otherwise, and moves (to a group's largest
-// score rounded up) only at a group with a score kAttnMoveAt above it.  Largest probability of the first group: 2^-33 at
-// least, 2^32 at most; of any: 2^64.  So the common group needs no maximum, no subtraction and no rescaling, and its test is
-// one comparison: a probability of 2^64 or more makes the row sum as large.
-// Each kernel applies the rule group by group, in ascending order within a parity: a row's numbers do not depend on the
+// bf16 are as precise at 2^60 as at 1.  It is an INTEGER, so that every correction factor is an exact power of two.  It is set
+// at the first group of 64 keys that holds a visible one, to 0 where that group's largest score lies within +-kAttnZeroRange and
+// to the score rounded up otherwise, and moves (to a group's largest score rounded up) only at a group with a score kAttnMoveAt
+// above it.  Largest probability of the first group: 2^-65 at least, 2^64 at most, so what falls below the smallest number is less
+// than 2^-61 of the row; of any: 2^96, which leaves 2^31 for the values and the number of keys.  The subtraction is free: the
+// products start from -m instead of 0.  So a group at which no point is set or moved needs no maximum and no rescaling, whatever
+// the scores, and its test is one comparison: a probability of 2^96 or more makes the group's sum as large.
+// Each kernel applies the rule group by group, in ascending order over both parities: a row's numbers do not depend on the
 // kernel.
-constexpr float kAttnZeroRange = 32.f, kAttnMoveAt = 64.f;
-constexpr float kAttnSumLimit = 0x1p63f;   // below 2^kAttnMoveAt by more than the exponential's error
+constexpr float kAttnZeroRange = 64.f, kAttnMoveAt = 96.f;
+// Below 2^kAttnMoveAt by more than the errors of the exponential and of a score, which rounds differently from -m and from 0: by
+// less than 0.1 up to kAttnShiftRange.  Queries with a point beyond that never skip the rule.
+constexpr float kAttnSumLimit = 0x1p95f, kAttnShiftRange = 0x1p16f;
 __device__ __forceinline__ float attn_reference(float m, float mx) {
   if (m == -INFINITY) {
     const float c = ceilf(mx);
@@ -375,10 +379,9 @@ __global__ void __launch_bounds__(64 * QS, 2) k_attn_mfma(int n_q_heads, const A
   // position such a page could stand for is masked (and its V zeroed) by the checked form of the loop, and the plain form
   // only sees pages of the cached prefix.
   const AttnLds lds = (AttnLds)smem_raw;
-  int vk[2], vv;   // byte offsets of a lane in a page: K rows 8 c + l / 8, V dims 32 c + l / 2 (+ 1024 c)
-#pragma unroll
-  for (int c = 0; c < 2; ++c) vk[c] = (8 * c + (lane >> 3)) * 128 + (((lane & 7) ^ ((4 * c + (lane >> 4)) & 7)) << 4);
-  vv = (lane >> 1) * 32 + (((lane & 1) ^ ((lane >> 4) & 1)) << 4);
+  // byte offsets of a lane in a page: K row l / 8, V dim l / 2 (in the second half row 8 + l / 8: 1024 on, position ^ 4; dim 32 + l / 2)
+  const int vk = (lane >> 3) * 128 + (((lane & 7) ^ (lane >> 4)) << 4);
+  const int vv = (lane >> 1) * 32 + (((lane & 1) ^ ((lane >> 4) & 1)) << 4);
   const int32_t *table_row = kv.block_table + static_cast<size_t>(slot) * kv.max_blocks_per_seq;
   const int last_entry = kv.max_blocks_per_seq - 1;
   // ids: lane NP j + i holds that of page wq + QS i of stage id0 + j
@@ -395,7 +398,7 @@ __global__ void __launch_bounds__(64 * QS, 2) k_attn_mfma(int n_q_heads, const A
     if (next_k - id0 == 64 / NP) fetch_ids(next_v);   // V is behind and still needs its own
 #pragma unroll
     for (int i = 0; i < NP; ++i)
-      attn_load_page(static_cast<const bf16 *>(kv.k_pool) + page(next_k, i), lds + k_put * kAttnHalfStage + (wq + QS * i) * 2048, vk[0], vk[1]);
+      attn_load_page(static_cast<const bf16 *>(kv.k_pool) + page(next_k, i), lds + k_put * kAttnHalfStage + (wq + QS * i) * 2048, vk, (vk ^ 64) + 1024);
     ++next_k;
     k_put = k_put + 1 == kAttnKStages ? 0 : k_put + 1;
   };
@@ -428,24 +431,25 @@ __global__ void __launch_bounds__(64 * QS, 2) k_attn_mfma(int n_q_heads, const A
   for (int kk = 0; kk < 4; ++kk) ka[kk] = qj * 128 + (((2 * kk + half) ^ ((qj >> 1) & 7)) << 4);
   const int va = qj * 32 + ((half ^ ((qj >> 3) & 1)) << 4);
 
-  // What a parity has summed: O^T, reference point of the lane's query (-inf: no visible key so far), row sum; whether every
-  // reference point of the wave is 0 (wave-uniform); the probabilities of its current group
+  // What a parity has summed (O^T and the row sum), scores and probabilities of its current group
   struct Half {
     floatx16 o[2];
-    float m, l;
-    bool at_zero;
+    float l;
     floatx16 st[2];
     bf16x8 pf[4];
   };
   Half he, ho;
+  // Reference point of the lane's query (-inf: no visible key so far); what its scores start from: -m, or 0 while there is none;
+  // whether the points of the wave are set, and within the range in which a group may skip the rule (wave-uniform)
+  float m = -INFINITY;
+  floatx16 from = {};
+  bool set = false;
   auto init = [](Half &h) {
 #pragma unroll
     for (int i = 0; i < 2; ++i)
 #pragma unroll
       for (int v = 0; v < 16; ++v) h.o[i][v] = 0.f;
-    h.m = -INFINITY;
     h.l = 0.f;
-    h.at_zero = false;
 #pragma unroll
     for (int pg = 0; pg < 4; ++pg)
 #pragma unroll
@@ -457,12 +461,11 @@ __global__ void __launch_bounds__(64 * QS, 2) k_attn_mfma(int n_q_heads, const A
   // K and V of the 64 keys of parity `par` of a stage: of K in the given slot, of V by the stage's number
   auto k_half = [&](int slot_k, int par) { return smem_raw + slot_k * kAttnHalfStage + par * 8192; };
   auto v_half = [&](int kt, int par) { return smem_raw + (kAttnKStages + (kt & 1)) * kAttnHalfStage + par * 8192; };
-  // S^T of a group
-  auto products = [&](Half &h, const unsigned char *ks) {
+  // S^T of a group, added to `start`
+  auto products = [&](Half &h, const unsigned char *ks, const floatx16 &start) {
 #pragma unroll
     for (int b = 0; b < 2; ++b) {
-#pragma unroll
-      for (int v = 0; v < 16; ++v) h.st[b][v] = 0.f;
+      h.st[b] = start;
 #pragma unroll
       for (int kk = 0; kk < 4; ++kk)
         h.st[b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(*reinterpret_cast<const bf16x8 *>(ks + b * 4096 + ka[kk]), qf[kk].v, h.st[b], 0, 0, 0);
@@ -489,76 +492,88 @@ __global__ void __launch_bounds__(64 * QS, 2) k_attn_mfma(int n_q_heads, const A
         h.o[i] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f.v, h.pf[pg], h.o[i], 0, 0, 0);
       }
   };
-  // The probabilities of a group by the general rule: masks (checked form), the largest score, a reference point set or
-  // moved where it has to be.
-  auto general = [&](Half &h, const unsigned char *ks, int kb, auto checked_tag) {   // kb: first key
-    constexpr bool CHECKED = decltype(checked_tag)::value;
-    products(h, ks);
-    if constexpr (CHECKED) {
-      if constexpr (TREE) {
-        // packed prefix tree (tree-ancestry mask): inside the block, the key in slot S + p is visible to local
-        // row r iff p is r itself or an ancestor of r, i.e. p <= r < end of p's subtree (rows are in pre-order)
-        if (kb + 63 >= S) {  // the wave's keys reach into the block (wave-uniform)
-          // branch-free: every subtree end is fetched (index clamped into the block) before any is looked at, so
-          // the 32 reads are in flight together
-          int e_sub[2][16];
+  auto mask = [&](Half &h, int kb) {
+    if constexpr (TREE) {
+      // packed prefix tree (tree-ancestry mask): inside the block, the key in slot S + p is visible to local
+      // row r iff p is r itself or an ancestor of r, i.e. p <= r < end of p's subtree (rows are in pre-order)
+      if (kb + 63 >= S) {  // the wave's keys reach into the block (wave-uniform)
+        // branch-free: the subtree ends of 32 keys are fetched (index clamped into the block) before any is looked at, so
+        // that 16 reads are in flight together (all 32 would not fit the registers)
 #pragma unroll
-          for (int b = 0; b < 2; ++b)
-#pragma unroll
-            for (int v = 0; v < 16; ++v) {
-              const int kpos = kb + 32 * b + 8 * (v >> 2) + 4 * half + (v & 3);
-              e_sub[b][v] = row_end[base + min(max(kpos - S, 0), Lq - 1)];
-            }
-#pragma unroll
-          for (int b = 0; b < 2; ++b)
-#pragma unroll
-            for (int v = 0; v < 16; ++v) {
-              const int kpos = kb + 32 * b + 8 * (v >> 2) + 4 * half + (v & 3);
-              const bool vis = (kpos <= pos_j) & ((kpos < S) | (e_sub[b][v] > base + my_row));
-              h.st[b][v] = vis ? h.st[b][v] : -INFINITY;
-            }
-        }
-      } else if (kb + 63 > S + row0) {  // the wave's keys reach past its first query: causal mask (wave-uniform)
-#pragma unroll
-        for (int b = 0; b < 2; ++b)
+        for (int b = 0; b < 2; ++b) {
+          int e_sub[16];
 #pragma unroll
           for (int v = 0; v < 16; ++v) {
             const int kpos = kb + 32 * b + 8 * (v >> 2) + 4 * half + (v & 3);
-            if (kpos > pos_j) h.st[b][v] = -INFINITY;
+            e_sub[v] = row_end[base + min(max(kpos - S, 0), Lq - 1)];
           }
+#pragma unroll
+          for (int v = 0; v < 16; ++v) {
+            const int kpos = kb + 32 * b + 8 * (v >> 2) + 4 * half + (v & 3);
+            const bool vis = (kpos <= pos_j) & ((kpos < S) | (e_sub[v] > base + my_row));
+            h.st[b][v] = vis ? h.st[b][v] : -INFINITY;
+          }
+        }
       }
+    } else if (kb + 63 > S + row0) {  // the wave's keys reach past its first query: causal mask (wave-uniform)
+#pragma unroll
+      for (int b = 0; b < 2; ++b)
+#pragma unroll
+        for (int v = 0; v < 16; ++v) {
+          const int kpos = kb + 32 * b + 8 * (v >> 2) + 4 * half + (v & 3);
+          if (kpos > pos_j) h.st[b][v] = -INFINITY;
+        }
     }
+  };
+  // The probabilities of a group (first key kb) by the general rule: masks (checked form), the largest score, a reference point
+  // set or moved where it has to be.  Returns whether `from` has changed (wave-uniform).
+  auto general = [&](Half &h, const unsigned char *ks, int kb, auto checked_tag) {
+    constexpr bool CHECKED = decltype(checked_tag)::value;
+    const floatx16 zero = {};
+    products(h, ks, zero);
+    if constexpr (CHECKED) mask(h, kb);
     float mx = fmaxf(h.st[0][0], h.st[1][0]);
 #pragma unroll
     for (int v = 1; v < 16; ++v) mx = fmaxf(fmaxf(mx, h.st[0][v]), h.st[1][v]);
-    const float m_new = attn_reference(h.m, half_max(mx));
+    const float m_new = attn_reference(m, half_max(mx));
+    int changed = 0;
     // when no reference point moved every factor is exactly 1 and the rescale is skipped (wave-uniform branch, same bits
     // either way)
-    if (__any(m_new != h.m)) {
-      const float corr = (h.m == -INFINITY) ? 0.f : ldexpf(1.0f, static_cast<int>(h.m - m_new));
-      h.l *= corr;
+    if (__any(m_new != m)) {
+      const float corr = (m == -INFINITY) ? 0.f : ldexpf(1.0f, static_cast<int>(m - m_new));
+      for (Half *x : {&he, &ho}) {
+        x->l *= corr;
 #pragma unroll
-      for (int i = 0; i < 2; ++i)
+        for (int i = 0; i < 2; ++i)
 #pragma unroll
-        for (int v = 0; v < 16; ++v) h.o[i][v] *= corr;
-      h.m = m_new;
-      h.at_zero = __all(h.m == 0.f);
+          for (int v = 0; v < 16; ++v) x->o[i][v] *= corr;
+      }
+      m = m_new;
+      set = __all(fabsf(m) <= kAttnShiftRange);
+      const float start = m == -INFINITY ? 0.f : 0.f - m;   // no visible key yet: p = 0 without producing inf - inf
+      changed = __any(start != from[0]);
+#pragma unroll
+      for (int v = 0; v < 16; ++v) from[v] = start;
     }
-    const float msub = h.m == -INFINITY ? 0.f : h.m;   // no visible key yet: p = 0 without producing inf - inf
+    if (__any(from[0] != 0.f)) {
+      products(h, ks, from);
+      if constexpr (CHECKED) mask(h, kb);
+    }
     floatx4 ps[2] = {};
 #pragma unroll
     for (int pg = 0; pg < 4; ++pg) {
       floatx8 pv;
 #pragma unroll
-      for (int e = 0; e < 8; ++e) pv[e] = __builtin_amdgcn_exp2f(h.st[pg >> 1][8 * (pg & 1) + e] - msub);
+      for (int e = 0; e < 8; ++e) pv[e] = __builtin_amdgcn_exp2f(h.st[pg >> 1][8 * (pg & 1) + e]);
       h.pf[pg] = __builtin_convertvector(pv, bf16x8);
       ps[pg & 1] = attn_add_page(h.pf[pg], ps[pg & 1]);
     }
     h.l += ps[0][0] + ps[1][0];
+    return changed;
   };
   // A turn: the products of half x -- V^T P^T of one group, K Q^T of the next but one -- beside the
-  // exponentials of half y, whose scores are there and whose reference points are taken for 0.  Returns whether y's
-  // probabilities stand (wave-uniform); l is its row sum then.
+  // exponentials of half y, whose scores are there.  Returns whether y's probabilities stand (wave-uniform), as they do unless a
+  // reference point is to be set or moved; l is its row sum then.
   // The order is fixed by hand: a matrix instruction, the fragment read of one further on, two exponentials, and what follows
   // from those of the slot before, so that neither pipe waits for the other.  The V fragments of the first four slots
   // are there (pre); those of the following turn are read from vn, if it is given, before this one's result is looked at.
@@ -569,7 +584,7 @@ __global__ void __launch_bounds__(64 * QS, 2) k_attn_mfma(int n_q_heads, const A
     for (int i = 0; i < 4; ++i) pre[i] = read_v(vs, i);
   };
   auto turn = [&](Half &x, const unsigned char *vs, const unsigned char *ks, Half &y, float &l, const unsigned char *vn) {
-    constexpr int kAhead = 5;
+    constexpr int kAhead = TREE && SPLIT ? 4 : 5;   // 5 does not fit the registers there
     // slot: 0 to 7 = V fragment (page s / 2, dims 32 (s % 2) ..), 8 + = K fragment (block s % 2, k-step (s - 8) / 2)
     constexpr int kSeq[16] = {0, 1, 2, 3, 8, 9, 4, 5, 10, 11, 6, 7, 12, 13, 14, 15};
     auto read = [&](int j) {
@@ -593,8 +608,7 @@ __global__ void __launch_bounds__(64 * QS, 2) k_attn_mfma(int n_q_heads, const A
       if (f < 8) {
         x.o[c] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fr[j], x.pf[f >> 1], x.o[c], 0, 0, 0);
       } else {
-        const floatx16 zero = {};
-        x.st[c] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fr[j], qf[(f - 8) >> 1].v, f < 10 ? zero : x.st[c], 0, 0, 0);
+        x.st[c] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fr[j], qf[(f - 8) >> 1].v, f < 10 ? from : x.st[c], 0, 0, 0);
       }
       if (j + kAhead < 16) fr[j + kAhead] = read(j + kAhead);
       // bare hardware exponential: results below 2^-126 may flush to zero, far beneath half a bf16 unit of any
@@ -612,12 +626,13 @@ __global__ void __launch_bounds__(64 * QS, 2) k_attn_mfma(int n_q_heads, const A
     if (vn != nullptr) read_pre(vn);
     pack(15);
     add(7);
-    l = y.l + (ps[0][0] + ps[1][0]);
+    const float sum = ps[0][0] + ps[1][0];
+    l = y.l + sum;
 #pragma unroll
     for (int pg = 0; pg < 4; ++pg)
       y.pf[pg] = __builtin_shufflevector(__builtin_shufflevector(pw[4 * pg], pw[4 * pg + 1], 0, 1, 2, 3),
                                          __builtin_shufflevector(pw[4 * pg + 2], pw[4 * pg + 3], 0, 1, 2, 3), 0, 1, 2, 3, 4, 5, 6, 7);
-    return static_cast<int>(y.at_zero) & __all(l < kAttnSumLimit);
+    return static_cast<int>(set) & __all(sum < kAttnSumLimit);
   };
   const auto plain = std::false_type{};
   const auto checked = std::true_type{};
@@ -628,14 +643,15 @@ __global__ void __launch_bounds__(64 * QS, 2) k_attn_mfma(int n_q_heads, const A
   int kt = kt0, k_at = 0;   // k_at: K slot of stage kt
   auto next_slot = [](int k) { return k + 1 == kAttnKStages ? 0 : k + 1; };
   if (kt < kt_plain) {
-    products(he, k_half(k_at, 0));
+    products(he, k_half(k_at, 0), from);
     read_pre(v_half(kt, 1));
+#pragma clang loop unroll(disable)   // a first iteration of its own costs code and spills
     for (; kt < kt_plain; ++kt) {
       float l;
       // first turn: o's probabilities are 0, any V will do
       const int ok_e = turn(ho, v_half(max(kt - 1, kt0), 1), k_half(k_at, 1), he, l, nullptr);
       if (ok_e) he.l = l;
-      else general(he, k_half(k_at, 0), kt * kAttnKeys, plain);
+      else if (general(he, k_half(k_at, 0), kt * kAttnKeys, plain)) products(ho, k_half(k_at, 1), from);
       landed();                                     // K of stage kt + 1, V of stage kt
       read_pre(v_half(kt, 0));
       if (next_k < kt1) issue_k();                  // K of stage kt + 2, over that of kt - 1
@@ -643,11 +659,12 @@ __global__ void __launch_bounds__(64 * QS, 2) k_attn_mfma(int n_q_heads, const A
       const int k_next = next_slot(k_at);
       const int ok_o = turn(he, v_half(kt, 0), k_half(k_next, 0), ho, l, v_half(kt, 1));   // last turn: the scores are not used
       if (ok_o) ho.l = l;
-      else general(ho, k_half(k_at, 1), kt * kAttnKeys + 64, plain);
+      else if (general(ho, k_half(k_at, 1), kt * kAttnKeys + 64, plain)) products(he, k_half(k_next, 0), from);
       k_at = k_next;
     }
     accumulate(ho, kt - 1, 1, plain);
   }
+#pragma clang loop unroll(disable)
   for (; kt < kt1; ++kt) {
     if (kt > kt0) landed();
     if (next_k < kt1 && next_k <= kt + 1) issue_k();
@@ -663,14 +680,9 @@ __global__ void __launch_bounds__(64 * QS, 2) k_attn_mfma(int n_q_heads, const A
     k_at = next_slot(k_at);
   }
 
-  // ---- fold the two parities, even first.  Integer exponents: exact powers of two.  Unsplit, parity 0 is never empty (key 0
-  // is in its first stage); a chunk of a split pass may hold no visible key for a row in either parity
+  // ---- fold the two parities, even first.  (A chunk of a split pass may hold no visible key for a row: m = -inf, sums 0.)
   if (!wave_active || row0 + qj >= Lq) return;
-  const float l_a = half_sum(he.l), l_b = half_sum(ho.l);
-  const float m_tot = fmaxf(he.m, ho.m);
-  const float ca = (he.m > -INFINITY) ? ldexpf(1.0f, static_cast<int>(he.m - m_tot)) : 0.f;
-  const float cb = (ho.m > -INFINITY) ? ldexpf(1.0f, static_cast<int>(ho.m - m_tot)) : 0.f;
-  const float l_tot = l_a * ca + l_b * cb;
+  const float l_tot = half_sum(he.l) + half_sum(ho.l);
   const float inv = SPLIT ? 1.0f : 1.0f / l_tot;
   const size_t rh = (static_cast<size_t>(blockIdx.z) * n_q_heads + head) * sp.total_q + base + row0 + qj;
 #pragma unroll
@@ -679,7 +691,7 @@ __global__ void __launch_bounds__(64 * QS, 2) k_attn_mfma(int n_q_heads, const A
     for (int g = 0; g < 4; ++g) {
       floatx4 ov;
 #pragma unroll
-      for (int e = 0; e < 4; ++e) ov[e] = he.o[i][4 * g + e] * ca + ho.o[i][4 * g + e] * cb;
+      for (int e = 0; e < 4; ++e) ov[e] = he.o[i][4 * g + e] + ho.o[i][4 * g + e];
       if constexpr (SPLIT) {
         *reinterpret_cast<floatx4 *>(sp.part_o + rh * kHd + i * 32 + 8 * g + 4 * half) = ov;
       } else {
@@ -690,7 +702,7 @@ __global__ void __launch_bounds__(64 * QS, 2) k_attn_mfma(int n_q_heads, const A
       }
     }
   if constexpr (SPLIT)
-    if (half == 0) sp.part_ml[rh] = make_float2(m_tot, l_tot);
+    if (half == 0) sp.part_ml[rh] = make_float2(m, l_tot);
 }
 
 // Folds the key chunks of a split pass: row r (cache slot row_slot[r]) has chunks 0 .. min(kAttnMaxChunks - 1,

@@ -6,13 +6,12 @@
 // walks (one token of one sequence: 4 workgroups on 256 compute units), so the launch lasts as long as one of them,
 // most of it latency.  What truly depends on the previous group is little: the accumulation of O and of the row sum, and a
 // reference point that hardly ever moves.  Here the scoring waves take one 64-key group each (S^T = K Q^T,
-// probabilities) and leave their probabilities and row sums in LDS.
-// Four accumulating waves -- (key parity, half of the head dimension) -- walk the groups in order and add V^T P^T: a chain
-// of four matrix instructions a group, with V straight from memory to registers (a V page is stored as the operand).
+// probabilities) and leave their probabilities in LDS.
+// Four accumulating waves -- (key parity, half of the head dimension) -- walk the groups in order and add V^T P^T and the row
+// sums: a chain of four matrix instructions a group, with V straight from memory to registers (a V page is stored as the operand).
 //
 // Every number is formed by the same instructions on the same operands in the same order as in k_attn_mfma (groups at
-// absolute positions, even and odd groups in separate sums, reference points by attn_reference group by group within a
-// parity), so the two kernels give the same bits and the choice between them may follow the batch.
+// absolute positions, even and odd groups in separate sums, reference points by attn_reference group by group), so the two kernels give the same bits and the choice between them may follow the batch.
 //
 // Query sets.  A set is QW = 32 columns: 32 rows of one query head, or, where a sequence has few rows, the rows of several
 // query heads of one kv head (16 rows of two heads, 8 rows of four), so that K and V are read once for all of them.  The
@@ -25,19 +24,18 @@
 
 namespace hsd {
 
-// LDS: probabilities of two steps of four groups (4 KB a group: [page][lane][8 bf16]), the reference points they are relative
-// to, whether a scoring wave's group moves one, and the odd parity's (O, reference point, sum) for the final fold
+// LDS: probabilities of two steps of four groups (4 KB a group: [page][lane][8 bf16]); which waves ask for the general rule; for
+// that, the groups' largest scores and the reference points that follow from them; the odd parity's (O, sum) for the final fold
 constexpr int kAttnWideScorers = 4;
 constexpr int kKsStride = kHd + 8;   // bf16 per K row in LDS
 template <int QW>
 struct AttnWideLds {
   uint4 p[2][kAttnWideScorers][QW / 8][64];
-  float mg[2][kAttnWideScorers][QW];
-  float sum[2][kAttnWideScorers][64];             // a lane's row sum over its group
-  int moves[2][kAttnWideScorers];
-  union {
+  float mx[kAttnWideScorers][QW], mg[2][kAttnWideScorers][QW];
+  int moves[2][8];
+  union __attribute__((aligned(16))) {   // (16-byte LDS accesses: a workgroup takes 1.6 times as long if they lie elsewhere)
     uint16_t k[kAttnWideScorers][64 * kKsStride];   // a scoring wave's own 64 keys (see k_row)
-    float fold[2][QW / 2 + 2][64];                  // after the last products
+    float fold[2][QW / 2 + 1][64];                  // after the last products
   };
 };
 // Offset of a key's row in AttnWideLds::k: rows 144 B apart, those of odd pages 16 B further, so that the fragment reads of
@@ -55,13 +53,21 @@ __device__ __forceinline__ float quarter_sum(float x) {
 }
 // NS scoring waves and four accumulating ones; a step covers NS 64-key groups.
 // grid: attn_grid_size(...) tasks, block 64 * (NS + 4), dynamic LDS sizeof(AttnWideLds).
-// One barrier a step, executed by every wave: behind it the step's probabilities are in LDS.  A step in which a group sets or
-// moves a reference point (the first takes it for 0) takes NS / 2 more, the same for every wave.
-// What bounds it (one token at 1055 keys, 8.5 us): 2.6 us until the first scores (descriptor, page
+// The walk over the steps has two forms.  The first takes every reference point for 0 and has one barrier a step, behind which
+// the step's probabilities are in LDS: nothing else is waited for.  Whether the first group sets another point, and whether a
+// sum shows a score that would move one, is found out beside the next step's work, so that every wave alike leaves this form
+// two barriers after such a step (nearly always the first).  The walk then starts again in the general form: a step whose points
+// stand has one barrier there too, but the outcome is waited for behind it; one that sets or moves a point has two more, behind
+// which the groups' largest scores and then the probabilities are in LDS.
+// us a launch, with points found and moved inside the one loop / in forms of their own: one token at 1055 keys 8.9 / 7.9, 7 blocks
+// of 1 to 47 rows 13.1 / 12.3, 64 tokens 17.9 / 17.4.  Where scores are so extreme that every set ends in the general form (first
+// groups beyond 64 binary orders, 44 in natural logarithms) one token takes 14.6.
+// What bounds it (one token at 1055 keys, 7.9 us): 2.6 us until the first scores (descriptor, page
 // ids, keys: three dependent reads), then the 270 KB of a kv head through one unit's load path (a bare read of 256 KB by a
 // workgroup takes 5 us with its launch), 1 us of last accumulation, fold and store.  Tried: eight scoring waves (32 columns: 13.4
 // us against 12.1); keys and values two steps ahead in registers (16 tokens a step 13.58 ms against 13.15); four more waves that
-// only request the keys into a ring of three or four steps (13.66; 64 tokens 9.05 ms against 8.62, one workgroup a unit).
+// only request the keys into a ring of three or four steps (13.66; 64 tokens 9.05 ms against 8.62, one workgroup a unit); starting
+// again from the first group's points in the common form before the general one (nothing gained where points move as well).
 static_assert(2 * sizeof(AttnWideLds<32>) <= 160 * 1024, "two workgroups a compute unit");
 template <int QW, bool TREE>
 __global__ void __launch_bounds__(64 * (kAttnWideScorers + 4), 4) k_attn_wide(int n_q_heads, int g4, const AttnTile *__restrict__ tiles,
@@ -106,13 +112,9 @@ __global__ void __launch_bounds__(64 * (kAttnWideScorers + 4), 4) k_attn_wide(in
   auto page_off = [&](int pages, int src) {
     return static_cast<size_t>(static_cast<uint32_t>(__builtin_amdgcn_readlane(pages, src))) * (kBlk * kHd);
   };
-  auto any_moves = [&](int s) {
-    const int *f = sm.moves[s & 1];
-    int m = 0;
-#pragma unroll
-    for (int k = 0; k < NS; ++k) m |= f[k];
-    return __builtin_amdgcn_readfirstlane(m) != 0;
-  };
+  auto any_moves = [&](int slot_m) { return __any(sm.moves[slot_m][lane & 7]); };
+  const auto common = std::false_type{};
+  const auto general = std::true_type{};
   if (wave >= 4) {
     // ---- a scoring wave: groups w, w + NS, w + 2 NS, ...
     const int w = wave - 4;
@@ -121,7 +123,7 @@ __global__ void __launch_bounds__(64 * (kAttnWideScorers + 4), 4) k_attn_wide(in
     Frag8 qf[KQ];
     // pages: lane 4 s + p holds the number of page p of this wave's group in step s0 + s (16 steps at a time)
     auto fetch_pages = [&](int s0) { return page_number(((s0 + (lane >> 2)) * NS + w) * 4 + (lane & 3)); };
-    int pages = fetch_pages(0);
+    int pages;
     {
       const bf16 *qp = q + static_cast<size_t>(base + my_row) * qdim + head * kHd + kg * 8;
 #pragma unroll
@@ -156,9 +158,6 @@ __global__ void __launch_bounds__(64 * (kAttnWideScorers + 4), 4) k_attn_wide(in
       return QW == 32 ? 32 * b + 8 * (v >> 2) + 4 * half + (v & 3) : 32 * (b >> 1) + 8 * (b & 1) + 16 * (kg >> 1) + 4 * (kg & 1) + v;
     };
     float st[NB][NV];
-    // The wave's group of a step: products, then masks and the lane's largest score
-    // (with 16 columns the first half's fragments are read ahead, while the wave learns whether the step before stands)
-    bf16x8 first[4];
     auto fragment = [&](int j) {   // QW = 32: block j / 4, k-step j % 4; QW = 16: j / 2, j % 2
       if constexpr (QW == 32) {
         return *reinterpret_cast<const bf16x8 *>(ks + k_row((j >> 2) * 32 + qj) + (j & 3) * 16 + half * 8);
@@ -167,46 +166,45 @@ __global__ void __launch_bounds__(64 * (kAttnWideScorers + 4), 4) k_attn_wide(in
         return *reinterpret_cast<const bf16x8 *>(ks + k_row(key) + (j & 1) * 32 + kg * 8);
       }
     };
-    auto read_first = [&]() {
-#pragma unroll
-      for (int j = 0; j < 4; ++j) first[j] = fragment(j);
-    };
-    auto products = [&]() {
+    auto products = [&](float from) {   // the scores, added to `from`
 #pragma unroll
       for (int b = 0; b < NB; ++b) {
         if constexpr (QW == 32) {
           floatx16 acc;
 #pragma unroll
-          for (int v = 0; v < 16; ++v) acc[v] = 0.f;
+          for (int v = 0; v < 16; ++v) acc[v] = from;
 #pragma unroll
           for (int kk = 0; kk < 4; ++kk)
             acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fragment(4 * b + kk), qf[kk].v, acc, 0, 0, 0);
 #pragma unroll
           for (int v = 0; v < NV; ++v) st[b][v] = acc[v];
         } else {
-          floatx4 acc = {0.f, 0.f, 0.f, 0.f};
+          floatx4 acc = {from, from, from, from};
 #pragma unroll
-          for (int kk = 0; kk < 2; ++kk)
-            acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(b < 2 ? first[2 * b + kk] : fragment(2 * b + kk), qf[kk].v, acc, 0, 0, 0);
+          for (int kk = 0; kk < 2; ++kk) acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fragment(2 * b + kk), qf[kk].v, acc, 0, 0, 0);
 #pragma unroll
           for (int v = 0; v < NV; ++v) st[b][v] = acc[v];
         }
       }
     };
-    auto mask = [&](int kb) {
+    auto mask = [&](int kb, auto form_tag) {
       if constexpr (TREE) {
         if (kb + 63 >= S) {  // the group reaches into the block: tree-ancestry mask (see k_attn_mfma)
+          // a block at a time, in the general form four keys: the registers of all would decide between one and two workgroups a unit
+          constexpr int NC = decltype(form_tag)::value ? 4 : NV;
 #pragma unroll
-          for (int b = 0; b < NB; ++b) {
-            int e_sub[NV];   // a block at a time: the registers of all would decide between one and two workgroups a unit
+          for (int c = 0; c < NB * NV / NC; ++c) {
+            const int b = c * NC / NV, v0 = c * NC % NV;
+            int e_sub[NC];
 #pragma unroll
-            for (int v = 0; v < NV; ++v) e_sub[v] = row_end[base + min(max(kb + key_of(b, v) - S, 0), Lq - 1)];
+            for (int v = 0; v < NC; ++v) e_sub[v] = row_end[base + min(max(kb + key_of(b, v0 + v) - S, 0), Lq - 1)];
 #pragma unroll
-            for (int v = 0; v < NV; ++v) {
-              const int kpos = kb + key_of(b, v);
+            for (int v = 0; v < NC; ++v) {
+              const int kpos = kb + key_of(b, v0 + v);
               const bool vis = (kpos <= pos_j) & ((kpos < S) | (e_sub[v] > base + my_row));
-              st[b][v] = vis ? st[b][v] : -INFINITY;
+              st[b][v0 + v] = vis ? st[b][v0 + v] : -INFINITY;
             }
+            if constexpr (NC < NV) __builtin_amdgcn_sched_barrier(0);
           }
         }
       } else if (kb + 63 > S + row0) {  // the group reaches past the first query: causal mask
@@ -226,75 +224,113 @@ __global__ void __launch_bounds__(64 * (kAttnWideScorers + 4), 4) k_attn_wide(in
       mx = half_max(mx);
       return QW == 16 ? quarter_max(mx) : mx;
     };
-    // Reference point of the lane's query in this wave's parity (attn_reference).  The first step takes it for 0, which it is
-    // unless the scores are extreme, so that its four groups need not wait for one another either.
-    float m_run = 0.f;
-    // the group's probabilities and the reference points they are relative to; returns the lane's row sum
-    auto probs = [&](int s) {
-      const float msub = m_run == -INFINITY ? 0.f : m_run;
-      floatx4 ps[2] = {};   // QW = 16: a lane holds even pages or odd ones, in ps[0]
+    // The group's probabilities; WITH_SUM: returns the lane's sum of them
+    auto probs = [&](int s, auto with_sum_tag) {
+      floatx4 ps = {};
 #pragma unroll
       for (int f = 0; f < QW / 8; ++f) {   // operand f: page f of the group, or pages 2 f and 2 f + 1
         floatx8 pv;
 #pragma unroll
-        for (int e = 0; e < 8; ++e) {
-          const float x = QW == 32 ? st[f >> 1][8 * (f & 1) + e] : st[2 * f + (e >> 2)][e & 3];
-          pv[e] = __builtin_amdgcn_exp2f(x - msub);
-        }
+        for (int e = 0; e < 8; ++e) pv[e] = __builtin_amdgcn_exp2f(QW == 32 ? st[f >> 1][8 * (f & 1) + e] : st[2 * f + (e >> 2)][e & 3]);
         Frag8 pf;
         pf.v = __builtin_convertvector(pv, bf16x8);
         sm.p[s & 1][w][f][lane] = pf.u;
-        ps[QW == 32 ? f & 1 : 0] = attn_add_page(pf.v, ps[QW == 32 ? f & 1 : 0]);
+        if constexpr (decltype(with_sum_tag)::value) ps = attn_add_page(pf.v, ps);
       }
-      const float sum = QW == 32 ? ps[0][0] + ps[1][0] : half_sum(ps[0][0]);
-      sm.sum[s & 1][w][lane] = sum;
-      if (kg == 0) sm.mg[s & 1][w][qj] = m_run;
-      return sum;
+      return ps[0];
     };
-    load_k(0);
-    store_k();
-    if (n_steps > 1) load_k(1);
-    // Behind a step's barrier: if a group of it sets or moves a reference point, the groups of a parity one after the other, each
-    // from the reference point its predecessor left.
-    auto settle = [&](int s) {
-      if (!any_moves(s)) return;
-      if (s == 0) m_run = -INFINITY;
-      for (int k = 0; k < NS / 2; ++k) {
-        if ((w >> 1) == k && s * NS + w < n_groups) {
-          m_run = attn_reference(m_run, query_max());
-          probs(s);
-        }
-        __syncthreads();
-        const int last = 2 * k + (w & 1);
-        if (s * NS + last < n_groups) m_run = sm.mg[s & 1][last][qj];
+    auto next_k = [&](int s) {   // K of the next step to LDS, that of the one after it requested
+      if (s + 1 >= n_steps) return;
+      store_k();
+      if (s + 2 < n_steps) {
+        if (((s + 2) & 15) == 0) pages = fetch_pages(s + 2);
+        load_k(s + 2);
       }
     };
-    for (int s = 0; s < n_steps; ++s) {
-      const int g = s * NS + w, kb = g * 64;
-      bool moves = false;
-      if constexpr (QW == 16) read_first();
-      if (s > 0) settle(s - 1);
-      if (g < n_groups) products();
+    auto first_k = [&](int s) {   // K of step s to LDS, that of the next one requested
+      pages = fetch_pages(s & ~15);
+      load_k(s);
+      store_k();
       if (s + 1 < n_steps) {
-        store_k();
-        if (s + 2 < n_steps) {
-          if (((s + 2) & 15) == 0) pages = fetch_pages(s + 2);
-          load_k(s + 2);
+        if (((s + 1) & 15) == 0) pages = fetch_pages(s + 1);
+        load_k(s + 1);
+      }
+    };
+    // The common form.  Returns whether it stands.
+    auto walk = [&]() {
+      if (lane == 0) sm.moves[1][4 + w] = 0;
+      bool asked = false;
+#pragma clang loop unroll(disable)   // a first iteration of its own doubles the code
+      for (int s = 0; s < n_steps; ++s) {
+        const int g = s * NS + w;
+        if (s > 1) asked = any_moves(s & 1);   // of step s - 2, complete since the barrier of s - 1
+        if (g < n_groups) products(0.f);
+        next_k(s);
+        if (g < n_groups) {
+          mask(g * 64, common);
+          probs(s, common);
+        }
+        if (asked) return false;
+        __syncthreads();   // the step's probabilities
+        // the first group holds a visible key of every query and sets its point
+        if (s == 0) {
+          const bool sets = w == 0 && __any(attn_reference(-INFINITY, query_max()) != 0.f);
+          if (lane == 0) sm.moves[0][4 + w] = sets;
         }
       }
-      if (g < n_groups) {
-        mask(kb);
-        const float sum = probs(s);
-        // A parity's first group, or a query without a visible key so far; elsewhere a score that moves a reference point
-        // shows in the row sum (kAttnSumLimit)
-        if (g < 2 || !__all(sum < kAttnSumLimit && m_run > -INFINITY))
-          moves = __any(attn_reference(g < 2 ? -INFINITY : m_run, query_max()) != m_run);
+      __syncthreads();   // the fold
+      return !(any_moves(0) || any_moves(1));
+    };
+    first_k(0);
+    if (walk()) return;
+    // The general form.  m: reference point of the lane's query
+    __syncthreads();   // every wave has seen the outcome
+    first_k(0);
+    float m = -INFINITY;
+#pragma clang loop unroll(disable)
+    for (int s = 0; s < n_steps; ++s) {
+      const int g = s * NS + w;
+      // phase 0: with the points as they are; where they do not stand (as at the first step), phase 1: the largest scores, and
+      // 2: with the points that follow from them
+#pragma clang loop unroll(disable)
+      for (int phase = s == 0 ? 1 : 0;; ++phase) {
+        float m_own = m, mx = -INFINITY;
+        if (phase == 2) {
+          m_own = sm.mg[s & 1][w][qj];
+          m = sm.mg[s & 1][min(NS, n_groups - s * NS) - 1][qj];
+        }
+        bool moves = false;
+        // no visible key yet: p = 0 without producing inf - inf
+        if (g < n_groups) products(phase == 1 || m_own == -INFINITY ? 0.f : 0.f - m_own);
+        if (phase != 1) next_k(s);
+        if (g < n_groups) {
+          int kb = g * 64;
+          asm volatile("" : "+s"(kb));   // the masks' addresses are made here: hoisted out of the phases they would spill
+          mask(kb, general);
+          if (phase == 1) mx = query_max();
+          else moves = !__all(probs(s, general) < kAttnSumLimit && fabsf(m) <= kAttnShiftRange);
+        }
+        if (phase == 1 && kg == 0) sm.mx[w][qj] = mx;
+        if (phase == 0 && lane == 0) sm.moves[s & 1][w] = moves;
+        __syncthreads();
+        if (phase == 2) break;
+        if (phase == 0) {
+          int f = 0;
+#pragma unroll
+          for (int k = 0; k < NS; ++k) f |= sm.moves[s & 1][k];
+          if (!__builtin_amdgcn_readfirstlane(f)) break;
+          first_k(s);
+        } else {
+          // every scoring wave finds the point behind its own group
+          float m_run = m;
+          for (int k = 0; k <= w; ++k)
+            if (s * NS + k < n_groups) m_run = attn_reference(m_run, sm.mx[k][qj]);
+          if (kg == 0) sm.mg[s & 1][w][qj] = m_run;
+          __syncthreads();
+        }
       }
-      if (lane == 0) sm.moves[s & 1][w] = moves;
-      __syncthreads();   // the step's probabilities
     }
-    settle(n_steps - 1);
-    __syncthreads();   // the fold below
+    __syncthreads();   // the fold
     return;
   }
 
@@ -310,7 +346,7 @@ __global__ void __launch_bounds__(64 * (kAttnWideScorers + 4), 4) k_attn_wide(in
   // V operands of a group.  QW = 32: page f, dims 32 i + l % 32, slots 8 (l / 32) ..  QW = 16: pages 2 (f / 2) + l / 32,
   // dims 32 i + 16 (f % 2) + l % 16, slots 8 (l / 16 % 2) ..
   Frag8 vf[KG][4];
-  int pages = fetch_pages(0);
+  int pages;
   auto load_v = [&](int s, int k) {
     const int l0 = ((s % SPF) * KG + k) * 4;
     if constexpr (QW == 32) {
@@ -327,28 +363,13 @@ __global__ void __launch_bounds__(64 * (kAttnWideScorers + 4), 4) k_attn_wide(in
       }
     }
   };
-#pragma unroll
-  for (int k = 0; k < KG; ++k) load_v(0, k);
   constexpr int NO = QW / 2;       // accumulators of a lane: 32 dims x QW queries over 64 lanes
   floatx16 o32;
   floatx4 o16[2];
-#pragma unroll
-  for (int v = 0; v < 16; ++v) o32[v] = 0.f;
-#pragma unroll
-  for (int v = 0; v < 8; ++v) o16[v >> 2][v & 3] = 0.f;
-  float m_run = -INFINITY, l_run = 0.f;
-  Frag8 pf[KG][QW / 8];
-  float mg[KG], rs[KG];
-  auto read_group = [&](int s, int k) {   // what the scoring wave left; with 16 columns ahead of the barriers' outcome
-    const int w = 2 * k + par;
-    mg[k] = sm.mg[s & 1][w][qj];
-#pragma unroll
-    for (int f = 0; f < QW / 8; ++f) pf[k][f].u = sm.p[s & 1][w][f][lane];
-    rs[k] = sm.sum[s & 1][w][lane];
-  };
-  auto accumulate = [&](int s, int k) {
+  float l = 0.f;
+  auto accumulate = [&](int s, int k) {   // returns the lane's sum over the group
     const int w = 2 * k + par, g = s * NS + w;
-    if (g >= n_groups) return;
+    if (g >= n_groups) return 0.f;
     if (g * 64 + 64 > n_valid) {
       // slots of positions that hold no data of this sequence must read as 0 (their probability is 0, but 0 * stale-NaN
       // would poison the product); slot order of a V page: see kv_v_slot
@@ -361,84 +382,139 @@ __global__ void __launch_bounds__(64 * (kAttnWideScorers + 4), 4) k_attn_wide(in
           if (g * 64 + page * kBlk + tok >= n_valid) vf[k][f].h[e] = 0;
         }
     }
-    if constexpr (QW == 32) read_group(s, k);
-    const float m_new = mg[k];
-    if (__any(m_new != m_run)) {
-      const float corr = (m_run == -INFINITY) ? 0.f : ldexpf(1.0f, static_cast<int>(m_run - m_new));
-      l_run *= corr;
-      if constexpr (QW == 32) {
+    Frag8 pf[QW / 8];
 #pragma unroll
-        for (int v = 0; v < 16; ++v) o32[v] *= corr;
-      } else {
-#pragma unroll
-        for (int v = 0; v < 8; ++v) o16[v >> 2][v & 3] *= corr;
-      }
-    }
-    m_run = m_new;
-    l_run += rs[k];
+    for (int f = 0; f < QW / 8; ++f) pf[f].u = sm.p[s & 1][w][f][lane];
+    floatx4 ps[2] = {};
     if constexpr (QW == 32) {
 #pragma unroll
-      for (int f = 0; f < 4; ++f) o32 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf[k][f].v, pf[k][f].v, o32, 0, 0, 0);
+      for (int f = 0; f < 4; ++f) {
+        o32 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf[k][f].v, pf[f].v, o32, 0, 0, 0);
+        ps[f & 1] = attn_add_page(pf[f].v, ps[f & 1]);
+      }
     } else {
+      // the lower lane half holds the even pages, the upper the odd ones
 #pragma unroll
-      for (int p = 0; p < 2; ++p)
+      for (int p = 0; p < 2; ++p) {
 #pragma unroll
-        for (int d = 0; d < 2; ++d) o16[d] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(vf[k][2 * p + d].v, pf[k][p].v, o16[d], 0, 0, 0);
-    }
-  };
-
-  auto wait_step = [&](int s) {   // the barriers of the scoring waves' step
-    __syncthreads();
-    if constexpr (QW == 16) {
-#pragma unroll
-      for (int k = 0; k < KG; ++k) read_group(s, k);
-    }
-    if (any_moves(s)) {
-      for (int k = 0; k < NS / 2; ++k) __syncthreads();
-      if constexpr (QW == 16) {
-#pragma unroll
-        for (int k = 0; k < KG; ++k) read_group(s, k);
+        for (int d = 0; d < 2; ++d) o16[d] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(vf[k][2 * p + d].v, pf[p].v, o16[d], 0, 0, 0);
+        ps[0] = attn_add_page(pf[p].v, ps[0]);
       }
     }
+    const float sum = QW == 32 ? ps[0][0] + ps[1][0] : half_sum(ps[0][0]);
+    l += sum;
+    return sum;
   };
-  wait_step(0);
-  for (int s = 0; s + 1 < n_steps; ++s) {
-    if ((s + 1) % SPF == 0) pages = fetch_pages(s + 1);
+  auto first_v = [&]() {
+    l = 0.f;
 #pragma unroll
-    for (int k = 0; k < KG; ++k) {
-      accumulate(s, k);
-      load_v(s + 1, k);
-    }
-    wait_step(s + 1);
-  }
+    for (int v = 0; v < 16; ++v) o32[v] = 0.f;
 #pragma unroll
-  for (int k = 0; k < KG; ++k) accumulate(n_steps - 1, k);
-
+    for (int v = 0; v < 8; ++v) o16[v >> 2][v & 3] = 0.f;
+    pages = fetch_pages(0);
+#pragma unroll
+    for (int k = 0; k < KG; ++k) load_v(0, k);
+  };
   // ---- fold the two parities (even first), as k_attn_mfma does
-  l_run = QW == 32 ? half_sum(l_run) : quarter_sum(l_run);
   float o[NO];
+  auto leave_odd = [&]() {
+    l = QW == 32 ? half_sum(l) : quarter_sum(l);
 #pragma unroll
-  for (int v = 0; v < NO; ++v) o[v] = QW == 32 ? o32[v] : o16[(v >> 2) & 1][v & 3];
-  if (par == 1) {
+    for (int v = 0; v < NO; ++v) o[v] = QW == 32 ? o32[v] : o16[(v >> 2) & 1][v & 3];
+    if (par == 1) {
 #pragma unroll
-    for (int v = 0; v < NO; ++v) sm.fold[i][v][lane] = o[v];
-    sm.fold[i][NO][lane] = m_run;
-    sm.fold[i][NO + 1][lane] = l_run;
+      for (int v = 0; v < NO; ++v) sm.fold[i][v][lane] = o[v];
+      sm.fold[i][NO][lane] = l;
+    }
+  };
+  // The common form.  Returns whether it stands.
+  auto walk = [&]() {
+    bool asked = false, moves = false;
+    auto take_in = [&](int s, int k) { moves |= !__all(accumulate(s, k) < kAttnSumLimit); };
+    __syncthreads();   // the first step's probabilities
+#pragma clang loop unroll(disable)
+    for (int s = 0; s + 1 < n_steps; ++s) {
+      if (s > 0) asked = any_moves((s + 1) & 1);   // of step s - 1
+      if ((s + 1) % SPF == 0) pages = fetch_pages(s + 1);
+      moves = false;
+#pragma unroll
+      for (int k = 0; k < KG; ++k) {
+        take_in(s, k);
+        load_v(s + 1, k);
+      }
+      if (lane == 0) sm.moves[s & 1][wave] = moves;
+      if (asked) return false;
+      __syncthreads();   // the next step's
+    }
+    moves = false;
+#pragma unroll
+    for (int k = 0; k < KG; ++k) take_in(n_steps - 1, k);
+    if (lane == 0) sm.moves[(n_steps - 1) & 1][wave] = moves;
+    if (lane == 0 && n_steps == 1) sm.moves[1][wave] = 0;
+    leave_odd();
+    __syncthreads();
+    return !(any_moves(0) || any_moves(1));
+  };
+  first_v();
+  if (!walk()) {
+    // The general form.  m: reference point of the lane's query
+    __syncthreads();
+    float m = -INFINITY;
+    // every group's move, also of the other parity, so that the factors come one by one as in k_attn_mfma
+    auto rescale = [&](int s, int w) {
+      if (s * NS + w >= n_groups) return;
+      const float m_new = sm.mg[s & 1][w][qj];
+      if (__any(m_new != m)) {
+        const float corr = (m == -INFINITY) ? 0.f : ldexpf(1.0f, static_cast<int>(m - m_new));
+        l *= corr;
+        if constexpr (QW == 32) {
+#pragma unroll
+          for (int v = 0; v < 16; ++v) o32[v] *= corr;
+        } else {
+#pragma unroll
+          for (int v = 0; v < 8; ++v) o16[v >> 2][v & 3] *= corr;
+        }
+      }
+      m = m_new;
+    };
+    first_v();
+#pragma clang loop unroll(disable)
+    for (int s = 0; s < n_steps; ++s) {
+      bool moved = s == 0;
+      if (s > 0) {
+        __syncthreads();   // phase 0
+        int f = 0;
+#pragma unroll
+        for (int k = 0; k < NS; ++k) f |= sm.moves[s & 1][k];
+        moved = __builtin_amdgcn_readfirstlane(f) != 0;
+      }
+      if (moved) {
+        __syncthreads();   // phase 1: largest scores, points
+        __syncthreads();
+        __syncthreads();   // phase 2
+      }
+      if (s + 1 < n_steps && (s + 1) % SPF == 0) pages = fetch_pages(s + 1);
+#pragma unroll
+      for (int k = 0; k < KG; ++k) {
+        if (moved) rescale(s, 2 * k);
+        if (moved && par == 1) rescale(s, 2 * k + 1);
+        accumulate(s, k);
+        if (moved && par == 0) rescale(s, 2 * k + 1);
+        if (s + 1 < n_steps) load_v(s + 1, k);
+      }
+    }
+    leave_odd();
+    __syncthreads();
   }
-  __syncthreads();
   if (par == 0 && row < Lq) {
-    const float m_b = sm.fold[i][NO][lane], l_b = sm.fold[i][NO + 1][lane];
-    const float m_tot = fmaxf(m_run, m_b);
-    const float ca = (m_run > -INFINITY) ? ldexpf(1.0f, static_cast<int>(m_run - m_tot)) : 0.f;
-    const float cb = (m_b > -INFINITY) ? ldexpf(1.0f, static_cast<int>(m_b - m_tot)) : 0.f;
-    const float inv = 1.0f / (l_run * ca + l_b * cb);
+    const float inv = 1.0f / (l + sm.fold[i][NO][lane]);
     // four dims in a row: 8 g + 4 (l / 32), or 16 g + 4 (l / 16)
     bf16 *op = out + static_cast<size_t>(base + row) * qdim + head * kHd + i * 32 + 4 * kg;
 #pragma unroll
     for (int gq = 0; gq < NO / 4; ++gq) {
       floatx4 ov;
 #pragma unroll
-      for (int e = 0; e < 4; ++e) ov[e] = (o[4 * gq + e] * ca + sm.fold[i][4 * gq + e][lane] * cb) * inv;
+      for (int e = 0; e < 4; ++e) ov[e] = (o[4 * gq + e] + sm.fold[i][4 * gq + e][lane]) * inv;
       *reinterpret_cast<bf16x4 *>(op + (256 / QW) * gq) = __builtin_convertvector(ov, bf16x4);
     }
   }
