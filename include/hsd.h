@@ -92,6 +92,8 @@ typedef struct hsd_weights {
  * is [16 tokens][64 dims]; a V page is stored transposed, [64 dims][16 token slots], token t in slot
  * 8*((t>>2)&1) + 4*(t>>3) + (t&3) (the order the attention kernel's matrix-core operands want).  The contents
  * are written and read only by the library.
+ * The pools need no more than their elements' alignment; bf16 pools that are not 16-byte aligned take a slower attention
+ * path with many query rows (same results; attn_key_chunk is without effect there).
  * free_list is a stack of free block ids, free_count its height; both live on the device and are
  * maintained by the library (hsd_kv_pool_init, verify, commit). */
 typedef struct hsd_kv_pool {

@@ -554,11 +554,12 @@ int launch_attn_wide(hipStream_t st, int n_wg, int n_q_heads, int g4, const Attn
 struct AttnPlan {
   bool mfma = false;   // bf16 with a grouping of query heads that fits the kernels; otherwise the plain kernel
   bool wide = false;   // k_attn_wide
+  bool split = false;  // k_attn_mfma with the keys split (desc.attn_key_chunk)
   int g4 = 0, qs = 0, q_tile = 0, n_y = 0, sub_tiles = 0, n_wg = 0;
 };
 
 template <typename T>
-AttnPlan plan_attention(const hsd_ctx *ctx, const hsd_batch *b, bool page_mode) {
+AttnPlan plan_attention(const hsd_ctx *ctx, const hsd_kv_pool *pool, const hsd_batch *b, bool page_mode) {
   AttnPlan p;
   const hsd_model_desc &d = ctx->desc;
   const int group = d.n_q_heads / d.n_kv_heads;
@@ -581,7 +582,11 @@ AttnPlan plan_attention(const hsd_ctx *ctx, const hsd_batch *b, bool page_mode) 
   const int64_t by_tile = g4 * (2 * rows + 32 * n) / 64, by_row = n + (rows - n) / 8;
   const int64_t sets = (g4 == 4 ? std::min(by_tile, by_row) : by_tile) * n_y;
   const int64_t cu = ctx->n_cu > 0 ? ctx->n_cu : 256;
-  p.wide = d.attn_key_chunk == 0 && 4 * sets <= 9 * cu;
+  // k_attn_mfma requests keys and values by LDS-direct loads of 16 bytes a lane, which want 16-byte aligned pools; pools that are
+  // only aligned to their elements go to k_attn_wide, which loads into registers, however many sets there are (and unsplit).
+  const bool aligned = ((reinterpret_cast<uintptr_t>(pool->k_pool) | reinterpret_cast<uintptr_t>(pool->v_pool)) & 15) == 0;
+  p.split = aligned && d.attn_key_chunk > 0;
+  p.wide = !aligned || (!p.split && 4 * sets <= 9 * cu);
   if (p.wide) {
     p.q_tile = 32;
     p.sub_tiles = 8;   // two 32-row tiles of four heads share an XCD
@@ -614,9 +619,9 @@ int launch_attention(const hsd_ctx *ctx, hipStream_t st, const hsd_batch *b, con
         return tree ? launch_attn_wide<32, true>(st, n_wg, d.n_q_heads, g4, ws.attn_tiles, kv, q, o, meta.row_end)
                     : launch_attn_wide<32, false>(st, n_wg, d.n_q_heads, g4, ws.attn_tiles, kv, q, o, nullptr);
       }
-      // Key split (desc.attn_key_chunk > 0): one workgroup per (query tile, chunk of keys); no sequence can hold
+      // Key split: one workgroup per (query tile, chunk of keys); no sequence can hold
       // more keys than its block-table row addresses, which bounds the chunks worth launching.
-      const int chunk = d.attn_key_chunk;
+      const int chunk = plan.split ? d.attn_key_chunk : 0;
       int n_chunks = 1;
       if (chunk > 0) {
         const int64_t max_keys = static_cast<int64_t>(b->max_blocks_per_seq) * HSD_KV_BLOCK_TOKENS;
@@ -679,7 +684,7 @@ int forward(hsd_ctx *ctx, hipStream_t st, const hsd_kv_pool *pool, const hsd_bat
   const bool relaxed = with_head && b->log_tau < 0.f;   // Eq. 11 with tau < 1: needs the draft tokens' own logits
   int rc;
 
-  const AttnPlan plan = plan_attention<T>(ctx, b, page_mode);
+  const AttnPlan plan = plan_attention<T>(ctx, pool, b, page_mode);
   const bool pass_by = weights_pass_by(d, pool, b);
   const bool dump = with_head && b->n_dump > 0 && b->logits_dump != nullptr;
   {

@@ -230,6 +230,42 @@ def test_reference_points_in_every_form(n_q, n_kv, factor, tree):
     assert np.abs(wide - plain).max() <= 2e-2
 
 
+@pytest.mark.parametrize("n_q, n_kv", [(16, 4), (2, 2)])
+@pytest.mark.parametrize("elements", [1, 2, 4])
+def test_pools_need_no_more_than_their_elements_alignment(n_q, n_kv, elements):
+    """K and V pools a few elements past a 16-byte boundary give the bits of aligned ones, with one block and with so many rows
+    that aligned pools take the general kernel, from both entry points; a key split is without effect on them."""
+    import paper_2602_12957_amd.binding as B
+    from paper_2602_12957_amd.runtime import _ptr
+    desc = W.tiny_model(2, 128, n_q, n_kv, 64, 128, 256, "bf16")
+    weights = W.make_weights(desc, 59)
+    rng = np.random.default_rng(elements)
+    n_cu = torch.cuda.get_device_properties(0).multi_processor_count
+    prefix = rng.integers(0, 256, size=300).astype(np.int32)
+    blocks = [rng.integers(0, 256, size=r).astype(np.int32) for r in (7, 32 * (3 * n_cu // n_q + 1))]
+    rows, n_dump = sum(len(b) for b in blocks), 200
+
+    def score(shift, members, mode, chunk=0):
+        eng = Engine(desc, weights, (rows + 300) // 16 + 4, 2, (rows + 300) // 16 + 4, rows, n_dump, attn_key_chunk=chunk)
+        if shift:
+            keep = [torch.zeros(p.numel() + shift, dtype=p.dtype, device=p.device) for p in (eng.k_pool, eng.v_pool)]
+            eng.k_pool, eng.v_pool = keep[0][shift:], keep[1][shift:]
+            assert eng.k_pool.data_ptr() % 16 == 2 * shift
+            eng.cpool = B.hsd_kv_pool(_ptr(eng.k_pool), _ptr(eng.v_pool), eng.n_blocks, _ptr(eng.free_list), _ptr(eng.free_count))
+        eng.reset()
+        eng.prefill([0], [prefix])
+        dump = np.arange(min(n_dump, sum(len(blocks[i]) for i in members)))
+        out = eng.verify(members, [blocks[i] for i in members], mode, dump_rows=dump).logits.cpu().numpy().copy()
+        assert int(eng.status.item()) == 0
+        eng.close()
+        return out
+
+    for members, mode in (([0], "region"), ([0, 1], "region"), ([0, 1], "page")):
+        aligned = score(0, members, mode)
+        np.testing.assert_array_equal(aligned, score(elements, members, mode))
+    np.testing.assert_array_equal(aligned, score(elements, members, mode, 128))
+
+
 # A row that sees one key gets that key's value, to the last bit: the probability, whatever its rounding to bf16, cancels in the
 # quotient.  mode, sequences, rows of a further sequence, key chunk: 16 and 32 columns of k_attn_wide, k_attn_mfma with 4 and 8
 # query sets and with a key split.
