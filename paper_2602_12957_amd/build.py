@@ -13,6 +13,8 @@ HIPCC_FLAGS = [
     # the command processor hands the first kernel arguments to a wave in registers instead of the wave reading them from
     # memory before it can form its first address
     "-mllvm", "-amdgpu-kernarg-preload-count=16",
+    # a clobber list that names a register the compiler keeps for itself (m0) promises nothing: refused
+    "-Werror=inline-asm",
 ]
 
 

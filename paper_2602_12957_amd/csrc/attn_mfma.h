@@ -305,22 +305,26 @@ typedef __attribute__((address_space(3))) unsigned char *AttnLds;
   } while (0)
 // A page of 2 KB (uniform address) to LDS (uniform) in two LDS-direct loads: lane l's 16 bytes at byte off0 of the page go to
 // dst + 16 l, those at off1 to dst + 1024 + 16 l.  In asm: the compiler would otherwise wait for every load in flight before
-// each LDS read.  No register is written; the reads wait by HSD_ATTN_VMCNT and a barrier.
+// each LDS read.  No register is written; the reads wait by HSD_ATTN_VMCNT and a barrier.  m0, which the loads take their LDS
+// address from, is a register the compiler keeps for itself and does not save around asm: it is put back as it was found.
 __device__ __forceinline__ void attn_load_page(const bf16 *page, AttnLds dst, int off0, int off1) {
   const uint32_t d = __builtin_amdgcn_readfirstlane(static_cast<uint32_t>(reinterpret_cast<uintptr_t>(dst)));
   const uint64_t p = reinterpret_cast<uint64_t>(page);
   const uint64_t up = (static_cast<uint64_t>(__builtin_amdgcn_readfirstlane(static_cast<uint32_t>(p >> 32))) << 32) |
                       static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(static_cast<uint32_t>(p)));
+  uint32_t m0;
   asm volatile(
-      "s_mov_b32 m0, %0\n\t"
+      "s_mov_b32 %0, m0\n\t"
+      "s_mov_b32 m0, %1\n\t"
       "s_nop 0\n\t"
-      "global_load_lds_dwordx4 %1, %3\n\t"
+      "global_load_lds_dwordx4 %2, %4\n\t"
       "s_add_u32 m0, m0, 0x400\n\t"
       "s_nop 0\n\t"
-      "global_load_lds_dwordx4 %2, %3"
-      :
+      "global_load_lds_dwordx4 %3, %4\n\t"
+      "s_mov_b32 m0, %0"
+      : "=&s"(m0)
       : "s"(d), "v"(off0), "v"(off1), "s"(up)
-      : "memory", "scc", "m0");
+      : "memory", "scc");
 }
 
 // QS = query sets (waves; 32 queries x one head each) per workgroup: 4 (region-level) or 8 (page-level).
