@@ -463,11 +463,11 @@ int launch_gemm(const hsd_ctx *ctx, hipStream_t st, int site, int M, int N, int 
     return HSD_EINVAL;   // this epilogue exists for the MFMA kernels only (the caller never gets here with it)
   } else {
     // fp32: k_gemm_f32, by tiles of one 64-column group.  Half a group and 16 rows while whole ones fill at most half of the
-    // units, 16 rows up to one tile a unit, 32 up to two, 64 beyond.  us, the vector-unit kernel / this one: 132 rows of d_model
-    // 256: down 23.1 / 10.5 (whole groups 16.5), QKV 8.3 / 5.7 (7.4), O 7.2 / 5.0 (6.0), gate/up 11.3 / 8.6; 1024 rows: gate/up 27.7 /
-    // 18.6, down 25.3 / 17.5, QKV 13.5 / 16.6, LM head 43.7 / 47.9, the pass 423 / 405.  The other end: at 2064 rows gate/up 45.8 /
-    // 48.1, down 38.4 / 40.3, LM head 84 / 94, the pass 1235 / 1265 (one kernel for all row counts, since the order of a row's sums
-    // must not follow the batch).
+    // units, 16 rows up to one tile a unit, 32 up to two, 64 beyond; from 32 rows on operands through LDS.  us, a vector-unit kernel
+    // (gemm_simple.h) / this one without LDS / this: 132 rows of d_model 256: down 23.1 / 10.5 (whole groups 16.5), QKV 8.3 / 5.7
+    // (7.4), O 7.2 / 5.0 (6.0), gate/up 11.3 / 8.3, LM head - / 14.0 / 10.8; 1024 rows: gate/up 26.8 / 18.1 / 14.4, down 24.5 / 17.1, QKV
+    // 13.4 / 16.3 / 11.3, LM head 41.8 / 46.6 / 31.4; 2064 rows: gate/up 43.3 / 46.3 / 33.1, down 36.4 / 39.3 / 24.9, QKV 24.5 / 26.4 / 18.5, O
+    // 10.9 / 12.1 / 8.2, LM head 79.5 / 91.4 / 64.8.  All forms sum a row in one order: it must not follow the batch.
     // bf16 (cross-check only): 16-row tiles while 64-row ones would not give every compute unit a workgroup; same bits.
     const int64_t n64 = static_cast<int64_t>(N / 64) * ((M + 63) / 64);
     const bool few = n64 < (ctx->n_cu > 0 ? ctx->n_cu : 256);

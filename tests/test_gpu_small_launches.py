@@ -154,7 +154,7 @@ def large_block():
     n = 64 * -(-n_cu // 16) + 16
     qkv = (desc.n_q_heads + 2 * desc.n_kv_heads) * desc.head_dim
     for cols in (qkv, desc.d_model, desc.d_ffn, desc.vocab):
-        assert cols // 64 * -(-n // 64) >= n_cu
+        assert cols // 64 * -(-n // 32) > 2 * n_cu
     weights = W.make_weights(desc, seed)
     draft = np.random.default_rng(3).integers(0, desc.vocab, size=n - 1).astype(np.int32)
     return weights, seed, draft, _round(desc, weights, seed, draft)
@@ -177,6 +177,39 @@ def test_fp32_small_tiles_match_the_large_block(large_block, first, rows):
     for a, b in zip(large, (out.argmax, out.margin, out.logits)):
         np.testing.assert_array_equal(a[first:first + rows], b.cpu().numpy())
     eng.close()
+
+
+@pytest.mark.parametrize("n_q, n_kv", [(16, 4), (3, 3), (1, 1)])
+def test_fp32_tile_forms_agree(n_q, n_kv):
+    """The forms of the fp32 GEMM -- half a column group or a whole one by 16 rows, 32 and 64 rows through LDS -- give a row the same
+    bits at every projection: blocks of a length for each on the way through one that takes the last form everywhere.  K of
+    the output projection is 64 n_q: 64 and 192 are no multiples of the longest chunk.  The first rows against the oracle."""
+    desc, seed = W.ModelDesc(1, 1024, n_q, n_kv, 64, 1024, 1024, "fp32"), 23
+    n_cu = torch.cuda.get_device_properties(0).multi_processor_count
+    groups = {"qkv": n_q + 2 * n_kv, "o": 16, "gate_up": 16, "lm_head": 16}
+    least = min(groups.values())
+
+    def form(g, rows, lm=False):                       # the launch's rule
+        t16, t32 = g * -(-rows // 16), g * -(-rows // 32)
+        return 0 if 2 * t16 <= n_cu and not lm else 1 if t16 <= n_cu else 2 if t32 <= 2 * n_cu else 3
+
+    large = 32 * (2 * n_cu // least + 1)
+    sizes = sorted({16 * max(1, n_cu // (4 * g)) for g in groups.values()} | {16 * (n_cu // g) for g in groups.values()}
+                   | {32 * (2 * n_cu // g) - 5 for g in groups.values()})
+    for name, g in groups.items():
+        seen = {form(g, r, name == "lm_head") for r in sizes} | {form(g, large, name == "lm_head")}
+        assert seen >= ({1, 2, 3} if name == "lm_head" else {0, 1, 2, 3}), (name, seen)
+    weights = W.make_weights(desc, seed)
+    draft = np.random.default_rng(n_q).integers(0, desc.vocab, size=large - 1).astype(np.int32)
+    want = _round(desc, weights, seed, draft)
+    for rows in sizes:
+        got = _round(desc, weights, seed, draft[:rows - 1])
+        for a, b in zip(want, got):
+            np.testing.assert_array_equal(a[:rows], b)
+    vis, prompt = W.make_prefix(desc, seed, 0, 37, 3)
+    cache, pending = O.prefill(desc, weights, vis, prompt)
+    ref = O.verify_block(desc, weights, cache, pending, draft[:15])[3]
+    assert np.abs(want[2][:16] - ref).max() <= 1e-4
 
 
 @pytest.mark.parametrize("rows", [1, 33])
