@@ -113,6 +113,7 @@ __global__ void __launch_bounds__(64 * (kAttnWideScorers + 4), 4) k_attn_wide(in
     return static_cast<size_t>(static_cast<uint32_t>(__builtin_amdgcn_readlane(pages, src))) * (kBlk * kHd);
   };
   auto any_moves = [&](int slot_m) { return __any(sm.moves[slot_m][lane & 7]); };
+  auto moves_at_end = [&]() { return __any(sm.moves[(lane >> 3) & 1][lane & 7]); };   // of the last two steps
   const auto common = std::false_type{};
   const auto general = std::true_type{};
   if (wave >= 4) {
@@ -123,7 +124,7 @@ __global__ void __launch_bounds__(64 * (kAttnWideScorers + 4), 4) k_attn_wide(in
     Frag8 qf[KQ];
     // pages: lane 4 s + p holds the number of page p of this wave's group in step s0 + s (16 steps at a time)
     auto fetch_pages = [&](int s0) { return page_number(((s0 + (lane >> 2)) * NS + w) * 4 + (lane & 3)); };
-    int pages;
+    int pages = fetch_pages(0);   // requested before q: the ids are on the way to the first keys
     {
       const bf16 *qp = q + static_cast<size_t>(base + my_row) * qdim + head * kHd + kg * 8;
 #pragma unroll
@@ -247,8 +248,7 @@ __global__ void __launch_bounds__(64 * (kAttnWideScorers + 4), 4) k_attn_wide(in
         load_k(s + 2);
       }
     };
-    auto first_k = [&](int s) {   // K of step s to LDS, that of the next one requested
-      pages = fetch_pages(s & ~15);
+    auto first_k = [&](int s) {   // K of step s to LDS (pages: those of s & ~15), that of the next one requested
       load_k(s);
       store_k();
       if (s + 1 < n_steps) {
@@ -279,12 +279,13 @@ __global__ void __launch_bounds__(64 * (kAttnWideScorers + 4), 4) k_attn_wide(in
         }
       }
       __syncthreads();   // the fold
-      return !(any_moves(0) || any_moves(1));
+      return !moves_at_end();
     };
     first_k(0);
     if (walk()) return;
     // The general form.  m: reference point of the lane's query
     __syncthreads();   // every wave has seen the outcome
+    pages = fetch_pages(0);
     first_k(0);
     float m = -INFINITY;
 #pragma clang loop unroll(disable)
@@ -319,6 +320,7 @@ __global__ void __launch_bounds__(64 * (kAttnWideScorers + 4), 4) k_attn_wide(in
 #pragma unroll
           for (int k = 0; k < NS; ++k) f |= sm.moves[s & 1][k];
           if (!__builtin_amdgcn_readfirstlane(f)) break;
+          pages = fetch_pages(s & ~15);
           first_k(s);
         } else {
           // every scoring wave finds the point behind its own group
@@ -453,7 +455,7 @@ __global__ void __launch_bounds__(64 * (kAttnWideScorers + 4), 4) k_attn_wide(in
     if (lane == 0 && n_steps == 1) sm.moves[1][wave] = 0;
     leave_odd();
     __syncthreads();
-    return !(any_moves(0) || any_moves(1));
+    return !moves_at_end();
   };
   first_v();
   if (!walk()) {
