@@ -17,7 +17,7 @@ namespace hsd {
 template <typename T>
 __global__ void __launch_bounds__(256) k_attn_simple(int n_q_heads, RowMeta meta, PagedKV kv,
                                                      const T *__restrict__ q, T *__restrict__ out) {
-  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
   const int r = blockIdx.x, head = blockIdx.y * 4 + wave;
   if (head >= n_q_heads) return;
   const int group = n_q_heads / kv.n_kv_heads, kvh = head / group;
@@ -28,16 +28,10 @@ __global__ void __launch_bounds__(256) k_attn_simple(int n_q_heads, RowMeta meta
   const T *kpool = static_cast<const T *>(kv.k_pool);
   const T *vpool = static_cast<const T *>(kv.v_pool);
 
-  // The query row is the same for the whole wave: it is read through the scalar unit (constant address space: an earlier kernel
-  // wrote it) and stays in scalar registers, which leaves room for a third wave per SIMD.
-  typedef const uint32_t __attribute__((address_space(4))) *ConstU32;
-  const ConstU32 qr = (ConstU32)(reinterpret_cast<const uint32_t *>(q + static_cast<size_t>(r) * (n_q_heads * kHd) + head * kHd));
   float qv[kHd];
+  const T *qr = q + static_cast<size_t>(r) * (n_q_heads * kHd) + head * kHd;
 #pragma unroll
-  for (int d = 0; d < kHd; ++d) {
-    if constexpr (std::is_same<T, float>::value) qv[d] = __uint_as_float(qr[d]);
-    else qv[d] = __uint_as_float((d & 1) ? (qr[d >> 1] & 0xffff0000u) : (qr[d >> 1] << 16));
-  }
+  for (int d = 0; d < kHd; d += 8) load8(qr + d, qv + d);
 
   // 16 consecutive values of a lane's dimension as they lie in a V page (one page, slot order: kv_v_slot)
   auto load_page = [&](int id, float *v) {
