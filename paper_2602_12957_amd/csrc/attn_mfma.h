@@ -49,7 +49,7 @@ namespace hsd {
 
 constexpr int kAttnKeys = 128;            // keys per LDS stage: 8 pages; keys 0-63 are parity 0's, 64-127 parity 1's
 // LDS: three stages of K rows, then two of V^T pages (a stage's V is wanted half a stage after its K, and its K may have to be
-// read a second time); 80 KB, two workgroups a compute unit
+// read a second time); 80 KB, so that two workgroups of four waves share a compute unit (eight waves of 242 registers or more fill it)
 constexpr int kAttnHalfStage = kAttnKeys * kHd * 2;
 constexpr int kAttnKStages = 3, kAttnVStages = 2;
 constexpr size_t kAttnLdsBytes = (kAttnKStages + kAttnVStages) * kAttnHalfStage;
@@ -588,7 +588,7 @@ __global__ void __launch_bounds__(64 * QS, 2) k_attn_mfma(int n_q_heads, const A
     for (int i = 0; i < 4; ++i) pre[i] = read_v(vs, i);
   };
   auto turn = [&](Half &x, const unsigned char *vs, const unsigned char *ks, Half &y, float &l, const unsigned char *vn) {
-    constexpr int kAhead = TREE && SPLIT ? 4 : 5;   // 5 does not fit the registers there
+    constexpr int kAhead = SPLIT && (TREE || QS == 4) ? 4 : 5;   // 5 does not fit the registers there
     // slot: 0 to 7 = V fragment (page s / 2, dims 32 (s % 2) ..), 8 + = K fragment (block s % 2, k-step (s - 8) / 2)
     constexpr int kSeq[16] = {0, 1, 2, 3, 8, 9, 4, 5, 10, 11, 6, 7, 12, 13, 14, 15};
     auto read = [&](int j) {

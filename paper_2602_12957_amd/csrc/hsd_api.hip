@@ -510,20 +510,15 @@ int lm_head_tiles(const hsd_ctx *ctx, int M) {
   }
 }
 
-// A compute unit has 160 KB of LDS; a request above half of it keeps a workgroup alone on its compute unit.
-constexpr size_t kLdsExclusive = 84 * 1024;
-
 template <int G4, int QS, bool TREE, bool SPLIT>
-int launch_attn_mfma(hipStream_t st, dim3 grid, int n_cu, int n_q_heads, const AttnTile *tiles, const PagedKV &kv,
-                     const bf16 *q, bf16 *o, const int32_t *row_end, const AttnSplit &sp) {
+int launch_attn_mfma(hipStream_t st, dim3 grid, int n_q_heads, const AttnTile *tiles, const PagedKV &kv, const bf16 *q, bf16 *o,
+                     const int32_t *row_end, const AttnSplit &sp) {
   auto kern = k_attn_mfma<G4, QS, TREE, SPLIT>;
   // set once per instantiation (initialisation of a function-local static is thread safe)
   static const hipError_t attr_rc = hipFuncSetAttribute(reinterpret_cast<const void *>(kern),
-                                                        hipFuncAttributeMaxDynamicSharedMemorySize, kLdsExclusive);
+                                                        hipFuncAttributeMaxDynamicSharedMemorySize, kAttnLdsBytes);
   if (attr_rc != hipSuccess) return HSD_EHIP;
-  const size_t n_wg = static_cast<size_t>(grid.x) * grid.y * grid.z;
-  const size_t lds = (n_cu > 0 && n_wg <= static_cast<size_t>(n_cu)) ? kLdsExclusive : kAttnLdsBytes;
-  hipLaunchKernelGGL(kern, grid, dim3(64 * QS), lds, st, n_q_heads, tiles, kv, q, o, row_end, sp);
+  hipLaunchKernelGGL(kern, grid, dim3(64 * QS), kAttnLdsBytes, st, n_q_heads, tiles, kv, q, o, row_end, sp);
   HSD_LAUNCH_CHECK();
   return HSD_OK;
 }
@@ -573,10 +568,9 @@ AttnPlan plan_attention(const hsd_ctx *ctx, const hsd_kv_pool *pool, const hsd_b
   const int n_y = p.n_y = d.n_kv_heads * ((group + g4 - 1) / g4);
   // Few query sets: the keys of each are spread over a workgroup's waves (k_attn_wide; same bits, so the choice may
   // follow the batch).  Its workgroups read K and V once per head where k_attn_mfma's read them once per four, so it
-  // loses when the chip is full.  Launch times in us, k_attn_mfma / k_attn_wide (events, 16 heads on 4 kv heads, 1055
-  // keys), by query sets: 4 (one token) 18.5 / 14.9, 4096 keys 47.7 / 33.5; 16 (1 block of 32 rows) 21.0 / 14.9; 128
-  // 21.9 / 15.5; 256 21.0 / 16.0; 208 (a block of 401) 23.7 / 20.0; 512: 8 blocks of 128 rows 21.6 / 20.0, 32 of 32
-  // 22.4 / 22.3, 64 of 16 24.8 / 25.5, 512 keys 15.7 / 15.5; 624 (3 of 401) 24.3 / 27.5; 1056 29 / 40.  The line is at
+  // loses when the chip is full.  us a launch, k_attn_mfma / k_attn_wide (in passes, 16 heads on 4 kv heads, 1055 cached keys), by query
+  // sets: 4 (one token) 14.7 / 7.9; 204 (a block of 401 rows) 18.9 / 12.3; 512: 8 blocks of 128 rows 18.4 / 15.8, 32 of 32 17.7 / 17.0;
+  // 624 (3 of 401) 20.1 / 21.5; 832 (4 of 401) 21.0 / 26.1.  The line is at
   // 2.25 sets per compute unit of what a batch of this size can be expected to have: half a tile lost per block.
   const int64_t rows = b->total_q, n = b->n_seq;
   const int64_t by_tile = g4 * (2 * rows + 32 * n) / 64, by_row = n + (rows - n) / 8;
@@ -632,10 +626,10 @@ int launch_attention(const hsd_ctx *ctx, hipStream_t st, const hsd_batch *b, con
       int rc = HSD_OK;
 #define HSD_ATTN_CASE(G4, QS)                                                                                      \
   if (g4 == G4 && qs == QS) {                                                                                      \
-    if (tree && chunk > 0) rc = launch_attn_mfma<G4, QS, true, true>(st, grid_z, ctx->n_cu, d.n_q_heads, ws.attn_tiles, kv, q, o, meta.row_end, sp);       \
-    else if (tree) rc = launch_attn_mfma<G4, QS, true, false>(st, grid_z, ctx->n_cu, d.n_q_heads, ws.attn_tiles, kv, q, o, meta.row_end, sp);             \
-    else if (chunk > 0) rc = launch_attn_mfma<G4, QS, false, true>(st, grid_z, ctx->n_cu, d.n_q_heads, ws.attn_tiles, kv, q, o, meta.row_end, sp);        \
-    else rc = launch_attn_mfma<G4, QS, false, false>(st, grid_z, ctx->n_cu, d.n_q_heads, ws.attn_tiles, kv, q, o, meta.row_end, sp);                      \
+    if (tree && chunk > 0) rc = launch_attn_mfma<G4, QS, true, true>(st, grid_z, d.n_q_heads, ws.attn_tiles, kv, q, o, meta.row_end, sp);       \
+    else if (tree) rc = launch_attn_mfma<G4, QS, true, false>(st, grid_z, d.n_q_heads, ws.attn_tiles, kv, q, o, meta.row_end, sp);             \
+    else if (chunk > 0) rc = launch_attn_mfma<G4, QS, false, true>(st, grid_z, d.n_q_heads, ws.attn_tiles, kv, q, o, meta.row_end, sp);        \
+    else rc = launch_attn_mfma<G4, QS, false, false>(st, grid_z, d.n_q_heads, ws.attn_tiles, kv, q, o, meta.row_end, sp);                      \
   }
       HSD_ATTN_CASE(4, 4) HSD_ATTN_CASE(4, 8) HSD_ATTN_CASE(2, 4) HSD_ATTN_CASE(2, 8) HSD_ATTN_CASE(1, 4) HSD_ATTN_CASE(1, 8)
 #undef HSD_ATTN_CASE

@@ -1,7 +1,8 @@
-"""What the compiler made of the residual projections' GEMM kernels and of the attention spread over a workgroup's waves, read
+"""What the compiler made of the residual projections' GEMM kernels, of both attention kernels and of the fp32 GEMM, read
 from the built library's own metadata: none may spill vector registers.  The GEMM epilogue runs once per tile with the
 accumulators live, so state that only the narrow tiles need has to stay out of the wide ones (a run-time choice there cost
-the persistent 256x256 kernel two spills); k_attn_wide has 128 registers, so that two workgroups fit a compute unit."""
+the persistent 256x256 kernel two spills); k_attn_wide has 128 registers, so that two workgroups fit a compute unit; k_attn_mfma
+needs 242 and more of its 256."""
 import os
 import shutil
 import subprocess
@@ -38,3 +39,9 @@ def test_residual_gemm_kernels_do_not_spill(tmp_path):
 def test_wide_attention_does_not_spill(tmp_path):
     forms = {k[".name"]: k[".vgpr_spill_count"] + k[".private_segment_fixed_size"] for k in _kernels(tmp_path) if "11k_attn_wideI" in k[".name"]}
     assert len(forms) == 4 and {n: s for n, s in forms.items() if s} == {}
+
+
+@pytest.mark.parametrize("name, number", [("11k_attn_mfmaI", 24), ("10k_gemm_f32I", 15)])
+def test_general_attention_and_fp32_gemm_do_not_spill(tmp_path, name, number):
+    forms = {k[".name"]: k[".vgpr_spill_count"] + k[".private_segment_fixed_size"] for k in _kernels(tmp_path) if name in k[".name"]}
+    assert len(forms) == number and {n: s for n, s in forms.items() if s} == {}
