@@ -63,9 +63,8 @@ __device__ __forceinline__ void gemm_tile_of(int pid, int M, int w_rows, int til
   else xcd_tile(pid, tiles_act, tiles_act * tiles_w, ta, tw);
 }
 
-// Bands.  With one to two thousand rows a one-round launch has about as many activation tiles as weight tiles, and a run of
-// the plain order gives each XCD every activation tile: eight times the activations from the memory-side cache, which bounds such
-// launches (the units ask L2 for 12 to 14 TB/s, a third of it missed).  So the tiles are cut into 2 or 4 bands of activation
+// Bands.  With six hundred to two thousand rows a one-round launch has about as many activation tiles as weight tiles, and a run of
+// the plain order gives each XCD every activation tile: eight times the activations from the memory-side cache.  So the tiles are cut into 2 or 4 bands of activation
 // tiles by 4 or 2 bands of weight tiles, a rectangle to each XCD (workgroup i runs on XCD i % 8).  band = log2 of the activation
 // bands; rectangles of uneven cuts leave workgroups without a tile (false).
 __device__ __forceinline__ bool band_tile(int pid, int tiles_act, int tiles_w, int band, int &ta, int &tw) {
@@ -82,10 +81,13 @@ inline int band_grid(int tiles_act, int tiles_w, int band) {
   return 8 * ((tiles_act + a - 1) / a) * ((tiles_w + w - 1) / w);
 }
 // The bands of a launch of tiles_act x tiles_w tiles of bp x bq rows, or -1: the plain order.  Bands where they still give at
-// most one workgroup per unit and an XCD reads less than 0.8 of what it reads in the plain order.  us, plain / bands (launches in
-// a row, d 1024): O at 1856 rows 13.2 / 9.7, 2304 15.1 / 12.0; down 1280 rows 21.3 / 19.7, 1856 25.1 / 23.8, 2304 30.9 / 29.1; QKV
-// 1856 14.0 / 13.1, 2304 14.8 / 13.8.  Below the line: O at 768 rows 6.7 / 6.7, QKV 1016 7.6 / 7.6, gate/up 168 8.5 / 9.5.
-inline int gemm_bands(int tiles_act, int tiles_w, int bp, int bq, int n_cu) {
+// most one workgroup per unit and an XCD reads less than 0.8 of what it reads in the plain order; with tiles of 64 rows and a
+// short walk over K the plain order stays.  us a launch inside passes, plain / bands (d 1024): down (K = 4096) 600 rows 17.7 / 17.4, 768
+// 20.6 / 20.1, 1016 21.4 / 20.8, 1280 27.9 / 26.9, 1856 27.5 / 25.8, 2304 33.6 / 32.2; O (K = 1024) 600 8.45 / 8.55, 768 9.0 / 9.35, 1016 9.1 /
+// 9.2, from 128-row tiles on 1280 10.9 / 10.8, 1856 11.9 / 11.55, 2304 13.75 / 13.6; QKV 1016 10.1 / 10.1, 1280 10.5 / 10.35, 1856 16.1 /
+// 15.5, 2304 16.6 / 16.15.  (The same launch over and over, its weights in the caches: O at 1856 rows 13.2 / 9.7.)
+inline int gemm_bands(int tiles_act, int tiles_w, int bp, int bq, int K, int n_cu) {
+  if (bp < 128 && K < 2048) return -1;
   int best = -1;
   int64_t least = int64_t{8} * (int64_t{tiles_act} * bp + int64_t{(tiles_w + 7) / 8} * bq) / 10;
   for (int band = 1; band <= 2; ++band) {

@@ -212,7 +212,7 @@ int launch_gemm_mfma_ws(hipStream_t st, int M, int N, int K, const void *A, cons
   if (attr_rc != hipSuccess) return HSD_EHIP;
   int tiles_act, tiles_w;
   gemm_tiles<Cfg, MODE>(M, N, tiles_act, tiles_w);
-  const int band = gemm_bands(tiles_act, tiles_w, Cfg::BP, Cfg::BQ, n_cu);
+  const int band = gemm_bands(tiles_act, tiles_w, Cfg::BP, Cfg::BQ, K, n_cu);
   hipLaunchKernelGGL(kern, dim3(band < 0 ? tiles_act * tiles_w : band_grid(tiles_act, tiles_w, band)), dim3(512), smem, st, M, N, K, band, static_cast<const bf16 *>(A),
                      static_cast<const bf16 *>(W), epi);
   HSD_LAUNCH_CHECK();
@@ -255,7 +255,7 @@ int launch_gemm_mfma_r(hipStream_t st, int M, int N, int K, const void *A, const
     if (pass_by) kern = kern_nt;
   }
   const int tiles_act = (M - m_base + Cfg::BP - 1) / Cfg::BP, tiles_w = N / Cfg::kCols / (MODE == kModeDual ? 1 : 2);
-  const int band = gemm_bands(tiles_act, tiles_w, Cfg::BP, Cfg::BQ, n_cu);
+  const int band = gemm_bands(tiles_act, tiles_w, Cfg::BP, Cfg::BQ, K, n_cu);
   hipLaunchKernelGGL(kern, dim3(band < 0 ? tiles_act * tiles_w : band_grid(tiles_act, tiles_w, band)), dim3(Cfg::kThreads), smem, st, M, N, K,
                      m_base, band, static_cast<const bf16 *>(A),
                      static_cast<const bf16 *>(W), epi);

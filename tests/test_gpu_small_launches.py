@@ -1,6 +1,6 @@
 """Kernels chosen for launches of few rows against the general ones, bit for bit: the 16-row kernel's tiles for the bf16
-projections, and its weights read past the caches, against a tile set by hand; the 16-row tiles of the fp32 path against
-the 64-row ones that a block with enough rows takes at every projection.  Every output sums its products in one fixed
+projections, and its weights read past the caches, against a tile set by hand; tiles dealt to the XCDs in bands; the smaller
+tiles of the fp32 path against the 64-row ones that a block with enough rows takes at every projection.  Every output sums its products in one fixed
 order in all of them, so the tolerance is zero.  The LM head's record where logits are not finite.  And the plain kernels
 on a bf16 model against the oracle, with the bar of the bf16 parity tests."""
 import numpy as np
@@ -177,6 +177,39 @@ def test_fp32_small_tiles_match_the_large_block(large_block, first, rows):
     for a, b in zip(large, (out.argmax, out.margin, out.logits)):
         np.testing.assert_array_equal(a[first:first + rows], b.cpu().numpy())
     eng.close()
+
+
+def _bands(rows, cols, bp, bq, k, n_cu):
+    """log2 of the activation bands that a launch of tiles of bp x bq over rows x cols is cut into on the XCDs, -1: none."""
+    if bp < 128 and k < 2048:
+        return -1
+    act, wgt, best = -(-rows // bp), cols // bq, -1
+    least = 8 * (act * bp + -(-wgt // 8) * bq) // 10
+    for band in (1, 2):
+        a, w = 1 << band, 8 >> band
+        reads = -(-act // a) * bp + -(-wgt // w) * bq
+        if act >= a and wgt >= w and 8 * -(-act // a) * -(-wgt // w) <= n_cu and reads < least:
+            best, least = band, reads
+    return best
+
+
+@pytest.mark.parametrize("rows", [576, 577, 641, 897, 1025, 1281, 1300, 1856, 2049, 2304])
+def test_banded_tile_order(rows):
+    """Launches whose tiles are dealt to the XCDs in rectangles (2 bands of activation tiles by 4 of weight tiles, or 4 by 2; also
+    where the tiles do not divide evenly, so that workgroups stay without one) against the generic kernel: a tile left out or
+    taken twice would leave rows or columns of O, down (64x64, 128x64 and 144x64 tiles) or QKV wrong."""
+    desc, seed = W.ModelDesc(1, 1024, 16, 4, 64, 2048, 512, "bf16"), 31
+    n_cu = torch.cuda.get_device_properties(0).multi_processor_count
+    if n_cu == 256:
+        tile = 64 if rows <= 1024 else 128 if rows <= 2048 else 144
+        assert _bands(rows, 1024, tile, 64, 2048, n_cu) == (-1 if rows <= 576 else 1 if rows <= 1280 else 2)     # down
+        assert _bands(rows, 1024, tile, 64, 1024, n_cu) == (-1 if rows <= 1024 else 1 if rows <= 1280 else 2)    # O
+        if 640 < rows <= 1440:
+            assert _bands(rows, 1536, 128 if rows <= 1280 else 144, 64, 1024, n_cu) == (1 if rows > 896 else -1)
+    weights = W.make_weights(desc, seed)
+    draft = np.random.default_rng(rows).integers(0, desc.vocab, size=rows - 1).astype(np.int32)
+    for a, b in zip(_round(desc, weights, seed, draft), _round(desc, weights, seed, draft, {"gemm_cfg": (2, 2, 2, 2, 0)})):
+        np.testing.assert_array_equal(a, b)
 
 
 @pytest.mark.parametrize("n_q, n_kv", [(16, 4), (3, 3), (1, 1)])
