@@ -313,3 +313,38 @@ def test_one_key_gives_its_value(n_q, n_kv, name):
     eng.close()
     assert np.isfinite(logits).all() and (np.abs(logits[:, d - 64:]) > 0.5).all()
     np.testing.assert_array_equal(logits[:, :d - 64], 0)
+
+
+@pytest.mark.parametrize("value", [np.inf, 60.0])
+@pytest.mark.parametrize("mode, rows, more, chunk", [("region", 4, 0, 0), ("region", 40, 0, 0), ("region", 40, 1, 0), ("page", 40, 1, 0), ("region", 40, 0, 128)])
+def test_one_query_leaves_the_others_alone(mode, rows, more, chunk, value):
+    """One token's queries are infinite, or so large that its reference points are far from 0 and move (keys and values as ever): the
+    other rows of its block, which share its wave, give the bits they give beside an ordinary query.  16 and 32 columns of
+    k_attn_wide, k_attn_mfma with 4 and 8 query sets and with a key split."""
+    desc = W.tiny_model(1, 128, 16, 4, 64, 128, 256, "bf16")
+    weights = W.make_weights(desc, 67)
+    weights["tok_embed"][:, 5] = 0
+    weights["tok_embed"][7, 5] = 0.02                 # token 7 alone has column 5, about 1 after the norm
+    rng = np.random.default_rng(rows)
+    n_cu = torch.cuda.get_device_properties(0).multi_processor_count
+    prefix = rng.integers(8, 256, size=300).astype(np.int32)
+    blocks = [rng.integers(8, 256, size=rows).astype(np.int32)] + [rng.integers(8, 256, size=32 * (3 * n_cu // 16 + 1)).astype(np.int32)] * more
+    blocks[0][rows // 2] = 7
+
+    def score(gain):
+        wqkv = weights["layers"][0]["wqkv"].copy()
+        wqkv[:16 * 64, 5] = 0 if gain == 0 else np.where(np.arange(16 * 64) % 2, 1, -1) * np.float32(3e38 if np.isinf(gain) else gain)
+        wqkv[16 * 64:, 5] = 0
+        total = sum(len(b) for b in blocks)
+        eng = Engine(desc, {**weights, "layers": [{**weights["layers"][0], "wqkv": wqkv}]}, (total + 300) // 16 + 4, 2, (total + 300) // 16 + 4, total,
+                     rows, attn_key_chunk=chunk)
+        eng.prefill([0], [prefix])
+        out = eng.verify(list(range(1 + more)), blocks, mode, dump_rows=np.arange(rows)).logits.cpu().numpy().copy()
+        assert int(eng.status.item()) == 0
+        eng.close()
+        return out
+
+    plain, odd = score(0), score(value)
+    others = np.arange(rows) != rows // 2
+    np.testing.assert_array_equal(odd[others], plain[others])
+    assert not np.array_equal(odd[rows // 2], plain[rows // 2]) and np.isfinite(odd[rows // 2]).all() == np.isfinite(value)
