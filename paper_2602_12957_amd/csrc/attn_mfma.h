@@ -22,18 +22,19 @@
 // pages are stored transposed and in exactly that token order ([dim][perm(token)], see kv_v_slot), hence the
 // A operand of the second product is one 16-byte LDS read per lane and no transpose is ever done here.
 //
-// What bounds it, and why a wave holds both parities.  A group of 64 keys is 16 matrix instructions (32 cycles each), eight
-// small ones (8 cycles) for the row sums, and 32 exponentials and 16 conversions per lane.  The matrix pipe and the vector unit run side by side only if
-// independent work of both kinds is in the instruction stream: microbenchmark, one wave per SIMD, ns per group: products
-// alone 225, vector part alone 190, both interleaved 230 to 260.  With one parity to a wave, four waves per SIMD in step behind a
-// barrier a stage, each waited for its own chain of reads, products, maximum, exponentials and products: 577 ns a group (four pages
-// of 8193 rows: 1907 us a layer).  Here, in every turn, the exponentials of one parity run beside the products of the other, in
-// an order fixed by hand; what the exponentials need beside (maximum, subtraction, rescaling) is taken out of the common case
-// (attn_reference; a pass over those pages takes 65 ms, and 72 with queries and keys scaled by 8, where most points are not 0:
-// 105 when such groups had to subtract and went through the general rule), and the keys and values are requested by LDS-direct loads, so that staging takes no registers and no store
-// instructions.  On the way (us a layer at that size): no running maximum 1757; both parities in a wave 1779; row sums
-// off the matrix pipe (attn_page_sum) and the order pinned 1594.  16 regions of 17 to 257 rows on 1055 keys: 29.7 -> 26.2.
-// What is left there: 10 % of the launch is its last tasks; a third of a wave's time are waits for LDS reads and at barriers.
+// What bounds it, and why a wave holds both parities.  A group of 64 keys is 16 matrix instructions (32 cycles each), eight small
+// ones (8 cycles) for the row sums, and 32 exponentials and 16 conversions per lane.  The matrix pipe and the vector unit run
+// side by side only if independent work of both kinds is in the instruction stream: microbenchmark, one wave per SIMD, ns per
+// group: products alone 225, vector part alone 190, both interleaved 230 to 260.  With one parity to a wave, four waves per SIMD
+// in step behind a barrier a stage, each waited for its own chain of reads, products, maximum, exponentials and products: 577 ns
+// a group (four pages of 8193 rows: 1907 us a layer).  Here, in every turn, the exponentials of one parity run beside the
+// products of the other, in an order fixed by hand; what the exponentials need beside (maximum, subtraction, rescaling) is taken
+// out of the common case (attn_reference: a pass over those pages takes 68 ms, and 72 with queries and keys scaled by 8, where
+// most reference points are not 0; 105 when such groups had to subtract and went through the general rule), and the keys and
+// values are requested by LDS-direct loads, so that staging takes no registers and no store instructions.  On the way (us a
+// layer at that size): no running maximum 1757; both parities in a wave 1779; row sums without v_dot2 1731; the order pinned 1594.
+// 16 regions of 17 to 257 rows on 1055 keys: 29.7 -> 26.2.  What is left there: the matrix pipe is busy for 64 % of the launch, 10 %
+// of it is its last tasks, and 28 % of a wave's time are waits for LDS reads and at barriers.
 //
 // The key loop has two forms.  Stages whose every key is visible to every query of the workgroup (the bulk of a
 // cached prefix) run with no mask and no validity checks; the last one or two stages of a
