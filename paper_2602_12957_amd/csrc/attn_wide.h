@@ -32,7 +32,7 @@ template <int QW>
 struct AttnWideLds {
   uint4 p[2][kAttnWideScorers][QW / 8][64];
   float mx[kAttnWideScorers][QW], mg[2][kAttnWideScorers][QW];
-  int moves[2][8];
+  int moves[2][4], sets;
   union __attribute__((aligned(16))) {   // (16-byte LDS accesses: a workgroup takes 1.6 times as long if they lie elsewhere)
     uint16_t k[kAttnWideScorers][64 * kKsStride];   // a scoring wave's own 64 keys (see k_row)
     float fold[2][QW / 2 + 1][64];                  // after the last products
@@ -55,13 +55,13 @@ __device__ __forceinline__ float quarter_sum(float x) {
 // grid: attn_grid_size(...) tasks, block 64 * (NS + 4), dynamic LDS sizeof(AttnWideLds).
 // The walk over the steps has two forms.  The first takes every reference point for 0 and has one barrier a step, behind which
 // the step's probabilities are in LDS: nothing else is waited for.  Whether the first group sets another point, and whether a
-// sum shows a score that would move one, is found out beside the next step's work, so that every wave alike leaves this form
-// two barriers after such a step (nearly always the first).  The walk then starts again in the general form: a step whose points
-// stand has one barrier there too, but the outcome is waited for behind it; one that sets or moves a point has two more, behind
-// which the groups' largest scores and then the probabilities are in LDS.
+// sum shows a score that would move one, is found out beside the next step's work, and every wave alike leaves this form.  The
+// walk then starts again in the general form, from the points of the first group: a step whose points stand has one barrier there
+// too, but the outcome is waited for behind it; one that moves a point has three more, behind which the groups' largest scores,
+// the points that follow and the probabilities are in LDS.
 // us a launch, with points found and moved inside the one loop / in forms of their own: one token at 1055 keys 8.9 / 7.9, 7 blocks
 // of 1 to 47 rows 13.1 / 12.3, 64 tokens 17.9 / 17.4.  Where scores are so extreme that every set ends in the general form (first
-// groups beyond 64 binary orders, 44 in natural logarithms) one token takes 14.6.
+// groups beyond 64 binary orders, 44 in natural logarithms, and later scores beyond 96) one token takes 14.
 // What bounds it (one token at 1055 keys, 7.9 us): 2.6 us until the first scores (descriptor, page
 // ids, keys: three dependent reads), then the 270 KB of a kv head through one unit's load path (a bare read of 256 KB by a
 // workgroup takes 5 us with its launch), 1 us of last accumulation, fold and store.  Tried: eight scoring waves (32 columns: 13.4
@@ -112,8 +112,11 @@ __global__ void __launch_bounds__(64 * (kAttnWideScorers + 4), 4) k_attn_wide(in
   auto page_off = [&](int pages, int src) {
     return static_cast<size_t>(static_cast<uint32_t>(__builtin_amdgcn_readlane(pages, src))) * (kBlk * kHd);
   };
-  auto any_moves = [&](int slot_m) { return __any(sm.moves[slot_m][lane & 7]); };
-  auto moves_at_end = [&]() { return __any(sm.moves[(lane >> 3) & 1][lane & 7]); };   // of the last two steps
+  // Whether the general form is asked for.  moves[x]: by the accumulating waves' sums of the last step with s % 2 = x; sets: by
+  // the first group's scores.  Looked at beside the work between the barriers of steps t - 1 and t, when the flags
+  // of step t - 2 are complete (at t = 1 the first group's); at the end those of the last two steps.
+  auto asks = [&](int t) { return __any(t == 1 ? sm.sets : sm.moves[t & 1][lane & 3]); };
+  auto asked_at_end = [&]() { return __any(sm.moves[(lane >> 2) & 1][lane & 3]) || (n_steps == 1 && __any(sm.sets)); };
   const auto common = std::false_type{};
   const auto general = std::true_type{};
   if (wave >= 4) {
@@ -258,43 +261,43 @@ __global__ void __launch_bounds__(64 * (kAttnWideScorers + 4), 4) k_attn_wide(in
     };
     // The common form.  Returns whether it stands.
     auto walk = [&]() {
-      if (lane == 0) sm.moves[1][4 + w] = 0;
       bool asked = false;
 #pragma clang loop unroll(disable)   // a first iteration of its own doubles the code
       for (int s = 0; s < n_steps; ++s) {
         const int g = s * NS + w;
-        if (s > 1) asked = any_moves(s & 1);   // of step s - 2, complete since the barrier of s - 1
+        if (s > 0) asked = asks(s);
         if (g < n_groups) products(0.f);
         next_k(s);
         if (g < n_groups) {
           mask(g * 64, common);
           probs(s, common);
+          if (g == 0) {   // this group holds a visible key of every query and sets its point
+            const float m = attn_reference(-INFINITY, query_max());
+            if (kg == 0) sm.mg[0][0][qj] = m;
+            const int sets = __any(m != 0.f);
+            if (lane == 0) sm.sets = sets;
+          }
         }
         if (asked) return false;
         __syncthreads();   // the step's probabilities
-        // the first group holds a visible key of every query and sets its point
-        if (s == 0) {
-          const bool sets = w == 0 && __any(attn_reference(-INFINITY, query_max()) != 0.f);
-          if (lane == 0) sm.moves[0][4 + w] = sets;
-        }
       }
       __syncthreads();   // the fold
-      return !moves_at_end();
+      return !asked_at_end();
     };
     first_k(0);
     if (walk()) return;
     // The general form.  m: reference point of the lane's query
     __syncthreads();   // every wave has seen the outcome
     pages = fetch_pages(0);
+    float m = sm.mg[0][0][qj];   // the first group's
     first_k(0);
-    float m = -INFINITY;
 #pragma clang loop unroll(disable)
     for (int s = 0; s < n_steps; ++s) {
       const int g = s * NS + w;
-      // phase 0: with the points as they are; where they do not stand (as at the first step), phase 1: the largest scores, and
-      // 2: with the points that follow from them
+      // phase 0: with the points as they are; where they do not stand, phase 1: the largest scores, and 2: with the points that
+      // follow from them
 #pragma clang loop unroll(disable)
-      for (int phase = s == 0 ? 1 : 0;; ++phase) {
+      for (int phase = 0;; ++phase) {
         float m_own = m, mx = -INFINITY;
         if (phase == 2) {
           m_own = sm.mg[s & 1][w][qj];
@@ -324,7 +327,7 @@ __global__ void __launch_bounds__(64 * (kAttnWideScorers + 4), 4) k_attn_wide(in
           first_k(s);
         } else {
           // every scoring wave finds the point behind its own group
-          float m_run = m;
+          float m_run = s == 0 ? -INFINITY : m;
           for (int k = 0; k <= w; ++k)
             if (s * NS + k < n_groups) m_run = attn_reference(m_run, sm.mx[k][qj]);
           if (kg == 0) sm.mg[s & 1][w][qj] = m_run;
@@ -436,7 +439,7 @@ __global__ void __launch_bounds__(64 * (kAttnWideScorers + 4), 4) k_attn_wide(in
     __syncthreads();   // the first step's probabilities
 #pragma clang loop unroll(disable)
     for (int s = 0; s + 1 < n_steps; ++s) {
-      if (s > 0) asked = any_moves((s + 1) & 1);   // of step s - 1
+      asked = asks(s + 1);
       if ((s + 1) % SPF == 0) pages = fetch_pages(s + 1);
       moves = false;
 #pragma unroll
@@ -455,13 +458,13 @@ __global__ void __launch_bounds__(64 * (kAttnWideScorers + 4), 4) k_attn_wide(in
     if (lane == 0 && n_steps == 1) sm.moves[1][wave] = 0;
     leave_odd();
     __syncthreads();
-    return !moves_at_end();
+    return !asked_at_end();
   };
   first_v();
   if (!walk()) {
     // The general form.  m: reference point of the lane's query
     __syncthreads();
-    float m = -INFINITY;
+    float m = sm.mg[0][0][qj];
     // every group's move, also of the other parity, so that the factors come one by one as in k_attn_mfma
     auto rescale = [&](int s, int w) {
       if (s * NS + w >= n_groups) return;
@@ -482,14 +485,11 @@ __global__ void __launch_bounds__(64 * (kAttnWideScorers + 4), 4) k_attn_wide(in
     first_v();
 #pragma clang loop unroll(disable)
     for (int s = 0; s < n_steps; ++s) {
-      bool moved = s == 0;
-      if (s > 0) {
-        __syncthreads();   // phase 0
-        int f = 0;
+      __syncthreads();   // phase 0
+      int f = 0;
 #pragma unroll
-        for (int k = 0; k < NS; ++k) f |= sm.moves[s & 1][k];
-        moved = __builtin_amdgcn_readfirstlane(f) != 0;
-      }
+      for (int k = 0; k < NS; ++k) f |= sm.moves[s & 1][k];
+      const bool moved = __builtin_amdgcn_readfirstlane(f) != 0;
       if (moved) {
         __syncthreads();   // phase 1: largest scores, points
         __syncthreads();
